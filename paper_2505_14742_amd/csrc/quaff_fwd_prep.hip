@@ -40,7 +40,9 @@ struct FwdPrepArgs {
     const uint16_t* B; uint16_t* Bt;                                    // B [16 x c_out] -> Bt [c_out x 16]
     uint32_t* part;               // [n][groups] maxima of each workgroup's rows: bf16 magnitude << 16 | tag
     uint32_t* epoch;              // launch counter of this workspace (any start value)
-    int groups; long long wait_ticks;
+    int groups;                   // workgroups of the launch: ceil(t / 8) own rows, the others (if any) only requantize what
+    int what_first;               // what is requantized by the workgroups from this one on
+    long long wait_ticks;
 };
 
 
@@ -73,6 +75,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
     const int64_t row0 = (int64_t)blk * kPrepRows;
     const int64_t row = row0 + (m & 7);
     const bool live = row < a.t;
+    const bool has_rows = row0 < a.t;              // uniform over the workgroup
     const uint16_t* xrow = a.X + (live ? row : 0) * a.ldx;
 
     // ---- this wavefront's columns: part p of the contraction range, slices 2 w' and 2 w' + 1 of its sixteen
@@ -116,13 +119,14 @@ fwd_prep_kernel(const FwdPrepArgs a) {
             }
         }
     };
-    if (HAS_LORA) load_a(0);
+    if (HAS_LORA && has_rows) load_a(0);
     const int64_t bt_total = HAS_LORA ? 16 * a.c_out : 0;     // Bt [c_out x 16] <- B [16 x c_out]
     const int64_t bt_e0 = (int64_t)blk * kPrepThreads + tid;
     uint16_t bt_first = 0;
     if (bt_e0 < bt_total) bt_first = a.B[(bt_e0 & 15) * a.c_out + (bt_e0 >> 4)];
-    const int64_t per = (a.c_out + G - 1) / G;
-    const int64_t j0 = (int64_t)blk * per, j1 = j0 + per < a.c_out ? j0 + per : a.c_out;
+    const int64_t per = (a.c_out + G - a.what_first - 1) / (G - a.what_first);
+    const int64_t j0 = blk < a.what_first ? a.c_out : (int64_t)(blk - a.what_first) * per;
+    const int64_t j1 = j0 + per < a.c_out ? j0 + per : a.c_out;
     float w_first[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -180,7 +184,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         const int i = (tid + v * kPrepThreads) * 4;
         if (i < c) *reinterpret_cast<f32x4*>(cs_copy + i) = cs_first[v];
     }
-    if (HAS_LORA) {
+    if (HAS_LORA && has_rows) {
         f32x4 acc[2];
         acc[0] = acc[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -231,7 +235,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         }
     }
     __syncthreads();
-    if (HAS_LORA) {
+    if (HAS_LORA && has_rows) {
         // fixed-order sums over the sixteen slices of each part
         for (int e = tid; e < kLoraParts * 32 * 4; e += kPrepThreads) {
             const int v = e & 3, ln = (e >> 2) & 31, p = e >> 7;
@@ -457,6 +461,22 @@ fwd_prep_kernel(const FwdPrepArgs a) {
 
 int fwd_prep_groups(int64_t t) { return (int)((t + kPrepRows - 1) / kPrepRows); }
 
+// Who requantizes what (c_out channels in rounds of 64).  With 2048 rows every workgroup owns rows and takes its share of
+// the channels afterwards.  With fewer rows the launch is filled up with workgroups that own none and only wait for
+// the maxima: one round each where that many compute units are left, two at most, so that the channels are done while
+// the row owners quantize; with less room everybody takes an equal share.  (Left to the row owners alone, 16 rows and
+// 9216 channels are 72 rounds in each of two workgroups: 188 us for the launch, 12 us this way; 512 rows and 3072
+// channels 13.4 -> 12.3 us.)  The extra workgroups announce
+// themselves like the others, with empty maxima: whoever publishes the new scales must know that they have read the old.
+static void fwd_prep_split(int64_t t, int64_t c_out, int* groups, int* what_first) {
+    const int rows = fwd_prep_groups(t);
+    const int64_t rounds = (c_out + kWhatChunk - 1) / kWhatChunk;
+    const int room = kPrepMaxGroups - rows;
+    const int extra = (int)(rounds < room ? rounds : room);
+    *groups = rows + extra;
+    *what_first = 2 * (int64_t)extra >= rounds ? rows : 0;
+}
+
 // shapes the one-launch preparation covers
 bool fwd_prep_covers(int64_t t, int64_t c_in, int32_t n, int32_t r) {
     return t >= 1 && fwd_prep_groups(t) <= kPrepMaxGroups && n >= 1 && n <= 64 && (r == 0 || r == 16) && c_in <= 8192;
@@ -487,7 +507,7 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
     a.W_O = W_O; a.c_out = c_out; a.what_int = what_int; a.delta_what = delta_what;
     a.Xq = Xq; a.delta = delta; a.xq_O = xq_O;
     a.A = A; a.scale = scale; a.T_hi = T_hi; a.T_lo = T_lo; a.B = B; a.Bt = Bt;
-    a.groups = fwd_prep_groups(t);
+    fwd_prep_split(t, c_out, &a.groups, &a.what_first);
     a.part = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + 256);
     a.epoch = reinterpret_cast<uint32_t*>(scratch);
     a.wait_ticks = wait_ticks;

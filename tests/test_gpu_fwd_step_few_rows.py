@@ -1,0 +1,33 @@
+"""One-launch forward preparation with fewer row owners than compute units: the launch is filled up with workgroups that
+only requantize what.  Token counts on both sides of each way the channels are shared out (one round of 64 channels per
+extra workgroup, two rounds, everybody, no room left), ragged rows and channels, with and without an adapter; the one
+call against the three separate calls bit for bit, also with the grid-wide wait forced to give up."""
+import sys
+
+import pytest
+
+from paper_2505_14742_amd import synth
+from tests.test_gpu_fwd_step import _compare
+
+pytestmark = pytest.mark.gpu
+
+# (t, c_in, c_out, rank): row owners + rounds <= 256; extra workgroups with two rounds; an equal share for everybody;
+# 255 owners and one extra; no extra
+_CASES = [(1, 256, 9232, 16), (16, 1040, 16384, 0), (9, 64, 16, 16), (1000, 256, 9216, 16), (1537, 128, 9232, 0),
+          (2040, 128, 4112, 16), (2041, 128, 4112, 16)]
+
+
+@pytest.mark.parametrize("wait", ["waits", "gives_up"])
+@pytest.mark.parametrize("t,c_in,c_out,r", _CASES, ids=["%dx%dx%d_r%d" % c for c in _CASES])
+def test_few_rows(t, c_in, c_out, r, wait):
+    from paper_2505_14742_amd import binding as q
+    ec = synth.EdgeCase("few_rows", t, c_in, c_out, [0, 5, 31, c_in - 1], r)
+    print("few rows", t, c_in, c_out, r, wait, flush=True)
+    sys.stdout.flush()
+    X, dY, W, O, A, B = synth.edge_case_inputs(ec, 91)
+    prev = q.debug_grid_wait_ticks(0) if wait == "gives_up" else None
+    try:
+        _compare(W, O, A if r else None, B if r else None, 0.5, [X, X[::-1].copy()], 0.2, "few rows t=%d" % t)
+    finally:
+        if prev is not None:
+            q.debug_grid_wait_ticks(prev)
