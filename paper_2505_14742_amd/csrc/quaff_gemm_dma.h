@@ -1,17 +1,21 @@
-// INT8 MFMA GEMM main kernel: operand tiles stream global -> LDS with direct-to-LDS loads (no register staging)
-// through a ring of buffers and fragments are double-buffered in registers.  Two main loops: 64-byte stages (one
-// barrier per 64-byte contraction step, in the middle of the step so that the MFMAs of one half cover the LDS latency
-// of the other) and, for contractions that are a multiple of 128, wide stages of 128 contraction bytes per row (one
-// barrier per two steps, whole cache lines per direct load); the wide loop also reads the B operand as [K x N] from
-// the packed weight codes for the input-gradient product.  The epilogue stages its operands through the idle ring.
+// INT8 MFMA GEMM kernel: operand tiles stream global -> LDS with direct-to-LDS loads (no register staging) through a ring
+// of stages of 128 contraction bytes per row (whole cache lines per direct load, one barrier per 128 bytes), fragments are
+// double-buffered in registers.  The B operand is contraction-contiguous or, for the input-gradient product, read as
+// [K x N] from the packed weight codes.  The epilogue stages its operands through the idle ring.
 // See quaff_gemm.hip for the computation.
 #pragma once
-#include "quaff_gemm_kernel.h"
+#include "quaff_internal.h"
 #include <type_traits>
 
 
 namespace quaff {
 
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 typedef __attribute__((address_space(3))) int8_t lds_i8;
 typedef __attribute__((address_space(3))) i32x4 lds_i32x4;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -93,18 +97,14 @@ struct BtStage {
     }
 };
 
-template <int BM, int BN, int WGM, int WGN, int STAGES>
+template <int BM, int BN, int WGM, int WGN, int NS>
 struct DmaCfg {
-    static constexpr int BK = 64, BM_ = BM, BN_ = BN;
+    static constexpr int BM_ = BM, BN_ = BN, NS_ = NS;    // NS = stages in the ring
     static constexpr int NW = WGM * WGN, NT = 64 * NW;    // wavefronts / threads per workgroup
     static constexpr int WM = BM / WGM, WN = BN / WGN;    // wavefront tile
     static constexpr int TM = WM / 32, TN = WN / 32;      // 32x32 MFMA blocks per wavefront tile
-    static constexpr int A_BYTES = BM * BK, STAGE_BYTES = (BM + BN) * BK;
-    static constexpr int NGROUP = (BM + BN) / 16;         // 16-row groups per stage, one direct load (1 KiB) each
-    static constexpr int NLOAD = (NGROUP + NW - 1) / NW;  // direct loads per lane per stage
-    static constexpr int STAGES_ = STAGES;
     static constexpr bool WAVE_SCALAR = NW >= 8 && TM * TN <= 6;
-    // Issue order inside a 32-byte contraction sub-step of the wide-stage loop.  Where two or three wavefronts share
+    // Issue order inside a 32-byte contraction sub-step.  Where two or three wavefronts share
     // a SIMD, the MFMAs go first and the LDS reads of the next sub-step follow the first half of them, so that the
     // wait at the top of the next sub-step finds every read landed (-1..-8 % measured).  With one wavefront per SIMD
     // (or only four MFMAs per sub-step) reads and MFMAs alternate one by one instead (bunching the reads, in any of
@@ -113,10 +113,11 @@ struct DmaCfg {
     // not by LDS reads).
     static constexpr bool MFMA_FIRST = NW >= 8 && TM * TN >= 6;
     static constexpr bool DMA_ASM = NW >= 8 && !MFMA_FIRST;      // see dma_load_16: only the 256x128 tile gains (3-6 %)
-    // wide-stage variant (gemm_mainloop_dma128): 128 contraction bytes per row, one direct load fills 8 rows
-    static constexpr int WSTAGE_BYTES = (BM + BN) * 128, A_WBYTES = BM * 128;
-    static constexpr int NGROUP_W = (BM + BN) / 8, NLOAD_W = (NGROUP_W + NW - 1) / NW;
-    static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
+    // a stage: 128 contraction bytes per row of A, then of B; one direct load (1 KiB) fills 8 rows
+    static constexpr int STAGE_BYTES = (BM + BN) * 128, A_BYTES = BM * 128;
+    static constexpr int NGROUP = (BM + BN) / 8;          // 8-row groups per stage
+    static constexpr int NLOAD = (NGROUP + NW - 1) / NW;  // direct loads per lane per stage
+    static constexpr int LDS_BYTES = NS * STAGE_BYTES;
     // epilogue staging (gemm_epilogue_staged): one 64-byte-per-row plane per int8 / bf16 operand below EPI_LIMIT,
     // the fp32 row and column scales in the last SCALE_BYTES of the allocation
     static constexpr int K2_PLANES_BYTES = (BM + BN) * 64;                    // A2 and B2, 64 contraction bytes
@@ -150,119 +151,55 @@ __device__ __forceinline__ bool tile_of_block(const TileMap& t, int bx, int by, 
     return lm < t.rm && tm < t.tiles_m && tn < t.tiles_n;
 }
 
+// Source of the contraction bytes past the end of a ragged contraction.
+static __device__ const __attribute__((aligned(16))) uint32_t kZeroChunk[4] = {0u, 0u, 0u, 0u};
+
 // The main loop.  `dma` and `rd` both point at the LDS ring; they are separate restrict-qualified parameters so that
 // the compiler does not serialise every LDS read behind all outstanding direct loads - the ordering between a
 // stage's loads and its reads is enforced here with explicit vmcnt waits and barriers.
-template <class C>
-__device__ __forceinline__ void gemm_mainloop_dma(const int8_t* __restrict__ gA, const int8_t* __restrict__ gB,
-                                                  const uint32_t (&voff)[C::NLOAD], int KT,
-                                                  lds_i8* __restrict__ dma, const lds_i8* __restrict__ rd, int wave,
-                                                  int a_frag_off, int b_frag_off, int b_step,
-                                                  i32x16 (&acc)[C::TM][C::TN]) {
-    constexpr int TM = C::TM, TN = C::TN, NLOAD = C::NLOAD, STAGES = C::STAGES_;
-
-    auto issue = [&](int tile, int stage) {
-        const int64_t k0 = (int64_t)tile * C::BK, kb = (int64_t)tile * b_step;   // b_step: bytes of B per stage
+// The ring holds NS stages of 128 contraction bytes per row: a direct load fetches 128-byte row segments - whole cache
+// lines - and one barrier serves four 32-byte MFMA steps.  Row r of a stage is 128 bytes, its 16-byte chunk c sits in slot
+// c ^ ((r >> 1) & 7): fragment reads (32 rows x one chunk per half wavefront) are then bank-conflict free.
+// BT: B is read as [K x N] from the packed weight codes (see BtStage); b_off[j] is then this lane's byte offset of the
+// 8-byte piece it addresses for column block j in the first 32-row sub-step of a stage.
+// RAGGED: K is not a multiple of 128 (`k_last` bytes, a multiple of 16, are left for the last stage).  In the last stage the
+// lanes whose 16-byte chunk (BT: contraction row) lies past the end fetch zeros instead, in both operands, so that no
+// byte outside the operands is touched and the products of the padding vanish; the iterations that request the last
+// stage are a second copy of the loop body, the others carry no extra instruction.  (A contraction that is a multiple of 64
+// used to run through stages of 64 bytes and one of 16 through a kernel that staged its operands in registers:
+// 1003 x 2064 x 1040 forward 26.3 -> 19.3 us, its input gradient 34.2 -> 25.3 us.)
+template <class C, bool BT, bool RAGGED>
+__device__ __forceinline__ void gemm_mainloop(const int8_t* __restrict__ gA, const int8_t* __restrict__ gB,
+                                              const uint32_t (&voff)[C::NLOAD], int KT, int k_last,
+                                              lds_i8* __restrict__ dma, const lds_i8* __restrict__ rd, int wave, int lane,
+                                              int a_frag_off, const int (&b_off)[C::TN], int64_t b_step,
+                                              i32x16 (&acc)[C::TM][C::TN]) {
+    constexpr int TM = C::TM, TN = C::TN, NLOAD = C::NLOAD;   // b_step: bytes between consecutive stages of B
+    auto issue = [&](int tile, int stage, auto last) {
+        const int8_t* const pa = gA + (int64_t)tile * 128;
+        const int8_t* const pb = gB + tile * b_step;
 #pragma unroll
         for (int j = 0; j < NLOAD; ++j) {
-            // group q of the stage: A rows first, then B rows.  A wavefront whose last slot falls past the end repeats
-            // its previous group (same bytes to the same place), so every wavefront issues NLOAD loads per stage
+            // A rows first, then B rows.  A wavefront whose last slot falls past the end repeats its previous group
+            // (same bytes to the same place), so every wavefront issues NLOAD loads per stage
             int q = j * C::NW + wave;
             if (q >= C::NGROUP) q -= C::NW;
-            const bool isA = q < C::A_BYTES / 1024;
-            const int8_t* src = (isA ? gA + k0 : gB + kb) + voff[j];
+            const bool isA = q < C::BM_ / 8;
+            const int8_t* src = (isA ? pa : pb) + voff[j];
+            if constexpr (decltype(last)::value) {
+                int k = ((lane & 7) ^ ((q * 4 + (lane >> 4)) & 7)) * 16;     // this lane's chunk of its row (see the loader)
+                if (BT && !isA) {
+                    int col;
+                    BtStage<C::BN_>::slot_source((q - C::BM_ / 8) * 64 + lane, k, col);
+                }
+                if (k >= k_last) src = reinterpret_cast<const int8_t*>(kZeroChunk);
+            }
             lds_i8* dst = dma + stage * C::STAGE_BYTES + q * 1024;
             dma_load_16<C::DMA_ASM>(src, dst);
         }
     };
     auto read_frags = [&](int stage, int ks, i32x4 (&fa)[TM], i32x4 (&fb)[TN]) {
         const lds_i8* base = rd + stage * C::STAGE_BYTES;
-        const int x = ks * 32;   // second half of the 64-byte row: chunk index ^ 2
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = *(const lds_i32x4*)(base + ((a_frag_off + i * 2048) ^ x));
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[j] = *(const lds_i32x4*)(base + C::A_BYTES + ((b_frag_off + j * 2048) ^ x));
-    };
-    auto mfmas = [&](const i32x4 (&fa)[TM], const i32x4 (&fb)[TN]) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    };
-    // issue order inside a half step: one LDS read (and at most one direct load), then a share of the MFMAs
-    constexpr int MFMA_PER_READ = (TM * TN) / (TM + TN) > 0 ? (TM * TN) / (TM + TN) : 1;
-
-    // prologue: fill the ring (tiles beyond the last are clamped to it: harmless rewrites of a free stage)
-#pragma unroll
-    for (int s = 0; s < STAGES; ++s) issue(s < KT ? s : KT - 1, s);
-    QUAFF_WAIT_VMCNT((STAGES - 1) * NLOAD);
-    __builtin_amdgcn_s_barrier();
-
-    i32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    read_frags(0, 0, fa0, fb0);
-    int stage = 0;
-    for (int kt = 0; kt < KT; ++kt) {
-        const int next = (stage + 1 == STAGES) ? 0 : stage + 1;
-        // first half: fragments of the second 32 bytes arrive while the first 32 are multiplied
-        read_frags(stage, 1, fa1, fb1);
-        mfmas(fa0, fb0);
-#pragma unroll
-        for (int u = 0; u < TM + TN; ++u) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, MFMA_PER_READ, 0);
-        }
-        // every wavefront has now read all of `stage`; tile kt+1 must have landed for everybody
-        QUAFF_WAIT_VMCNT((STAGES - 2) * NLOAD);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        {
-            int t = kt + STAGES;
-            issue(t < KT ? t : KT - 1, stage);
-        }
-        read_frags(next, 0, fa0, fb0);
-        mfmas(fa1, fb1);
-#pragma unroll
-        for (int u = 0; u < TM + TN; ++u) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (u < NLOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, MFMA_PER_READ, 0);
-        }
-        stage = next;
-    }
-    QUAFF_WAIT_VMCNT(0);
-}
-
-// Wide-stage variant: the ring holds two stages of 128 contraction bytes per row (the same LDS as four 64-byte stages),
-// so that a direct load fetches 128-byte row segments - whole cache lines - instead of 64-byte ones, and one barrier
-// serves two 64-byte contraction steps.  Row r of a stage is 128 bytes, its 16-byte chunk c sits in slot
-// c ^ ((r >> 1) & 7): fragment reads (32 rows x one chunk per half wavefront) are then bank-conflict free.
-// K must be a multiple of 128.
-// BT: B is read as [K x N] from the packed weight codes (see BtStage); b_off[j] is then this lane's byte offset of the
-// 8-byte piece it addresses for column block j in the first 32-row sub-step of a stage.
-template <class C, bool BT = false>
-__device__ __forceinline__ void gemm_mainloop_dma128(const int8_t* __restrict__ gA, const int8_t* __restrict__ gB,
-                                                     const uint32_t (&voff)[C::NLOAD_W], int KT,
-                                                     lds_i8* __restrict__ dma, const lds_i8* __restrict__ rd, int wave,
-                                                     int a_frag_off, const int (&b_off)[C::TN], int64_t b_step,
-                                                     i32x16 (&acc)[C::TM][C::TN]) {
-    constexpr int TM = C::TM, TN = C::TN, NLOAD = C::NLOAD_W;   // b_step: bytes between consecutive stages of B
-    auto issue = [&](int tile, int stage) {
-        const int8_t* const pa = gA + (int64_t)tile * 128;
-        const int8_t* const pb = gB + tile * b_step;
-#pragma unroll
-        for (int j = 0; j < NLOAD; ++j) {
-            int q = j * C::NW + wave;
-            if (q >= C::NGROUP_W) q -= C::NW;
-            const bool isA = q < C::BM_ / 8;
-            const int8_t* src = (isA ? pa : pb) + voff[j];
-            lds_i8* dst = dma + stage * C::WSTAGE_BYTES + q * 1024;
-            dma_load_16<C::DMA_ASM>(src, dst);
-        }
-    };
-    auto read_frags = [&](int stage, int ks, i32x4 (&fa)[TM], i32x4 (&fb)[TN]) {
-        const lds_i8* base = rd + stage * C::WSTAGE_BYTES;
         const int x = ks * 32;
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[i] = *(const lds_i32x4*)(base + ((a_frag_off + i * 4096) ^ x));
@@ -270,12 +207,12 @@ __device__ __forceinline__ void gemm_mainloop_dma128(const int8_t* __restrict__ 
         for (int j = 0; j < TN; ++j) {
             if constexpr (BT) {
                 constexpr int RS = BtStage<C::BN_>::ROW_STRIDE;
-                const lds_i8* pb = base + C::A_WBYTES + b_off[j] + ks * 32 * RS;
+                const lds_i8* pb = base + C::A_BYTES + b_off[j] + ks * 32 * RS;
                 const i32x2 lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)pb);
                 const i32x2 hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(pb + 8 * RS));
                 fb[j] = (i32x4){lo[0], lo[1], hi[0], hi[1]};
             } else {
-                fb[j] = *(const lds_i32x4*)(base + C::A_WBYTES + ((b_off[0] + j * 4096) ^ x));
+                fb[j] = *(const lds_i32x4*)(base + C::A_BYTES + ((b_off[0] + j * 4096) ^ x));
             }
         }
     };
@@ -320,17 +257,21 @@ __device__ __forceinline__ void gemm_mainloop_dma128(const int8_t* __restrict__ 
             __builtin_amdgcn_sched_group_barrier(0x008, MFMA_PER_READ, 0);
         }
     };
-    constexpr int NS = C::STAGES_ / 2;            // wide stages in the ring
+    constexpr int NS = C::NS_;
     static_assert(NS >= 2 && (NS - 1) * NLOAD < 64, "ring depth / vmcnt range");
+    // prologue: fill the ring (tiles beyond the last are clamped to it: harmless rewrites of a free stage)
 #pragma unroll
-    for (int s = 0; s < NS; ++s) issue(s < KT ? s : KT - 1, s);
+    for (int s = 0; s < NS; ++s) {
+        if (RAGGED && s >= KT - 1) issue(KT - 1, s, std::true_type{});
+        else issue(s < KT ? s : KT - 1, s, std::false_type{});
+    }
     QUAFF_WAIT_VMCNT((NS - 1) * NLOAD);
     __builtin_amdgcn_s_barrier();
 
     i32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
     read_frags(0, 0, fa0, fb0);
     int s = 0;
-    for (int kt = 0; kt < KT; ++kt) {
+    auto step = [&](int kt, auto last) {
         const int next = s + 1 == NS ? 0 : s + 1;
         read_frags(s, 1, fa1, fb1);
         mfmas(fa0, fb0);
@@ -350,17 +291,54 @@ __device__ __forceinline__ void gemm_mainloop_dma128(const int8_t* __restrict__ 
         if constexpr (C::MFMA_FIRST) read_frags(next, 0, fa0, fb0);
         {
             int t = kt + NS;
-            issue(t < KT ? t : KT - 1, s);
+            issue(t < KT ? t : KT - 1, s, last);
         }
         if constexpr (!C::MFMA_FIRST) read_frags(next, 0, fa0, fb0);
         mfmas(fa1, fb1);
         order_reads(true);
         s = next;
-    }
+    };
+    int kt = 0;
+    for (; kt < (RAGGED ? KT - 1 - NS : KT); ++kt) step(kt, std::false_type{});
+    if constexpr (RAGGED)
+        for (; kt < KT; ++kt) step(kt, std::true_type{});        // (these request the last stage)
     QUAFF_WAIT_VMCNT(0);
 }
 
-// Epilogue of the fast kernel.  The operands of the short second product (A2, B2) and of the low-rank term (T, L)
+// Epilogue of the accumulator dump, for the wavefront tile whose first element is (row0, col0).
+template <int TM, int TN>
+__device__ __forceinline__ void gemm_epilogue_dump(const GemmArgs& g, i32x16 (&acc)[TM][TN], int64_t row0, int64_t col0,
+                                                   int l32, int lhi) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int64_t ib = row0 + i * 32;
+        const int64_t frag_row = ib + l32 < g.M ? ib + l32 : g.M - 1;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t jb = col0 + j * 32, col = jb + l32;
+            const int64_t ccol = col < g.N ? col : g.N - 1;
+            if (ib >= g.M || jb >= g.N) continue;
+            i32x16 acc2;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc2[v] = 0;
+            for (int kk = 0; kk < g.K2; kk += 32) {
+                i32x4 a = *reinterpret_cast<const i32x4*>(g.A2 + frag_row * g.K2 + kk + lhi * 16);
+                i32x4 b = *reinterpret_cast<const i32x4*>(g.B2 + ccol * g.K2 + kk + lhi * 16);
+                acc2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc2, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                int64_t row = ib + (v >> 2) * 8 + lhi * 4 + (v & 3);
+                if (row < g.M && col < g.N) {
+                    g.acc1[row * g.N + col] = acc[i][j][v];
+                    if (g.acc2) g.acc2[row * g.N + col] = acc2[v];
+                }
+            }
+        }
+    }
+}
+
+// Epilogue.  The operands of the short second product (A2, B2) and of the low-rank term (T, L)
 // are first copied into the now idle LDS ring with direct loads - one memory round trip for the whole workgroup
 // instead of one per 32x32 block - in the same 64-byte-row, XOR-swizzled layout as the main loop's stages.
 // A whole tile whose staged operands all fit at once (r <= 32) is then finished block by block: acc2 = A2 B2^T
@@ -840,14 +818,14 @@ constexpr unsigned long long kSplitFull = 0x5146474956450000ull;        // | XCD
 constexpr unsigned long long kSplitAbandoned = 0x5146414241440000ull;
 __device__ __forceinline__ unsigned xcc_id() { return __builtin_amdgcn_s_getreg(((4 - 1) << 11) | 20) & 15u; }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool DUMP, int MINB = 1, int PAIR = 0, bool STAGED = false,
-          bool ACCUM = false, bool OUT16 = false, bool BT = false, int KSPLIT = 1>
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool DUMP, bool ACCUM = false, bool OUT16 = false,
+          bool BT = false, bool RAGGED = false, int KSPLIT = 1>
 __global__ void __launch_bounds__(64 * WGM * WGN, MINB)
 gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
-    using C = DmaCfg<BM, BN, WGM, WGN, STAGES>;
+    using C = DmaCfg<BM, BN, WGM, WGN, NS>;
     extern __shared__ __attribute__((aligned(1024))) int8_t lds_raw[];
     lds_i8* lds = (lds_i8*)lds_raw;
-    static_assert(KSPLIT == 1 || (KSPLIT == 2 && PAIR == 2), "the split exists for the wide-stage main loop");
+    static_assert(KSPLIT == 1 || (KSPLIT == 2 && !RAGGED && !DUMP), "a split contraction has whole stages");
 
     int tile_m, tile_n;
     // (split: the two workgroups of a tile are neighbours in y, so they carry the same blockIdx.x = XCD)
@@ -862,160 +840,43 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     const int l32 = lane & 31, lhi = lane >> 5;
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
 
-    // loader: a direct load fills 16 rows x 64 bytes of a stage (A rows first, then B rows); lane -> (row = lane / 4,
-    // slot = lane % 4) and the slot holds global chunk slot ^ ((row / 4) & 3), the swizzle the fragment reads undo
-    if constexpr (PAIR == 2) {
-        // wide stages: a direct load fills 8 rows x 128 bytes; lane -> (row = lane / 8, slot = lane % 8) and the slot
-        // holds global chunk slot ^ ((row >> 1) & 7)
-        uint32_t voffw[C::NLOAD_W];
-#pragma unroll
-        for (int j = 0; j < C::NLOAD_W; ++j) {
-            int q = j * C::NW + wave;
-            if (q >= C::NGROUP_W) q -= C::NW;
-            const bool isA = q < BM / 8;
-            const int local = (isA ? q : q - BM / 8) * 8 + (lane >> 3);
-            const int chunk = (lane & 7) ^ ((local >> 1) & 7);
-            int64_t row = (isA ? m0 : n0) + local;
-            int64_t lim = (isA ? g.M : g.N) - 1;
-            row = row < lim ? row : lim;
-            voffw[j] = (uint32_t)(row * (isA ? g.lda : g.ldb) + chunk * 16);
-            if (!BT && !isA && g.b_layout == kPackedNK) voffw[j] = (uint32_t)weight_code_offset(row, chunk * 16, g.ldb);
-            if (BT && !isA) {
-                // B stored [K x N]: the stage's B part is 128 contraction rows of BN bytes; this lane fills the
-                // 16-byte slot number (q - BM / 8) * 64 + lane of it
-                int krow, lcol;
-                BtStage<BN>::slot_source((q - BM / 8) * 64 + lane, krow, lcol);
-                int64_t col = n0 + lcol;
-                col = col < g.N - 16 ? col : g.N - 16;      // clamp: columns past the edge are never stored
-                voffw[j] = (uint32_t)weight_code_offset(krow, col, g.ldb);
-            }
-        }
-        const int64_t b_step = BT ? 128 * g.ldb : g.b_layout == kPackedNK ? 256 : 128;
-        const int fragw = l32 * 128 + ((lhi ^ ((l32 >> 1) & 7)) * 16);
-        int b_off[C::TN];
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j) {
-            if constexpr (BT) {
-                b_off[j] = BtStage<BN>::piece_offset(lane, wn * C::WN / 32 + j);
-            } else {
-                b_off[j] = wn * C::WN * 128 + fragw + j * 4096;
-            }
-        }
-        i32x16 accw[C::TM][C::TN];
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) accw[i][j][v] = 0;
-        const int KT = (int)(g.K / 128) / KSPLIT;
-        const int a_frag = wm * C::WM * 128 + fragw;
-        gemm_mainloop_dma128<C, BT>(g.A + (int64_t)kh * KT * 128, g.B + kh * KT * b_step, voffw, KT, lds, lds, wave, a_frag,
-                                    b_off, b_step, accw);
-        bool active = true;                                  // does this wavefront finish (dequantise, store) its block
-        if constexpr (KSPLIT == 2) {
-            // Workgroup kh finishes the tile's row half kh: its wavefronts of the other half ("givers") ship their
-            // accumulators to the partner workgroup, its wavefronts of row half kh ("takers") add what the partner's
-            // same-numbered wavefronts ship.  Thread tid of one workgroup writes slot tid, thread tid of the other
-            // reads it: piece q of a thread at [q][tid], so that every store and load covers whole lines.
-            constexpr int NV = C::TM * C::TN * 4;          // 16-byte pieces of a lane's accumulators
-            const int64_t tile_id = (int64_t)tile_m * tmap.tiles_n + tile_n;
-            // (the two flags of a tile sit 128 bytes apart, each in a line of its own)
-            unsigned long long* flags = reinterpret_cast<unsigned long long*>(g.split_scratch) + tile_id * 32;
-            i32x4* xb = reinterpret_cast<i32x4*>(static_cast<char*>(g.split_scratch) +
-                                                 (size_t)tmap.tiles_m * tmap.tiles_n * 256) +
-                        tile_id * NV * C::NT + tid;
-            const bool giver = (wm >= WGM / 2) == (kh == 0);
-            active = !giver;
-            if (giver) {
-#pragma unroll
-                for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            xb[((i * C::TN + j) * 4 + q) * C::NT] = (i32x4){accw[i][j][4 * q], accw[i][j][4 * q + 1],
-                                                                             accw[i][j][4 * q + 2], accw[i][j][4 * q + 3]};
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's pieces have reached the L2
-            }
-            __syncthreads();     // all givers of this workgroup have written; nobody reads the ring any more
-            if (tid == 0) {
-                // raise this workgroup's flag ...
-                const unsigned long long old = __hip_atomic_exchange(flags + 16 * kh, kSplitFull | xcc_id(), __ATOMIC_RELAXED,
-                                                                     __HIP_MEMORY_SCOPE_AGENT);
-                if (old == kSplitAbandoned)     // (the partner stopped waiting and does the work itself)
-                    __hip_atomic_store(flags + 16 * kh, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // ... and wait, for a bounded time, for the partner's
-                unsigned long long* theirs = flags + 16 * (1 - kh);
-                const long long t0 = (long long)wall_clock64();
-                unsigned long long w;
-                int take = 0;
-                for (;;) {
-                    w = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if ((w & ~15ull) == kSplitFull) break;
-                    if ((long long)wall_clock64() - t0 >= g.split_wait_ticks) {
-                        w = __hip_atomic_exchange(theirs, kSplitAbandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(2);
-                }
-                if ((w & ~15ull) == kSplitFull) {
-                    take = (unsigned)(w & 15ull) == xcc_id();
-                    if (!take) __hip_atomic_store(theirs, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                *reinterpret_cast<volatile int*>(lds_raw) = take;
-            }
-            __syncthreads();
-            const int take = *reinterpret_cast<volatile int*>(lds_raw);
-            __syncthreads();
-            if (take) {
-                if (active) {
-#pragma unroll
-                    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const i32x4 v = xb[((i * C::TN + j) * 4 + q) * C::NT];
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) accw[i][j][4 * q + e] += v[e];
-                            }
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                }
-                __syncthreads();                 // all pieces read: the partner's flag goes back to zero
-                if (tid == 0) __hip_atomic_store(flags + 16 * (1 - kh), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                // the other half of the contraction, computed here (the givers' sums are not used again)
-                gemm_mainloop_dma128<C, BT>(g.A + (int64_t)(1 - kh) * KT * 128, g.B + (1 - kh) * KT * b_step, voffw, KT,
-                                            lds, lds, wave, a_frag, b_off, b_step, accw);
-            }
-        }
-        if constexpr (STAGED && !DUMP)
-            gemm_epilogue_staged<C, ACCUM, OUT16>(g, accw, lds, lds, m0, n0, wm, wn, wave, lane, active);
-        else
-            gemm_epilogue<C::TM, C::TN, DUMP>(g, accw, m0 + wm * C::WM, n0 + wn * C::WN, l32, lhi);
-        return;
-    }
-    static_assert(!BT || PAIR == 2, "the [K x N] B layout exists for the wide-stage main loop only");
+    // loader: a direct load fills 8 rows x 128 bytes; lane -> (row = lane / 8, slot = lane % 8) and the slot holds global
+    // chunk slot ^ ((row >> 1) & 7), the swizzle the fragment reads undo.  Offsets are 32-bit, from the tile's first row.
+    const int8_t* const tileA = g.A + m0 * g.lda;
+    const int8_t* const tileB = BT ? g.B : g.B + n0 * g.ldb;      // (n0 is even: the packed rows come in pairs)
     uint32_t voff[C::NLOAD];
-    {
-        const int r = lane >> 2, chunk = (lane & 3) ^ ((lane >> 4) & 3);
 #pragma unroll
-        for (int j = 0; j < C::NLOAD; ++j) {
-            int q = j * C::NW + wave;
-            if (q >= C::NGROUP) q -= C::NW;
-            const bool isA = q < BM / 16;
-            int local = (isA ? q : q - BM / 16) * 16 + r;
-            int64_t row = (isA ? m0 : n0) + local;
-            int64_t lim = (isA ? g.M : g.N) - 1;
-            row = row < lim ? row : lim;                        // clamp: rows past the edge are never stored
-            voff[j] = (uint32_t)(row * (isA ? g.lda : g.ldb) + chunk * 16);
-            if (!isA && g.b_layout == kPackedNK) voff[j] = (uint32_t)weight_code_offset(row, chunk * 16, g.ldb);
+    for (int j = 0; j < C::NLOAD; ++j) {
+        int q = j * C::NW + wave;
+        if (q >= C::NGROUP) q -= C::NW;
+        const bool isA = q < BM / 8;
+        int row = (isA ? q : q - BM / 8) * 8 + (lane >> 3);
+        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+        const int64_t lim = (isA ? g.M - m0 : g.N - n0) - 1;
+        row = row < lim ? row : (int)lim;                        // clamp: rows past the edge are never stored
+        voff[j] = (uint32_t)row * (uint32_t)(isA ? g.lda : g.ldb) + chunk * 16;
+        if (!BT && !isA && g.b_layout == kPackedNK) voff[j] = (uint32_t)weight_code_offset(row, chunk * 16, g.ldb);
+        if (BT && !isA) {
+            // B stored [K x N]: the stage's B part is 128 contraction rows of BN bytes; this lane fills the
+            // 16-byte slot number (q - BM / 8) * 64 + lane of it
+            int krow, lcol;
+            BtStage<BN>::slot_source((q - BM / 8) * 64 + lane, krow, lcol);
+            int64_t col = n0 + lcol;
+            col = col < g.N - 16 ? col : g.N - 16;      // clamp: columns past the edge are never stored
+            voff[j] = (uint32_t)weight_code_offset(krow, col, g.ldb);
         }
     }
-    const int frag = l32 * 64 + ((lhi ^ ((l32 >> 2) & 3)) * 16);
-    const int a_frag_off = wm * C::WM * 64 + frag, b_frag_off = wn * C::WN * 64 + frag;
-
+    const int64_t b_step = BT ? 128 * g.ldb : g.b_layout == kPackedNK ? 256 : 128;
+    const int frag = l32 * 128 + ((lhi ^ ((l32 >> 1) & 7)) * 16);
+    int b_off[C::TN];
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) {
+        if constexpr (BT) {
+            b_off[j] = BtStage<BN>::piece_offset(lane, wn * C::WN / 32 + j);
+        } else {
+            b_off[j] = wn * C::WN * 128 + frag + j * 4096;
+        }
+    }
     i32x16 acc[C::TM][C::TN];
 #pragma unroll
     for (int i = 0; i < C::TM; ++i)
@@ -1023,15 +884,99 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-
-    gemm_mainloop_dma<C>(g.A, g.B, voff, (int)(g.K / C::BK), lds, lds, wave, a_frag_off, b_frag_off,
-                         g.b_layout == kPackedNK ? 128 : 64, acc);
-
-    if constexpr (STAGED && !DUMP)
-        gemm_epilogue_staged<C, ACCUM, OUT16>(g, acc, lds, lds, m0, n0, wm, wn, wave, lane);
+    const int KT = RAGGED ? (int)((g.K + 127) / 128) : (int)(g.K / 128) / KSPLIT;
+    const int k_last = (int)(g.K - (int64_t)(KT - 1) * 128);
+    const int a_frag = wm * C::WM * 128 + frag;
+    gemm_mainloop<C, BT, RAGGED>(tileA + (int64_t)kh * KT * 128, tileB + kh * KT * b_step, voff, KT, k_last, lds, lds, wave,
+                                 lane, a_frag, b_off, b_step, acc);
+    bool active = true;                                  // does this wavefront finish (dequantise, store) its block
+    if constexpr (KSPLIT == 2) {
+        // Workgroup kh finishes the tile's row half kh: its wavefronts of the other half ("givers") ship their
+        // accumulators to the partner workgroup, its wavefronts of row half kh ("takers") add what the partner's
+        // same-numbered wavefronts ship.  Thread tid of one workgroup writes slot tid, thread tid of the other
+        // reads it: piece q of a thread at [q][tid], so that every store and load covers whole lines.
+        constexpr int NV = C::TM * C::TN * 4;          // 16-byte pieces of a lane's accumulators
+        const int64_t tile_id = (int64_t)tile_m * tmap.tiles_n + tile_n;
+        // (the two flags of a tile sit 128 bytes apart, each in a line of its own)
+        unsigned long long* flags = reinterpret_cast<unsigned long long*>(g.split_scratch) + tile_id * 32;
+        i32x4* xb = reinterpret_cast<i32x4*>(static_cast<char*>(g.split_scratch) +
+                                             (size_t)tmap.tiles_m * tmap.tiles_n * 256) +
+                    tile_id * NV * C::NT + tid;
+        const bool giver = (wm >= WGM / 2) == (kh == 0);
+        active = !giver;
+        if (giver) {
+#pragma unroll
+            for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+                for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        xb[((i * C::TN + j) * 4 + q) * C::NT] = (i32x4){acc[i][j][4 * q], acc[i][j][4 * q + 1],
+                                                                         acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's pieces have reached the L2
+        }
+        __syncthreads();     // all givers of this workgroup have written; nobody reads the ring any more
+        if (tid == 0) {
+            // raise this workgroup's flag ...
+            const unsigned long long old = __hip_atomic_exchange(flags + 16 * kh, kSplitFull | xcc_id(), __ATOMIC_RELAXED,
+                                                                 __HIP_MEMORY_SCOPE_AGENT);
+            if (old == kSplitAbandoned)     // (the partner stopped waiting and does the work itself)
+                __hip_atomic_store(flags + 16 * kh, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // ... and wait, for a bounded time, for the partner's
+            unsigned long long* theirs = flags + 16 * (1 - kh);
+            const long long t0 = (long long)wall_clock64();
+            unsigned long long w;
+            int take = 0;
+            for (;;) {
+                w = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((w & ~15ull) == kSplitFull) break;
+                if ((long long)wall_clock64() - t0 >= g.split_wait_ticks) {
+                    w = __hip_atomic_exchange(theirs, kSplitAbandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(2);
+            }
+            if ((w & ~15ull) == kSplitFull) {
+                take = (unsigned)(w & 15ull) == xcc_id();
+                if (!take) __hip_atomic_store(theirs, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            *reinterpret_cast<volatile int*>(lds_raw) = take;
+        }
+        __syncthreads();
+        const int take = *reinterpret_cast<volatile int*>(lds_raw);
+        __syncthreads();
+        if (take) {
+            if (active) {
+#pragma unroll
+                for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const i32x4 v = xb[((i * C::TN + j) * 4 + q) * C::NT];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+                        }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            __syncthreads();                 // all pieces read: the partner's flag goes back to zero
+            if (tid == 0) __hip_atomic_store(flags + 16 * (1 - kh), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            // the other half of the contraction, computed here (the givers' sums are not used again)
+            gemm_mainloop<C, BT, false>(tileA + (int64_t)(1 - kh) * KT * 128, tileB + (1 - kh) * KT * b_step, voff, KT,
+                                        k_last, lds, lds, wave, lane, a_frag, b_off, b_step, acc);
+        }
+    }
+    if constexpr (DUMP)
+        gemm_epilogue_dump<C::TM, C::TN>(g, acc, m0 + wm * C::WM, n0 + wn * C::WN, l32, lhi);
     else
-        gemm_epilogue<C::TM, C::TN, DUMP>(g, acc, m0 + wm * C::WM, n0 + wn * C::WN, l32, lhi);
+        gemm_epilogue_staged<C, ACCUM, OUT16>(g, acc, lds, lds, m0, n0, wm, wn, wave, lane, active);
 }
+
+// Tile shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
+enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTileSplit };
+hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
+hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 
 // host side: choose the XCD region grid for a grid of bm x bn tiles.  Padded work first (a surplus workgroup idles a
 // compute unit for a whole pass), then the operand rows an XCD has to fetch into its own L2: rm * bm rows of A plus

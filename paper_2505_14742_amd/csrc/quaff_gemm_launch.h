@@ -1,0 +1,47 @@
+// Host side of one tile shape of the INT8 MFMA GEMM (quaff_gemm_dma.h): kernel selection and launch.  The two readings of
+// the B operand are compiled in translation units of their own (quaff_gemm_fwd.hip, quaff_gemm_bwd.hip).
+#pragma once
+#include "quaff_gemm_dma.h"
+
+namespace quaff {
+
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT>
+static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stream) {
+    using C = DmaCfg<BM, BN, WGM, WGN, NS>;
+    int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
+    TileMap tm = make_tile_map(tiles_m, tiles_n, BM, BN, MINB);
+    while ((tm.rm + tm.gm - 1) / tm.gm > 65535) tm.gm *= 2;
+    // x % 8 = XCD, x / 8 = tile row inside a group of gm, y = tile column, z = group; a split contraction doubles y
+    // (the two halves of a tile are neighbours)
+    const int groups = (tm.rm + tm.gm - 1) / tm.gm;
+    dim3 grid(8 * (unsigned)tm.gm, (unsigned)tm.rn * KSPLIT, (unsigned)groups), block(C::NT);
+    if (tm.rn * KSPLIT > 65535) return hipErrorInvalidValue;
+    // the epilogue operands are staged through the idle LDS ring (launch_gemm splits wider second products off)
+    if (!dump && (int64_t)(g.K2 / 64) * C::K2_PLANES_BYTES > C::EPI_LIMIT) return hipErrorInvalidValue;
+    const size_t lds = dump ? C::LDS_BYTES : C::LDS_ALLOC;
+    auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT>;
+    if constexpr (KSPLIT == 2) {
+        if (dump || g.C16 || g.accumulate) return hipErrorInvalidValue;
+    } else {
+        if (dump) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED>;
+        else if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED>;
+        else if (g.accumulate) {
+            // (only a forward product has a wide second product to accumulate onto)
+            if constexpr (BT) return hipErrorInvalidValue;
+            else k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, true, false, BT, RAGGED>;
+        }
+    }
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k, grid, block, lds, stream, g, tm);
+    return hipGetLastError();
+}
+
+// BM x BN tile, WGM x WGN wavefronts, NS stages in the ring, MINB workgroups per compute unit to compile for
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT>
+static hipError_t launch_dma(const GemmArgs& g, bool dump, hipStream_t stream) {
+    if (g.K % 128 != 0) return launch_dma_form<BM, BN, WGM, WGN, NS, MINB, BT, true, 1>(g, dump, stream);
+    return launch_dma_form<BM, BN, WGM, WGN, NS, MINB, BT, false, 1>(g, dump, stream);
+}
+
+}  // namespace quaff

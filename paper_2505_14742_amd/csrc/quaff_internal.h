@@ -190,11 +190,11 @@ struct GemmArgs {
     // (r-contiguous); part p starts M * r elements after part p - 1
     const uint16_t* T_hi; const uint16_t* T_lo; const uint16_t* L; int32_t r;
     float* C; int64_t ldc;         // fp32 output (mode 0)
-    uint16_t* C16;                 // fast kernel only: bf16 output instead of C (same ldc, in elements; not with accumulate)
-    int32_t accumulate;            // fast kernel only: add the result to what C already holds instead of overwriting it
+    uint16_t* C16;                 // bf16 output instead of C (same ldc, in elements; not with accumulate)
+    int32_t accumulate;            // add the result to what C already holds instead of overwriting it
                                    // (selects a separate kernel instantiation)
     int32_t* acc1; int32_t* acc2;  // int32 dumps (mode 1), dense ld = N
-    // optional scratch for a contraction split over two workgroups per tile (fast kernel; gemm_split_bytes(M, N) bytes,
+    // optional scratch for a contraction split over two workgroups per tile (gemm_split_bytes(M, N) bytes,
     // 256-byte aligned; nullptr = never split) and the bound of the taker's wait in 100 MHz ticks
     void* split_scratch; long long split_wait_ticks;
 };
