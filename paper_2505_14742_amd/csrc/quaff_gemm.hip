@@ -7,8 +7,9 @@
 //   C[i, j] = row_scale[i] * ( acc1[i, j] * col_scale[j] + acc2[i, j] * col_scale2[j] ) + sum_p T[i, p] L[j, p]
 //   acc1 = A B^T   (K long, the hot loop),   acc2 = A2 B2^T   (K2 = padded outlier count, done in the epilogue)
 //
-// One kernel template (quaff_gemm_dma.h) serves every shape: direct-to-LDS operand streaming through a ring of stages,
-// v_mfma_i32_32x32x32_i8, XCD-aware tile order; this file chooses the tile shape.
+// One kernel template (quaff_gemm_dma.h) serves every output that fills the chip: direct-to-LDS operand streaming through a
+// ring of stages, v_mfma_i32_32x32x32_i8, XCD-aware tile order; a second one (quaff_gemm_rows.hip) the small ones.  This file
+// chooses between them and the tile shape.
 #include "quaff_gemm_dma.h"
 
 namespace quaff {
@@ -26,7 +27,7 @@ constexpr TileChoice kChoices[4] = {
 
 // Estimated time of a tile shape on 256 compute units: full rounds of spc tiles per unit, then the remainder at one
 // tile per unit per pass.  The shape that wastes the fewest compute-unit passes wins.
-int choose_tile(int64_t M, int64_t N) {
+int choose_tile(int64_t M, int64_t N, double* best_work) {
     int best = 0;
     double best_cost = -1.0;
     for (int c = 0; c < 4; ++c) {
@@ -37,6 +38,36 @@ int choose_tile(int64_t M, int64_t N) {
         double passes = (double)full * t.spc + (double)((rem + 255) / 256);
         double cost = passes * t.bm * t.bn * t.ineff;
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = c; }
+    }
+    *best_work = best_cost;
+    return best;
+}
+
+// Small outputs.  Estimated time of a shape of quaff_gemm_rows.hip: launch and epilogue, then the slower of the two ways its
+// operands arrive - one compute unit's share at `cu_rate`, or all of it at `chip_rate` - and 1.5 us for every further
+// round of 256 tiles (their epilogues do not overlap their loads).  Against it stand 8 us and, per 1024 bytes of contraction,
+// 4.4 us (6.1 with every compute unit busy) per pass of 128 x 192 tiles.  The constants are fitted to 1231 measured products of
+// 1 to 4096 rows, 16 to 16384 columns and contractions: the choice takes 0.41 (forward) and 0.45 (input gradient) of the
+// time of the large tiles alone in the geometric mean and is within 6 % of the best of all measured shapes; in 5 of the
+// 1231 it is more than 3 % slower than the large tiles.  The factor 1.1 keeps close calls where they were.
+struct RowsChoice { int shape, bm, bn; double fixed_us, cu_rate, chip_rate; };   // rates in KB/us and MB/us
+constexpr RowsChoice kRowsForward[4] = {
+    {kRows16x16, 16, 16, 3.2, 83, 11.5}, {kRows32x32, 32, 32, 3.6, 79, 10.2}, {kRows32x64, 32, 64, 4.4, 84, 10.1}, {kRows64x96, 64, 96, 7.9, 80, 7.7}};
+constexpr RowsChoice kRowsGradient[2] = {{kRows16x64, 16, 64, 4.0, 115, 11}, {kRows32x64, 32, 64, 4.5, 85, 10.1}};
+
+int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work) {
+    const double passes = tile_work / (128.0 * 192.0 * kChoices[kTile128x192].ineff);
+    const int64_t wide_tiles = ((M + 127) / 128) * ((N + 191) / 192);
+    const double busy = wide_tiles < 256 ? wide_tiles / 256.0 : 1.0;
+    double best_us = (8.0 + (double)K * 1e-3 * passes * (4.4 + 1.75 * busy)) / 1.1;
+    int best = kRowsNone;
+    for (int c = 0; c < (gradient ? 2 : 4); ++c) {
+        const RowsChoice& r = gradient ? kRowsGradient[c] : kRowsForward[c];
+        const double tiles = (double)((M + r.bm - 1) / r.bm) * (double)((N + r.bn - 1) / r.bn);
+        const double tile_kb = (r.bm + r.bn) * (double)K * 1e-3, rounds = tiles / 256.0;
+        const double per_cu = tile_kb * (rounds > 1.0 ? __builtin_ceil(rounds) : 1.0) / r.cu_rate, chip = tile_kb * tiles * 1e-3 / r.chip_rate;
+        const double us = r.fixed_us + (per_cu > chip ? per_cu : chip) + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0);
+        if (us < best_us) { best_us = us; best = r.shape; }
     }
     return best;
 }
@@ -88,7 +119,12 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
     if (g.split_scratch && !dump_acc && !g.C16 && !g.accumulate && g.K2 <= 128 && split_applies(g.M, g.N, g.K))
         tile = kTileSplit;
     else
-        tile = choose_tile(g.M, g.N);
+    {
+        double work;
+        tile = choose_tile(g.M, g.N, &work);
+        const int rows = choose_rows(g.M, g.N, g.K, g.b_layout == kPackedKN, work);
+        if (rows != kRowsNone) return launch_gemm_rows(g, rows, stream);
+    }
     // The 128 x 192 tile with at most one tile per compute unit takes a ring of three stages (120 KB of LDS: one
     // workgroup per unit): the operands of the stage after next are then in flight too, which is what a product whose
     // operands come from HBM rather than from the Infinity Cache needs (measured back to back on operand sets that

@@ -977,6 +977,9 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
 enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTileSplit };
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
+// The shapes of quaff_gemm_rows.hip (a dump is recognised by g.acc1).
+enum RowsShape { kRows16x16 = 0, kRows32x32, kRows32x64, kRows64x96, kRows16x64, kRowsNone };
+hipError_t launch_gemm_rows(const GemmArgs& g, int shape, hipStream_t stream);
 
 // host side: choose the XCD region grid for a grid of bm x bn tiles.  Padded work first (a surplus workgroup idles a
 // compute unit for a whole pass), then the operand rows an XCD has to fetch into its own L2: rm * bm rows of A plus
