@@ -7,7 +7,7 @@
 // HBM-bound: Q is read once.  bf16 MFMA 16x16x32 with fp32 accumulation.  Both operands have the tokens on the slow
 // axis while the MFMA wants them contiguous per lane, so 64-token tiles of both are staged row-major in LDS (two
 // buffers used in turn, one barrier per tile, the next tile's global loads in flight while this one is multiplied) and
-// a lane gathers its eight tokens with 2-byte reads.  P arrives as the hi/lo bf16 parts the down-projection kernel
+// a lane gets its eight tokens by two transposing reads.  P arrives as the hi/lo bf16 parts the down-projection kernel
 // writes (one pair per half of its contraction range) and is folded to one hi/lo pair while it is staged.  Both
 // products of a layer run in one launch.  The token range is cut into slabs over workgroups; the slabs' partial
 // results are summed in a fixed order by a second launch that fills the chip, so the result is deterministic.
@@ -23,10 +23,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kGradCols = 128;       // columns of Q per workgroup (eight 16-column MFMA blocks, two per wavefront)
+constexpr int kGradCols = 128;       // columns of Q per workgroup of four wavefronts (two 16-column MFMA blocks each)
 constexpr int kGradTokens = 64;      // tokens per staged tile
-constexpr int kGradRowBytes = 264;   // LDS row stride of a Q tile: 256 bytes of data + 8, so that the four 8-row groups
-                                     // of a gather fall into disjoint banks
 
 __device__ __forceinline__ uint32_t grad_f32_to_bf16_rne(float f) {
     uint32_t u = __float_as_uint(f);
@@ -41,13 +39,13 @@ void lora_grad_plan(int64_t t, int64_t c, int* nslab, int* rows_per_slab) {
     // longer with every slab (measured at 2048 tokens: 16 slabs 41 / 31 us per call for the two Phi-3 attention
     // projections, 8 slabs 36 / 29 us, 4 slabs 38 / 31 us)
     if (want > 8) want = 8;
+    // up to 256 tokens one slab, written straight to the result: the launch that sums them costs more than the tiles
+    if (tiles <= 4) want = 1;
     if (want > tiles) want = tiles;
-    if (want < 1) want = 1;
     const int64_t rows = ((tiles + want - 1) / want) * kGradTokens;
     *rows_per_slab = (int)rows;
     *nslab = (int)((tiles * kGradTokens + rows - 1) / rows);
 }
-int lora_grad_chunks(int64_t c) { return (int)((c + kGradCols - 1) / kGradCols); }
 
 // partial[slab][p][j] = sum over the slab's tokens i of P[i, p] Q[i, j];  P = the sum of the kLoraParts hi/lo pairs of T.
 // One of the two products of a launch (blockIdx.z selects it).
@@ -55,18 +53,34 @@ struct GradProblem {
     const uint16_t* Q; int64_t ldq; int c;
     const uint16_t* T_hi; const uint16_t* T_lo;       // [kLoraParts][t][r]
     int rows_per_slab, nslab, chunks;
-    float* partial; float* out; int transposed;
+    float* partial; int transposed;                   // [nslab][r][c], or [nslab][c][r] if transposed
+    float* out;                                       // their sum (nslab = 1: partial = out)
 };
 struct GradPair { GradProblem p[2]; };
 
-template <int R16>
-__global__ void __launch_bounds__(256)
+// The transposing LDS read: in each group of 16 lanes, lane i receives 16-bit element i % 4 of the 8-byte pieces addressed by
+// lanes i / 4 + 4 j, j = 0..3; lane a of a group therefore addresses row a / 4 of four, elements 4 (a % 4) .. + 3 of 16.
+typedef short grad_v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) grad_v4s lds_grad_v4s;
+
+// LDS position of 32-byte pair `pair` (16 columns) of token row `row` in a Q tile of NPAIR pairs per row: the pairs of the
+// eight rows that half a wavefront's transposing read touches (four rows, and four rows 8 further on) lie in different banks.
+template <int NPAIR>
+__device__ __forceinline__ int grad_q_offset(int row, int pair) {
+    return row * NPAIR * 32 + (pair ^ (row & 3) ^ ((row >> 1) & 4)) * 32;
+}
+
+// NW wavefronts, 32 columns each.  (The operands used to be gathered with 2-byte LDS reads, ten times as many instructions
+// at rank 64 as the MFMAs they feed; with the slab sum below, the whole call at 4096 x (4096, 11008) and rank 64 went from 147
+// to 99 us, 512 x (3072, 3072) at rank 16 from 18.5 to 15.7.)
+template <int R16, int NW>
+__global__ void __launch_bounds__(NW * 64)
 lora_grad_kernel(GradPair pair, int64_t t) {
-    constexpr int r = R16 * 16;
-    constexpr int PSTR = r * 2 + 4;                       // bytes per token of a staged P tile (+4: disjoint banks)
-    constexpr int QTILE = kGradTokens * kGradRowBytes, PTILE = kGradTokens * PSTR;
+    constexpr int r = R16 * 16, NT = NW * 64, COLS = NW * 32;
+    constexpr int PSTR = r * 2 == 128 ? 160 : r * 2;      // bytes per token of a staged P tile (four rows in disjoint banks)
+    constexpr int QTILE = kGradTokens * COLS * 2, PTILE = kGradTokens * PSTR;
     constexpr int PV = kGradTokens * r / 8;               // 16-byte vectors of a P tile
-    constexpr int PJ = (PV + 255) / 256;                  // ... per thread
+    constexpr int PJ = (PV + NT - 1) / NT;                // ... per thread
     const GradProblem& pb = pair.p[blockIdx.z];
     if ((int)blockIdx.x >= pb.chunks || (int)blockIdx.y >= pb.nslab) return;
     const uint16_t* __restrict__ Q = pb.Q;
@@ -79,15 +93,16 @@ lora_grad_kernel(GradPair pair, int64_t t) {
     uint8_t* const pt = grad_lds + 2 * QTILE;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
-    const int c0 = blockIdx.x * kGradCols;
+    const int c0 = blockIdx.x * COLS;
     const int64_t t_pad = (t + kGradTokens - 1) / kGradTokens * kGradTokens;
     const int64_t i_begin = (int64_t)blockIdx.y * pb.rows_per_slab;
     const int64_t i_end = i_begin + pb.rows_per_slab < t_pad ? i_begin + pb.rows_per_slab : t_pad;
 
-    // loaders.  Q: 64 rows x 256 bytes = 1024 vectors of 16 bytes, four per thread (rows tid / 16 + 16 h).
+    // loaders.  Q: 64 rows x COLS columns, four 16-byte vectors per thread (rows tid / (COLS / 8) + 16 h).
     // P: token tok, rank indices p0 .. p0 + 7 of each of the four arrays (hi / lo of the two contraction parts).
-    const int ld_row = tid >> 4;
-    int ld_col = c0 + (tid & 15) * 8;
+    constexpr int QV = COLS / 8;
+    const int ld_row = tid / QV;
+    int ld_col = c0 + (tid % QV) * 8;
     if (ld_col > c - 8) ld_col = c - 8;        // columns past the edge repeat valid data and are never stored
     struct TileRegs { u32x4 q[4]; u32x4 p[PJ][2 * kLoraParts]; };
     auto load_tile = [&](int64_t i0, TileRegs& tr) {
@@ -101,7 +116,7 @@ lora_grad_kernel(GradPair pair, int64_t t) {
         }
 #pragma unroll
         for (int j = 0; j < PJ; ++j) {
-            const int v = tid + 256 * j;
+            const int v = tid + NT * j;
             const int tok = v / (r / 8), p0 = (v % (r / 8)) * 8;
             const int64_t i = i0 + tok;
 #pragma unroll
@@ -119,14 +134,12 @@ lora_grad_kernel(GradPair pair, int64_t t) {
         const u32x4 (&qreg)[4] = tr.q;
         const u32x4 (&preg)[PJ][2 * kLoraParts] = tr.p;
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            uint8_t* dst = qt + buf * QTILE + (ld_row + 16 * h) * kGradRowBytes + (tid & 15) * 16;
-            *reinterpret_cast<u32x2*>(dst) = (u32x2){qreg[h][0], qreg[h][1]};
-            *reinterpret_cast<u32x2*>(dst + 8) = (u32x2){qreg[h][2], qreg[h][3]};
-        }
+        for (int h = 0; h < 4; ++h)
+            *reinterpret_cast<u32x4*>(qt + buf * QTILE + grad_q_offset<COLS / 16>(ld_row + 16 * h, (tid % QV) >> 1) + (tid & 1) * 16) =
+                qreg[h];
 #pragma unroll
         for (int j = 0; j < PJ; ++j) {
-            const int v = tid + 256 * j;
+            const int v = tid + NT * j;
             if (v >= PV) continue;
             const int tok = v / (r / 8), p0 = (v % (r / 8)) * 8;
             uint32_t hi2[4], lo2[4];
@@ -151,22 +164,14 @@ lora_grad_kernel(GradPair pair, int64_t t) {
                 hi2[w] = hpair;
                 lo2[w] = lpair;
             }
-            uint32_t* dh = reinterpret_cast<uint32_t*>(pt + (buf * 2 + 0) * PTILE + tok * PSTR + p0 * 2);
-            uint32_t* dl = reinterpret_cast<uint32_t*>(pt + (buf * 2 + 1) * PTILE + tok * PSTR + p0 * 2);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) { dh[w] = hi2[w]; dl[w] = lo2[w]; }
+            *reinterpret_cast<u32x4*>(pt + (buf * 2 + 0) * PTILE + tok * PSTR + p0 * 2) = (u32x4){hi2[0], hi2[1], hi2[2], hi2[3]};
+            *reinterpret_cast<u32x4*>(pt + (buf * 2 + 1) * PTILE + tok * PSTR + p0 * 2) = (u32x4){lo2[0], lo2[1], lo2[2], lo2[3]};
         }
     };
-    // eight tokens (rows row0 .. row0 + 7 of a staged tile) of one 2-byte column, as an MFMA operand
-    auto gather8 = [&](const uint8_t* base, int stride) {
-        u32x4 q;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const uint32_t lo = *reinterpret_cast<const uint16_t*>(base + (2 * jj) * stride);
-            const uint32_t hi = *reinterpret_cast<const uint16_t*>(base + (2 * jj + 1) * stride);
-            q[jj] = lo | (hi << 16);
-        }
-        return q;
+    auto join8 = [](const uint8_t* first4, const uint8_t* last4) {
+        const grad_v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_grad_v4s*)first4);
+        const grad_v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_grad_v4s*)last4);
+        return __builtin_bit_cast(u32x4, (short __attribute__((ext_vector_type(8)))){a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
     };
 
     f32x4 acc[R16][2];
@@ -178,18 +183,19 @@ lora_grad_kernel(GradPair pair, int64_t t) {
     auto multiply_tile = [&](int buf) {
 #pragma unroll
         for (int sub = 0; sub < kGradTokens / 32; ++sub) {
-            const int row0 = sub * 32 + g * 8;
+            const int row = sub * 32 + g * 8 + (n >> 2), in = (n & 3) * 8;       // this lane's row of the first four tokens
             u32x4 ah[R16], al[R16];
 #pragma unroll
             for (int b = 0; b < R16; ++b) {
-                ah[b] = gather8(pt + (buf * 2 + 0) * PTILE + row0 * PSTR + (b * 16 + n) * 2, PSTR);
-                al[b] = gather8(pt + (buf * 2 + 1) * PTILE + row0 * PSTR + (b * 16 + n) * 2, PSTR);
+                const uint8_t* ph = pt + (buf * 2 + 0) * PTILE + row * PSTR + b * 32 + in;
+                ah[b] = join8(ph, ph + 4 * PSTR);
+                al[b] = join8(ph + PTILE, ph + PTILE + 4 * PSTR);
             }
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
-                // second operand: tokens row0 .. row0 + 7 of column c0 + 16 (2 wave + f) + n
-                const u32x4 q = gather8(qt + buf * QTILE + row0 * kGradRowBytes + ((wave * 2 + f) * 16 + n) * 2,
-                                        kGradRowBytes);
+                // second operand: eight tokens of column c0 + 16 (2 wave + f) + n
+                const uint8_t* q0 = qt + buf * QTILE + in;
+                const u32x4 q = join8(q0 + grad_q_offset<COLS / 16>(row, wave * 2 + f), q0 + grad_q_offset<COLS / 16>(row + 4, wave * 2 + f));
 #pragma unroll
                 for (int b = 0; b < R16; ++b) {
                     acc[b][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ah[b]),
@@ -226,31 +232,42 @@ lora_grad_kernel(GradPair pair, int64_t t) {
         const int col = c0 + (wave * 2 + f) * 16 + n;
         if (col >= c) continue;
 #pragma unroll
-        for (int b = 0; b < R16; ++b)
+        for (int b = 0; b < R16; ++b) {
+            if (pb.transposed) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) out[(int64_t)(b * 16 + g * 4 + v) * c + col] = acc[b][f][v];
+                for (int v = 0; v < 4; ++v) out[(int64_t)col * r + b * 16 + g * 4 + v] = acc[b][f][v];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[(int64_t)(b * 16 + g * 4 + v) * c + col] = acc[b][f][v];
+            }
+        }
     }
 }
 
-// out = sum over slabs (fixed order) of partial[slab]; transposed = write out[j][p] instead of out[p][j]
+// out = sum over slabs (fixed order) of partial[slab], four elements per thread.  (The partial results lie as the result does:
+// with dA's slabs in the other order, read across, this launch took 20 us at 4096 x 4096 and rank 64.)
 __global__ void __launch_bounds__(256)
 lora_grad_reduce_kernel(GradPair pair, int r) {
     const GradProblem& pb = pair.p[blockIdx.y];
     const float* __restrict__ partial = pb.partial;
     float* __restrict__ out = pb.out;
-    const int nslab = pb.nslab, c = pb.c, transposed = pb.transposed;
-    const int64_t total = (int64_t)r * c;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        // consecutive threads take consecutive output addresses
-        const int64_t p = transposed ? e % r : e / c, j = transposed ? e / r : e % c;
-        float s = 0.0f;
-        for (int sl = 0; sl < nslab; ++sl) s += partial[((int64_t)sl * r + p) * c + j];
-        out[e] = s;
+    const int nslab = pb.nslab;
+    if (nslab == 1) return;
+    const int64_t total = (int64_t)r * pb.c;               // a multiple of 256
+    for (int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; e < total; e += (int64_t)gridDim.x * 1024) {
+        f32x4 v[8], s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int sl = 0; sl < 8; ++sl) v[sl] = *reinterpret_cast<const f32x4*>(partial + (sl < nslab ? sl : 0) * total + e);
+#pragma unroll
+        for (int sl = 0; sl < 8; ++sl)
+            if (sl < nslab) s += v[sl];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) out[e + u] = s[u];
     }
 }
 
-size_t lora_grad_lds_bytes(int32_t r) {
-    return 2 * (size_t)kGradTokens * kGradRowBytes + 4 * (size_t)kGradTokens * (r * 2 + 4);
+size_t lora_grad_lds_bytes(int32_t r, int cols) {
+    return 2 * (size_t)kGradTokens * cols * 2 + 4 * (size_t)kGradTokens * (r * 2 == 128 ? 160 : r * 2);
 }
 
 // Both gradient products of a layer in one launch:
@@ -263,26 +280,30 @@ hipError_t launch_lora_grad_pair(const uint16_t* X, int64_t ldx, int64_t c_in, c
                                  float* dB, int64_t t, int32_t r, hipStream_t stream) {
     ProfScope prof(K_LORA_GRAD, stream);
     GradPair pair;
+    // From rank 32 on a workgroup takes 256 columns: the tokens' P (512 bytes a token at rank 64, against 256 of Q per 128
+    // columns) is fetched and folded half as often (4096 x (4096, 11008), rank 64: whole call 105 against 99 us; rank 16: level).
+    const bool wide = r >= 32;
+    const int cols = wide ? 2 * kGradCols : kGradCols;
     auto fill = [&](GradProblem& p, const uint16_t* Q, int64_t ldq, int64_t c, const uint16_t* hi, const uint16_t* lo,
                     float* partial, float* out, int transposed) {
         p.Q = Q; p.ldq = ldq; p.c = (int)c; p.T_hi = hi; p.T_lo = lo;
         lora_grad_plan(t, c, &p.nslab, &p.rows_per_slab);
-        p.chunks = lora_grad_chunks(c);
-        p.partial = partial; p.out = out; p.transposed = transposed;
+        p.chunks = (int)((c + cols - 1) / cols);
+        p.partial = p.nslab == 1 ? out : partial; p.out = out; p.transposed = transposed;
     };
     fill(pair.p[0], X, ldx, c_in, T1_hi, T1_lo, partial_a, dA, 1);
     fill(pair.p[1], dY, lddy, c_out, T2_hi, T2_lo, partial_b, dB, 0);
     const int gx = pair.p[0].chunks > pair.p[1].chunks ? pair.p[0].chunks : pair.p[1].chunks;
     const int gy = pair.p[0].nslab > pair.p[1].nslab ? pair.p[0].nslab : pair.p[1].nslab;
     dim3 grid((unsigned)gx, (unsigned)gy, 2);
-    const size_t lds = lora_grad_lds_bytes(r);
+    const size_t lds = lora_grad_lds_bytes(r, cols);
 #define QUAFF_GRAD(N)                                                                                                 \
     case N: {                                                                                                         \
-        auto kern = lora_grad_kernel<N>;                                                                              \
+        auto kern = wide ? lora_grad_kernel<N, 8> : lora_grad_kernel<N, 4>;                                           \
         hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                      \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                    \
         if (ea != hipSuccess) return ea;                                                                              \
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds, stream, pair, t);                                              \
+        hipLaunchKernelGGL(kern, grid, dim3(wide ? 512 : 256), lds, stream, pair, t);                                 \
     } break;
     switch (r / 16) {
         QUAFF_GRAD(1) QUAFF_GRAD(2) QUAFF_GRAD(3) QUAFF_GRAD(4)
@@ -290,9 +311,10 @@ hipError_t launch_lora_grad_pair(const uint16_t* X, int64_t ldx, int64_t c_in, c
 #undef QUAFF_GRAD
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (pair.p[0].nslab == 1 && pair.p[1].nslab == 1) return hipSuccess;
     const int64_t cmax = c_in > c_out ? c_in : c_out;
-    int64_t blocks = ((int64_t)r * cmax + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
+    int64_t blocks = ((int64_t)r * cmax + 1023) / 1024;
+    if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((unsigned)blocks, 2), dim3(256), 0, stream, pair, (int)r);
     return hipGetLastError();
 }
