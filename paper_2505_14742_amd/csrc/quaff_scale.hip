@@ -73,16 +73,20 @@ momentum_what_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_
 // Dense variant of the column abs-max for outlier sets that touch most 64-byte segments of a row anyway (the
 // paper's 4 % - 10 % budgets): every column of a 2048-column chunk is reduced over the slab's rows with coalesced
 // 16-byte loads (bf16 magnitudes compare as integers), then the chunk's outlier columns are picked out of LDS.
-__global__ void __launch_bounds__(256)
+// Four groups of 256 threads share a slab's rows: as many loads in flight as with four times the slabs, whose partial
+// maxima every workgroup of the next launch would have to fold.
+constexpr int kDenseGroups = 4, kDenseThreads = 256 * kDenseGroups;
+__global__ void __launch_bounds__(kDenseThreads)
 colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int64_t ldx, const int32_t* __restrict__ O,
                     int n, uint32_t* __restrict__ part, const float* __restrict__ s_O, float* __restrict__ s_prev,
                     int rows_per_slab) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    __shared__ uint16_t cm[2048];
+    __shared__ __attribute__((aligned(16))) uint16_t cm[kDenseGroups][2048];
     __shared__ int krange[2];
     const int chunk0 = blockIdx.x * 2048, slab = blockIdx.y;
+    const int lane = threadIdx.x & 255, grp = threadIdx.x >> 8;
     if (blockIdx.x == 0 && slab == 0)
-        for (int k = threadIdx.x; k < n; k += 256) s_prev[k] = s_O[k];
+        for (int k = threadIdx.x; k < n; k += kDenseThreads) s_prev[k] = s_O[k];
     if (threadIdx.x < 2) {
         // first outlier index >= chunk0 (thread 0) and >= chunk0 + 2048 (thread 1): O is sorted
         const int target = chunk0 + 2048 * (int)threadIdx.x;
@@ -93,17 +97,17 @@ colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int
         }
         krange[threadIdx.x] = lo;
     }
-    const int64_t col = chunk0 + (int64_t)threadIdx.x * 8;
+    const int64_t col = chunk0 + (int64_t)lane * 8;
     const int64_t r0 = (int64_t)slab * rows_per_slab;
     const int64_t r1 = r0 + rows_per_slab < t ? r0 + rows_per_slab : t;
     uint32_t mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (col < c_in) {
         const uint16_t* src = X + col;
-        for (int64_t row = r0; row < r1; row += 4) {   // four independent loads in flight
+        for (int64_t row = r0 + grp; row < r1; row += 4 * kDenseGroups) {   // four independent loads in flight
             u32x4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                int64_t rr = row + u < r1 ? row + u : r1 - 1;
+                const int64_t rr = row + u * kDenseGroups < r1 ? row + u * kDenseGroups : r1 - 1;
                 v[u] = *reinterpret_cast<const u32x4*>(src + rr * ldx);
             }
 #pragma unroll
@@ -116,46 +120,81 @@ colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int
                 }
         }
     }
+    u32x4 packed;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) cm[threadIdx.x * 8 + w] = (uint16_t)mx[w];
+    for (int w = 0; w < 4; ++w) packed[w] = mx[2 * w] | (mx[2 * w + 1] << 16);
+    *reinterpret_cast<u32x4*>(&cm[grp][lane * 8]) = packed;
     __syncthreads();
-    for (int k = krange[0] + threadIdx.x; k < krange[1]; k += 256)
-        part[(int64_t)slab * n + k] = (uint32_t)cm[O[k] - chunk0] << 16;   // |x| as fp32 bits
+    for (int k = krange[0] + threadIdx.x; k < krange[1]; k += kDenseThreads) {
+        const int at = O[k] - chunk0;
+        uint32_t m = 0;
+#pragma unroll
+        for (int u = 0; u < kDenseGroups; ++u) m = max(m, (uint32_t)cm[u][at]);
+        part[(int64_t)slab * n + k] = m << 16;                              // |x| as fp32 bits
+    }
 }
 
-// momentum_what_kernel for more than 64 outlier channels: a workgroup owns 32 output channels and its 16 thread
-// groups split the outlier range, so that the n x c_out read of W_O is spread over enough workgroups.
-constexpr int kWideCh = 32, kWideGroups = 16;
-__global__ void __launch_bounds__(kWideCh * kWideGroups)
+// momentum_what_kernel for more than 64 outlier channels.  A workgroup owns 16 output channels; its 64 thread groups
+// take four consecutive outliers of every 256, NB times.  What bounds it is the chain of memory round trips, so both long
+// reads are in flight at once: this workgroup's part of W_O (kept in registers, one sweep instead of one for the maxima
+// and one for the codes) and the partial maxima, folded with one column of them per thread (coalesced, an LDS atomic per
+// thread instead of one per partial maximum).  The codes leave through LDS: sixteen output channels are contiguous in what_int.
+// HELD = false: more outliers than 256 NB, which a second sweep of W_O fetches again.
+// Measured at 2048 x 8192 -> 3072 with 819 outliers: 34.7 -> 11.2 us (before: 32 channels a workgroup, 128 slabs of partial
+// maxima folded with one LDS atomic each, W_O swept twice in chains of eight loads).
+constexpr int kWideCh = 16, kWideThreads = 1024, kWideGroups = kWideThreads / kWideCh;
+template <int NB, bool HELD>
+__global__ void __launch_bounds__(kWideThreads)
 momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad,
                           const float* __restrict__ wmax_O, const float* __restrict__ s_prev, float gamma,
                           const int32_t* __restrict__ O, float* __restrict__ s_O, float* __restrict__ colscale,
                           float* __restrict__ cmax_out, const float* __restrict__ W_O, int64_t c_out,
                           int8_t* __restrict__ what_int, float* __restrict__ delta_what) {
-    constexpr int NT = kWideCh * kWideGroups;
-    extern __shared__ float sm1[];                                  // [n] : s_k - 1
-    uint32_t* smax = reinterpret_cast<uint32_t*>(sm1 + n);         // [n]
-    float* red = sm1 + 2 * n;                                       // [kWideGroups][kWideCh]
-    for (int k = threadIdx.x; k < n; k += NT) smax[k] = 0u;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int SPAN = 4 * kWideGroups * NB;                      // outliers per sweep
+    constexpr int ROW = SPAN + 16;                                  // LDS row of codes: 16 channels in 16 different banks
+    __shared__ __attribute__((aligned(16))) uint32_t codes[kWideCh * ROW / 4];
+    __shared__ float red[kWideThreads / 64][kWideCh];
+    extern __shared__ uint32_t smax[];                              // [n] : maxima, then s_k - 1
+    float* const sm1 = reinterpret_cast<float*>(smax);
+    const int jj = threadIdx.x % kWideCh, grp = threadIdx.x / kWideCh;
+    const int64_t j0 = (int64_t)blockIdx.x * kWideCh, j = j0 + jj;
+    const int64_t jc = j < c_out ? j : c_out - 1;
+    float w[NB][4];
+    auto first_k = [&](int base, int b) { return base + (b * kWideGroups + grp) * 4; };
+    auto load = [&](int base) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = first_k(base, b) + u;
+                w[b][u] = W_O[(int64_t)(k < n ? k : n - 1) * c_out + jc];
+            }
+    };
+    if (HELD) load(0);
+    for (int k = threadIdx.x; k < n; k += kWideThreads) smax[k] = 0u;
     __syncthreads();
-    const int total = nslab * n;
-    for (int e0 = threadIdx.x; e0 < total; e0 += 16 * NT) {
-        uint32_t v[16];
+    // thread (share, k): column k of the slabs share, share + shares, ...
+    const int width = n < kWideThreads ? (n + 63) / 64 * 64 : kWideThreads, shares = kWideThreads / width;
+    const int share = threadIdx.x / width;
+    for (int k = threadIdx.x % width; k < n && share < shares; k += width) {
+        uint32_t m = 0u;
+        for (int s0 = share; s0 < nslab; s0 += 16 * shares) {
+            uint32_t v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            int e = e0 + u * NT;
-            v[u] = part[e < total ? e : total - 1];
-        }
+            for (int u = 0; u < 16; ++u) {
+                const int sl = s0 + u * shares;                     // (a repeated slab changes no maximum)
+                v[u] = part[(int64_t)(sl < nslab ? sl : s0) * n + k];
+            }
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            int e = e0 + u * NT;
-            if (e < total) atomicMax(&smax[e % n], v[u]);
+            for (int u = 0; u < 16; ++u) m = max(m, v[u]);
         }
+        atomicMax(&smax[k], m);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < n; k += NT) {
-        float cmax = __uint_as_float(smax[k]);
-        float s = momentum_scale(cmax, wmax_O[k], s_prev[k], gamma);
+    for (int k = threadIdx.x; k < n; k += kWideThreads) {
+        const float cmax = __uint_as_float(smax[k]);
+        const float s = momentum_scale(cmax, wmax_O[k], s_prev[k], gamma);
         sm1[k] = __fsub_rn(s, 1.0f);
         if (blockIdx.x == 0) {
             s_O[k] = s;
@@ -164,48 +203,55 @@ momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, i
         }
     }
     __syncthreads();
-    const int jj = threadIdx.x % kWideCh, grp = threadIdx.x / kWideCh;
-    const int64_t j = (int64_t)blockIdx.x * kWideCh + jj;
-    const int64_t jc = j < c_out ? j : c_out - 1;
-    const int per = n_pad / kWideGroups;                  // a multiple of 4 (n_pad is a multiple of 64)
-    const int kb = grp * per, ke = kb + per < n ? kb + per : n;
-    // pass 1: this group's share of max_k |what[k, j]|
+    // max_k |what[k, j]|: this thread's share, the wavefront's four groups, the wavefronts
     float m = 0.0f;
-    for (int k0 = kb; k0 < ke; k0 += 8) {
-        float w[8];
+    for (int base = 0; base < n; base += SPAN) {
+        if (!HELD) load(base);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) w[u] = W_O[(int64_t)(k0 + u < ke ? k0 + u : ke - 1) * c_out + jc];
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(__fmul_rn(sm1[k0 + u < ke ? k0 + u : ke - 1], w[u])));
+            for (int u = 0; u < 4; ++u) {
+                const int k = first_k(base, b) + u;
+                const float v = k < n ? __fmul_rn(sm1[k < n ? k : 0], w[b][u]) : 0.0f;
+                if (HELD) w[b][u] = v;
+                m = fmaxf(m, fabsf(v));
+            }
+        if (HELD) break;
     }
-    red[grp * kWideCh + jj] = m;
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if ((threadIdx.x & 63) < kWideCh) red[threadIdx.x >> 6][jj] = m;
     __syncthreads();
-    m = 0.0f;
 #pragma unroll
-    for (int g2 = 0; g2 < kWideGroups; ++g2) m = fmaxf(m, red[g2 * kWideCh + jj]);
+    for (int v = 0; v < kWideThreads / 64; ++v) m = fmaxf(m, red[v][jj]);
     float d, c;
     rtn_steps(m, d, c);
-    if (j >= c_out) return;
-    if (grp == 0) delta_what[j] = d;
-    // pass 2: codes of this group's range (zero beyond n), four per 32-bit store
-    uint32_t* dst = reinterpret_cast<uint32_t*>(what_int + j * n_pad + kb);
-    for (int k0 = kb; k0 < kb + per; k0 += 8) {
-        float w[8];
+    if (grp == 0 && j < c_out) delta_what[j] = d;
+    const int channels = c_out - j0 < kWideCh ? (int)(c_out - j0) : kWideCh;
+    for (int base = 0; base < n_pad; base += SPAN) {
+        if (!HELD) load(base);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u;
-            w[u] = W_O[(int64_t)(k < n ? k : n - 1) * c_out + j];
-        }
-        uint32_t q[2] = {0u, 0u};
+        for (int b = 0; b < NB; ++b) {
+            const int k0 = first_k(base, b);
+            uint32_t q = 0u;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u;
-            int code = 0;
-            if (k < n) code = rtn_code(__fmul_rn(sm1[k], w[u]), c);
-            q[u >> 2] |= (uint32_t)(code & 0xFF) << (8 * (u & 3));
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + u;
+                float v = w[b][u];
+                if (!HELD) v = k < n ? __fmul_rn(sm1[k < n ? k : 0], v) : 0.0f;
+                q |= (uint32_t)(rtn_code(v, c) & 0xFF) << (8 * u);  // (zero beyond n: code 0)
+            }
+            codes[(jj * ROW + k0 - base) >> 2] = q;
         }
-        dst[(k0 - kb) >> 2] = q[0];
-        if (k0 + 4 < kb + per) dst[((k0 - kb) >> 2) + 1] = q[1];
+        __syncthreads();
+        const int span = n_pad - base < SPAN ? n_pad - base : SPAN, per_row = span / 16;   // 16-byte chunks
+        for (int e = threadIdx.x; e < channels * per_row; e += kWideThreads) {
+            const int row = e / per_row, at = (e - row * per_row) * 16;
+            *reinterpret_cast<u32x4*>(what_int + (j0 + row) * n_pad + base + at) =
+                *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(codes) + row * ROW + at);
+        }
+        if (HELD) break;
+        __syncthreads();
     }
 }
 
@@ -249,16 +295,16 @@ hipError_t launch_scale_update(const uint16_t* X, int64_t t, int64_t c_in, int64
     int nslab = scale_update_blocks(t);
     const bool dense = (int64_t)n * 64 >= c_in;          // most 64-byte segments of a row hold an outlier anyway
     if (dense) {
-        // enough (chunk, slab) workgroups to fill the chip, within the slab count the workspace was sized for
+        // one (chunk, slab) workgroup per compute unit, within the slab count the workspace was sized for
         const int chunks = (int)((c_in + 2047) / 2048);
-        int want = (512 + chunks - 1) / chunks;
+        const int want = (256 + chunks - 1) / chunks;
         if (want < nslab) nslab = want;
         const int rows = (int)((t + nslab - 1) / nslab);
         nslab = (int)((t + rows - 1) / rows);
         float* s_prev = ws + (int64_t)nslab * n;
         {
             ProfScope prof(K_COLMAX, stream);
-            hipLaunchKernelGGL(colmax_dense_kernel, dim3(chunks, nslab), dim3(256), 0, stream, X, t, c_in, ldx, O, n,
+            hipLaunchKernelGGL(colmax_dense_kernel, dim3(chunks, nslab), dim3(kDenseThreads), 0, stream, X, t, c_in, ldx, O, n,
                                part, s_O, s_prev, rows);
         }
         return launch_momentum(part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O, colscale, cmax_out, W_O, c_out,
@@ -285,13 +331,24 @@ hipError_t launch_momentum(const uint32_t* part, int nslab, int n, int n_pad, co
                            dim3(kWhatThreads), 2 * n * sizeof(float), stream, part, nslab, n, n_pad, wmax_O, s_prev,
                            gamma, O, s_O, colscale, cmax_out, W_O, c_out, what_int, delta_what);
     } else {
-        const size_t lds = (2 * (size_t)n + kWideCh * kWideGroups) * sizeof(float);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(momentum_what_wide_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(momentum_what_wide_kernel, dim3((unsigned)((c_out + kWideCh - 1) / kWideCh)),
-                           dim3(kWideCh * kWideGroups), lds, stream, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O,
-                           s_O, colscale, cmax_out, W_O, c_out, what_int, delta_what);
+        const size_t lds = (size_t)n * sizeof(uint32_t);
+        const dim3 grid((unsigned)((c_out + kWideCh - 1) / kWideCh));
+#define QUAFF_WIDE(NB, HELD)                                                                                          \
+    {                                                                                                                 \
+        auto k = momentum_what_wide_kernel<NB, HELD>;                                                                 \
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),                                          \
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                     \
+        if (e != hipSuccess) return e;                                                                                \
+        hipLaunchKernelGGL(k, grid, dim3(kWideThreads), lds, stream, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O, \
+                           colscale, cmax_out, W_O, c_out, what_int, delta_what);                                     \
+    }
+        // the smallest number of registers that holds a thread's share of W_O; beyond 2048 outliers it is fetched twice
+        if (n <= 256) QUAFF_WIDE(1, true)
+        else if (n <= 512) QUAFF_WIDE(2, true)
+        else if (n <= 1024) QUAFF_WIDE(4, true)
+        else if (n <= 2048) QUAFF_WIDE(8, true)
+        else QUAFF_WIDE(8, false)
+#undef QUAFF_WIDE
     }
     return hipGetLastError();
 }
