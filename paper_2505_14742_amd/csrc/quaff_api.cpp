@@ -62,6 +62,16 @@ BwdWs ws_bwd(int64_t t, int64_t c_in, int64_t c_out, int32_t r) {
     return w;
 }
 
+// Exchange area of a small output whose contraction several workgroups share.  Optional: it follows everything else in the
+// workspace and a call given less room takes the unsplit product.
+size_t split_fwd(int64_t t, int64_t c_in, int64_t c_out) { return align_up(quaff::gemm_small_split_bytes(t, c_out, c_in, false)); }
+size_t split_bwd(int64_t t, int64_t c_in, int64_t c_out) { return align_up(quaff::gemm_small_split_bytes(t, c_in, c_out, true)); }
+void set_small_split(quaff::GemmArgs& g, void* workspace, size_t used, size_t need, size_t available) {
+    if (!workspace || need == 0 || available < used + need || !aligned16(workspace)) return;
+    g.small_split_scratch = static_cast<char*>(workspace) + used;
+    g.split_wait_ticks = g_grid_wait_ticks.load();
+}
+
 struct GradWs { size_t t1_hi, t1_lo, t2_hi, t2_lo, part_a, part_b, at, total; };
 GradWs ws_grad(int64_t t, int64_t c_in, int64_t c_out, int32_t r) {
     GradWs w{};
@@ -119,6 +129,8 @@ size_t quaff_prepare_workspace_bytes(int64_t c_in, int64_t c_out) {
 size_t quaff_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || n_outlier < 0 || lora_rank < 0) return 0;
     size_t a = ws_scale(t, n_outlier), b = ws_fwd(t, c_in, c_out, lora_rank).total, c = ws_bwd(t, c_in, c_out, lora_rank).total;
+    b += split_fwd(t, c_in, c_out);
+    c += split_bwd(t, c_in, c_out);
     size_t m = a > b ? a : b;
     return (m > c ? m : c) + 256;
 }
@@ -242,6 +254,7 @@ static int linear_fwd_impl(const int8_t* Xq, const float* delta_x, const int8_t*
         g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank;
     }
     g.C = Y; g.C16 = Y16; g.ldc = ldy;
+    set_small_split(g, workspace, ws_fwd(t, c_in, c_out, lora_rank).total, split_fwd(t, c_in, c_out), workspace_bytes);
     return hip_status(quaff::launch_gemm(g, false, s));
 }
 
@@ -281,7 +294,7 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
                               int64_t c_in, int64_t c_out, const uint16_t* lora_A, const uint16_t* lora_B,
                               int32_t lora_rank, float lora_scale, float* dX, uint16_t* dX16, int64_t lddx,
                               void* workspace, size_t workspace_bytes, void* stream,
-                              const std::function<int()>* before_product = nullptr) {
+                              const std::function<int()>* before_product = nullptr, size_t split_at = 0) {
     if (!dY || !Wq_packed || !delta_w || (!dX && !dX16)) return QUAFF_ERR_NULL;
     if (dX16 && c_out % 64 != 0) return QUAFF_ERR_SHAPE;
     if (dX16 && (!aligned16(dX16) || lddx % 8 != 0)) return QUAFF_ERR_ALIGN;
@@ -326,6 +339,7 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
     }
     g.C = dX; g.C16 = dX16; g.ldc = lddx;
     if (w.total > w.split) { g.split_scratch = base + w.split; g.split_wait_ticks = g_grid_wait_ticks.load(); }
+    set_small_split(g, workspace, split_at ? split_at : w.total, split_bwd(t, c_in, c_out), workspace_bytes);
     // (the one-call backward step forks its weight-gradient work here: the quantizer and the down-projection are
     // enqueued, the long product is not yet)
     if (before_product && (st = (*before_product)()) != QUAFF_OK) return st;
@@ -401,7 +415,7 @@ int quaff_lora_bwd_weights(const uint16_t* X, int64_t ldx, const uint16_t* dY, i
 
 size_t quaff_bwd_step_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || lora_rank <= 0) return 0;
-    return ws_bwd(t, c_in, c_out, lora_rank).total + ws_grad(t, c_in, c_out, lora_rank).total + 256;
+    return ws_bwd(t, c_in, c_out, lora_rank).total + ws_grad(t, c_in, c_out, lora_rank).total + split_bwd(t, c_in, c_out) + 256;
 }
 
 int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uint16_t* X, int64_t ldx,
@@ -451,7 +465,8 @@ int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uin
         return QUAFF_OK;
     };
     int st = linear_bwd_dx_impl(dY, t, lddy, Wq_packed, delta_w, c_in, c_out, lora_A, lora_B, lora_rank, lora_scale, dX,
-                                nullptr, lddx, workspace, wb.total, stream, &fork);
+                                nullptr, lddx, workspace, workspace_bytes, stream, &fork,
+                                wb.total + w.total);
     if (forked) {
         // Whatever happened after the fork, the caller's stream joins everything that was put on the side stream,
         // so that the buffers that work reads and writes stay ordered before the caller's next use of them.
@@ -520,7 +535,7 @@ int quaff_calibrate_outliers(const uint16_t* X, int64_t t_total, int64_t c_in, i
 size_t quaff_fwd_step_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || n_outlier < 0 || lora_rank < 0) return 0;
     return ws_scale(t, n_outlier) + ws_fwd(t, c_in, c_out, lora_rank).total +
-           quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64) + 256;
+           quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64) + split_fwd(t, c_in, c_out) + 256;
 }
 
 long long quaff_debug_grid_wait_ticks(long long ticks) {
@@ -543,7 +558,8 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     if (n_outlier > 0 && !xq_O) return QUAFF_ERR_NULL;
     char* base = static_cast<char*>(workspace);
     void* ws_lin = base + scale_bytes;
-    const size_t ws_lin_bytes = wf.total;
+    const size_t ws_lin_bytes = workspace_bytes - scale_bytes;
+    const size_t split_at = scale_bytes + wf.total + align_up(prep_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // One launch prepares everything the product needs where it can (a few thousand tokens, at most 64 outlier
     // channels, rank 0 or 16); two combined launches cover the other usual cases; everything else is the three calls
@@ -584,6 +600,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
         if (st != QUAFF_OK) return st;
         if (lora_rank > 0) { g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank; }
         g.C = Y; g.ldc = ldy;
+        set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out), workspace_bytes);
         return hip_status(quaff::launch_gemm(g, false, s));
     }
     float* wsf = static_cast<float*>(workspace);
@@ -615,6 +632,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     if (st != QUAFF_OK) return st;
     g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank;
     g.C = Y; g.ldc = ldy;
+    set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out), workspace_bytes);
     return hip_status(quaff::launch_gemm(g, false, s));
 }
 

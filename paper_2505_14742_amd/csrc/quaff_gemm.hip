@@ -55,7 +55,7 @@ constexpr RowsChoice kRowsForward[4] = {
     {kRows16x16, 16, 16, 3.2, 83, 11.5}, {kRows32x32, 32, 32, 3.6, 79, 10.2}, {kRows32x64, 32, 64, 4.4, 84, 10.1}, {kRows64x96, 64, 96, 7.9, 80, 7.7}};
 constexpr RowsChoice kRowsGradient[2] = {{kRows16x64, 16, 64, 4.0, 115, 11}, {kRows32x64, 32, 64, 4.5, 85, 10.1}};
 
-int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work) {
+int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work, double* us_estimate) {
     const double passes = tile_work / (128.0 * 192.0 * kChoices[kTile128x192].ineff);
     const int64_t wide_tiles = ((M + 127) / 128) * ((N + 191) / 192);
     const double busy = wide_tiles < 256 ? wide_tiles / 256.0 : 1.0;
@@ -69,6 +69,7 @@ int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work
         const double us = r.fixed_us + (per_cu > chip ? per_cu : chip) + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0);
         if (us < best_us) { best_us = us; best = r.shape; }
     }
+    *us_estimate = best_us;
     return best;
 }
 }  // namespace
@@ -89,6 +90,33 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
     if (!split_applies(M, N, K)) return 0;
     const size_t tiles = (size_t)((M + 255) / 256) * (size_t)((N + 191) / 192);
     return tiles * 256 + tiles * 512 * 96 * 4;   // two flags per tile in lines of their own, then 96 accumulators of 512 threads
+}
+
+// Outputs of at most 128 tiles of 128 x 192 leave half of the compute units idle or more while every tile walks its
+// contraction alone; two or four workgroups per tile share it where that pays for the exchange of their sums through the L2.
+// Estimated in the terms of choose_rows (`k` = 1024 of contraction, `busy` = tiles per compute unit), constants fitted to 170
+// measured products each way; 4 % must be gained.  Forward, one / two / four workgroups per tile, us: 512 x 3072 outputs 19.7 /
+// 17.0 / 18.3 at K = 3072, 43.3 / 29.0 / 26.2 at 8192, 10.6 / 11.6 / 13.1 at 1024; 1024 x 3072 outputs 20.2 / 20.7 at 3072,
+// 44.0 / 34.7 at 8192; 256 x 3072 outputs at 8192 30.6 (64 x 96 tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x
+// 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.
+static int small_split(int64_t M, int64_t N, int64_t K, bool gradient) {
+    const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
+    if (tiles > 128 || K % 256 != 0) return 1;
+    double work, best_us;
+    choose_tile(M, N, &work);
+    const double k = (double)K / 1024.0, busy = tiles / 256.0;
+    double alone = 8.1 + 4.7 * k;
+    if (choose_rows(M, N, K, gradient, work, &best_us) != kRowsNone && best_us < alone) alone = best_us;
+    const double two = 1.04 * (9.7 + 6.5 * busy + (2.2 + 1.6 * busy) * k);
+    const double four = 1.04 * (11.0 + 13.0 * busy + (1.15 + 3.1 * busy) * k);
+    if (tiles <= 64 && K % 512 == 0 && four < alone && four < two) return 4;
+    return two < alone ? 2 : 1;
+}
+size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, bool gradient) {
+    const int parts = small_split(M, N, K, gradient);
+    if (parts == 1) return 0;
+    const size_t tiles = (size_t)((M + 127) / 128) * (size_t)((N + 191) / 192);
+    return tiles * ((size_t)split_flags(parts) * 128 + (size_t)split_slot_sets(parts) * 256 * 96 * 4);
 }
 
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
@@ -120,9 +148,19 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
         tile = kTileSplit;
     else
     {
-        double work;
+        const bool gradient = g.b_layout == kPackedKN;
+        if (g.small_split_scratch && !dump_acc && !g.C16 && !g.accumulate && g.K2 <= 128) {
+            const int parts = small_split(g.M, g.N, g.K, gradient);
+            if (parts > 1) {
+                GemmArgs split = g;
+                split.split_scratch = g.small_split_scratch;
+                const int t = parts == 2 ? kTileSplitSmall2 : kTileSplitSmall4;
+                return gradient ? launch_gemm_kn(split, t, false, stream) : launch_gemm_nk(split, t, false, stream);
+            }
+        }
+        double work, us;
         tile = choose_tile(g.M, g.N, &work);
-        const int rows = choose_rows(g.M, g.N, g.K, g.b_layout == kPackedKN, work);
+        const int rows = choose_rows(g.M, g.N, g.K, gradient, work, &us);
         if (rows != kRowsNone) return launch_gemm_rows(g, rows, stream);
     }
     // The 128 x 192 tile with at most one tile per compute unit takes a ring of three stages (120 KB of LDS: one

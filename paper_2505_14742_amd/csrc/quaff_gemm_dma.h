@@ -807,15 +807,17 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
     }
 }
 
-// Contraction split over the two workgroups of a tile (KSPLIT = 2).  The "giver" (second half of the contraction)
-// writes its int32 accumulators, register image by register image, into the exchange buffer and raises the tile's
-// flag; the "taker" (first half) adds them to its own and runs the epilogue: the sums are integers, so the result is
-// the unsplit product bit for bit.  The hand-over relies on the two workgroups sharing an L2, which the launch grid
-// arranges (same XCD) but the hardware does not promise: the giver records the XCD it ran on, and a taker on another
-// one - or one whose bounded wait runs out - computes the second half itself instead.  The flag is exchanged, never
+// Contraction split over KSPLIT (2 or 4) workgroups of a tile.  Each finishes the blocks of the wavefronts it owns: the
+// other workgroups write their int32 accumulators of those blocks, register image by register image, into the exchange
+// buffer and raise a flag towards the owner, which adds them to its own and runs the epilogue: the sums are integers, so the
+// result is the unsplit product bit for bit.  The hand-over relies on the workgroups of a tile sharing an L2, which the
+// launch grid arranges (same XCD) but the hardware does not promise: the giver records the XCD it ran on, and an owner on
+// another one - or one whose bounded wait runs out - computes the other parts itself instead.  A flag is exchanged, never
 // just written: whoever finds the other's mark resets the word to zero, so a finished launch always leaves zeros.
 constexpr unsigned long long kSplitFull = 0x5146474956450000ull;        // | XCD of the giver
 constexpr unsigned long long kSplitAbandoned = 0x5146414241440000ull;
+constexpr int split_flags(int ksplit) { return ksplit == 2 ? 2 : ksplit * ksplit; }       // 128-byte lines per tile
+constexpr int split_slot_sets(int ksplit) { return ksplit == 2 ? 1 : ksplit; }
 __device__ __forceinline__ unsigned xcc_id() { return __builtin_amdgcn_s_getreg(((4 - 1) << 11) | 20) & 15u; }
 
 template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool DUMP, bool ACCUM = false, bool OUT16 = false,
@@ -825,12 +827,13 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     using C = DmaCfg<BM, BN, WGM, WGN, NS>;
     extern __shared__ __attribute__((aligned(1024))) int8_t lds_raw[];
     lds_i8* lds = (lds_i8*)lds_raw;
-    static_assert(KSPLIT == 1 || (KSPLIT == 2 && !RAGGED && !DUMP), "a split contraction has whole stages");
+    static_assert(KSPLIT == 1 || ((KSPLIT == 2 || KSPLIT == 4) && C::NW % KSPLIT == 0 && !RAGGED && !DUMP),
+                  "a split contraction has whole stages, and a workgroup owns whole wavefronts' blocks");
 
     int tile_m, tile_n;
-    // (split: the two workgroups of a tile are neighbours in y, so they carry the same blockIdx.x = XCD)
-    const int kh = KSPLIT == 2 ? (int)(blockIdx.y & 1) : 0;
-    if (!tile_of_block(tmap, blockIdx.x, KSPLIT == 2 ? blockIdx.y >> 1 : blockIdx.y, blockIdx.z, tile_m, tile_n)) return;
+    // (split: the workgroups of a tile are neighbours in y, so they carry the same blockIdx.x = XCD)
+    const int kh = (int)(blockIdx.y % KSPLIT);
+    if (!tile_of_block(tmap, blockIdx.x, blockIdx.y / KSPLIT, blockIdx.z, tile_m, tile_n)) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     // The wavefront number is uniform; telling the compiler so moves the loader's address selects to scalar code,
@@ -890,81 +893,99 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     gemm_mainloop<C, BT, RAGGED>(tileA + (int64_t)kh * KT * 128, tileB + kh * KT * b_step, voff, KT, k_last, lds, lds, wave,
                                  lane, a_frag, b_off, b_step, acc);
     bool active = true;                                  // does this wavefront finish (dequantise, store) its block
-    if constexpr (KSPLIT == 2) {
-        // Workgroup kh finishes the tile's row half kh: its wavefronts of the other half ("givers") ship their
-        // accumulators to the partner workgroup, its wavefronts of row half kh ("takers") add what the partner's
-        // same-numbered wavefronts ship.  Thread tid of one workgroup writes slot tid, thread tid of the other
-        // reads it: piece q of a thread at [q][tid], so that every store and load covers whole lines.
+    if constexpr (KSPLIT > 1) {
+        // Workgroup kh owns the blocks of wavefronts kh * NW / KSPLIT and following: its other wavefronts ("givers") ship their
+        // accumulators, its owned ones add what the other workgroups' same-numbered wavefronts ship.  A thread writes and
+        // reads the slot of its own number: piece q of a thread at [q][tid], so that every store and load covers whole
+        // lines.  With two workgroups a slot has one writer; with four every workgroup has a set of its own.
         constexpr int NV = C::TM * C::TN * 4;          // 16-byte pieces of a lane's accumulators
+        constexpr int SETS = split_slot_sets(KSPLIT), FLAGS = split_flags(KSPLIT);
         const int64_t tile_id = (int64_t)tile_m * tmap.tiles_n + tile_n;
-        // (the two flags of a tile sit 128 bytes apart, each in a line of its own)
-        unsigned long long* flags = reinterpret_cast<unsigned long long*>(g.split_scratch) + tile_id * 32;
+        // (the flags of a tile sit 128 bytes apart, each in a line of its own)
+        unsigned long long* flags = reinterpret_cast<unsigned long long*>(g.split_scratch) + tile_id * FLAGS * 16;
+        auto flag = [&](int from, int to) { return flags + 16 * (KSPLIT == 2 ? from : from * KSPLIT + to); };
         i32x4* xb = reinterpret_cast<i32x4*>(static_cast<char*>(g.split_scratch) +
-                                             (size_t)tmap.tiles_m * tmap.tiles_n * 256) +
-                    tile_id * NV * C::NT + tid;
-        const bool giver = (wm >= WGM / 2) == (kh == 0);
-        active = !giver;
-        if (giver) {
+                                             (size_t)tmap.tiles_m * tmap.tiles_n * FLAGS * 128) +
+                    tile_id * SETS * NV * C::NT + tid;
+        auto set = [&](int from) { return xb + (SETS > 1 ? (int64_t)from * NV * C::NT : 0); };
+        active = wave / (C::NW / KSPLIT) == kh;
+        if (!active) {
+            i32x4* const dst = set(kh);
 #pragma unroll
             for (int i = 0; i < C::TM; ++i)
 #pragma unroll
                 for (int j = 0; j < C::TN; ++j)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        xb[((i * C::TN + j) * 4 + q) * C::NT] = (i32x4){acc[i][j][4 * q], acc[i][j][4 * q + 1],
-                                                                         acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                        dst[((i * C::TN + j) * 4 + q) * C::NT] = (i32x4){acc[i][j][4 * q], acc[i][j][4 * q + 1],
+                                                                          acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's pieces have reached the L2
         }
         __syncthreads();     // all givers of this workgroup have written; nobody reads the ring any more
-        if (tid == 0) {
-            // raise this workgroup's flag ...
-            const unsigned long long old = __hip_atomic_exchange(flags + 16 * kh, kSplitFull | xcc_id(), __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_AGENT);
-            if (old == kSplitAbandoned)     // (the partner stopped waiting and does the work itself)
-                __hip_atomic_store(flags + 16 * kh, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // ... and wait, for a bounded time, for the partner's
-            unsigned long long* theirs = flags + 16 * (1 - kh);
-            const long long t0 = (long long)wall_clock64();
-            unsigned long long w;
-            int take = 0;
-            for (;;) {
-                w = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((w & ~15ull) == kSplitFull) break;
-                if ((long long)wall_clock64() - t0 >= g.split_wait_ticks) {
-                    w = __hip_atomic_exchange(theirs, kSplitAbandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
+        if (tid < 64) {
+            // lane p of the first wavefront deals with workgroup p of the tile
+            const bool peer = tid < KSPLIT && tid != kh;
+            bool full = false, ok = true;
+            if (peer) {
+                // raise this workgroup's flag ...
+                const unsigned long long old = __hip_atomic_exchange(flag(kh, tid), kSplitFull | xcc_id(), __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT);
+                if (old == kSplitAbandoned)     // (the peer stopped waiting and does the work itself)
+                    __hip_atomic_store(flag(kh, tid), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                // ... and wait, for a bounded time, for the peer's
+                unsigned long long* theirs = flag(tid, kh);
+                const long long t0 = (long long)wall_clock64();
+                unsigned long long w;
+                for (;;) {
+                    w = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((w & ~15ull) == kSplitFull) break;
+                    if ((long long)wall_clock64() - t0 >= g.split_wait_ticks) {
+                        w = __hip_atomic_exchange(theirs, kSplitAbandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
                 }
-                __builtin_amdgcn_s_sleep(2);
+                full = (w & ~15ull) == kSplitFull;
+                ok = full && (unsigned)(w & 15ull) == xcc_id();
             }
-            if ((w & ~15ull) == kSplitFull) {
-                take = (unsigned)(w & 15ull) == xcc_id();
-                if (!take) __hip_atomic_store(theirs, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            *reinterpret_cast<volatile int*>(lds_raw) = take;
+            const bool all_ok = __all(ok);
+            // (parts that arrived but will not be used: their flags go back to zero here)
+            if (full && !all_ok) __hip_atomic_store(flag(tid, kh), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) *reinterpret_cast<volatile int*>(lds_raw) = all_ok;
         }
         __syncthreads();
         const int take = *reinterpret_cast<volatile int*>(lds_raw);
         __syncthreads();
         if (take) {
             if (active) {
+#pragma unroll 1
+                for (int p = 1; p < KSPLIT; ++p) {
+                    const i32x4* const src = set((kh + p) % KSPLIT);
 #pragma unroll
-                for (int i = 0; i < C::TM; ++i)
+                    for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < C::TN; ++j)
+                        for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const i32x4 v = xb[((i * C::TN + j) * 4 + q) * C::NT];
+                            for (int q = 0; q < 4; ++q) {
+                                const i32x4 v = src[((i * C::TN + j) * 4 + q) * C::NT];
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-                        }
+                                for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+                            }
+                }
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
-            __syncthreads();                 // all pieces read: the partner's flag goes back to zero
-            if (tid == 0) __hip_atomic_store(flags + 16 * (1 - kh), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();                 // all pieces read: the peers' flags go back to zero
+            if (tid < KSPLIT && tid != kh)
+                __hip_atomic_store(flag(tid, kh), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
-            // the other half of the contraction, computed here (the givers' sums are not used again)
-            gemm_mainloop<C, BT, false>(tileA + (int64_t)(1 - kh) * KT * 128, tileB + (1 - kh) * KT * b_step, voff, KT,
-                                        k_last, lds, lds, wave, lane, a_frag, b_off, b_step, acc);
+            // the other parts of the contraction, computed here (the givers' sums are not used again)
+#pragma unroll 1
+            for (int p = 1; p < KSPLIT; ++p) {
+                const int part = (kh + p) % KSPLIT;
+                gemm_mainloop<C, BT, false>(tileA + (int64_t)part * KT * 128, tileB + part * KT * b_step, voff, KT, k_last, lds,
+                                            lds, wave, lane, a_frag, b_off, b_step, acc);
+                __syncthreads();             // nobody reads the ring any more
+            }
         }
     }
     if constexpr (DUMP)
@@ -974,7 +995,8 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
 }
 
 // Tile shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
-enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTileSplit };
+enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTileSplit, kTileSplitSmall2,
+                kTileSplitSmall4 };
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 // The shapes of quaff_gemm_rows.hip (a dump is recognised by g.acc1).

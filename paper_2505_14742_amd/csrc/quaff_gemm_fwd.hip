@@ -11,6 +11,8 @@ hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_
         case kTile128x192: return launch_dma<128, 192, 2, 2, 2, 2, false>(g, dump_acc, stream);
         case kTile128x192Deep: return launch_dma<128, 192, 2, 2, 3, 2, false>(g, dump_acc, stream);
         case kTileSplit: return launch_dma_form<256, 192, 4, 2, 2, 1, false, false, 2>(g, dump_acc, stream);
+        case kTileSplitSmall2: return launch_dma_form<128, 192, 2, 2, 3, 2, false, false, 2>(g, dump_acc, stream);
+        case kTileSplitSmall4: return launch_dma_form<128, 192, 2, 2, 3, 2, false, false, 4>(g, dump_acc, stream);
     }
     return hipErrorInvalidValue;
 }

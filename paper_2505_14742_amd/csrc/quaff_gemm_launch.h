@@ -11,8 +11,8 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
     int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
     TileMap tm = make_tile_map(tiles_m, tiles_n, BM, BN, MINB);
     while ((tm.rm + tm.gm - 1) / tm.gm > 65535) tm.gm *= 2;
-    // x % 8 = XCD, x / 8 = tile row inside a group of gm, y = tile column, z = group; a split contraction doubles y
-    // (the two halves of a tile are neighbours)
+    // x % 8 = XCD, x / 8 = tile row inside a group of gm, y = tile column, z = group; a split contraction multiplies y
+    // (the parts of a tile are neighbours)
     const int groups = (tm.rm + tm.gm - 1) / tm.gm;
     dim3 grid(8 * (unsigned)tm.gm, (unsigned)tm.rn * KSPLIT, (unsigned)groups), block(C::NT);
     if (tm.rn * KSPLIT > 65535) return hipErrorInvalidValue;
@@ -20,7 +20,7 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
     if (!dump && (int64_t)(g.K2 / 64) * C::K2_PLANES_BYTES > C::EPI_LIMIT) return hipErrorInvalidValue;
     const size_t lds = dump ? C::LDS_BYTES : C::LDS_ALLOC;
     auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT>;
-    if constexpr (KSPLIT == 2) {
+    if constexpr (KSPLIT > 1) {
         if (dump || g.C16 || g.accumulate) return hipErrorInvalidValue;
     } else {
         if (dump) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED>;

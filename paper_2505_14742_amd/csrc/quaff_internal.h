@@ -197,8 +197,11 @@ struct GemmArgs {
     // optional scratch for a contraction split over two workgroups per tile (gemm_split_bytes(M, N) bytes,
     // 256-byte aligned; nullptr = never split) and the bound of the taker's wait in 100 MHz ticks
     void* split_scratch; long long split_wait_ticks;
+    // the same for a small output whose contraction two or four workgroups share (gemm_small_split_bytes)
+    void* small_split_scratch;
 };
 size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);   // 0 for products that are not split
+size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, bool gradient);   // the same
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream);
 
 }  // namespace quaff
