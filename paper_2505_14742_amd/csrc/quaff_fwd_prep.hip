@@ -461,17 +461,23 @@ fwd_prep_kernel(const FwdPrepArgs a) {
 
 int fwd_prep_groups(int64_t t) { return (int)((t + kPrepRows - 1) / kPrepRows); }
 
-// Who requantizes what (c_out channels in rounds of 64).  With 2048 rows every workgroup owns rows and takes its share of
-// the channels afterwards.  With fewer rows the launch is filled up with workgroups that own none and only wait for
-// the maxima: one round each where that many compute units are left, two at most, so that the channels are done while
-// the row owners quantize; with less room everybody takes an equal share.  (Left to the row owners alone, 16 rows and
-// 9216 channels are 72 rounds in each of two workgroups: 188 us for the launch, 12 us this way; 512 rows and 3072
-// channels 13.4 -> 12.3 us.)  The extra workgroups announce
-// themselves like the others, with empty maxima: whoever publishes the new scales must know that they have read the old.
-static void fwd_prep_split(int64_t t, int64_t c_out, int* groups, int* what_first) {
+// Who requantizes what (c_out channels in rounds of 64).  With 1024 rows and more the workgroups that own them take their
+// share of the channels afterwards.  With fewer rows the launch is filled up with workgroups that own none and only wait for
+// the maxima: one round each where that fits, two at most, so that the channels are done while the row owners
+// quantize; with less room everybody takes an equal share.  (Left to the row owners alone, 16 rows and 9216 channels are 72
+// rounds in each of two workgroups: 188 us for the launch, 12 us this way.)  Every workgroup polls one word per outlier and
+// workgroup, so filling up costs as well: forward steps, row owners alone / filled up to 128 / to 256 workgroups, us: 1024 x 1536
+// -> 8192 35.5 / 35.3 / 42.3, 768 x 1536 -> 8192 34.9 / 35.6 / 38.9, 512 x 3072 -> 8192 42.6 / 38.9 / 40.1.  Hence 128; 192
+// where that gives a handful of rows one round each (32 x 1536 -> 8192 19.3 -> 18.6), 256 with rows so long that the owners
+// arrive late (256 x 8192 -> 16384 71.2 -> 67.1), and none where short rows' owners have at most a round each (512 x 1536 -> 3072
+// 27.2 / 28.6 / 28.7).  The extra workgroups announce themselves like the others, with empty maxima: whoever publishes the
+// new scales must know that they have read the old.
+static void fwd_prep_split(int64_t t, int64_t c_in, int64_t c_out, int* groups, int* what_first) {
     const int rows = fwd_prep_groups(t);
     const int64_t rounds = (c_out + kWhatChunk - 1) / kWhatChunk;
-    const int room = kPrepMaxGroups - rows;
+    const int cap = c_in > 4096 ? kPrepMaxGroups : rows <= 8 && rows + rounds <= 192 ? 192 : 128;
+    const bool none = c_in <= 2048 && rounds <= rows && (c_in > 1024 || rows >= 48);
+    const int room = none || rows > cap ? 0 : cap - rows;
     const int extra = (int)(rounds < room ? rounds : room);
     *groups = rows + extra;
     *what_first = 2 * (int64_t)extra >= rounds ? rows : 0;
@@ -507,7 +513,7 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
     a.W_O = W_O; a.c_out = c_out; a.what_int = what_int; a.delta_what = delta_what;
     a.Xq = Xq; a.delta = delta; a.xq_O = xq_O;
     a.A = A; a.scale = scale; a.T_hi = T_hi; a.T_lo = T_lo; a.B = B; a.Bt = Bt;
-    fwd_prep_split(t, c_out, &a.groups, &a.what_first);
+    fwd_prep_split(t, c, c_out, &a.groups, &a.what_first);
     a.part = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + 256);
     a.epoch = reinterpret_cast<uint32_t*>(scratch);
     a.wait_ticks = wait_ticks;

@@ -31,3 +31,15 @@ def test_few_rows(t, c_in, c_out, r, wait):
     finally:
         if prev is not None:
             q.debug_grid_wait_ticks(prev)
+
+
+# how far the launch is filled up: to 128 workgroups with two rounds each and with an equal share for everybody, to 192, to
+# 256 (long rows), not at all (short rows whose owners have a round each at most; 128 owners and more)
+_FILLS = [(128, 128, 12800, 16), (500, 1040, 9216, 16), (64, 272, 10240, 0), (72, 272, 7696, 16), (40, 4112, 1040, 16),
+          (260, 1040, 2064, 16), (384, 1024, 3072, 16), (1024, 128, 9232, 0), (1030, 128, 9232, 16)]
+
+
+@pytest.mark.parametrize("wait", ["waits", "gives_up"])
+@pytest.mark.parametrize("t,c_in,c_out,r", _FILLS, ids=["%dx%dx%d_r%d" % c for c in _FILLS])
+def test_how_far_filled(t, c_in, c_out, r, wait):
+    test_few_rows(t, c_in, c_out, r, wait)
