@@ -160,4 +160,86 @@ __device__ __forceinline__ void quant_rows_body(int block, const uint16_t* __res
     }
 }
 
+// The same for long rows without outlier codes: the workgroup's NT threads share ROWS rows, every thread holding the same
+// NV x 8 columns of all of them, so that a column scale is fetched once per workgroup and stays in registers.  (With a
+// row to itself a quarter of the workgroup fetches each scale twice per element, maximum pass and code pass: four times the
+// traffic of dY through the L1.  cs may be null.)
+template <int NT, int ROWS, int NV>
+__device__ __forceinline__ void quant_rows_shared_body(int block, const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx,
+                                                       const float* __restrict__ cs, int8_t* __restrict__ Xq,
+                                                       float* __restrict__ delta) {
+    __shared__ float red[NT / 64][ROWS];
+    __shared__ float steps[ROWS];
+    const int64_t row0 = (int64_t)block * ROWS;
+    if (row0 >= t) return;                          // (uniform over the workgroup)
+    const int live = t - row0 < ROWS ? (int)(t - row0) : ROWS;
+    u32x4 raw[ROWS][NV];
+    f32x4 s[NV][2];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int col = (i * NT + threadIdx.x) * 8;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            raw[r][i] = (u32x4){0, 0, 0, 0};
+            if (col < c && r < live) raw[r][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(X + (row0 + r) * ldx + col));
+        }
+        s[i][0] = s[i][1] = (f32x4){1.0f, 1.0f, 1.0f, 1.0f};
+        if (cs && col < c) {
+            s[i][0] = *reinterpret_cast<const f32x4*>(cs + col);
+            s[i][1] = *reinterpret_cast<const f32x4*>(cs + col + 4);
+        }
+    }
+    auto scaled = [&](int r, int i, float (&v)[8]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            v[2 * u] = __fmul_rn(__uint_as_float(raw[r][i][u] << 16), s[i][u >> 1][2 * (u & 1)]);
+            v[2 * u + 1] = __fmul_rn(__uint_as_float(raw[r][i][u] & 0xFFFF0000u), s[i][u >> 1][2 * (u & 1) + 1]);
+        }
+    };
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        float m = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if ((i * NT + wave * 64) * 8 < c) {     // (columns past the end are zeros)
+                float v[8];
+                scaled(r, i, v);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(v[u]));
+            }
+        }
+        m = wave_max(m);
+        if ((threadIdx.x & 63) == 0) red[wave][r] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x < ROWS) {
+        float m = 0.0f, d, cc;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) m = fmaxf(m, red[w][threadIdx.x]);
+        rtn_steps(m, d, cc);
+        steps[threadIdx.x] = cc;
+        if ((int)threadIdx.x < live) delta[row0 + threadIdx.x] = d;
+    }
+    // (the scaled values are computed again: kept from the first pass they would take twice the registers of the rows)
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) asm volatile("" : "+v"(raw[r][i]));
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const float cc = steps[r];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int col = (i * NT + threadIdx.x) * 8;
+            if (col < c && r < live) {
+                float v[8];
+                scaled(r, i, v);
+                *reinterpret_cast<u32x2*>(Xq + (row0 + r) * (int64_t)c + col) = pack_codes(v, cc);
+            }
+        }
+    }
+}
+
 }  // namespace quaff

@@ -10,6 +10,9 @@
 
 namespace quaff {
 
+// rows per quantizing workgroup: TPR threads take one, or all of them share eight (TPR = 1024)
+constexpr int quant_rows_per_block(int TPR) { return TPR <= 256 ? 64 * kLoraWaves / TPR : 8; }
+
 template <int R16, int TPR, int NV>
 __global__ void __launch_bounds__(64 * kLoraWaves)
 quant_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const float* __restrict__ cs,
@@ -24,13 +27,16 @@ quant_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx,
         // The hardware deals consecutive workgroups to the eight XCDs in turn and every XCD has its own L2: the
         // quantizing workgroups of a row block are renumbered so that they land on the XCD whose down-projection
         // workgroups (index = row block of 16 RG rows, same residue modulo 8) read the same rows at about the same time.
-        constexpr int QPG = 16 / ((64 * kLoraWaves) / TPR);   // quantizing workgroups per 16-row block (1 or 4)
+        constexpr int ROWS = quant_rows_per_block(TPR), QPG = 16 / ROWS;   // quantizing workgroups per 16-row block
         const int local = blockIdx.x - lora_blocks;
         const int xcd = local & 7, m = local >> 3;
         const int mq = m / QPG;
         const int rb = ((mq / RG) * 8 + xcd) * RG + mq % RG;   // 16-row block
-        quant_rows_body<64 * kLoraWaves, TPR, NV>(rb * QPG + m % QPG, X, t, c, ldx, cs, nullptr, 0, 0, Xq, delta,
-                                                  nullptr);
+        if constexpr (TPR <= 256)
+            quant_rows_body<64 * kLoraWaves, TPR, NV>(rb * QPG + m % QPG, X, t, c, ldx, cs, nullptr, 0, 0, Xq, delta,
+                                                      nullptr);
+        else
+            quant_rows_shared_body<64 * kLoraWaves, ROWS, NV>(rb * QPG + m % QPG, X, t, c, ldx, cs, Xq, delta);
     }
 }
 
@@ -276,13 +282,20 @@ static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const flo
 #define QUAFF_QL(TPR, NV)                                                                                             \
     hipLaunchKernelGGL((quant_lora_kernel<R16, TPR, NV>),                                                             \
                        dim3((unsigned)(lora_row_blocks * kLoraParts +                                                 \
-                                       8 * RG * ((row_blocks + 8 * RG - 1) / (8 * RG)) * (16 / (NT / TPR)))),         \
+                                       8 * RG * ((row_blocks + 8 * RG - 1) / (8 * RG)) * (16 / quant_rows_per_block(TPR)))),         \
                        dim3(NT), 0,                                                                                   \
                        stream, X, t, c, ldx, cs, Xq, delta, L, scale, T_hi, T_lo, lora_row_blocks)
     if (vec <= 64 * 2) QUAFF_QL(64, 2);
     else if (vec <= 64 * 4) QUAFF_QL(64, 4);
     else if (vec <= 64 * 6) QUAFF_QL(64, 6);
     else if (vec <= 64 * 8) QUAFF_QL(64, 8);
+    // From rank 48 on a compute unit holds one workgroup of this launch, and with more than 2048 rows the quantizing ones come
+    // in several rounds: eight rows each, sharing the column scales, instead of four.  This launch, us: rank 64, 4096 x 11008
+    // 65.6 -> 58.0, 4096 x 4864 32.9 -> 29.2; rank 48 55.4 -> 52.8 and 27.2 -> 24.6.  At 2048 rows (rank 64: 24.8 / 25.8 at 6144
+    // columns, 35.7 / 36.5 at 9216) and at lower ranks, where two workgroups of four rows share a unit (rank 32, 4096 x 11008
+    // 56.7 / 60.3), four rows are level or faster.
+    else if (R16 >= 3 && t > 2048 && vec <= 1024) { if constexpr (R16 >= 3) QUAFF_QL(1024, 1); }
+    else if (R16 >= 3 && t > 2048 && vec <= 1024 * 2) { if constexpr (R16 >= 3) QUAFF_QL(1024, 2); }
     else if (vec <= 256 * 3) QUAFF_QL(256, 3);
     else if (vec <= 256 * 4) QUAFF_QL(256, 4);
     else if (vec <= 256 * 6) QUAFF_QL(256, 6);
