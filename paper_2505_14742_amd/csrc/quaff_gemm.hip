@@ -142,22 +142,22 @@ hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
     return launch_gemm_one(g, dump_acc, stream);
 }
 
+// Which kernel a product with an adapter takes depends on its sizes alone, not on the type of its output and not on the room
+// in the workspace: the kernels add the low-rank term in different orders, and a call's last bits may not depend on either.
 hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
+    const bool gradient = g.b_layout == kPackedKN, one_launch = !dump_acc && !g.accumulate && g.K2 <= 128;
+    const int parts = one_launch ? small_split(g.M, g.N, g.K, gradient) : 1;
     int tile;
-    if (g.split_scratch && !dump_acc && !g.C16 && !g.accumulate && g.K2 <= 128 && split_applies(g.M, g.N, g.K))
+    if (g.split_scratch && one_launch && split_applies(g.M, g.N, g.K)) {
         tile = kTileSplit;
-    else
-    {
-        const bool gradient = g.b_layout == kPackedKN;
-        if (g.small_split_scratch && !dump_acc && !g.C16 && !g.accumulate && g.K2 <= 128) {
-            const int parts = small_split(g.M, g.N, g.K, gradient);
-            if (parts > 1) {
-                GemmArgs split = g;
-                split.split_scratch = g.small_split_scratch;
-                const int t = parts == 2 ? kTileSplitSmall2 : kTileSplitSmall4;
-                return gradient ? launch_gemm_kn(split, t, false, stream) : launch_gemm_nk(split, t, false, stream);
-            }
-        }
+    } else if (parts > 1 && g.small_split_scratch) {
+        GemmArgs split = g;
+        split.split_scratch = g.small_split_scratch;
+        tile = parts == 2 ? kTileSplitSmall2 : kTileSplitSmall4;
+        return gradient ? launch_gemm_kn(split, tile, false, stream) : launch_gemm_nk(split, tile, false, stream);
+    } else if (parts > 1 && g.r > 0) {
+        tile = kTile128x192;             // (no room for the exchange: the shared form's tile and epilogue, one workgroup each)
+    } else {
         double work, us;
         tile = choose_tile(g.M, g.N, &work);
         const int rows = choose_rows(g.M, g.N, g.K, gradient, work, &us);
@@ -172,7 +172,7 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
     // compiler's schedule is 2 - 8 % slower).  With more tiles than units two workgroups per unit overlap each
     // other's epilogues instead, which needs the smaller ring.
     if (tile == kTile128x192 && ((g.M + 127) / 128) * ((g.N + 191) / 192) <= 256) tile = kTile128x192Deep;
-    return g.b_layout == kPackedKN ? launch_gemm_kn(g, tile, dump_acc, stream) : launch_gemm_nk(g, tile, dump_acc, stream);
+    return gradient ? launch_gemm_kn(g, tile, dump_acc, stream) : launch_gemm_nk(g, tile, dump_acc, stream);
 }
 
 }  // namespace quaff

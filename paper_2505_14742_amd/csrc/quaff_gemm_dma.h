@@ -511,7 +511,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int64_t ib = row0 + i * 32;
-            if (ib >= g.M) continue;             // uniform over the wavefront
+            if (ib >= g.M || !active) continue;  // uniform over the wavefront
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
 #pragma unroll

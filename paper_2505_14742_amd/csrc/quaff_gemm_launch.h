@@ -21,7 +21,8 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
     const size_t lds = dump ? C::LDS_BYTES : C::LDS_ALLOC;
     auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT>;
     if constexpr (KSPLIT > 1) {
-        if (dump || g.C16 || g.accumulate) return hipErrorInvalidValue;
+        if (dump || g.accumulate) return hipErrorInvalidValue;
+        if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, KSPLIT>;
     } else {
         if (dump) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED>;
         else if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED>;

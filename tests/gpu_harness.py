@@ -221,3 +221,18 @@ def check_step(L: Layer, R: OracleLayer, X_u16, dY_u16, gamma, rows=None, backwa
         out["bwd_err"] = assert_close_fp32(host(L.dX[idx]), dX_o, tag + " dX")
     torch.cuda.synchronize()
     return out
+
+
+def smallest_workspace(call, full):
+    """The smallest workspace size, at most `full`, that call(size) accepts."""
+    lo, hi = 0, full
+    while lo < hi:
+        mid = (lo + hi) // 2
+        try:
+            call(mid)
+            hi = mid
+        except q.QuaffError as e:
+            if e.status != q.ERR_WORKSPACE:
+                raise
+            lo = mid + 1
+    return lo

@@ -88,3 +88,43 @@ def test_bf16_outputs(case):
     _check(host(Y16), Y_o, case + " Y")
     dX_o = orc.linear_bwd_dx(dY, Wq, dw, A if has_lora else None, B if has_lora else None, scale)[0]
     _check(host(dX16), dX_o, case + " dX")
+
+
+# Sizes at which a product takes one of its special forms: the contraction shared by four workgroups (forward; gradient) and
+# by two, ragged rows with a rank that needs two staging rounds, the long contraction shared by two workgroups of the 256-row
+# tile with ragged rows.  (t, c_in, c_out, rank)
+_FORMS = [(512, 8192, 2048, 16), (256, 3072, 8192, 16), (512, 3072, 3072, 32), (257, 8192, 3072, 48), (2000, 3072, 12288, 16)]
+
+
+@pytest.mark.parametrize("t,c_in,c_out,r", _FORMS, ids=["%dx%dx%d_r%d" % c for c in _FORMS])
+def test_bf16_is_the_rounded_fp32_result_in_every_form(t, c_in, c_out, r):
+    """Same sizes, same arithmetic: the bf16 calls give the fp32 calls' results rounded, with all the workspace the library
+    asks for and with the smallest that it accepts, and the fp32 results do not depend on the workspace's size either."""
+    import torch
+    from paper_2505_14742_amd import binding as q
+    from tests.gpu_harness import DEV, Layer, bf16_dev, smallest_workspace
+    X, dY, W, O, A, B = synth.edge_case_inputs(synth.EdgeCase("bf16_forms", t, c_in, c_out, [3, 77, c_in - 1], r), 61)
+    print("bf16 forms", t, c_in, c_out, r, flush=True)
+    L = Layer(W, O, A, B, 0.5, t)
+    Xd, Gd = bf16_dev(X), bf16_dev(dY)
+    L.fwd_step(Xd, 0.2)
+    full = torch.empty(q.workspace_bytes(t, c_in, c_out, L.n, r), dtype=torch.int8, device=DEV)
+
+    def fwd(ws, bf16):
+        out = torch.full((t, c_out), 0x7FC0 if bf16 else float("nan"), dtype=torch.int16 if bf16 else torch.float32, device=DEV)
+        q.linear_fwd(L.Xq, L.delta_x, L.xq_O, L.Wq_packed, L.delta_w, c_in, c_out, L.what_int, L.delta_what, L.n, Xd, L.A, L.B,
+                     r, 0.5, out, ws, bf16_out=bf16)
+        return out
+
+    def bwd(ws, bf16):
+        out = torch.full((t, c_in), 0x7FC0 if bf16 else float("nan"), dtype=torch.int16 if bf16 else torch.float32, device=DEV)
+        q.linear_bwd_dx(Gd, L.Wq_packed, L.delta_w, c_in, c_out, L.A, L.B, r, 0.5, out, ws, bf16_out=bf16)
+        return out
+
+    for what, call in (("Y", fwd), ("dX", bwd)):
+        small = full[:smallest_workspace(lambda size: call(full[:size], False), full.numel())]
+        want = call(full, False)
+        assert torch.isfinite(want).all()
+        assert torch.equal(call(small, False), want), what + " depends on the size of the workspace"
+        for ws in (full, small):
+            assert torch.equal(call(ws, True).view(torch.bfloat16), want.to(torch.bfloat16)), what + " is not RNE(fp32 %s)" % what
