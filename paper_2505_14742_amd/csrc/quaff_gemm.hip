@@ -98,7 +98,10 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 // measured products each way; 4 % must be gained.  Forward, one / two / four workgroups per tile, us: 512 x 3072 outputs 19.7 /
 // 17.0 / 18.3 at K = 3072, 43.3 / 29.0 / 26.2 at 8192, 10.6 / 11.6 / 13.1 at 1024; 1024 x 3072 outputs 20.2 / 20.7 at 3072,
 // 44.0 / 34.7 at 8192; 256 x 3072 outputs at 8192 30.6 (64 x 96 tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x
-// 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.
+// 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.  The workgroups of a tile run on one XCD and one of them
+// fills a compute unit: no more of them than the 32 units of an XCD, or the last tiles start when the first have ended
+// (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 /
+// 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
 static int small_split(int64_t M, int64_t N, int64_t K, bool gradient) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
     if (tiles > 128 || K % 256 != 0) return 1;
@@ -109,8 +112,11 @@ static int small_split(int64_t M, int64_t N, int64_t K, bool gradient) {
     if (choose_rows(M, N, K, gradient, work, &best_us) != kRowsNone && best_us < alone) alone = best_us;
     const double two = 1.04 * (9.7 + 6.5 * busy + (2.2 + 1.6 * busy) * k);
     const double four = 1.04 * (11.0 + 13.0 * busy + (1.15 + 3.1 * busy) * k);
-    if (tiles <= 64 && K % 512 == 0 && four < alone && four < two) return 4;
-    return two < alone ? 2 : 1;
+    // (tiles on the busiest XCD: the grid is cut into eight regions of equal size, rounded up)
+    const TileMap map = make_tile_map((int)((M + 127) / 128), (int)((N + 191) / 192), 128, 192, 1);
+    const int on_xcd = map.rm * map.rn;
+    if (4 * on_xcd <= 32 && K % 512 == 0 && four < alone && four < two) return 4;
+    return 2 * on_xcd <= 32 && two < alone ? 2 : 1;
 }
 size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, bool gradient) {
     const int parts = small_split(M, N, K, gradient);

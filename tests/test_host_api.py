@@ -128,3 +128,23 @@ def test_binding_raises_with_status_text():
     with pytest.raises(q.QuaffError) as e:
         q._check(q.ERR_ALIGN)
     assert "ALIGN" in str(e.value)
+
+
+def test_a_shared_contraction_fits_its_xcd():
+    """The workgroups that share a tile's contraction run on one XCD, 32 compute units, one workgroup each, and an output is
+    dealt to the XCDs in eight equal regions of tiles.  The workspace holds an exchange area exactly where the contraction is
+    shared, and its size tells between how many: in no grid of tiles may the workgroups of a region be more than 32."""
+    one_part = lambda t, c_out: q.fwd_step_workspace_bytes(t, 16, c_out, 0, 0)      # (never shared: 16 is no whole stage)
+    up = lambda size: (size + 255) // 256 * 256
+    shared = set()
+    for tm in range(1, 129):
+        for tn in range(1, 128 // tm + 1):
+            region = min(-(-tm // xm) * -(-tn // (8 // xm)) for xm in (1, 2, 4, 8))
+            area = {1: 0, 2: up(tm * tn * (2 * 128 + 256 * 96 * 4)), 4: up(tm * tn * (16 * 128 + 4 * 256 * 96 * 4))}
+            for t, c_out in ((128 * tm, 192 * tn), (128 * tm - 127, 192 * tn - 176)):
+                for K in (1024, 3072, 4096, 8192, 16384):
+                    extra = q.fwd_step_workspace_bytes(t, K, c_out, 0, 0) - one_part(t, c_out)
+                    parts, = (p for p in area if area[p] == extra)
+                    assert parts == 1 or parts * region <= 32, (tm, tn, K, parts, region)
+                    shared.add(parts)
+    assert shared == {1, 2, 4}
