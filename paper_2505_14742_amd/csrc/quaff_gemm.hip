@@ -45,11 +45,15 @@ int choose_tile(int64_t M, int64_t N, double* best_work) {
 
 // Small outputs.  Estimated time of a shape of quaff_gemm_rows.hip: launch and epilogue, then the slower of the two ways its
 // operands arrive - one compute unit's share at `cu_rate`, or all of it at `chip_rate` - and 1.5 us for every further
-// round of 256 tiles (their epilogues do not overlap their loads).  Against it stand 8 us and, per 1024 bytes of contraction,
-// 4.4 us (6.1 with every compute unit busy) per pass of 128 x 192 tiles.  The constants are fitted to 1231 measured products of
-// 1 to 4096 rows, 16 to 16384 columns and contractions: the choice takes 0.41 (forward) and 0.45 (input gradient) of the
-// time of the large tiles alone in the geometric mean and is within 6 % of the best of all measured shapes; in 5 of the
-// 1231 it is more than 3 % slower than the large tiles.  The factor 1.1 keeps close calls where they were.
+// round of 256 tiles (their epilogues do not overlap their loads).  Against it stand, per 1024 bytes of contraction, 4.4 us (6.1
+// with every compute unit busy) per pass of 128 x 192 tiles and 8 us; 7 where tiles without an edge have little to multiply
+// (768 x 1536 and 384 x 3072 outputs, large tiles / 32 x 64 tiles: forward 8.2 / 9.5 us at K = 256, 10.5 / 11.3 at 768; input
+// gradient with its quantizer 9.6 / 11.6 at 256, 10.9 / 12.3 at 512; with edges, 722 x 1776 outputs at 256, 10.0 / 9.6).  The
+// factor 1.1 keeps close calls with the large tiles.  Over 2388 products of 1 to 2500 rows, 64 to 12000 columns and 128 to 14000
+// contractions, every shape and split timed, the choice takes 0.45 (forward) and 0.62 (input gradient, quantizer included) of
+// the time of the large tiles in the geometric mean; one is more than 2 % slower than them (575 x 2080 at 512: 12.4 / 12.0).
+// Against the best of all shapes it is 1.4 % slower in the mean and more than 20 % in 46, most of them long
+// contractions for which the 64 x 96 tile is taken for faster than it is (256 x 2048 at 8192: 31.5 us, 32 x 64 tiles 18.9).
 struct RowsChoice { int shape, bm, bn; double fixed_us, cu_rate, chip_rate; };   // rates in KB/us and MB/us
 constexpr RowsChoice kRowsForward[4] = {
     {kRows16x16, 16, 16, 3.2, 83, 11.5}, {kRows32x32, 32, 32, 3.6, 79, 10.2}, {kRows32x64, 32, 64, 4.4, 84, 10.1}, {kRows64x96, 64, 96, 7.9, 80, 7.7}};
@@ -59,7 +63,8 @@ int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work
     const double passes = tile_work / (128.0 * 192.0 * kChoices[kTile128x192].ineff);
     const int64_t wide_tiles = ((M + 127) / 128) * ((N + 191) / 192);
     const double busy = wide_tiles < 256 ? wide_tiles / 256.0 : 1.0;
-    double best_us = (8.0 + (double)K * 1e-3 * passes * (4.4 + 1.75 * busy)) / 1.1;
+    const bool short_and_whole = K <= 1024 && M % 128 == 0 && N % 192 == 0;
+    double best_us = ((short_and_whole ? 7.0 : 8.0) + (double)K * 1e-3 * passes * (4.4 + 1.75 * busy)) / 1.1;
     int best = kRowsNone;
     for (int c = 0; c < (gradient ? 2 : 4); ++c) {
         const RowsChoice& r = gradient ? kRowsGradient[c] : kRowsForward[c];
