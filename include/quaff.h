@@ -184,8 +184,9 @@ int quaff_linear_fwd(const int8_t* Xq, const float* delta_x, const int8_t* xq_O,
  * tokens): its workgroups announce themselves through a word of `workspace` and wait for each other.  That wait is
  * bounded (see quaff_debug_grid_wait_ticks); a workgroup that gives up recomputes the maxima from X itself, so the
  * results are the same whether or not all workgroups are resident at once.  `workspace` is read and written while
- * the call runs and must not be shared with work that may run at the same time (as for every call here); what an
- * earlier call left in it does not matter.
+ * the call runs and must not be shared with work that may run at the same time (as for every call here); what it
+ * holds before the call does not matter: the words the workgroups exchange are zeros again when a call ends, and each
+ * carries a 34-bit mark of its launch, which other data in their place would have to repeat by chance.
  * `workspace` must hold quaff_fwd_step_workspace_bytes(t, c_in, c_out, n_outlier, lora_rank) bytes.
  */
 size_t quaff_fwd_step_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank);

@@ -535,7 +535,7 @@ int quaff_calibrate_outliers(const uint16_t* X, int64_t t_total, int64_t c_in, i
 size_t quaff_fwd_step_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || n_outlier < 0 || lora_rank < 0) return 0;
     return ws_scale(t, n_outlier) + ws_fwd(t, c_in, c_out, lora_rank).total +
-           quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64) + split_fwd(t, c_in, c_out) + 256;
+           align_up(quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64)) + split_fwd(t, c_in, c_out) + 256;
 }
 
 long long quaff_debug_grid_wait_ticks(long long ticks) {
@@ -552,19 +552,23 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     const size_t scale_bytes = ws_scale(t, n_outlier);
     const FwdWs wf = ws_fwd(t, c_in, c_out, lora_rank);
     const size_t prep_bytes = quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64);
-    if (!workspace || workspace_bytes < scale_bytes + wf.total + prep_bytes) return QUAFF_ERR_WORKSPACE;
+    // (an odd count of outliers: half a row of the words less is accepted, as it was with 32 bits for each outlier; calls
+    // that need it then take the launches of longer inputs)
+    const size_t prep_at = scale_bytes + wf.total, prep_least = prep_bytes - (n_outlier < 64 && n_outlier % 2 ? 1024 : 0);
+    if (!workspace || workspace_bytes < prep_at + prep_least) return QUAFF_ERR_WORKSPACE;
     if (!aligned16(workspace)) return QUAFF_ERR_ALIGN;
     if (!colscale) return QUAFF_ERR_NULL;
     if (n_outlier > 0 && !xq_O) return QUAFF_ERR_NULL;
     char* base = static_cast<char*>(workspace);
     void* ws_lin = base + scale_bytes;
     const size_t ws_lin_bytes = workspace_bytes - scale_bytes;
-    const size_t split_at = scale_bytes + wf.total + align_up(prep_bytes);
+    const size_t split_at = prep_at + align_up(prep_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // One launch prepares everything the product needs where it can (a few thousand tokens, at most 64 outlier
     // channels, rank 0 or 16); two combined launches cover the other usual cases; everything else is the three calls
     // one after the other.
-    const bool fused = quaff::fwd_prep_covers(t, c_in, n_outlier, lora_rank);
+    const size_t words_bytes = quaff::fwd_prep_covers(t, c_in, n_outlier, lora_rank) ? quaff::fwd_prep_words_bytes(t, c_in, c_out, n_outlier) : 0;
+    const bool fused = words_bytes > 0 && workspace_bytes >= prep_at + quaff::kFwdPrepWordsAt + words_bytes;
     const bool combined = !fused && n_outlier > 0 && n_outlier <= 1024 && (int64_t)n_outlier * 64 < c_in && lora_rank > 0;
     if (!fused && !combined) {
         int st = quaff_scale_update(X, t, c_in, ldx, O, n_outlier, W_O, wmax_O, c_out, gamma, s_O, colscale, what_int,
@@ -593,13 +597,14 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
         int st = hip_status(quaff::launch_fwd_prep(X, t, c_in, ldx, O, n_outlier, wmax_O, gamma, s_O, colscale, cmax_out,
                                                    W_O, c_out, what_int, delta_what, Xq, delta_x, xq_O, lora_A, lora_B,
                                                    lora_rank, lora_scale, t_hi, t_lo, lt,
-                                                   base + scale_bytes + wf.total, g_grid_wait_ticks.load(), s));
+                                                   base + prep_at, g_grid_wait_ticks.load(), s));
         if (st != QUAFF_OK) return st;
         quaff::GemmArgs g;
         st = fwd_common(Xq, delta_x, xq_O, t, Wq_packed, delta_w, c_in, c_out, what_int, delta_what, n_outlier, g);
         if (st != QUAFF_OK) return st;
         if (lora_rank > 0) { g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank; }
         g.C = Y; g.ldc = ldy;
+        g.clear = base + prep_at + quaff::kFwdPrepWordsAt; g.clear_bytes = (int32_t)words_bytes;
         set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out), workspace_bytes);
         return hip_status(quaff::launch_gemm(g, false, s));
     }

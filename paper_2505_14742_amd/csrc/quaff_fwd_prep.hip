@@ -6,11 +6,15 @@
 // The column maxima are the one step that needs all rows: every workgroup writes the maxima of its rows, does the
 // work that does not depend on them (down-projection, copy of the column scales) and then reads everybody's maxima.
 // No read-modify-write atomic is involved (256 workgroups arriving at one counter within a microsecond serialise at
-// one memory round trip each): a maximum travels as a 32-bit word whose upper half is the bf16 magnitude and whose
-// lower half is a tag, the low 16 bits of (epoch + 1); `epoch` is a word of the workspace that every workgroup reads
-// before it writes and that is set to epoch + 1 once all maxima of the launch have been seen - so words left by an
-// earlier launch, or by anything else that used the memory, do not carry this launch's tag.  A workgroup has
-// everything when all n x groups words carry the tag.  The wait is bounded: a workgroup that has not seen them within
+// one memory round trip each): the maxima of two columns travel as a 64-bit word, two bf16 magnitudes of 15 bits under a
+// mark of 34 bits that is hashed from (epoch + 1); `epoch` is a word of the workspace that every workgroup reads before it
+// writes and that is set to epoch + 1 once all maxima of the launch have been seen.  The words are zeros again when the
+// call ends (the product's launch, which follows this one, clears them), so no word of an earlier call is ever there to
+// be taken for one of this launch, whatever the memory was used for in between and whatever `epoch` then holds; other
+// data would have to carry the mark by chance in every word of a workgroup (2^-34 a word, 2^-49 where it holds one
+// column).  A word for each column under a mark of 49 bits throughout doubles the bytes that every workgroup polls: 16 x
+// 3072 -> 9216 forward 21.5 -> 22.8 us.  A workgroup has everything when all words carry the mark.  The wait is
+// bounded: a workgroup that has not seen them within
 // `wait_ticks` (100 MHz ticks) computes the maxima of ALL rows itself from X - slower, the same bits - so the result
 // never depends on how many workgroups the hardware keeps resident at once.  Every workgroup that saw all maxima
 // (the last one to write always does) publishes s, 1/s and cmax - the same values - and the new epoch: by then every
@@ -30,6 +34,13 @@ constexpr int kPrepMaxGroups = 256;                // one workgroup per compute 
 constexpr int kPrepLtBlock = 640;                  // bytes of 16 rows of a wavefront's slice of A in LDS: 16 x 32 + padding
 constexpr int kWhatChunk = 64;                     // output channels of what requantized per round
 
+constexpr int kMagBits = 15;                       // a bf16 magnitude
+constexpr uint32_t kMagMask = (1u << kMagBits) - 1;
+// the mark of a launch: the upper bits of a multiplicative hash (2^64 over the golden ratio) of its epoch
+__device__ __forceinline__ uint64_t prep_mark(uint64_t epoch) {
+    return epoch * 0x9E3779B97F4A7C15ull >> (2 * kMagBits) << (2 * kMagBits);
+}
+
 struct FwdPrepArgs {
     const uint16_t* X; int64_t t; int c; int64_t ldx;
     const int32_t* O; int n; int n_pad;
@@ -38,8 +49,8 @@ struct FwdPrepArgs {
     int8_t* Xq; float* delta; int8_t* xq_O;
     const uint16_t* A; float scale; uint16_t* T_hi; uint16_t* T_lo;     // LoRA (HAS_LORA)
     const uint16_t* B; uint16_t* Bt;                                    // B [16 x c_out] -> Bt [c_out x 16]
-    uint32_t* part;               // [n][groups] maxima of each workgroup's rows: bf16 magnitude << 16 | tag
-    uint32_t* epoch;              // launch counter of this workspace (any start value)
+    uint64_t* part;               // [ceil(n / 2)][groups] maxima of each workgroup's rows: mark | odd column | even column
+    uint64_t* epoch;              // launch counter of this workspace (any start value)
     int groups;                   // workgroups of the launch: ceil(t / 8) own rows, the others (if any) only requantize what
     int what_first;               // what is requantized by the workgroups from this one on
     long long wait_ticks;
@@ -151,8 +162,8 @@ fwd_prep_kernel(const FwdPrepArgs a) {
     }
     // Device-scope atomic loads and stores go past the per-XCD L2s: no cache write-back or invalidation is needed to
     // hand the words from one workgroup to another.
-    const uint32_t epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t tag = (epoch + 1u) & 0xFFFFu;
+    const uint64_t epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t mark = prep_mark(epoch + 1);
     // ---- maxima of this workgroup's rows on the outlier columns: lanes 8 k .. 8 k + 7 hold the eight rows of column k
     uint16_t xo_raw = 0;     // X[row0 + tid % 8, O[tid / 8]]: also what the compact outlier codes are made from
     {
@@ -169,8 +180,10 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         // visible, because whoever sees all maxima may overwrite them: the barrier follows the LDS writes of the
         // loaded values.  (The epoch feeds the stored word itself.)
         __syncthreads();
-        if (k < n && rr == 0)
-            __hip_atomic_store(&a.part[(int64_t)k * G + blk], v | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t odd = (uint32_t)__shfl_down((int)v, 8, 64);    // column k + 1 (zero beyond n)
+        if (k < n && (tid & 15) == 0)
+            __hip_atomic_store(&a.part[(int64_t)(k >> 1) * G + blk], mark | (uint64_t)(odd >> 16) << kMagBits | (v >> 16),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 
     // ---- work that needs no other workgroup: transposed copy of B, copy of the column scales, down-projection
@@ -254,37 +267,44 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         }
     }
 
-    // ---- bounded wait for the other workgroups' maxima: wavefront w reads columns w, w + 16, ... (G contiguous words
-    // each) and reduces them with wavefront shuffles; the pass is repeated until every word carries this launch's tag
+    // ---- bounded wait for the other workgroups' maxima: wavefront w reads pairs w and w + 16 of columns (G contiguous words
+    // each) and reduces them with wavefront shuffles; the pass is repeated until every word carries this launch's mark
     const long long t0 = (long long)wall_clock64();
     for (;;) {
         if (tid == 0) flag_all = 1;
         if (tid < 64) smax[tid] = 0u;
         __syncthreads();
         bool mine = true;
-        // a wavefront has at most four columns (n <= 64) of at most four words per lane (G <= 256): all loads first
-        uint32_t wv4[4][4];
+        // a wavefront has at most two pairs of columns (n <= 64) of at most four words per lane (G <= 256): all loads first
+        uint64_t wv4[2][4];
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc)
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
-                const int k = wave + kc * kLoraWaves, i = lane + ii * 64;
-                wv4[kc][ii] = tag;                        // (absent words count as present, magnitude 0)
-                if (k < n && i < G)
-                    wv4[kc][ii] = __hip_atomic_load(&a.part[(int64_t)k * G + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-            const int k = wave + kc * kLoraWaves;
-            uint32_t v = 0;
+        for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
             for (int ii = 0; ii < 4; ++ii) {
-                mine = mine && (wv4[kc][ii] & 0xFFFFu) == tag;
-                v = max(v, wv4[kc][ii] & 0xFFFF0000u);
+                const int kp = wave + kc * kLoraWaves, i = lane + ii * 64;
+                wv4[kc][ii] = mark;                       // (absent words count as present, magnitudes 0)
+                if (2 * kp < n && i < G)
+                    wv4[kc][ii] = __hip_atomic_load(&a.part[(int64_t)kp * G + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off, 64));
-            if (lane == 0 && k < n) smax[k] = v;
+        for (int kc = 0; kc < 2; ++kc) {
+            const int k = 2 * (wave + kc * kLoraWaves);
+            const int mark_at = k + 1 < n ? 2 * kMagBits : kMagBits;       // (a last column alone: the other magnitude is 0)
+            uint32_t v0 = 0, v1 = 0;
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii) {
+                mine = mine && ((wv4[kc][ii] ^ mark) >> mark_at) == 0;
+                const uint32_t mags = (uint32_t)wv4[kc][ii];
+                v0 = max(v0, mags & kMagMask);
+                v1 = max(v1, mags >> kMagBits & kMagMask);
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                v0 = max(v0, (uint32_t)__shfl_xor((int)v0, off, 64));
+                v1 = max(v1, (uint32_t)__shfl_xor((int)v1, off, 64));
+            }
+            if (lane == 0 && k < n) smax[k] = v0 << 16;
+            if (lane == 0 && k + 1 < n) smax[k + 1] = v1 << 16;
         }
         if (!mine) flag_all = 0;
         __syncthreads();
@@ -333,7 +353,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
             if (a.cmax_out) a.cmax_out[tid] = cmax;
         }
     }
-    if (tid == 0 && flag_ok) __hip_atomic_store(a.epoch, epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0 && flag_ok) __hip_atomic_store(a.epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
 
     // ---- per-token quantization of this workgroup's rows, from the registers
@@ -488,7 +508,14 @@ bool fwd_prep_covers(int64_t t, int64_t c_in, int32_t n, int32_t r) {
     return t >= 1 && fwd_prep_groups(t) <= kPrepMaxGroups && n >= 1 && n <= 64 && (r == 0 || r == 16) && c_in <= 8192;
 }
 
-size_t fwd_prep_scratch_bytes(int32_t n) { return ((size_t)n * kPrepMaxGroups * 4 + 255) / 256 * 256 + 256; }
+// the words of one launch, and the most that any number of rows and channels takes with n outliers; each after 256 bytes
+// that hold the epoch
+size_t fwd_prep_words_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n) {
+    int groups, what_first;
+    fwd_prep_split(t, c_in, c_out, &groups, &what_first);
+    return (size_t)((n + 1) / 2) * groups * 8;
+}
+size_t fwd_prep_scratch_bytes(int32_t n) { return kFwdPrepWordsAt + (size_t)((n + 1) / 2) * kPrepMaxGroups * 8; }
 
 template <int NSTEP>
 static hipError_t launch_prep(bool has_lora, dim3 grid, size_t lds, hipStream_t stream, const FwdPrepArgs& a) {
@@ -514,8 +541,8 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
     a.Xq = Xq; a.delta = delta; a.xq_O = xq_O;
     a.A = A; a.scale = scale; a.T_hi = T_hi; a.T_lo = T_lo; a.B = B; a.Bt = Bt;
     fwd_prep_split(t, c, c_out, &a.groups, &a.what_first);
-    a.part = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + 256);
-    a.epoch = reinterpret_cast<uint32_t*>(scratch);
+    a.part = reinterpret_cast<uint64_t*>(static_cast<char*>(scratch) + kFwdPrepWordsAt);
+    a.epoch = reinterpret_cast<uint64_t*>(scratch);
     a.wait_ticks = wait_ticks;
     // steps per wavefront: two slices of the down-projection's sixteen per part
     const int cp = (((int)c + kLoraParts * 64 - 1) / (kLoraParts * 64)) * 64;

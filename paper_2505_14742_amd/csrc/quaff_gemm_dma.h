@@ -820,6 +820,12 @@ constexpr int split_flags(int ksplit) { return ksplit == 2 ? 2 : ksplit * ksplit
 constexpr int split_slot_sets(int ksplit) { return ksplit == 2 ? 1 : ksplit; }
 __device__ __forceinline__ unsigned xcc_id() { return __builtin_amdgcn_s_getreg(((4 - 1) << 11) | 20) & 15u; }
 
+// Part `part` of `parts` of the memory that a product clears on its way out (GemmArgs::clear): the words of the launch before it.
+__device__ __forceinline__ void clear_words(const GemmArgs& g, int part, int parts, int threads) {
+    for (int i = part * threads + (int)threadIdx.x; i < g.clear_bytes / 8; i += parts * threads)
+        static_cast<unsigned long long*>(g.clear)[i] = 0ull;
+}
+
 template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool DUMP, bool ACCUM = false, bool OUT16 = false,
           bool BT = false, bool RAGGED = false, int KSPLIT = 1>
 __global__ void __launch_bounds__(64 * WGM * WGN, MINB)
@@ -992,6 +998,8 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         gemm_epilogue_dump<C::TM, C::TN>(g, acc, m0 + wm * C::WM, n0 + wn * C::WN, l32, lhi);
     else
         gemm_epilogue_staged<C, ACCUM, OUT16>(g, acc, lds, lds, m0, n0, wm, wn, wave, lane, active);
+    if constexpr (!DUMP && !ACCUM && !OUT16 && !BT)
+        if (g.clear_bytes > 0 && kh == 0) clear_words(g, tile_m * tmap.tiles_n + tile_n, tmap.tiles_m * tmap.tiles_n, C::NT);
 }
 
 // Tile shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.

@@ -258,6 +258,8 @@ gemm_i8_rows_kernel(const GemmArgs g, const TileMap tmap) {
             for (int v = 0; v < 4; ++v) out[v] = c[v];
         }
     }
+    if constexpr (!BT)
+        if (g.clear_bytes > 0) clear_words(g, tile_m * tmap.tiles_n + tile_n, tmap.tiles_m * tmap.tiles_n, C::NT);
 }
 
 template <int MB, int NB, int NW, int D, bool BT>

@@ -147,10 +147,13 @@ bool launch_what_quant(const uint32_t* part, int nslab, int32_t n, const float* 
                        int8_t* Xq, float* delta, int8_t* xq_O, hipStream_t stream, hipError_t* err);
 
 // The whole forward preparation (abs-max, momentum, what, quantizer, down-projection, transposed B) in one launch and
-// one pass over X (quaff_fwd_prep.hip).  `scratch` (fwd_prep_scratch_bytes(n) bytes, 256-byte aligned) holds the arrival
-// word of the bounded grid-wide wait and the per-workgroup column maxima; wait_ticks bounds that wait (100 MHz ticks).
+// one pass over X (quaff_fwd_prep.hip).  `scratch` (16-byte aligned) holds the launch counter of the bounded grid-wide wait
+// and, from byte kFwdPrepWordsAt on, fwd_prep_words_bytes bytes of per-workgroup column maxima, which whoever launches it
+// has to clear afterwards (GemmArgs::clear); wait_ticks bounds that wait (100 MHz ticks).
 bool fwd_prep_covers(int64_t t, int64_t c_in, int32_t n, int32_t r);
-size_t fwd_prep_scratch_bytes(int32_t n);
+constexpr size_t kFwdPrepWordsAt = 256;
+size_t fwd_prep_words_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n);
+size_t fwd_prep_scratch_bytes(int32_t n);        // the most that these and the counter take, for any t, c_in and c_out
 hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const int32_t* O, int32_t n,
                            const float* wmax_O, float gamma, float* s_O, float* colscale, float* cmax_out,
                            const float* W_O, int64_t c_out, int8_t* what_int, float* delta_what, int8_t* Xq,
@@ -199,6 +202,7 @@ struct GemmArgs {
     void* split_scratch; long long split_wait_ticks;
     // the same for a small output whose contraction two or four workgroups share (gemm_small_split_bytes)
     void* small_split_scratch;
+    void* clear; int32_t clear_bytes;   // forward product with fp32 output: memory to fill with zeros (multiples of 8 bytes)
 };
 size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);   // 0 for products that are not split
 size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, bool gradient);   // the same
