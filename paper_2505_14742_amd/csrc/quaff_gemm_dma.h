@@ -823,7 +823,7 @@ __device__ __forceinline__ unsigned xcc_id() { return __builtin_amdgcn_s_getreg(
 // Part `part` of `parts` of the memory that a product clears on its way out (GemmArgs::clear): the words of the launch before it.
 __device__ __forceinline__ void clear_words(const GemmArgs& g, int part, int parts, int threads) {
     for (int i = part * threads + (int)threadIdx.x; i < g.clear_bytes / 8; i += parts * threads)
-        static_cast<unsigned long long*>(g.clear)[i] = 0ull;
+        __hip_atomic_store(static_cast<unsigned long long*>(g.clear) + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool DUMP, bool ACCUM = false, bool OUT16 = false,
