@@ -481,22 +481,29 @@ fwd_prep_kernel(const FwdPrepArgs a) {
 
 int fwd_prep_groups(int64_t t) { return (int)((t + kPrepRows - 1) / kPrepRows); }
 
-// Who requantizes what (c_out channels in rounds of 64).  With 1024 rows and more the workgroups that own them take their
-// share of the channels afterwards.  With fewer rows the launch is filled up with workgroups that own none and only wait for
-// the maxima: one round each where that fits, two at most, so that the channels are done while the row owners
-// quantize; with less room everybody takes an equal share.  (Left to the row owners alone, 16 rows and 9216 channels are 72
-// rounds in each of two workgroups: 188 us for the launch, 12 us this way.)  Every workgroup polls one word per outlier and
-// workgroup, so filling up costs as well: forward steps, row owners alone / filled up to 128 / to 256 workgroups, us: 1024 x 1536
-// -> 8192 35.5 / 35.3 / 42.3, 768 x 1536 -> 8192 34.9 / 35.6 / 38.9, 512 x 3072 -> 8192 42.6 / 38.9 / 40.1.  Hence 128; 192
-// where that gives a handful of rows one round each (32 x 1536 -> 8192 19.3 -> 18.6), 256 with rows so long that the owners
-// arrive late (256 x 8192 -> 16384 71.2 -> 67.1), and none where short rows' owners have at most a round each (512 x 1536 -> 3072
-// 27.2 / 28.6 / 28.7).  The extra workgroups announce themselves like the others, with empty maxima: whoever publishes the
-// new scales must know that they have read the old.
+// Who requantizes what (c_out channels in rounds of 64).  The launch is filled up to `cap` workgroups with ones that own no
+// rows and only wait for the maxima: one round each where that fits, two at most, so that the channels are done while the
+// row owners quantize; with less room everybody takes an equal share, and with no room (128 owners, 1024 rows, and more;
+// 256 with rows of more than 4096 columns) the owners take theirs after their rows.  16 rows and 9216 channels are 72 rounds
+// in each of two owners, 188 us for the launch, 12 us filled up.  The extra workgroups announce themselves like the others,
+// with empty maxima: whoever publishes the new scales must know that they have read the old.
+// Every workgroup polls one word per pair of outliers and workgroup, so filling up costs as well.  Forward steps, us, owners
+// alone / filled up to 128 / to 256 workgroups: 1024 x 1536 -> 8192 35.5 / 35.3 / 42.3, 512 x 3072 -> 8192 42.6 / 38.9 / 40.1,
+// 640 x 512 -> 8192 24.5 / 23.2 / 25.7.  Hence 128; 192 where that gives a handful of rows one round each (32 x 1536 -> 8192 19.3 ->
+// 18.6), 256 with rows so long that the owners arrive late (256 x 8192 -> 16384 71.2 -> 67.1).  None where it does not pay, from
+// 1018 forward steps timed with and without:
+//   up to 2048 columns and at most one round for each owner: 512 x 1536 -> 3072 27.2 / 28.6, 256 x 1024 -> 1024 15.2 / 16.6; below
+//   768 columns few owners are level or better off filled up (256 x 512 -> 2048 15.7 / 14.6), from 48 on they are not
+//   (640 x 640 -> 3072 20.9 / 21.9);
+//   from 1024 to 1535 columns also with two rounds for each of 64 owners or more: 512 x 1024 -> 5120 27.3 / 28.7, 640 x 1152 -> 8192
+//   28.5 / 29.6; at 896 and at 1536 columns filled up takes 0.97 to 1.03 of the time.
+// By this rule 4 of the 1018 are more than 1.5 % slower than owners alone, at most 2.5 % (384 x 1152 -> 5120).
 static void fwd_prep_split(int64_t t, int64_t c_in, int64_t c_out, int* groups, int* what_first) {
     const int rows = fwd_prep_groups(t);
     const int64_t rounds = (c_out + kWhatChunk - 1) / kWhatChunk;
     const int cap = c_in > 4096 ? kPrepMaxGroups : rows <= 8 && rows + rounds <= 192 ? 192 : 128;
-    const bool none = c_in <= 2048 && rounds <= rows && (c_in > 1024 || rows >= 48);
+    const bool none = (c_in <= 2048 && rounds <= rows && (c_in >= 768 || rows >= 48)) ||
+                      (c_in >= 1024 && c_in < 1536 && rows >= 64 && rounds <= 2 * (int64_t)rows);
     const int room = none || rows > cap ? 0 : cap - rows;
     const int extra = (int)(rounds < room ? rounds : room);
     *groups = rows + extra;
