@@ -153,6 +153,15 @@ hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
     return launch_gemm_one(g, dump_acc, stream);
 }
 
+// Forward contractions that are 64 more than a multiple of 128: stages of 64 bytes instead of a last stage of 128 that is half
+// zeros.  Forward products, us, 64 / 128 bytes: 2048 x 3072 outputs (128 x 192 tiles) 8.2 / 9.2 at K = 192, 10.8 / 11.5 at 576, 12.5 /
+// 12.8 at 832 (2048 x 1024 there 11.4 / 11.1), 14.0 / 14.0 at 1088, 20.7 / 19.9 at 2112; 4096 x 8192 (256 x 256) 27.9 / 29.3 at 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at
+// 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute unit with the narrow ring and gains
+// at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.
+static bool narrow_stages(int tile, int64_t K) {
+    return K % 128 == 64 && tile <= kTile128x192 && (tile == kTile256x128 || K < (tile == kTile128x192 ? 768 : 1024));
+}
+
 // Which kernel a product with an adapter takes depends on its sizes alone, not on the type of its output and not on the room
 // in the workspace: the kernels add the low-rank term in different orders, and a call's last bits may not depend on either.
 hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
@@ -182,7 +191,9 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
     // the register budget of two workgroups per unit like the two-stage form (with the whole file to itself the
     // compiler's schedule is 2 - 8 % slower).  With more tiles than units two workgroups per unit overlap each
     // other's epilogues instead, which needs the smaller ring.
-    if (tile == kTile128x192 && ((g.M + 127) / 128) * ((g.N + 191) / 192) <= 256) tile = kTile128x192Deep;
+    if (!gradient && narrow_stages(tile, g.K))
+        tile += kTileNarrow;
+    else if (tile == kTile128x192 && ((g.M + 127) / 128) * ((g.N + 191) / 192) <= 256) tile = kTile128x192Deep;
     return gradient ? launch_gemm_kn(g, tile, dump_acc, stream) : launch_gemm_nk(g, tile, dump_acc, stream);
 }
 

@@ -1,5 +1,6 @@
 // INT8 MFMA GEMM kernel: operand tiles stream global -> LDS with direct-to-LDS loads (no register staging) through a ring
-// of stages of 128 contraction bytes per row (whole cache lines per direct load, one barrier per 128 bytes), fragments are
+// of stages of 128 contraction bytes per row (whole cache lines per direct load, one barrier per 128 bytes; 64 for some
+// contractions that are no multiple of 128), fragments are
 // double-buffered in registers.  The B operand is contraction-contiguous or, for the input-gradient product, read as
 // [K x N] from the packed weight codes.  The epilogue stages its operands through the idle ring.
 // See quaff_gemm.hip for the computation.
@@ -97,9 +98,9 @@ struct BtStage {
     }
 };
 
-template <int BM, int BN, int WGM, int WGN, int NS>
+template <int BM, int BN, int WGM, int WGN, int NS, int BK = 128>
 struct DmaCfg {
-    static constexpr int BM_ = BM, BN_ = BN, NS_ = NS;    // NS = stages in the ring
+    static constexpr int BM_ = BM, BN_ = BN, NS_ = NS;    // NS = stages in the ring, BK = contraction bytes of a stage
     static constexpr int NW = WGM * WGN, NT = 64 * NW;    // wavefronts / threads per workgroup
     static constexpr int WM = BM / WGM, WN = BN / WGN;    // wavefront tile
     static constexpr int TM = WM / 32, TN = WN / 32;      // 32x32 MFMA blocks per wavefront tile
@@ -113,9 +114,10 @@ struct DmaCfg {
     // not by LDS reads).
     static constexpr bool MFMA_FIRST = NW >= 8 && TM * TN >= 6;
     static constexpr bool DMA_ASM = NW >= 8 && !MFMA_FIRST;      // see dma_load_16: only the 256x128 tile gains (3-6 %)
-    // a stage: 128 contraction bytes per row of A, then of B; one direct load (1 KiB) fills 8 rows
-    static constexpr int STAGE_BYTES = (BM + BN) * 128, A_BYTES = BM * 128;
-    static constexpr int NGROUP = (BM + BN) / 8;          // 8-row groups per stage
+    // a stage: BK contraction bytes per row of A, then of B; one direct load (1 KiB) fills 8 rows (16 with BK = 64)
+    static_assert(BK == 128 || BK == 64, "stage width");
+    static constexpr int STAGE_BYTES = (BM + BN) * BK, A_BYTES = BM * BK;
+    static constexpr int NGROUP = STAGE_BYTES / 1024;     // direct loads per stage
     static constexpr int NLOAD = (NGROUP + NW - 1) / NW;  // direct loads per lane per stage
     static constexpr int LDS_BYTES = NS * STAGE_BYTES;
     // epilogue staging (gemm_epilogue_staged): one 64-byte-per-row plane per int8 / bf16 operand below EPI_LIMIT,
@@ -165,9 +167,8 @@ static __device__ const __attribute__((aligned(16))) uint32_t kZeroChunk[4] = {0
 // RAGGED: K is not a multiple of 128 (`k_last` bytes, a multiple of 16, are left for the last stage).  In the last stage the
 // lanes whose 16-byte chunk (BT: contraction row) lies past the end fetch zeros instead, in both operands, so that no
 // byte outside the operands is touched and the products of the padding vanish; the iterations that request the last
-// stage are a second copy of the loop body, the others carry no extra instruction.  (A contraction that is a multiple of 64
-// used to run through stages of 64 bytes and one of 16 through a kernel that staged its operands in registers:
-// 1003 x 2064 x 1040 forward 26.3 -> 19.3 us, its input gradient 34.2 -> 25.3 us.)
+// stage are a second copy of the loop body, the others carry no extra instruction.  (1003 x 2064 x
+// 1040 forward 19.3 us, its input gradient 25.3; operands staged in registers instead: 26.3 and 34.2 us.)
 template <class C, bool BT, bool RAGGED>
 __device__ __forceinline__ void gemm_mainloop(const int8_t* __restrict__ gA, const int8_t* __restrict__ gB,
                                               const uint32_t (&voff)[C::NLOAD], int KT, int k_last,
@@ -302,6 +303,90 @@ __device__ __forceinline__ void gemm_mainloop(const int8_t* __restrict__ gA, con
     for (; kt < (RAGGED ? KT - 1 - NS : KT); ++kt) step(kt, std::false_type{});
     if constexpr (RAGGED)
         for (; kt < KT; ++kt) step(kt, std::true_type{});        // (these request the last stage)
+    QUAFF_WAIT_VMCNT(0);
+}
+
+// Stages of 64 contraction bytes per row, one barrier each, for forward contractions that are 64 more than a multiple of 128
+// (the rule stands in quaff_gemm.hip): no half stage of zeros, and the 256 x 128 tile's ring leaves room for a second
+// workgroup on a compute unit.  Row r of a stage is 64 bytes, its 16-byte chunk c sits in slot c ^ ((r >> 2) & 3).
+template <class C>
+__device__ __forceinline__ void gemm_mainloop_narrow(const int8_t* __restrict__ gA, const int8_t* __restrict__ gB,
+                                                     const uint32_t (&voff)[C::NLOAD], int KT,
+                                                     lds_i8* __restrict__ dma, const lds_i8* __restrict__ rd, int wave,
+                                                     int a_frag_off, int b_frag_off, int b_step,
+                                                     i32x16 (&acc)[C::TM][C::TN]) {
+    constexpr int TM = C::TM, TN = C::TN, NLOAD = C::NLOAD, STAGES = C::NS_;
+
+    auto issue = [&](int tile, int stage) {
+        const int64_t k0 = (int64_t)tile * 64, kb = (int64_t)tile * b_step;   // b_step: bytes of B per stage
+#pragma unroll
+        for (int j = 0; j < NLOAD; ++j) {
+            // group q of the stage: A rows first, then B rows.  A wavefront whose last slot falls past the end repeats
+            // its previous group (same bytes to the same place), so every wavefront issues NLOAD loads per stage
+            int q = j * C::NW + wave;
+            if (q >= C::NGROUP) q -= C::NW;
+            const bool isA = q < C::A_BYTES / 1024;
+            const int8_t* src = (isA ? gA + k0 : gB + kb) + voff[j];
+            lds_i8* dst = dma + stage * C::STAGE_BYTES + q * 1024;
+            dma_load_16<C::DMA_ASM>(src, dst);
+        }
+    };
+    auto read_frags = [&](int stage, int ks, i32x4 (&fa)[TM], i32x4 (&fb)[TN]) {
+        const lds_i8* base = rd + stage * C::STAGE_BYTES;
+        const int x = ks * 32;   // second half of the 64-byte row: chunk index ^ 2
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[i] = *(const lds_i32x4*)(base + ((a_frag_off + i * 2048) ^ x));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[j] = *(const lds_i32x4*)(base + C::A_BYTES + ((b_frag_off + j * 2048) ^ x));
+    };
+    auto mfmas = [&](const i32x4 (&fa)[TM], const i32x4 (&fb)[TN]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    };
+    // issue order inside a half step: one LDS read (and at most one direct load), then a share of the MFMAs
+    constexpr int MFMA_PER_READ = (TM * TN) / (TM + TN) > 0 ? (TM * TN) / (TM + TN) : 1;
+
+    // prologue: fill the ring (tiles beyond the last are clamped to it: harmless rewrites of a free stage)
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) issue(s < KT ? s : KT - 1, s);
+    QUAFF_WAIT_VMCNT((STAGES - 1) * NLOAD);
+    __builtin_amdgcn_s_barrier();
+
+    i32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
+    read_frags(0, 0, fa0, fb0);
+    int stage = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+        const int next = (stage + 1 == STAGES) ? 0 : stage + 1;
+        // first half: fragments of the second 32 bytes arrive while the first 32 are multiplied
+        read_frags(stage, 1, fa1, fb1);
+        mfmas(fa0, fb0);
+#pragma unroll
+        for (int u = 0; u < TM + TN; ++u) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, MFMA_PER_READ, 0);
+        }
+        // every wavefront has now read all of `stage`; tile kt+1 must have landed for everybody
+        QUAFF_WAIT_VMCNT((STAGES - 2) * NLOAD);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        {
+            int t = kt + STAGES;
+            issue(t < KT ? t : KT - 1, stage);
+        }
+        read_frags(next, 0, fa0, fb0);
+        mfmas(fa1, fb1);
+#pragma unroll
+        for (int u = 0; u < TM + TN; ++u) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if (u < NLOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, MFMA_PER_READ, 0);
+        }
+        stage = next;
+    }
     QUAFF_WAIT_VMCNT(0);
 }
 
@@ -827,10 +912,11 @@ __device__ __forceinline__ void clear_words(const GemmArgs& g, int part, int par
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool DUMP, bool ACCUM = false, bool OUT16 = false,
-          bool BT = false, bool RAGGED = false, int KSPLIT = 1>
+          bool BT = false, bool RAGGED = false, int KSPLIT = 1, int BK = 128>
 __global__ void __launch_bounds__(64 * WGM * WGN, MINB)
 gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
-    using C = DmaCfg<BM, BN, WGM, WGN, NS>;
+    using C = DmaCfg<BM, BN, WGM, WGN, NS, BK>;
+    static_assert(BK == 128 || (!BT && !RAGGED && KSPLIT == 1), "narrow stages: whole ones, forward");
     extern __shared__ __attribute__((aligned(1024))) int8_t lds_raw[];
     lds_i8* lds = (lds_i8*)lds_raw;
     static_assert(KSPLIT == 1 || ((KSPLIT == 2 || KSPLIT == 4) && C::NW % KSPLIT == 0 && !RAGGED && !DUMP),
@@ -850,7 +936,10 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
 
     // loader: a direct load fills 8 rows x 128 bytes; lane -> (row = lane / 8, slot = lane % 8) and the slot holds global
-    // chunk slot ^ ((row >> 1) & 7), the swizzle the fragment reads undo.  Offsets are 32-bit, from the tile's first row.
+    // chunk slot ^ ((row >> 1) & 7), the swizzle the fragment reads undo (narrow stages: 16 rows x 64 bytes, lane / 4, lane % 4,
+    // slot ^ ((row >> 2) & 3)).  Offsets are 32-bit, from the tile's first row.
+    constexpr int LPR = BK / 16, RPL = 64 / LPR;         // lanes per row and rows per direct load
+    auto swizzle = [](int row) { return BK == 128 ? (row >> 1) & 7 : (row >> 2) & 3; };
     const int8_t* const tileA = g.A + m0 * g.lda;
     const int8_t* const tileB = BT ? g.B : g.B + n0 * g.ldb;      // (n0 is even: the packed rows come in pairs)
     uint32_t voff[C::NLOAD];
@@ -858,9 +947,9 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     for (int j = 0; j < C::NLOAD; ++j) {
         int q = j * C::NW + wave;
         if (q >= C::NGROUP) q -= C::NW;
-        const bool isA = q < BM / 8;
-        int row = (isA ? q : q - BM / 8) * 8 + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+        const bool isA = q < BM / RPL;
+        int row = (isA ? q : q - BM / RPL) * RPL + lane / LPR;
+        const int chunk = (lane % LPR) ^ swizzle(row);
         const int64_t lim = (isA ? g.M - m0 : g.N - n0) - 1;
         row = row < lim ? row : (int)lim;                        // clamp: rows past the edge are never stored
         voff[j] = (uint32_t)row * (uint32_t)(isA ? g.lda : g.ldb) + chunk * 16;
@@ -875,15 +964,15 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
             voff[j] = (uint32_t)weight_code_offset(krow, col, g.ldb);
         }
     }
-    const int64_t b_step = BT ? 128 * g.ldb : g.b_layout == kPackedNK ? 256 : 128;
-    const int frag = l32 * 128 + ((lhi ^ ((l32 >> 1) & 7)) * 16);
+    const int64_t b_step = BT ? 128 * g.ldb : g.b_layout == kPackedNK ? 2 * BK : BK;
+    const int frag = l32 * BK + ((lhi ^ swizzle(l32)) * 16);
     int b_off[C::TN];
 #pragma unroll
     for (int j = 0; j < C::TN; ++j) {
         if constexpr (BT) {
             b_off[j] = BtStage<BN>::piece_offset(lane, wn * C::WN / 32 + j);
         } else {
-            b_off[j] = wn * C::WN * 128 + frag + j * 4096;
+            b_off[j] = wn * C::WN * BK + frag + j * 32 * BK;
         }
     }
     i32x16 acc[C::TM][C::TN];
@@ -893,11 +982,14 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-    const int KT = RAGGED ? (int)((g.K + 127) / 128) : (int)(g.K / 128) / KSPLIT;
+    const int KT = RAGGED ? (int)((g.K + 127) / 128) : (int)(g.K / BK) / KSPLIT;
     const int k_last = (int)(g.K - (int64_t)(KT - 1) * 128);
-    const int a_frag = wm * C::WM * 128 + frag;
-    gemm_mainloop<C, BT, RAGGED>(tileA + (int64_t)kh * KT * 128, tileB + kh * KT * b_step, voff, KT, k_last, lds, lds, wave,
-                                 lane, a_frag, b_off, b_step, acc);
+    const int a_frag = wm * C::WM * BK + frag;
+    if constexpr (BK == 64)
+        gemm_mainloop_narrow<C>(tileA, tileB, voff, KT, lds, lds, wave, a_frag, b_off[0], (int)b_step, acc);
+    else
+        gemm_mainloop<C, BT, RAGGED>(tileA + (int64_t)kh * KT * 128, tileB + kh * KT * b_step, voff, KT, k_last, lds, lds, wave,
+                                     lane, a_frag, b_off, b_step, acc);
     bool active = true;                                  // does this wavefront finish (dequantise, store) its block
     if constexpr (KSPLIT > 1) {
         // Workgroup kh owns the blocks of wavefronts kh * NW / KSPLIT and following: its other wavefronts ("givers") ship their
@@ -1004,7 +1096,8 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
 
 // Tile shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
 enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTileSplit, kTileSplitSmall2,
-                kTileSplitSmall4 };
+                kTileSplitSmall4,
+                kTileNarrow };   // kTileNarrow + one of the first four: stages of 64 bytes (forward only)
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 // The shapes of quaff_gemm_rows.hip (a dump is recognised by g.acc1).

@@ -13,6 +13,10 @@ hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_
         case kTileSplit: return launch_dma_form<256, 192, 4, 2, 2, 1, false, false, 2>(g, dump_acc, stream);
         case kTileSplitSmall2: return launch_dma_form<128, 192, 2, 2, 3, 2, false, false, 2>(g, dump_acc, stream);
         case kTileSplitSmall4: return launch_dma_form<128, 192, 2, 2, 3, 2, false, false, 4>(g, dump_acc, stream);
+        case kTileNarrow + kTile256x256: return launch_dma_form<256, 256, 2, 4, 3, 1, false, false, 1, 64>(g, dump_acc, stream);
+        case kTileNarrow + kTile256x288: return launch_dma_form<256, 288, 4, 3, 3, 1, false, false, 1, 64>(g, dump_acc, stream);
+        case kTileNarrow + kTile256x128: return launch_dma_form<256, 128, 4, 2, 3, 1, false, false, 1, 64>(g, dump_acc, stream);
+        case kTileNarrow + kTile128x192: return launch_dma_form<128, 192, 2, 2, 4, 2, false, false, 1, 64>(g, dump_acc, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -5,9 +5,9 @@
 
 namespace quaff {
 
-template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT>
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT, int BK = 128>
 static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stream) {
-    using C = DmaCfg<BM, BN, WGM, WGN, NS>;
+    using C = DmaCfg<BM, BN, WGM, WGN, NS, BK>;
     int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
     TileMap tm = make_tile_map(tiles_m, tiles_n, BM, BN, MINB);
     while ((tm.rm + tm.gm - 1) / tm.gm > 65535) tm.gm *= 2;
@@ -19,17 +19,17 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
     // the epilogue operands are staged through the idle LDS ring (launch_gemm splits wider second products off)
     if (!dump && (int64_t)(g.K2 / 64) * C::K2_PLANES_BYTES > C::EPI_LIMIT) return hipErrorInvalidValue;
     const size_t lds = dump ? C::LDS_BYTES : C::LDS_ALLOC;
-    auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT>;
+    auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT, BK>;
     if constexpr (KSPLIT > 1) {
         if (dump || g.accumulate) return hipErrorInvalidValue;
-        if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, KSPLIT>;
+        if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, KSPLIT, BK>;
     } else {
-        if (dump) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED>;
-        else if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED>;
+        if (dump) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED, 1, BK>;
+        else if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, 1, BK>;
         else if (g.accumulate) {
             // (only a forward product has a wide second product to accumulate onto)
             if constexpr (BT) return hipErrorInvalidValue;
-            else k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, true, false, BT, RAGGED>;
+            else k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, true, false, BT, RAGGED, 1, BK>;
         }
     }
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

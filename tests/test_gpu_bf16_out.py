@@ -92,8 +92,9 @@ def test_bf16_outputs(case):
 
 # Sizes at which a product takes one of its special forms: the contraction shared by four workgroups (forward; gradient) and
 # by two, ragged rows with a rank that needs two staging rounds, the long contraction shared by two workgroups of the 256-row
-# tile with ragged rows.  (t, c_in, c_out, rank)
-_FORMS = [(512, 8192, 2048, 16), (256, 3072, 8192, 16), (512, 3072, 3072, 32), (257, 8192, 3072, 48), (2000, 3072, 12288, 16)]
+# tile with ragged rows; forward contractions of 64-byte stages.  (t, c_in, c_out, rank)
+_FORMS = [(512, 8192, 2048, 16), (256, 3072, 8192, 16), (512, 3072, 3072, 32), (257, 8192, 3072, 48), (2000, 3072, 12288, 16),
+          (1530, 320, 3072, 16), (2050, 448, 9216, 32)]
 
 
 @pytest.mark.parametrize("t,c_in,c_out,r", _FORMS, ids=["%dx%dx%d_r%d" % c for c in _FORMS])
