@@ -179,11 +179,11 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         // The previous scales must have been READ (not just requested) by this workgroup before its maxima become
         // visible, because whoever sees all maxima may overwrite them: the barrier follows the LDS writes of the
         // loaded values.  (The epoch feeds the stored word itself.)
-        __syncthreads();
         const uint32_t odd = (uint32_t)__shfl_down((int)v, 8, 64);    // column k + 1 (zero beyond n)
+        const uint64_t word = mark | (uint64_t)(odd >> 16) << kMagBits | (v >> 16);
+        __syncthreads();
         if (k < n && (tid & 15) == 0)
-            __hip_atomic_store(&a.part[(int64_t)(k >> 1) * G + blk], mark | (uint64_t)(odd >> 16) << kMagBits | (v >> 16),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&a.part[(int64_t)(k >> 1) * G + blk], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 
     // ---- work that needs no other workgroup: transposed copy of B, copy of the column scales, down-projection
@@ -312,7 +312,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         if (tid == 0) flag_timeout = (long long)wall_clock64() - t0 >= a.wait_ticks;
         __syncthreads();
         if (flag_timeout) break;
-        __builtin_amdgcn_s_sleep(16);
+        __builtin_amdgcn_s_sleep(2);       // (16 x 3072 -> 9216 forward 21.4 us; 21.9 with eight times the pause)
     }
     if (tid == 0) flag_ok = flag_all;
     __syncthreads();

@@ -905,7 +905,8 @@ constexpr int split_flags(int ksplit) { return ksplit == 2 ? 2 : ksplit * ksplit
 constexpr int split_slot_sets(int ksplit) { return ksplit == 2 ? 1 : ksplit; }
 __device__ __forceinline__ unsigned xcc_id() { return __builtin_amdgcn_s_getreg(((4 - 1) << 11) | 20) & 15u; }
 
-// Part `part` of `parts` of the memory that a product clears on its way out (GemmArgs::clear): the words of the launch before it.
+// Part `part` of `parts` of the memory that a product clears (GemmArgs::clear): the words of the launch before it.  First thing
+// in the kernel, so that the stores' way to memory is not the end of it.
 __device__ __forceinline__ void clear_words(const GemmArgs& g, int part, int parts, int threads) {
     for (int i = part * threads + (int)threadIdx.x; i < g.clear_bytes / 8; i += parts * threads)
         __hip_atomic_store(static_cast<unsigned long long*>(g.clear) + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -926,6 +927,8 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     // (split: the workgroups of a tile are neighbours in y, so they carry the same blockIdx.x = XCD)
     const int kh = (int)(blockIdx.y % KSPLIT);
     if (!tile_of_block(tmap, blockIdx.x, blockIdx.y / KSPLIT, blockIdx.z, tile_m, tile_n)) return;
+    if constexpr (!DUMP && !ACCUM && !OUT16 && !BT)
+        if (g.clear_bytes > 0 && kh == 0) clear_words(g, tile_m * tmap.tiles_n + tile_n, tmap.tiles_m * tmap.tiles_n, C::NT);
 
     const int tid = threadIdx.x, lane = tid & 63;
     // The wavefront number is uniform; telling the compiler so moves the loader's address selects to scalar code,
@@ -1090,8 +1093,6 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         gemm_epilogue_dump<C::TM, C::TN>(g, acc, m0 + wm * C::WM, n0 + wn * C::WN, l32, lhi);
     else
         gemm_epilogue_staged<C, ACCUM, OUT16>(g, acc, lds, lds, m0, n0, wm, wn, wave, lane, active);
-    if constexpr (!DUMP && !ACCUM && !OUT16 && !BT)
-        if (g.clear_bytes > 0 && kh == 0) clear_words(g, tile_m * tmap.tiles_n + tile_n, tmap.tiles_m * tmap.tiles_n, C::NT);
 }
 
 // Tile shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.

@@ -36,6 +36,8 @@ gemm_i8_rows_kernel(const GemmArgs g, const TileMap tmap) {
     lds_i8* const lds = (lds_i8*)lds_raw;
     int tile_m, tile_n;
     if (!tile_of_block(tmap, blockIdx.x, blockIdx.y, blockIdx.z, tile_m, tile_n)) return;
+    if constexpr (!BT)
+        if (g.clear_bytes > 0) clear_words(g, tile_m * tmap.tiles_n + tile_n, tmap.tiles_m * tmap.tiles_n, C::NT);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, quad = lane >> 4;
     const int64_t m0 = (int64_t)tile_m * C::BM, n0 = (int64_t)tile_n * C::BN;
@@ -258,8 +260,6 @@ gemm_i8_rows_kernel(const GemmArgs g, const TileMap tmap) {
             for (int v = 0; v < 4; ++v) out[v] = c[v];
         }
     }
-    if constexpr (!BT)
-        if (g.clear_bytes > 0) clear_words(g, tile_m * tmap.tiles_n + tile_n, tmap.tiles_m * tmap.tiles_n, C::NT);
 }
 
 template <int MB, int NB, int NW, int D, bool BT>
