@@ -64,8 +64,8 @@ BwdWs ws_bwd(int64_t t, int64_t c_in, int64_t c_out, int32_t r) {
 
 // Exchange area of a small output whose contraction several workgroups share.  Optional: it follows everything else in the
 // workspace and a call given less room takes the unsplit product.
-size_t split_fwd(int64_t t, int64_t c_in, int64_t c_out) { return align_up(quaff::gemm_small_split_bytes(t, c_out, c_in, false)); }
-size_t split_bwd(int64_t t, int64_t c_in, int64_t c_out) { return align_up(quaff::gemm_small_split_bytes(t, c_in, c_out, true)); }
+size_t split_fwd(int64_t t, int64_t c_in, int64_t c_out, int32_t r) { return align_up(quaff::gemm_small_split_bytes(t, c_out, c_in, r, false)); }
+size_t split_bwd(int64_t t, int64_t c_in, int64_t c_out, int32_t r) { return align_up(quaff::gemm_small_split_bytes(t, c_in, c_out, r, true)); }
 void set_small_split(quaff::GemmArgs& g, void* workspace, size_t used, size_t need, size_t available) {
     if (!workspace || need == 0 || available < used + need || !aligned16(workspace)) return;
     g.small_split_scratch = static_cast<char*>(workspace) + used;
@@ -129,8 +129,8 @@ size_t quaff_prepare_workspace_bytes(int64_t c_in, int64_t c_out) {
 size_t quaff_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || n_outlier < 0 || lora_rank < 0) return 0;
     size_t a = ws_scale(t, n_outlier), b = ws_fwd(t, c_in, c_out, lora_rank).total, c = ws_bwd(t, c_in, c_out, lora_rank).total;
-    b += split_fwd(t, c_in, c_out);
-    c += split_bwd(t, c_in, c_out);
+    b += split_fwd(t, c_in, c_out, lora_rank);
+    c += split_bwd(t, c_in, c_out, lora_rank);
     size_t m = a > b ? a : b;
     return (m > c ? m : c) + 256;
 }
@@ -254,7 +254,7 @@ static int linear_fwd_impl(const int8_t* Xq, const float* delta_x, const int8_t*
         g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank;
     }
     g.C = Y; g.C16 = Y16; g.ldc = ldy;
-    set_small_split(g, workspace, ws_fwd(t, c_in, c_out, lora_rank).total, split_fwd(t, c_in, c_out), workspace_bytes);
+    set_small_split(g, workspace, ws_fwd(t, c_in, c_out, lora_rank).total, split_fwd(t, c_in, c_out, lora_rank), workspace_bytes);
     return hip_status(quaff::launch_gemm(g, false, s));
 }
 
@@ -339,7 +339,7 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
     }
     g.C = dX; g.C16 = dX16; g.ldc = lddx;
     if (w.total > w.split) { g.split_scratch = base + w.split; g.split_wait_ticks = g_grid_wait_ticks.load(); }
-    set_small_split(g, workspace, split_at ? split_at : w.total, split_bwd(t, c_in, c_out), workspace_bytes);
+    set_small_split(g, workspace, split_at ? split_at : w.total, split_bwd(t, c_in, c_out, lora_rank), workspace_bytes);
     // (the one-call backward step forks its weight-gradient work here: the quantizer and the down-projection are
     // enqueued, the long product is not yet)
     if (before_product && (st = (*before_product)()) != QUAFF_OK) return st;
@@ -415,7 +415,7 @@ int quaff_lora_bwd_weights(const uint16_t* X, int64_t ldx, const uint16_t* dY, i
 
 size_t quaff_bwd_step_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || lora_rank <= 0) return 0;
-    return ws_bwd(t, c_in, c_out, lora_rank).total + ws_grad(t, c_in, c_out, lora_rank).total + split_bwd(t, c_in, c_out) + 256;
+    return ws_bwd(t, c_in, c_out, lora_rank).total + ws_grad(t, c_in, c_out, lora_rank).total + split_bwd(t, c_in, c_out, lora_rank) + 256;
 }
 
 int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uint16_t* X, int64_t ldx,
@@ -535,7 +535,7 @@ int quaff_calibrate_outliers(const uint16_t* X, int64_t t_total, int64_t c_in, i
 size_t quaff_fwd_step_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank) {
     if (t <= 0 || c_in <= 0 || c_out <= 0 || n_outlier < 0 || lora_rank < 0) return 0;
     return ws_scale(t, n_outlier) + ws_fwd(t, c_in, c_out, lora_rank).total +
-           align_up(quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64)) + split_fwd(t, c_in, c_out) + 256;
+           align_up(quaff::fwd_prep_scratch_bytes(n_outlier < 64 ? n_outlier : 64)) + split_fwd(t, c_in, c_out, lora_rank) + 256;
 }
 
 long long quaff_debug_grid_wait_ticks(long long ticks) {
@@ -605,7 +605,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
         if (lora_rank > 0) { g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank; }
         g.C = Y; g.ldc = ldy;
         g.clear = base + prep_at + quaff::kFwdPrepWordsAt; g.clear_bytes = (int32_t)words_bytes;
-        set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out), workspace_bytes);
+        set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out, lora_rank), workspace_bytes);
         return hip_status(quaff::launch_gemm(g, false, s));
     }
     float* wsf = static_cast<float*>(workspace);
@@ -637,7 +637,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     if (st != QUAFF_OK) return st;
     g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank;
     g.C = Y; g.ldc = ldy;
-    set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out), workspace_bytes);
+    set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out, lora_rank), workspace_bytes);
     return hip_status(quaff::launch_gemm(g, false, s));
 }
 

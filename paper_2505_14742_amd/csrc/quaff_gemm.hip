@@ -54,12 +54,20 @@ int choose_tile(int64_t M, int64_t N, double* best_work) {
 // the time of the large tiles in the geometric mean; one is more than 2 % slower than them (575 x 2080 at 512: 12.4 / 12.0).
 // Against the best of all shapes it is 1.4 % slower in the mean and more than 20 % in 46, most of them long
 // contractions for which the 64 x 96 tile is taken for faster than it is (256 x 2048 at 8192: 31.5 us, 32 x 64 tiles 18.9).
-struct RowsChoice { int shape, bm, bn; double fixed_us, cu_rate, chip_rate; };   // rates in KB/us and MB/us
+// An adapter of a high rank is fetched and multiplied block by block here, in one pass over staged operands there: with a short
+// contraction and more than `lora_from` rounds the small tiles lose lora_us for every further round and (rank / 16)^2 - 1.  From
+// 600 products timed at rank 0 and at 16, 32 or 64 in every shape, and 500 in the shape chosen here and with the large tiles: at
+// rank 64 and 2 to 3 rounds of 32 x 64 tiles the loss is 7.5 us forward and 4.6 in the gradient (700 x 1936 gradient at K = 128,
+// large tiles / 32 x 64 tiles: 16.8 / 24.7 us; 132 x 8480 at 192 and rank 32 12.5 / 17.4), at rank 16 level, and beyond K = 768 the
+// small tiles are ahead all the same (3889 x 256 gradient at 1664 and rank 48: 33.3 / 30.1).  Of 1700 products with an adapter or
+// more than one round 22 are still more than 2.5 % slower than the large tiles; without this term 60 are.
+struct RowsChoice { int shape, bm, bn; double fixed_us, cu_rate, chip_rate, lora_us, lora_from; };   // rates in KB/us and MB/us
 constexpr RowsChoice kRowsForward[4] = {
-    {kRows16x16, 16, 16, 3.2, 83, 11.5}, {kRows32x32, 32, 32, 3.6, 79, 10.2}, {kRows32x64, 32, 64, 4.4, 84, 10.1}, {kRows64x96, 64, 96, 7.9, 80, 7.7}};
-constexpr RowsChoice kRowsGradient[2] = {{kRows16x64, 16, 64, 4.0, 115, 11}, {kRows32x64, 32, 64, 4.5, 85, 10.1}};
+    {kRows16x16, 16, 16, 3.2, 83, 11.5, 0.0, 1.0}, {kRows32x32, 32, 32, 3.6, 79, 10.2, 0.0, 1.0},
+    {kRows32x64, 32, 64, 4.4, 84, 10.1, 0.5, 1.5}, {kRows64x96, 64, 96, 7.9, 80, 7.7, 0.9, 0.4}};
+constexpr RowsChoice kRowsGradient[2] = {{kRows16x64, 16, 64, 4.0, 115, 11, 0.12, 1.5}, {kRows32x64, 32, 64, 4.5, 85, 10.1, 0.5, 1.5}};
 
-int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work, double* us_estimate) {
+int choose_rows(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double tile_work, double* us_estimate) {
     const double passes = tile_work / (128.0 * 192.0 * kChoices[kTile128x192].ineff);
     const int64_t wide_tiles = ((M + 127) / 128) * ((N + 191) / 192);
     const double busy = wide_tiles < 256 ? wide_tiles / 256.0 : 1.0;
@@ -71,7 +79,8 @@ int choose_rows(int64_t M, int64_t N, int64_t K, bool gradient, double tile_work
         const double tiles = (double)((M + r.bm - 1) / r.bm) * (double)((N + r.bn - 1) / r.bn);
         const double tile_kb = (r.bm + r.bn) * (double)K * 1e-3, rounds = tiles / 256.0;
         const double per_cu = tile_kb * (rounds > 1.0 ? __builtin_ceil(rounds) : 1.0) / r.cu_rate, chip = tile_kb * tiles * 1e-3 / r.chip_rate;
-        const double us = r.fixed_us + (per_cu > chip ? per_cu : chip) + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0);
+        const double lora = rank > 16 && K <= 768 && rounds > r.lora_from ? r.lora_us * (rounds - r.lora_from) * ((rank / 16) * (rank / 16) - 1) : 0.0;
+        const double us = r.fixed_us + (per_cu > chip ? per_cu : chip) + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0) + lora;
         if (us < best_us) { best_us = us; best = r.shape; }
     }
     *us_estimate = best_us;
@@ -107,14 +116,14 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 // fills a compute unit: no more of them than the 32 units of an XCD, or the last tiles start when the first have ended
 // (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 /
 // 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
-static int small_split(int64_t M, int64_t N, int64_t K, bool gradient) {
+static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
     if (tiles > 128 || K % 256 != 0) return 1;
     double work, best_us;
     choose_tile(M, N, &work);
     const double k = (double)K / 1024.0, busy = tiles / 256.0;
     double alone = 8.1 + 4.7 * k;
-    if (choose_rows(M, N, K, gradient, work, &best_us) != kRowsNone && best_us < alone) alone = best_us;
+    if (choose_rows(M, N, K, rank, gradient, work, &best_us) != kRowsNone && best_us < alone) alone = best_us;
     const double two = 1.04 * (9.7 + 6.5 * busy + (2.2 + 1.6 * busy) * k);
     const double four = 1.04 * (11.0 + 13.0 * busy + (1.15 + 3.1 * busy) * k);
     // (tiles on the busiest XCD: the grid is cut into eight regions of equal size, rounded up)
@@ -123,8 +132,8 @@ static int small_split(int64_t M, int64_t N, int64_t K, bool gradient) {
     if (4 * on_xcd <= 32 && K % 512 == 0 && four < alone && four < two) return 4;
     return 2 * on_xcd <= 32 && two < alone ? 2 : 1;
 }
-size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, bool gradient) {
-    const int parts = small_split(M, N, K, gradient);
+size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient) {
+    const int parts = small_split(M, N, K, rank, gradient);
     if (parts == 1) return 0;
     const size_t tiles = (size_t)((M + 127) / 128) * (size_t)((N + 191) / 192);
     return tiles * ((size_t)split_flags(parts) * 128 + (size_t)split_slot_sets(parts) * 256 * 96 * 4);
@@ -158,15 +167,19 @@ hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
 // 12.8 at 832 (2048 x 1024 there 11.4 / 11.1), 14.0 / 14.0 at 1088, 20.7 / 19.9 at 2112; 4096 x 8192 (256 x 256) 27.9 / 29.3 at 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at
 // 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute unit with the narrow ring and gains
 // at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.
-static bool narrow_stages(int tile, int64_t K) {
-    return K % 128 == 64 && tile <= kTile128x192 && (tile == kTile256x128 || K < (tile == kTile128x192 ? 768 : 1024));
+// Not with both outliers and an adapter on the two largest tiles: their epilogue's operands fit side by side in the wide
+// ring only (2423 x 320 -> 5536, rank 16: 23.0 / 17.6).
+static bool narrow_stages(const GemmArgs& g, int tile) {
+    if (g.K % 128 != 64 || tile > kTile128x192) return false;
+    if (tile == kTile256x128) return true;
+    return tile == kTile128x192 ? g.K < 768 : g.K < 1024 && (g.K2 == 0 || g.r == 0);
 }
 
 // Which kernel a product with an adapter takes depends on its sizes alone, not on the type of its output and not on the room
 // in the workspace: the kernels add the low-rank term in different orders, and a call's last bits may not depend on either.
 hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
     const bool gradient = g.b_layout == kPackedKN, one_launch = !dump_acc && !g.accumulate && g.K2 <= 128;
-    const int parts = one_launch ? small_split(g.M, g.N, g.K, gradient) : 1;
+    const int parts = one_launch ? small_split(g.M, g.N, g.K, g.r, gradient) : 1;
     int tile;
     if (g.split_scratch && one_launch && split_applies(g.M, g.N, g.K)) {
         tile = kTileSplit;
@@ -180,7 +193,7 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
     } else {
         double work, us;
         tile = choose_tile(g.M, g.N, &work);
-        const int rows = choose_rows(g.M, g.N, g.K, gradient, work, &us);
+        const int rows = choose_rows(g.M, g.N, g.K, g.r, gradient, work, &us);
         if (rows != kRowsNone) return launch_gemm_rows(g, rows, stream);
     }
     // The 128 x 192 tile with at most one tile per compute unit takes a ring of three stages (120 KB of LDS: one
@@ -191,7 +204,7 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
     // the register budget of two workgroups per unit like the two-stage form (with the whole file to itself the
     // compiler's schedule is 2 - 8 % slower).  With more tiles than units two workgroups per unit overlap each
     // other's epilogues instead, which needs the smaller ring.
-    if (!gradient && narrow_stages(tile, g.K))
+    if (!gradient && narrow_stages(g, tile))
         tile += kTileNarrow;
     else if (tile == kTile128x192 && ((g.M + 127) / 128) * ((g.N + 191) / 192) <= 256) tile = kTile128x192Deep;
     return gradient ? launch_gemm_kn(g, tile, dump_acc, stream) : launch_gemm_nk(g, tile, dump_acc, stream);

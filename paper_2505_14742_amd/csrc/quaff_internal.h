@@ -205,7 +205,7 @@ struct GemmArgs {
     void* clear; int32_t clear_bytes;   // forward product with fp32 output: memory to fill with zeros (multiples of 8 bytes)
 };
 size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);   // 0 for products that are not split
-size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, bool gradient);   // the same
+size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient);   // the same
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream);
 
 }  // namespace quaff
