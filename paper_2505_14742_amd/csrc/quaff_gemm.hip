@@ -108,10 +108,12 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 
 // Outputs of at most 128 tiles of 128 x 192 leave half of the compute units idle or more while every tile walks its
 // contraction alone; two or four workgroups per tile share it where that pays for the exchange of their sums through the L2.
-// Estimated in the terms of choose_rows (`k` = 1024 of contraction, `busy` = tiles per compute unit), constants fitted to 170
-// measured products each way; 4 % must be gained.  Forward, one / two / four workgroups per tile, us: 512 x 3072 outputs 19.7 /
-// 17.0 / 18.3 at K = 3072, 43.3 / 29.0 / 26.2 at 8192, 10.6 / 11.6 / 13.1 at 1024; 1024 x 3072 outputs 20.2 / 20.7 at 3072,
-// 44.0 / 34.7 at 8192; 256 x 3072 outputs at 8192 30.6 (64 x 96 tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x
+// Estimated in the terms of choose_rows (`k` = 1024 of contraction, `busy` = tiles per compute unit); 4 % must be gained.
+// Of 1815 products with at most 128 tiles and whole stages, timed every way, 191 are shared: 0.86 of the time of the best unshared
+// shape in the geometric mean, 24 of them slower than it by more than 3 % (18 % at most); 23 others would gain more than 5 %.
+// Forward, one / two / four workgroups per tile, us: 512 x 3072 outputs 19.7 / 17.0 / 18.3 at K = 3072, 43.3 / 29.0 / 26.2 at 8192,
+// 10.6 / 11.6 / 13.1 at 1024; 1024 x 3072 outputs 20.2 / 20.7 at 3072, 44.0 / 34.7 at 8192; 256 x 3072 outputs at 8192 30.6 (64 x 96
+// tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x
 // 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.  The workgroups of a tile run on one XCD and one of them
 // fills a compute unit: no more of them than the 32 units of an XCD, or the last tiles start when the first have ended
 // (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 /

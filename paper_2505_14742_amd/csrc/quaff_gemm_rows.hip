@@ -7,9 +7,9 @@
 // columns, so that every operand byte is fetched exactly once per workgroup, straight into MFMA fragments, with D steps in
 // flight per wavefront and no barrier before the end - and the int32 partial sums meet in LDS (exact in any order).  Block b
 // of a round is then finished by wavefront b, whose epilogue operands were requested before the exchange.
-// Measured (one launch, us; before: the 128 x 192 tile with its ring of stages): 16 x 3072 -> 9216 forward 21.4 -> 7.8 (28 MB
-// of codes at 3.6 TB/s), 16 x 8192 -> 3072 44.5 -> 8.0, 64 x 3072 -> 3072 22.8 -> 7.4, 256 x 3072 -> 3072 20.9 -> 15.9,
-// 16 x 512 -> 512 9.4 -> 3.4; input gradient 16 x 3072 <- 9216 50.5 -> 16.1, 64 x 3072 <- 3072 21.9 -> 7.1.
+// Measured (one launch, us, the 128 x 192 tile with its ring of stages / this kernel): 16 x 3072 -> 9216 forward 21.4 / 7.8 (28 MB
+// of codes at 3.6 TB/s), 16 x 8192 -> 3072 44.5 / 8.0, 64 x 3072 -> 3072 22.8 / 7.4, 256 x 3072 -> 3072 20.9 / 15.9,
+// 16 x 512 -> 512 9.4 / 3.4; input gradient 16 x 3072 <- 9216 50.5 / 16.1, 64 x 3072 <- 3072 21.9 / 7.1.
 // A step of 128 bytes (whole lines of A, lanes exchanging halves) was no faster.
 #include "quaff_gemm_dma.h"
 

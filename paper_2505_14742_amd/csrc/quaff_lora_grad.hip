@@ -70,9 +70,9 @@ __device__ __forceinline__ int grad_q_offset(int row, int pair) {
     return row * NPAIR * 32 + (pair ^ (row & 3) ^ ((row >> 1) & 4)) * 32;
 }
 
-// NW wavefronts, 32 columns each.  (The operands used to be gathered with 2-byte LDS reads, ten times as many instructions
-// at rank 64 as the MFMAs they feed; with the slab sum below, the whole call at 4096 x (4096, 11008) and rank 64 went from 147
-// to 99 us, 512 x (3072, 3072) at rank 16 from 18.5 to 15.7.)
+// NW wavefronts, 32 columns each.  (Gathering the operands with 2-byte LDS reads takes ten times as many instructions at rank
+// 64 as the MFMAs they feed.  The whole call at 4096 x (4096, 11008) and rank 64: 99 us, with gathered operands and slabs that lie
+// across the result 147; 512 x (3072, 3072) at rank 16: 15.7 and 18.5.)
 template <int R16, int NW>
 __global__ void __launch_bounds__(NW * 64)
 lora_grad_kernel(GradPair pair, int64_t t) {

@@ -290,10 +290,11 @@ static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const flo
     else if (vec <= 64 * 6) QUAFF_QL(64, 6);
     else if (vec <= 64 * 8) QUAFF_QL(64, 8);
     // From rank 48 on a compute unit holds one workgroup of this launch, and with more than 2048 rows the quantizing ones come
-    // in several rounds: eight rows each, sharing the column scales, instead of four.  This launch, us: rank 64, 4096 x 11008
-    // 65.6 -> 58.0, 4096 x 4864 32.9 -> 29.2; rank 48 55.4 -> 52.8 and 27.2 -> 24.6.  At 2048 rows (rank 64: 24.8 / 25.8 at 6144
-    // columns, 35.7 / 36.5 at 9216) and at lower ranks, where two workgroups of four rows share a unit (rank 32, 4096 x 11008
-    // 56.7 / 60.3), four rows are level or faster.
+    // in several rounds: eight rows each, sharing the column scales, instead of four.  This launch, us, four / eight rows: rank
+    // 64, 4096 x 11008 65.6 / 58.0, 4096 x 4864 32.9 / 29.2; rank 48 55.4 / 52.8 and 27.2 / 24.6.  At 2048 rows rank 64 is level (24.8 /
+    // 25.8 at 6144 columns, 35.7 / 36.5 at 9216, 60.0 / 59.8 at 16384) and rank 48 is not beyond 8192 columns (25.2 / 25.8, 36.4 / 31.8,
+    // 60.4 / 53.0): one line for both ranks leaves that out.  At lower ranks, where two workgroups of four rows share a unit, four
+    // are level or faster (rank 32, 4096 x 11008 56.7 / 60.3).
     else if (R16 >= 3 && t > 2048 && vec <= 1024) { if constexpr (R16 >= 3) QUAFF_QL(1024, 1); }
     else if (R16 >= 3 && t > 2048 && vec <= 1024 * 2) { if constexpr (R16 >= 3) QUAFF_QL(1024, 2); }
     else if (vec <= 256 * 3) QUAFF_QL(256, 3);

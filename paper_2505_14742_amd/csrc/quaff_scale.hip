@@ -140,8 +140,8 @@ colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int
 // and one for the codes) and the partial maxima, folded with one column of them per thread (coalesced, an LDS atomic per
 // thread instead of one per partial maximum).  The codes leave through LDS: sixteen output channels are contiguous in what_int.
 // HELD = false: more outliers than 256 NB, which a second sweep of W_O fetches again.
-// Measured at 2048 x 8192 -> 3072 with 819 outliers: 34.7 -> 11.2 us (before: 32 channels a workgroup, 128 slabs of partial
-// maxima folded with one LDS atomic each, W_O swept twice in chains of eight loads).
+// Measured at 2048 x 8192 -> 3072 with 819 outliers: 11.2 us; with 32 channels a workgroup, 128 slabs of partial maxima
+// folded with one LDS atomic each and W_O swept twice in chains of eight loads 34.7 us.
 constexpr int kWideCh = 16, kWideThreads = 1024, kWideGroups = kWideThreads / kWideCh;
 template <int NB, bool HELD>
 __global__ void __launch_bounds__(kWideThreads)
