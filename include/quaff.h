@@ -74,7 +74,8 @@ size_t quaff_packed_weight_bytes(int64_t c_in, int64_t c_out);
  * to read single codes back; -1 for indices outside [0, c_in) x [0, c_out). */
 int64_t quaff_packed_weight_offset(int64_t c_in, int64_t c_out, int64_t k, int64_t j);
 
-/* Bytes of scratch that the per-step calls below need for the given problem (the maximum over the calls). */
+/* Bytes of scratch that the per-step calls below need for the given problem (the maximum over the calls).  Part of it only
+ * makes a call faster: a call accepts a somewhat smaller workspace and gives the same results with it. */
 size_t quaff_workspace_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank);
 
 /*

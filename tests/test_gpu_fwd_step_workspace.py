@@ -11,15 +11,16 @@ from paper_2505_14742_amd import synth
 pytestmark = pytest.mark.gpu
 
 _FIELDS = ["s_O", "colscale", "what_int", "delta_what", "Xq", "delta_x", "xq_O", "Y"]
-# (t, c_in, c_out, rank): two row owners and workgroups that only requantize what; owners alone; 255 owners and one more
-_CASES = [(16, 1040, 9216, 16), (700, 512, 512, 0), (2040, 4112, 4112, 16)]
+# (t, c_in, c_out, number of outliers, rank): two row owners and workgroups that only requantize what; owners alone, a last
+# column without a partner; 255 owners and one more, an odd count of columns (the smallest workspace has no room for its words)
+_CASES = [(16, 1040, 9216, 4, 16), (700, 512, 512, 1, 0), (2040, 4112, 4112, 3, 16)]
 
 
-def _pair(t, c_in, c_out, r):
+def _pair(t, c_in, c_out, n, r):
     import torch
     from tests.gpu_harness import Layer, bf16_dev
-    ec = synth.EdgeCase("fwd_workspace", t, c_in, c_out, [0, 9, c_in // 2, c_in - 1], r)
-    print("forward workspace", t, c_in, c_out, r, flush=True)
+    ec = synth.EdgeCase("fwd_workspace", t, c_in, c_out, [9, c_in // 2, c_in - 1, 0][:n], r)
+    print("forward workspace", t, c_in, c_out, n, r, flush=True)
     sys.stdout.flush()
     X, dY, W, O, A, B = synth.edge_case_inputs(ec, 41)
     loud = bf16_dev(X)                                  # outlier columns 50 times the others
@@ -39,12 +40,12 @@ def _same_step(layers, X, call, tag):
         assert torch.equal(getattr(three, f), getattr(one, f)), "%s: %s differs" % (tag, f)
 
 
-@pytest.mark.parametrize("t,c_in,c_out,r", _CASES, ids=["%dx%dx%d_r%d" % c for c in _CASES])
-def test_what_the_workspace_held_does_not_matter(t, c_in, c_out, r):
+@pytest.mark.parametrize("t,c_in,c_out,n,r", _CASES, ids=["%dx%dx%d_n%d_r%d" % c for c in _CASES])
+def test_what_the_workspace_held_does_not_matter(t, c_in, c_out, n, r):
     import torch
     from paper_2505_14742_amd import binding as q
     from tests.gpu_harness import DEV
-    layers, loud, quiet = _pair(t, c_in, c_out, r)
+    layers, loud, quiet = _pair(t, c_in, c_out, n, r)
     one = layers[1]
     ws = torch.zeros((q.fwd_step_workspace_bytes(t, c_in, c_out, one.n, r) + 7) // 8, dtype=torch.int64, device=DEV)
     one.ws_step, one.ws_step_t = ws.view(torch.int8), t
@@ -72,12 +73,12 @@ def test_what_the_workspace_held_does_not_matter(t, c_in, c_out, r):
         step(quiet, "words hold " + pattern)
 
 
-@pytest.mark.parametrize("t,c_in,c_out,r", _CASES, ids=["%dx%dx%d_r%d" % c for c in _CASES])
-def test_smallest_workspace(t, c_in, c_out, r):
+@pytest.mark.parametrize("t,c_in,c_out,n,r", _CASES, ids=["%dx%dx%d_n%d_r%d" % c for c in _CASES])
+def test_smallest_workspace(t, c_in, c_out, n, r):
     import torch
     from paper_2505_14742_amd import binding as q
     from tests.gpu_harness import DEV, smallest_workspace
-    layers, loud, quiet = _pair(t, c_in, c_out, r)
+    layers, loud, quiet = _pair(t, c_in, c_out, n, r)
     one = layers[1]
     full = torch.empty(q.fwd_step_workspace_bytes(t, c_in, c_out, one.n, r), dtype=torch.int8, device=DEV)
 
