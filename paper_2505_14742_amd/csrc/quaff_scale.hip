@@ -134,34 +134,34 @@ colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int
     }
 }
 
-// momentum_what_kernel for more than 64 outlier channels.  A workgroup owns 16 output channels; its 64 thread groups
-// take four consecutive outliers of every 256, NB times.  What bounds it is the chain of memory round trips, so both long
+// momentum_what_kernel for more than 64 outlier channels.  A workgroup owns 16 output channels; its NT / 16 thread
+// groups take four consecutive outliers of every NT / 4, NB times.  What bounds it is the chain of memory round trips, so both long
 // reads are in flight at once: this workgroup's part of W_O (kept in registers, one sweep instead of one for the maxima
 // and one for the codes) and the partial maxima, folded with one column of them per thread (coalesced, an LDS atomic per
 // thread instead of one per partial maximum).  The codes leave through LDS: sixteen output channels are contiguous in what_int.
-// HELD = false: more outliers than 256 NB, which a second sweep of W_O fetches again.
+// HELD = false: more outliers than NB NT / 4, which a second sweep of W_O fetches again.
 // Measured at 2048 x 8192 -> 3072 with 819 outliers: 11.2 us; with 32 channels a workgroup, 128 slabs of partial maxima
 // folded with one LDS atomic each and W_O swept twice in chains of eight loads 34.7 us.
-constexpr int kWideCh = 16, kWideThreads = 1024, kWideGroups = kWideThreads / kWideCh;
-template <int NB, bool HELD>
-__global__ void __launch_bounds__(kWideThreads)
+constexpr int kWideCh = 16;
+template <int NT, int NB, bool HELD>
+__global__ void __launch_bounds__(NT)
 momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad,
                           const float* __restrict__ wmax_O, const float* __restrict__ s_prev, float gamma,
                           const int32_t* __restrict__ O, float* __restrict__ s_O, float* __restrict__ colscale,
                           float* __restrict__ cmax_out, const float* __restrict__ W_O, int64_t c_out,
                           int8_t* __restrict__ what_int, float* __restrict__ delta_what) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int SPAN = 4 * kWideGroups * NB;                      // outliers per sweep
+    constexpr int GROUPS = NT / kWideCh, SPAN = 4 * GROUPS * NB;        // outliers per sweep
     constexpr int ROW = SPAN + 16;                                  // LDS row of codes: 16 channels in 16 different banks
     __shared__ __attribute__((aligned(16))) uint32_t codes[kWideCh * ROW / 4];
-    __shared__ float red[kWideThreads / 64][kWideCh];
+    __shared__ float red[NT / 64][kWideCh];
     extern __shared__ uint32_t smax[];                              // [n] : maxima, then s_k - 1
     float* const sm1 = reinterpret_cast<float*>(smax);
     const int jj = threadIdx.x % kWideCh, grp = threadIdx.x / kWideCh;
     const int64_t j0 = (int64_t)blockIdx.x * kWideCh, j = j0 + jj;
     const int64_t jc = j < c_out ? j : c_out - 1;
     float w[NB][4];
-    auto first_k = [&](int base, int b) { return base + (b * kWideGroups + grp) * 4; };
+    auto first_k = [&](int base, int b) { return base + (b * GROUPS + grp) * 4; };
     auto load = [&](int base) {
 #pragma unroll
         for (int b = 0; b < NB; ++b)
@@ -172,10 +172,10 @@ momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, i
             }
     };
     if (HELD) load(0);
-    for (int k = threadIdx.x; k < n; k += kWideThreads) smax[k] = 0u;
+    for (int k = threadIdx.x; k < n; k += NT) smax[k] = 0u;
     __syncthreads();
     // thread (share, k): column k of the slabs share, share + shares, ...
-    const int width = n < kWideThreads ? (n + 63) / 64 * 64 : kWideThreads, shares = kWideThreads / width;
+    const int width = n < NT ? (n + 63) / 64 * 64 : NT, shares = NT / width;
     const int share = threadIdx.x / width;
     for (int k = threadIdx.x % width; k < n && share < shares; k += width) {
         uint32_t m = 0u;
@@ -192,7 +192,7 @@ momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, i
         atomicMax(&smax[k], m);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < n; k += kWideThreads) {
+    for (int k = threadIdx.x; k < n; k += NT) {
         const float cmax = __uint_as_float(smax[k]);
         const float s = momentum_scale(cmax, wmax_O[k], s_prev[k], gamma);
         sm1[k] = __fsub_rn(s, 1.0f);
@@ -223,7 +223,7 @@ momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, i
     if ((threadIdx.x & 63) < kWideCh) red[threadIdx.x >> 6][jj] = m;
     __syncthreads();
 #pragma unroll
-    for (int v = 0; v < kWideThreads / 64; ++v) m = fmaxf(m, red[v][jj]);
+    for (int v = 0; v < NT / 64; ++v) m = fmaxf(m, red[v][jj]);
     float d, c;
     rtn_steps(m, d, c);
     if (grp == 0 && j < c_out) delta_what[j] = d;
@@ -245,7 +245,7 @@ momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, i
         }
         __syncthreads();
         const int span = n_pad - base < SPAN ? n_pad - base : SPAN, per_row = span / 16;   // 16-byte chunks
-        for (int e = threadIdx.x; e < channels * per_row; e += kWideThreads) {
+        for (int e = threadIdx.x; e < channels * per_row; e += NT) {
             const int row = e / per_row, at = (e - row * per_row) * 16;
             *reinterpret_cast<u32x4*>(what_int + (j0 + row) * n_pad + base + at) =
                 *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(codes) + row * ROW + at);
@@ -333,21 +333,28 @@ hipError_t launch_momentum(const uint32_t* part, int nslab, int n, int n_pad, co
     } else {
         const size_t lds = (size_t)n * sizeof(uint32_t);
         const dim3 grid((unsigned)((c_out + kWideCh - 1) / kWideCh));
-#define QUAFF_WIDE(NB, HELD)                                                                                          \
+#define QUAFF_WIDE(NT, NB, HELD)                                                                                      \
     {                                                                                                                 \
-        auto k = momentum_what_wide_kernel<NB, HELD>;                                                                 \
+        auto k = momentum_what_wide_kernel<NT, NB, HELD>;                                                             \
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),                                          \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                     \
         if (e != hipSuccess) return e;                                                                                \
-        hipLaunchKernelGGL(k, grid, dim3(kWideThreads), lds, stream, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O, \
+        hipLaunchKernelGGL(k, grid, dim3(NT), lds, stream, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O,      \
                            colscale, cmax_out, W_O, c_out, what_int, delta_what);                                     \
     }
-        // the smallest number of registers that holds a thread's share of W_O; beyond 2048 outliers it is fetched twice
-        if (n <= 256) QUAFF_WIDE(1, true)
-        else if (n <= 512) QUAFF_WIDE(2, true)
-        else if (n <= 1024) QUAFF_WIDE(4, true)
-        else if (n <= 2048) QUAFF_WIDE(8, true)
-        else QUAFF_WIDE(8, false)
+        // The smallest number of registers that holds a thread's share of W_O; beyond 2048 outliers it is fetched twice.  Up to
+        // 256 outliers half the threads hold as much with one register set more, and more workgroups fit a compute unit:
+        // scale updates of 46 tokens, us, 1024 / 512 threads: 65 outliers, 3072 channels 7.4 / 7.2, 13648 channels 11.9 / 8.9; 158
+        // outliers 7.8 / 7.6 and 13.0 / 10.2.  With more maxima to fold and every workgroup resident 1024 are faster: 2048 tokens,
+        // 256 outliers, 4096 channels 9.5 / 9.8, 11008 channels 15.0 / 13.7.
+        const bool resident = c_out <= 256 * kWideCh;
+        if (n <= 128) QUAFF_WIDE(512, 1, true)
+        else if (n <= 256 && !resident) QUAFF_WIDE(512, 2, true)
+        else if (n <= 256) QUAFF_WIDE(1024, 1, true)
+        else if (n <= 512) QUAFF_WIDE(1024, 2, true)
+        else if (n <= 1024) QUAFF_WIDE(1024, 4, true)
+        else if (n <= 2048) QUAFF_WIDE(1024, 8, true)
+        else QUAFF_WIDE(1024, 8, false)
 #undef QUAFF_WIDE
     }
     return hipGetLastError();
