@@ -118,7 +118,7 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 // fills a compute unit: no more of them than the 32 units of an XCD, or the last tiles start when the first have ended
 // (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 /
 // 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
-static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient) {
+static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double gain = 1.04) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
     if (tiles > 128 || K % 256 != 0) return 1;
     double work, best_us;
@@ -126,14 +126,19 @@ static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradi
     const double k = (double)K / 1024.0, busy = tiles / 256.0;
     double alone = 8.1 + 4.7 * k;
     if (choose_rows(M, N, K, rank, gradient, work, &best_us) != kRowsNone && best_us < alone) alone = best_us;
-    const double two = 1.04 * (9.7 + 6.5 * busy + (2.2 + 1.6 * busy) * k);
-    const double four = 1.04 * (11.0 + 13.0 * busy + (1.15 + 3.1 * busy) * k);
+    const double two = gain * (9.7 + 6.5 * busy + (2.2 + 1.6 * busy) * k);
+    const double four = gain * (11.0 + 13.0 * busy + (1.15 + 3.1 * busy) * k);
     // (tiles on the busiest XCD: the grid is cut into eight regions of equal size, rounded up)
     const TileMap map = make_tile_map((int)((M + 127) / 128), (int)((N + 191) / 192), 128, 192, 1);
     const int on_xcd = map.rm * map.rn;
     if (4 * on_xcd <= 32 && K % 512 == 0 && four < alone && four < two) return 4;
     return 2 * on_xcd <= 32 && two < alone ? 2 : 1;
 }
+// Beside the weight gradients of rank 32 and more on a second stream, whose workgroups (88 to 106 KB of LDS) leave no room on a
+// compute unit for one of these, some wait for a partner that has no unit yet: 15 % must be gained.  Backward steps with a second
+// stream, us, shared / not: 2998 x 896 <- 3840 at rank 32 74.7 / 67.8, at rank 64 80.3 / 72.1, 2048 x 1536 <- 4096 at rank 32 68.3 /
+// 64.0 (expected gain 4 %); 512 x 3072 <- 3072 at rank 32 46.0 / 50.3 (15 %), 1024 x 2048 <- 8192 78.6 / 92.4 (30 %).
+bool gemm_small_split_pays_beside(int64_t M, int64_t N, int64_t K, int32_t rank) { return small_split(M, N, K, rank, true, 1.15) > 1; }
 size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient) {
     const int parts = small_split(M, N, K, rank, gradient);
     if (parts == 1) return 0;

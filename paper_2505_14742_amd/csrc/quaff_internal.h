@@ -206,6 +206,7 @@ struct GemmArgs {
 };
 size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);   // 0 for products that are not split
 size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient);   // the same
+bool gemm_small_split_pays_beside(int64_t M, int64_t N, int64_t K, int32_t rank);    // input gradient beside the weight gradients
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream);
 
 }  // namespace quaff

@@ -83,8 +83,9 @@ def _steps(t, c_in, c_out, r):
     return q, L, Xd, dYd, ws, backward
 
 
-# four parts (and weight gradients whose workgroups leave no room beside the sharing ones: rank 64), two parts, ragged
-_STEPS = [(256, 4096, 4096, 64), (512, 3072, 3072, 16), (257, 3056, 8192, 32)]
+# four parts (and weight gradients whose workgroups leave no room beside the sharing ones: rank 64), two parts, ragged; two parts
+# that are not worth it beside such weight gradients
+_STEPS = [(256, 4096, 4096, 64), (512, 3072, 3072, 16), (257, 3056, 8192, 32), (1900, 1536, 4096, 32)]
 
 
 @pytest.mark.parametrize("t,c_in,c_out,r", _STEPS, ids=["%dx%dx%d_r%d" % c for c in _STEPS])
