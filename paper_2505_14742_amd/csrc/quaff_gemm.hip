@@ -113,11 +113,10 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 // shape in the geometric mean, 24 of them slower than it by more than 3 % (18 % at most); 23 others would gain more than 5 %.
 // Forward, one / two / four workgroups per tile, us: 512 x 3072 outputs 19.7 / 17.0 / 18.3 at K = 3072, 43.3 / 29.0 / 26.2 at 8192,
 // 10.6 / 11.6 / 13.1 at 1024; 1024 x 3072 outputs 20.2 / 20.7 at 3072, 44.0 / 34.7 at 8192; 256 x 3072 outputs at 8192 30.6 (64 x 96
-// tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x
-// 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.  The workgroups of a tile run on one XCD and one of them
-// fills a compute unit: no more of them than the 32 units of an XCD, or the last tiles start when the first have ended
-// (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 /
-// 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
+// tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.
+// The workgroups of a tile run on one XCD and one of them fills a compute unit: no more of them than the 32 units of an XCD,
+// or the last tiles start when the first have ended (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two
+// workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 / 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
 static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double gain = 1.04) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
     if (tiles > 128 || K % 256 != 0) return 1;
@@ -171,9 +170,9 @@ hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
 
 // Forward contractions that are 64 more than a multiple of 128: stages of 64 bytes instead of a last stage of 128 that is half
 // zeros.  Forward products, us, 64 / 128 bytes: 2048 x 3072 outputs (128 x 192 tiles) 8.2 / 9.2 at K = 192, 10.8 / 11.5 at 576, 12.5 /
-// 12.8 at 832 (2048 x 1024 there 11.4 / 11.1), 14.0 / 14.0 at 1088, 20.7 / 19.9 at 2112; 4096 x 8192 (256 x 256) 27.9 / 29.3 at 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at
-// 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute unit with the narrow ring and gains
-// at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.
+// 12.8 at 832 (2048 x 1024 there 11.4 / 11.1), 14.0 / 14.0 at 1088, 20.7 / 19.9 at 2112; 4096 x 8192 outputs (256 x 256) 27.9 / 29.3 at
+// 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute
+// unit with the narrow ring and gains at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.
 // Not with both outliers and an adapter on the two largest tiles: their epilogue's operands fit side by side in the wide
 // ring only (2423 x 320 -> 5536, rank 16: 23.0 / 17.6).
 static bool narrow_stages(const GemmArgs& g, int tile) {
