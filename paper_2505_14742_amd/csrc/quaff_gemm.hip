@@ -173,12 +173,12 @@ hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
 // 12.8 at 832 (2048 x 1024 there 11.4 / 11.1), 14.0 / 14.0 at 1088, 20.7 / 19.9 at 2112; 4096 x 8192 outputs (256 x 256) 27.9 / 29.3 at
 // 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute
 // unit with the narrow ring and gains at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.
-// Not with both outliers and an adapter on the two largest tiles: their epilogue's operands fit side by side in the wide
-// ring only (2423 x 320 -> 5536, rank 16: 23.0 / 17.6).
+// Not with outliers on the two largest tiles: their epilogue's operands fit side by side in the wide ring only (2423 x 320 -> 5536,
+// rank 16: 23.0 / 17.6; forward step of 4712 x 960 -> 15360 at rank 0: 170 / 154).
 static bool narrow_stages(const GemmArgs& g, int tile) {
     if (g.K % 128 != 64 || tile > kTile128x192) return false;
     if (tile == kTile256x128) return true;
-    return tile == kTile128x192 ? g.K < 768 : g.K < 1024 && (g.K2 == 0 || g.r == 0);
+    return tile == kTile128x192 ? g.K < 768 : g.K < 1024 && g.K2 == 0;
 }
 
 // Which kernel a product with an adapter takes depends on its sizes alone, not on the type of its output and not on the room
