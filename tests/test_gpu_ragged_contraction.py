@@ -15,9 +15,11 @@ _CASES = [(70, 16, 16), (130, 112, 144), (300, 144, 272), (520, 304, 400), (257,
 
 
 # forward contractions of whole 64-byte stages, an odd number of them: 1, 3, 5, 7, 11 and 17 stages and the ring of four or three;
-# 128 x 192, 256 x 128, 256 x 256 and 256 x 288 tiles with edges and without; more than 128 outliers (a second launch adds up)
+# 128 x 192, 256 x 128, 256 x 256 and 256 x 288 tiles with edges and without; more than 128 outliers (a second launch adds up);
+# no outliers, where the two largest tiles take these stages
 _HALF = [(1530, 64, 3056, 2), (2048, 192, 3072, 2), (2001, 704, 2064, 2), (2050, 320, 9216, 2), (8192, 1088, 1024, 2),
-         (4000, 192, 8000, 2), (2000, 320, 9104, 2), (1530, 448, 3056, 150)]
+         (4000, 192, 8000, 2), (2000, 320, 9104, 2), (1530, 448, 3056, 150), (4000, 192, 8000, 0),
+         (2000, 320, 9104, 0), (2000, 960, 9104, 0)]
 
 
 @pytest.mark.parametrize("t,c_in,c_out,n", _HALF, ids=["%dx%dx%d_n%d" % c for c in _HALF])
