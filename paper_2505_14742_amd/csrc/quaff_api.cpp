@@ -294,7 +294,7 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
                               int64_t c_in, int64_t c_out, const uint16_t* lora_A, const uint16_t* lora_B,
                               int32_t lora_rank, float lora_scale, float* dX, uint16_t* dX16, int64_t lddx,
                               void* workspace, size_t workspace_bytes, void* stream,
-                              const std::function<int()>* before_product = nullptr, size_t split_at = 0, bool crowded = false) {
+                              const std::function<int()>* before_product = nullptr, size_t split_at = 0, bool beside = false) {
     if (!dY || !Wq_packed || !delta_w || (!dX && !dX16)) return QUAFF_ERR_NULL;
     if (dX16 && c_out % 64 != 0) return QUAFF_ERR_SHAPE;
     if (dX16 && (!aligned16(dX16) || lddx % 8 != 0)) return QUAFF_ERR_ALIGN;
@@ -339,7 +339,8 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
     }
     g.C = dX; g.C16 = dX16; g.ldc = lddx;
     if (w.total > w.split) { g.split_scratch = base + w.split; g.split_wait_ticks = g_grid_wait_ticks.load(); }
-    if (!crowded || quaff::gemm_small_split_pays_beside(t, c_in, c_out, lora_rank))
+    g.beside = beside;
+    if (!beside || lora_rank < 32 || quaff::gemm_small_split_pays_beside(t, c_in, c_out, lora_rank))
         set_small_split(g, workspace, split_at ? split_at : w.total, split_bwd(t, c_in, c_out, lora_rank), workspace_bytes);
     // (the one-call backward step forks its weight-gradient work here: the quantizer and the down-projection are
     // enqueued, the long product is not yet)
@@ -467,7 +468,7 @@ int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uin
     };
     int st = linear_bwd_dx_impl(dY, t, lddy, Wq_packed, delta_w, c_in, c_out, lora_A, lora_B, lora_rank, lora_scale, dX,
                                 nullptr, lddx, workspace, workspace_bytes, stream, &fork,
-                                wb.total + w.total, use_side && lora_rank >= 32);
+                                wb.total + w.total, use_side);
     if (forked) {
         // Whatever happened after the fork, the caller's stream joins everything that was put on the side stream,
         // so that the buffers that work reads and writes stay ordered before the caller's next use of them.

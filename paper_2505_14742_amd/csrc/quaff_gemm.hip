@@ -15,73 +15,70 @@
 namespace quaff {
 
 namespace {
-// Tile shapes.  `spc` = workgroups that fit on one compute unit at once (LDS and registers);
-// `ineff` = measured cost per MAC relative to the 256x256 shape on a large problem.
-struct TileChoice { int bm, bn, spc; double ineff; };
-constexpr TileChoice kChoices[4] = {
-    {256, 256, 1, 1.00},   // 8 wavefronts, 128x64 each
-    {256, 288, 1, 1.03},   // 12 wavefronts, 64x96 each: 2048 x 9216 outputs are exactly 256 such tiles
-    {256, 128, 1, 1.18},   // 8 wavefronts, 64x64 each (its wide-stage ring leaves room for one workgroup per unit)
-    {128, 192, 2, 1.20},   // 4 wavefronts, 64x96 each: 2048 x 3072 outputs are exactly 256 such tiles
-};
+// Shapes a product can take, and the time of each, estimated in us:
+//   fixed + round ((n - 1) / fit) + next (n - 1) + n ((bm + bn) K (kb + busy b) 1e-6 + lora rank')
+// with n the tiles of the busiest compute unit (an XCD's region of the tile grid over its 32 units, rounded up), fit the
+// workgroups of the shape that are resident on a unit together, b the share of the units that have a tile, and rank' the 32-column
+// rounds of the adapter's staged operands or, for the shapes of quaff_gemm_rows.hip, which fetch them block by block,
+// (rank / 16)^2.  (bm + bn) K are the operand bytes of a tile: what bounds every shape is their delivery, 55 to 85 KB/us to one
+// compute unit and less of it with all units busy.
+// The constants are fitted to 1178 products (20 to 6000 rows, 64 to 16384 columns, contractions of 208 to 14000, ranks 0 to 64,
+// 0 to 100 outliers; launch alone, every shape timed).  The shape chosen takes 1.013 (forward) and 1.010 (input gradient) of the time of
+// the best one in the geometric mean, at worst 1.42 (320 x 9088 at K = 256: 64 x 64 tiles for 128 x 128).  Without the three shapes
+// of 64 and 128 rows the same choice takes 1.22 and 1.29: one of the wider ones leaves most units idle or walks
+// the contraction alone on a few (us, before / now: 1003 x 2064 at 1040 15.1 / 10.0, 2048 x 1024 at 3072 19.3 / 12.2,
+// 768 x 1536 at 1536 13.7 / 7.8, gradient 1003 x 1040 at 2064 with its quantizer 26.0 / 15.3).
+struct Shape { int id, bm, bn, fit; double fixed, round, next, kb, busy, lora; };
+constexpr Shape kForward[10] = {
+    {kTile256x256, 256, 256, 1, 10.67, 8.75, 3.70, 15.58, 6.01, 2.96},
+    {kTile256x288, 256, 288, 1, 10.01, 11.07, 4.79, 17.48, 5.89, 3.00},
+    {kTile256x128, 256, 128, 1, 7.69, 6.87, 3.05, 13.31, 5.20, 1.90},
+    {kTile128x192, 128, 192, 2, 8.69, 8.82, 0.00, 8.89, 6.71, 1.77},       // more tiles than units
+    {kTile128x128, 128, 128, 1, 5.50, 3.60, 1.12, 12.43, 3.68, 0.96},
+    {kTile64x128, 64, 128, 2, 4.36, 2.11, 0.91, 11.60, 1.45, 0.51},
+    {kTile64x64, 64, 64, 3, 4.40, 2.17, 0.12, 14.44, 0.00, 0.39},
+    {kRows32x64, 32, 64, 4, 4.29, 0.99, 1.67, 15.61, 1.90, 0.20},
+    {kRows32x32, 32, 32, 8, 3.56, 3.95, 0.36, 17.59, 1.69, 0.10},
+    {kRows16x16, 16, 16, 8, 3.21, 0.75, 0.53, 17.28, 0.00, 0.04}};
+constexpr Shape kGradient[9] = {
+    {kTile256x256, 256, 256, 1, 9.11, 10.04, 0.00, 15.96, 5.69, 3.00},
+    {kTile256x288, 256, 288, 1, 9.07, 10.46, 4.51, 16.95, 5.99, 3.00},
+    {kTile256x128, 256, 128, 1, 5.92, 4.85, 1.86, 13.42, 4.89, 2.24},
+    {kTile128x192, 128, 192, 2, 5.64, 2.32, 2.27, 8.62, 6.34, 1.94},       // more tiles than units
+    {kTile128x128, 128, 128, 1, 4.73, 3.13, 1.07, 12.78, 3.56, 1.18},
+    {kTile64x128, 64, 128, 2, 3.93, 2.08, 0.57, 12.19, 0.79, 0.68},
+    {kTile64x64, 64, 64, 3, 4.28, 2.23, 0.00, 13.43, 0.00, 0.46},
+    {kRows32x64, 32, 64, 4, 4.73, 10.03, 0.74, 13.88, 3.24, 0.19},
+    {kRows16x64, 16, 64, 2, 4.10, 0.00, 2.82, 9.55, 3.47, 0.11}};
+// The 128 x 192 tile with at most one tile for every unit takes a ring of three stages (120 KB of LDS: one workgroup per unit) and
+// eight wavefronts.  The third stage keeps the operands of the stage after next in flight, which is what a product whose operands
+// come from HBM rather than from the Infinity Cache needs (back to back on operand sets that rotate through more than the
+// cache holds, two stages / three: o_proj forward 36.2 / 30.5 us, qkv dX 79.2 / 69.8, 8192 -> 3072 forward 74.1 / 61.7; on cached
+// operands level).  Eight wavefronts of 32 x 96 against four of 64 x 96: 2048 x 3072 outputs 26.3 / 27.5 us at K = 3072, 55.9 / 57.8 at
+// 8192, level at 9216; gradient with its quantizer 34.7 / 36.5, 71.7 / 71.6; 2048 x 2176 at 768 and similar 0.8 of the time.  With more
+// tiles than units two workgroups per unit overlap each other's epilogues instead, which needs the smaller ring and four wavefronts
+// (4480 x 13376 at 576, rank 64: 115 us, 134 with the deep ring).
+constexpr Shape kDeep[2] = {{kTile128x192Deep, 128, 192, 1, 6.69, 4.59, 1.80, 12.68, 4.17, 1.26},
+                            {kTile128x192Deep, 128, 192, 1, 5.83, 4.04, 1.49, 13.27, 3.81, 1.42}};
 
-// Estimated time of a tile shape on 256 compute units: full rounds of spc tiles per unit, then the remainder at one
-// tile per unit per pass.  The shape that wastes the fewest compute-unit passes wins.
-int choose_tile(int64_t M, int64_t N, double* best_work) {
-    int best = 0;
-    double best_cost = -1.0;
-    for (int c = 0; c < 4; ++c) {
-        const TileChoice& t = kChoices[c];
-        int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        int64_t slots = 256 * t.spc;
-        int64_t full = tiles / slots, rem = tiles % slots;
-        double passes = (double)full * t.spc + (double)((rem + 255) / 256);
-        double cost = passes * t.bm * t.bn * t.ineff;
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = c; }
-    }
-    *best_work = best_cost;
-    return best;
-}
-
-// Small outputs.  Estimated time of a shape of quaff_gemm_rows.hip: launch and epilogue, then the slower of the two ways its
-// operands arrive - one compute unit's share at `cu_rate`, or all of it at `chip_rate` - and 1.5 us for every further
-// round of 256 tiles (their epilogues do not overlap their loads).  Against it stand, per 1024 bytes of contraction, 4.4 us (6.1
-// with every compute unit busy) per pass of 128 x 192 tiles and 8 us; 7 where tiles without an edge have little to multiply
-// (768 x 1536 and 384 x 3072 outputs, large tiles / 32 x 64 tiles: forward 8.2 / 9.5 us at K = 256, 10.5 / 11.3 at 768; input
-// gradient with its quantizer 9.6 / 11.6 at 256, 10.9 / 12.3 at 512; with edges, 722 x 1776 outputs at 256, 10.0 / 9.6).  The
-// factor 1.1 keeps close calls with the large tiles.  Over 2388 products of 1 to 2500 rows, 64 to 12000 columns and 128 to 14000
-// contractions, every shape and split timed, the choice takes 0.45 (forward) and 0.62 (input gradient, quantizer included) of
-// the time of the large tiles in the geometric mean; one is more than 2 % slower than them (575 x 2080 at 512: 12.4 / 12.0).
-// Against the best of all shapes it is 1.4 % slower in the mean and more than 20 % in 46, most of them long
-// contractions for which the 64 x 96 tile is taken for faster than it is (256 x 2048 at 8192: 31.5 us, 32 x 64 tiles 18.9).
-// An adapter of a high rank is fetched and multiplied block by block here, in one pass over staged operands there: with a short
-// contraction and more than `lora_from` rounds the small tiles lose lora_us for every further round and (rank / 16)^2 - 1.  From
-// 600 products timed at rank 0 and at 16, 32 or 64 in every shape, and 500 in the shape chosen here and with the large tiles: at
-// rank 64 and 2 to 3 rounds of 32 x 64 tiles the loss is 7.5 us forward and 4.6 in the gradient (700 x 1936 gradient at K = 128,
-// large tiles / 32 x 64 tiles: 16.8 / 24.7 us; 132 x 8480 at 192 and rank 32 12.5 / 17.4), at rank 16 level, and beyond K = 768 the
-// small tiles are ahead all the same (3889 x 256 gradient at 1664 and rank 48: 33.3 / 30.1).  Of 1700 products with an adapter or
-// more than one round 22 are still more than 2.5 % slower than the large tiles; without this term 60 are.
-struct RowsChoice { int shape, bm, bn; double fixed_us, cu_rate, chip_rate, lora_us, lora_from; };   // rates in KB/us and MB/us
-constexpr RowsChoice kRowsForward[4] = {
-    {kRows16x16, 16, 16, 3.2, 83, 11.5, 0.0, 1.0}, {kRows32x32, 32, 32, 3.6, 79, 10.2, 0.0, 1.0},
-    {kRows32x64, 32, 64, 4.4, 84, 10.1, 0.5, 1.5}, {kRows64x96, 64, 96, 7.9, 80, 7.7, 0.9, 0.4}};
-constexpr RowsChoice kRowsGradient[2] = {{kRows16x64, 16, 64, 4.0, 115, 11, 0.12, 1.5}, {kRows32x64, 32, 64, 4.5, 85, 10.1, 0.5, 1.5}};
-
-int choose_rows(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double tile_work, double* us_estimate) {
-    const double passes = tile_work / (128.0 * 192.0 * kChoices[kTile128x192].ineff);
-    const int64_t wide_tiles = ((M + 127) / 128) * ((N + 191) / 192);
-    const double busy = wide_tiles < 256 ? wide_tiles / 256.0 : 1.0;
-    const bool short_and_whole = K <= 1024 && M % 128 == 0 && N % 192 == 0;
-    double best_us = ((short_and_whole ? 7.0 : 8.0) + (double)K * 1e-3 * passes * (4.4 + 1.75 * busy)) / 1.1;
-    int best = kRowsNone;
-    for (int c = 0; c < (gradient ? 2 : 4); ++c) {
-        const RowsChoice& r = gradient ? kRowsGradient[c] : kRowsForward[c];
-        const double tiles = (double)((M + r.bm - 1) / r.bm) * (double)((N + r.bn - 1) / r.bn);
-        const double tile_kb = (r.bm + r.bn) * (double)K * 1e-3, rounds = tiles / 256.0;
-        const double per_cu = tile_kb * (rounds > 1.0 ? __builtin_ceil(rounds) : 1.0) / r.cu_rate, chip = tile_kb * tiles * 1e-3 / r.chip_rate;
-        const double lora = rank > 16 && K <= 768 && rounds > r.lora_from ? r.lora_us * (rounds - r.lora_from) * ((rank / 16) * (rank / 16) - 1) : 0.0;
-        const double us = r.fixed_us + (per_cu > chip ? per_cu : chip) + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0) + lora;
-        if (us < best_us) { best_us = us; best = r.shape; }
+int choose_shape(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double* us_estimate) {
+    const int count = gradient ? 9 : 10, staged = (rank + 31) / 32, fetched = (rank / 16) * (rank / 16);
+    int best = -1;
+    double best_us = 0.0;
+    for (int c = 0; c < count; ++c) {
+        Shape s = gradient ? kGradient[c] : kForward[c];
+        const int64_t tm = (M + s.bm - 1) / s.bm, tn = (N + s.bn - 1) / s.bn, tiles = tm * tn;
+        if (s.id == kTile128x192 && tiles <= 256) s = kDeep[gradient];
+        int64_t n = (tiles + 255) / 256;
+        if (n <= 16) {                    // (with many tiles per unit the regions' edges don't matter)
+            const TileGrid r = tile_grid((int)tm, (int)tn, s.bm, s.bn);
+            n = ((int64_t)r.rm * r.rn + 31) / 32;
+        }
+        const double busy = tiles < 256 ? (double)tiles / 256.0 : 1.0;
+        const double us = s.fixed + s.round * (double)((n - 1) / s.fit) + s.next * (double)(n - 1) +
+                          (double)n * ((s.bm + s.bn) * (double)K * 1e-6 * (s.kb + s.busy * busy) +
+                                       s.lora * (s.id >= kRows16x16 ? fetched : staged));
+        if (best < 0 || us < best_us) { best_us = us; best = s.id; }
     }
     *us_estimate = best_us;
     return best;
@@ -106,25 +103,20 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
     return tiles * 256 + tiles * 512 * 96 * 4;   // two flags per tile in lines of their own, then 96 accumulators of 512 threads
 }
 
-// Outputs of at most 128 tiles of 128 x 192 leave half of the compute units idle or more while every tile walks its
-// contraction alone; two or four workgroups per tile share it where that pays for the exchange of their sums through the L2.
-// Estimated in the terms of choose_rows (`k` = 1024 of contraction, `busy` = tiles per compute unit); 4 % must be gained.
-// Of 1815 products with at most 128 tiles and whole stages, timed every way, 191 are shared: 0.86 of the time of the best unshared
-// shape in the geometric mean, 24 of them slower than it by more than 3 % (18 % at most); 23 others would gain more than 5 %.
-// Forward, one / two / four workgroups per tile, us: 512 x 3072 outputs 19.7 / 17.0 / 18.3 at K = 3072, 43.3 / 29.0 / 26.2 at 8192,
-// 10.6 / 11.6 / 13.1 at 1024; 1024 x 3072 outputs 20.2 / 20.7 at 3072, 44.0 / 34.7 at 8192; 256 x 3072 outputs at 8192 30.6 (64 x 96
-// tiles) / 27.6 / 21.6.  Input gradient with its quantizer: 512 x 3072 <- 3072 27.3 / 23.9 / 25.4, <- 8192 52.9 / 36.6 / 32.6.
+// Outputs of at most 128 tiles of 128 x 192 with a long contraction: two or four workgroups per tile share it where that pays for the
+// exchange of their sums through the L2.  Estimated in the terms of choose_shape (`k` = 1024 of contraction, `busy` = tiles per
+// compute unit); 4 % must be gained over the best unshared shape, which happens from K = 8192 on.  One workgroup per tile in its
+// best shape / two or four, us: forward 1098 x 2048 outputs at 8192 35.4 / 34.3, 763 x 1408 at 14336 37.8 / 33.8 (four), 479 x 2176 at
+// 16384 44.4 / 35.4, 2021 x 1152 at 16384 61.5 / 52.6; input gradient with its quantizer 970 x 2944 <- 16384 83.8 / 78.4.
 // The workgroups of a tile run on one XCD and one of them fills a compute unit: no more of them than the 32 units of an XCD,
 // or the last tiles start when the first have ended (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two
 // workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 / 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
 static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double gain = 1.04) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
     if (tiles > 128 || K % 256 != 0) return 1;
-    double work, best_us;
-    choose_tile(M, N, &work);
+    double alone;
+    choose_shape(M, N, K, rank, gradient, &alone);
     const double k = (double)K / 1024.0, busy = tiles / 256.0;
-    double alone = 8.1 + 4.7 * k;
-    if (choose_rows(M, N, K, rank, gradient, work, &best_us) != kRowsNone && best_us < alone) alone = best_us;
     const double two = gain * (9.7 + 6.5 * busy + (2.2 + 1.6 * busy) * k);
     const double four = gain * (11.0 + 13.0 * busy + (1.15 + 3.1 * busy) * k);
     // (tiles on the busiest XCD: the grid is cut into eight regions of equal size, rounded up)
@@ -169,16 +161,15 @@ hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
 }
 
 // Forward contractions that are 64 more than a multiple of 128: stages of 64 bytes instead of a last stage of 128 that is half
-// zeros.  Forward products, us, 64 / 128 bytes: 2048 x 3072 outputs (128 x 192 tiles) 8.2 / 9.2 at K = 192, 10.8 / 11.5 at 576, 12.5 /
-// 12.8 at 832 (2048 x 1024 there 11.4 / 11.1), 14.0 / 14.0 at 1088, 20.7 / 19.9 at 2112; 4096 x 8192 outputs (256 x 256) 27.9 / 29.3 at
-// 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute
-// unit with the narrow ring and gains at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.
-// Not with outliers on the two largest tiles: their epilogue's operands fit side by side in the wide ring only (2423 x 320 -> 5536,
-// rank 16: 23.0 / 17.6; forward step of 4712 x 960 -> 15360 at rank 0: 170 / 154).
+// zeros.  Forward products, us, 64 / 128 bytes: 4096 x 8192 outputs (256 x 256) 27.9 / 29.3 at K = 192, 44.9 / 46.0 at 832, 52.0 / 51.5 at
+// 1088, 140.9 / 136.7 at 4160.  The 256 x 128 tile has room for two workgroups on a compute unit with the narrow ring and gains
+// at any length: 8192 x 3072 21.9 / 25.4 at 192, 64.8 / 70.3 at 2112, 112.8 / 119.0 at 4160.  Not with outliers on the two largest
+// tiles: their epilogue's operands fit side by side in the wide ring only (2423 x 320 -> 5536, rank 16: 23.0 / 17.6; forward step of
+// 4712 x 960 -> 15360 at rank 0: 170 / 154).  Not on the narrower tiles: the deep ring of the 128 x 192 tile is ahead (4160 x 896 at 320
+// 12.1 / 9.5, 549 x 2624 at 192 11.9 / 9.1) and its two-stage ring level (4800 x 1728 at 320 19.9 / 20.1).
 static bool narrow_stages(const GemmArgs& g, int tile) {
-    if (g.K % 128 != 64 || tile > kTile128x192) return false;
-    if (tile == kTile256x128) return true;
-    return tile == kTile128x192 ? g.K < 768 : g.K < 1024 && g.K2 == 0;
+    if (g.K % 128 != 64 || tile > kTile256x128) return false;
+    return tile == kTile256x128 || (g.K < 1024 && g.K2 == 0);
 }
 
 // Which kernel a product with an adapter takes depends on its sizes alone, not on the type of its output and not on the room
@@ -197,22 +188,14 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
     } else if (parts > 1 && g.r > 0) {
         tile = kTile128x192;             // (no room for the exchange: the shared form's tile and epilogue, one workgroup each)
     } else {
-        double work, us;
-        tile = choose_tile(g.M, g.N, &work);
-        const int rows = choose_rows(g.M, g.N, g.K, g.r, gradient, work, &us);
-        if (rows != kRowsNone) return launch_gemm_rows(g, rows, stream);
+        double us;
+        tile = choose_shape(g.M, g.N, g.K, g.r, gradient, &us);
+        if (tile >= kRows16x16) return launch_gemm_rows(g, tile, stream);
     }
-    // The 128 x 192 tile with at most one tile per compute unit takes a ring of three stages (120 KB of LDS: one
-    // workgroup per unit): the operands of the stage after next are then in flight too, which is what a product whose
-    // operands come from HBM rather than from the Infinity Cache needs (measured back to back on operand sets that
-    // rotate through more than the cache holds: o_proj forward 36.2 -> 30.5 us, qkv dX 79.2 -> 69.8, 8192 -> 3072
-    // forward 74.1 -> 61.7; on cached operands the two rings are level, 29.4 / 65.6 / 60.1 us).  It is compiled for
-    // the register budget of two workgroups per unit like the two-stage form (with the whole file to itself the
-    // compiler's schedule is 2 - 8 % slower).  With more tiles than units two workgroups per unit overlap each
-    // other's epilogues instead, which needs the smaller ring.
-    if (!gradient && narrow_stages(g, tile))
-        tile += kTileNarrow;
-    else if (tile == kTile128x192 && ((g.M + 127) / 128) * ((g.N + 191) / 192) <= 256) tile = kTile128x192Deep;
+    if (!gradient && narrow_stages(g, tile)) tile += kTileNarrow;
+    // (the same bits; its wavefronts leave half of a compute unit's registers to the weight gradients on the second stream: training step
+    // of 2048 x 3072 -> 9216 191.6 us, 214.1 with eight wavefronts of 165 registers)
+    if (g.beside && tile == kTile128x192Deep) tile = kTile128x192Beside;
     return gradient ? launch_gemm_kn(g, tile, dump_acc, stream) : launch_gemm_nk(g, tile, dump_acc, stream);
 }
 

@@ -1095,31 +1095,34 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         gemm_epilogue_staged<C, ACCUM, OUT16>(g, acc, lds, lds, m0, n0, wm, wn, wave, lane, active);
 }
 
-// Tile shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
-enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTileSplit, kTileSplitSmall2,
-                kTileSplitSmall4,
-                kTileNarrow };   // kTileNarrow + one of the first four: stages of 64 bytes (forward only)
+// Shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
+enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTile128x192Beside, kTile128x128, kTile64x128, kTile64x64,
+                kTileSplit, kTileSplitSmall2, kTileSplitSmall4,
+                kTileNarrow,           // kTileNarrow + one of the first three: stages of 64 bytes (forward only)
+                kRows16x16 = 16, kRows32x32, kRows32x64, kRows16x64 };   // quaff_gemm_rows.hip
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
-// The shapes of quaff_gemm_rows.hip (a dump is recognised by g.acc1).
-enum RowsShape { kRows16x16 = 0, kRows32x32, kRows32x64, kRows64x96, kRows16x64, kRowsNone };
-hipError_t launch_gemm_rows(const GemmArgs& g, int shape, hipStream_t stream);
+hipError_t launch_gemm_mid(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);     // 64 and 128 rows, both readings
+hipError_t launch_gemm_rows(const GemmArgs& g, int shape, hipStream_t stream);   // (a dump is recognised by g.acc1)
 
 // host side: choose the XCD region grid for a grid of bm x bn tiles.  Padded work first (a surplus workgroup idles a
 // compute unit for a whole pass), then the operand rows an XCD has to fetch into its own L2: rm * bm rows of A plus
 // rn * bn rows of B, every one K bytes long.  (Eight L2s that share nothing cannot fetch less than the sum of these
 // over the XCDs: 78.6 MB for a 2048 x 9216 x 3072 product in 256 x 288 tiles, against 34.6 MB of operands.)
-inline TileMap make_tile_map(int tiles_m, int tiles_n, int bm, int bn, int wgs_per_cu) {
-    TileMap best{tiles_m, tiles_n, 1, 8, tiles_m, (tiles_n + 7) / 8, 3, 1};
-    long best_cost = -1;
-    const int xms[4] = {1, 2, 4, 8};
-    for (int xm : xms) {
-        int xn = 8 / xm;
-        int rm = (tiles_m + xm - 1) / xm, rn = (tiles_n + xn - 1) / xn;
-        long cost = (long)rm * rn * 1000000 + (long)rm * bm + (long)rn * bn;
-        const int xn_log2 = xn == 1 ? 0 : xn == 2 ? 1 : xn == 4 ? 2 : 3;
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = TileMap{tiles_m, tiles_n, xm, xn, rm, rn, xn_log2, 1}; }
+struct TileGrid { int xm_log2, rm, rn; };
+inline TileGrid tile_grid(int tiles_m, int tiles_n, int bm, int bn) {
+    TileGrid best{0, 0, 0};
+    int64_t best_cost = -1;
+    for (int l = 0; l < 4; ++l) {
+        const int rm = (tiles_m + (1 << l) - 1) >> l, rn = (tiles_n + (8 >> l) - 1) >> (3 - l);
+        const int64_t cost = (int64_t)rm * rn * 1000000 + (int64_t)rm * bm + (int64_t)rn * bn;
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = TileGrid{l, rm, rn}; }
     }
+    return best;
+}
+inline TileMap make_tile_map(int tiles_m, int tiles_n, int bm, int bn, int wgs_per_cu) {
+    const TileGrid r = tile_grid(tiles_m, tiles_n, bm, bn);
+    TileMap best{tiles_m, tiles_n, 1 << r.xm_log2, 8 >> r.xm_log2, r.rm, r.rn, 3 - r.xm_log2, 1};
     // tile rows per group: the block of concurrent tiles (32 compute units per XCD) with the fewest operand rows
     const int conc = 32 * wgs_per_cu;
     if (best.rm * best.rn > conc) {

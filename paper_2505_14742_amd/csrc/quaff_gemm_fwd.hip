@@ -9,14 +9,14 @@ hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_
         case kTile256x288: return launch_dma<256, 288, 4, 3, 2, 1, false>(g, dump_acc, stream);
         case kTile256x128: return launch_dma<256, 128, 4, 2, 2, 1, false>(g, dump_acc, stream);
         case kTile128x192: return launch_dma<128, 192, 2, 2, 2, 2, false>(g, dump_acc, stream);
-        case kTile128x192Deep: return launch_dma<128, 192, 2, 2, 3, 2, false>(g, dump_acc, stream);
+        case kTile128x192Deep: return launch_dma<128, 192, 4, 2, 3, 2, false>(g, dump_acc, stream);
+        case kTile128x128: case kTile64x128: case kTile64x64: return launch_gemm_mid(g, tile, dump_acc, stream);
         case kTileSplit: return launch_dma_form<256, 192, 4, 2, 2, 1, false, false, 2>(g, dump_acc, stream);
         case kTileSplitSmall2: return launch_dma_form<128, 192, 2, 2, 3, 2, false, false, 2>(g, dump_acc, stream);
         case kTileSplitSmall4: return launch_dma_form<128, 192, 2, 2, 3, 2, false, false, 4>(g, dump_acc, stream);
         case kTileNarrow + kTile256x256: return launch_dma_form<256, 256, 2, 4, 3, 1, false, false, 1, 64>(g, dump_acc, stream);
         case kTileNarrow + kTile256x288: return launch_dma_form<256, 288, 4, 3, 3, 1, false, false, 1, 64>(g, dump_acc, stream);
         case kTileNarrow + kTile256x128: return launch_dma_form<256, 128, 4, 2, 3, 1, false, false, 1, 64>(g, dump_acc, stream);
-        case kTileNarrow + kTile128x192: return launch_dma_form<128, 192, 2, 2, 4, 2, false, false, 1, 64>(g, dump_acc, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -286,7 +286,6 @@ hipError_t launch_gemm_rows(const GemmArgs& g, int shape, hipStream_t stream) {
             case kRows16x16: return launch_rows<1, 1, 8, 4, false>(g, stream);
             case kRows32x32: return launch_rows<2, 2, 4, 4, false>(g, stream);
             case kRows32x64: return launch_rows<2, 4, 8, 3, false>(g, stream);
-            case kRows64x96: return launch_rows<4, 6, 8, 2, false>(g, stream);
         }
     }
     return hipErrorInvalidValue;

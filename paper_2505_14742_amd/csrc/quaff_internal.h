@@ -203,6 +203,7 @@ struct GemmArgs {
     // the same for a small output whose contraction two or four workgroups share (gemm_small_split_bytes)
     void* small_split_scratch;
     void* clear; int32_t clear_bytes;   // forward product with fp32 output: memory to fill with zeros (multiples of 8 bytes)
+    bool beside;                        // other kernels run beside this product on another stream
 };
 size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);   // 0 for products that are not split
 size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient);   // the same

@@ -1,0 +1,55 @@
+"""Outputs that take the tiles of 64 x 64, 64 x 128 and 128 x 128 (each in both directions below), with ragged rows, columns and
+contractions, more tiles than compute units, every rank, no, one, several and many outlier slices; compared with the oracle in
+full (accumulators bit for bit).  Then the 128 x 192 tile with eight and with four wavefronts (the backward step beside a second
+stream): the same bits."""
+import sys
+
+import pytest
+import torch
+
+from paper_2505_14742_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# (t, c_in, c_out, number of outliers, rank) and the tiles of the forward product and the input gradient
+_CASES = [(500, 3056, 3088, 1, 16),     # 64 x 128, 64 x 128
+          (241, 1360, 4112, 70, 64),    # 64 x 128, 64 x 64
+          (1003, 1040, 2064, 13, 32),   # 128 x 128, 64 x 128
+          (1290, 2032, 1936, 5, 48),    # 128 x 128, 128 x 128
+          (192, 1216, 3600, 0, 0),      # 64 x 64, none of them
+          (900, 2704, 3216, 130, 16),   # 128 x 128 (accumulating onto the outliers' product), 128 x 128
+          (449, 1296, 1680, 2, 32),     # 64 x 64, 64 x 64
+          (64, 208, 16016, 3, 16)]      # one tile row, 126 columns of tiles
+
+
+@pytest.mark.parametrize("t,c_in,c_out,n,r", _CASES, ids=["%dx%dx%d_n%d_r%d" % c for c in _CASES])
+def test_mid_tiles(t, c_in, c_out, n, r):
+    from tests.gpu_harness import Layer, OracleLayer, check_prepare, check_step
+    O = [k * (c_in - 1) // max(n - 1, 1) for k in range(n)]
+    ec = synth.EdgeCase("mid_tiles", t, c_in, c_out, O, r)
+    print("mid tiles", t, c_in, c_out, n, r, flush=True)
+    sys.stdout.flush()
+    X, dY, W, O, A, B = synth.edge_case_inputs(ec, 131)
+    L, R = Layer(W, O, A if r else None, B if r else None, 1.0, t), OracleLayer(W, O, A if r else None, B if r else None, 1.0)
+    check_prepare(L, R)
+    check_step(L, R, X, dY, 0.2, tag="mid tiles %d x %d x %d" % (t, c_in, c_out))
+
+
+@pytest.mark.parametrize("t,c_in,c_out,r", [(2048, 3072, 1024, 16), (1999, 3056, 784, 48)])
+def test_deep_tile_beside_a_second_stream(t, c_in, c_out, r):
+    from paper_2505_14742_amd import binding as q
+    from tests.gpu_harness import DEV, Layer, bf16_dev
+    print("deep tile, second stream", t, c_in, c_out, r, flush=True)
+    sys.stdout.flush()
+    X, dY, W, O, A, B = synth.edge_case_inputs(synth.EdgeCase("deep_tile", t, c_in, c_out, [2, c_in - 3], r), 133)
+    L = Layer(W, O, A, B, 1.0, t)
+    Xd, dYd = bf16_dev(X), bf16_dev(dY)
+    L.linear_bwd_dx(dYd)
+    ws = torch.empty(q.bwd_step_workspace_bytes(t, c_in, c_out, r), dtype=torch.int8, device=DEV)
+    out = [torch.empty(s, device=DEV) for s in ((t, c_in), (c_in, r), (r, c_out))]
+    side = q.SideStream()
+    for how in (None, side, side):
+        for x in out:
+            x.fill_(-3.0)
+        q.linear_bwd_step(dYd, Xd, L.Wq_packed, L.delta_w, c_in, c_out, L.A, L.B, r, 1.0, *out, ws, side=how)
+        assert torch.equal(out[0], L.dX)
