@@ -566,6 +566,19 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     const size_t ws_lin_bytes = workspace_bytes - scale_bytes;
     const size_t split_at = prep_at + align_up(prep_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // A single launch for few rows or columns; its conditions include those of the calls below, which answer what it refuses.
+    if (dims_ok(t, c_in, c_out) && X && Xq && delta_x && Wq_packed && delta_w && Y && ldx >= c_in && out_ld_ok(ldy, c_out) &&
+        gamma >= 0.0f && gamma <= 1.0f && n_outlier <= c_in && (n_outlier == 0 || (O && W_O && wmax_O && s_O && what_int && delta_what)) &&
+        (lora_rank == 0 || (lora_A && lora_B)) && aligned16(X) && aligned16(Xq) && aligned16(colscale) && aligned16(Wq_packed) &&
+        (n_outlier == 0 || (aligned16(what_int) && aligned16(xq_O))) && (lora_rank == 0 || (aligned16(lora_A) && aligned16(lora_B))) &&
+        ldx % 8 == 0) {
+        const int blocks = quaff::fwd_few_blocks(t, c_in, c_out, n_outlier, lora_rank);
+        const size_t few_words = n_outlier > 0 && blocks > 0 ? (size_t)quaff::fwd_few_groups(t, c_out, blocks) * 8 : 0;
+        if (blocks > 0 && (few_words == 0 || workspace_bytes >= prep_at + quaff::kFwdPrepWordsAt + few_words))
+            return hip_status(quaff::launch_fwd_few(blocks, X, t, c_in, ldx, O, n_outlier, wmax_O, gamma, s_O, colscale, cmax_out, W_O, c_out,
+                                                    what_int, delta_what, Xq, delta_x, xq_O, static_cast<const int8_t*>(Wq_packed), delta_w,
+                                                    lora_A, lora_B, lora_rank, lora_scale, Y, ldy, base + prep_at, s));
+    }
     // One launch prepares everything the product needs where it can (a few thousand tokens, at most 64 outlier
     // channels, rank 0 or 16); two combined launches cover the other usual cases; everything else is the three calls
     // one after the other.

@@ -269,7 +269,11 @@ fwd_prep_kernel(const FwdPrepArgs a) {
 
     // ---- bounded wait for the other workgroups' maxima: wavefront w reads pairs w and w + 16 of columns (G contiguous words
     // each) and reduces them with wavefront shuffles; the pass is repeated until every word carries this launch's mark
+    // (never given up before the second pass: only loads issued after this workgroup's own words have reached memory, which the
+    // return of the first pass's loads shows, guarantee that the last workgroup to write finds all words)
     const long long t0 = (long long)wall_clock64();
+    long long bound = 0x7FFFFFFFFFFFFFFFll;
+    asm volatile("" : "+v"(bound));              // (a copy of the loop's body for the first pass costs up to 2 us)
     for (;;) {
         if (tid == 0) flag_all = 1;
         if (tid < 64) smax[tid] = 0u;
@@ -309,9 +313,10 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         if (!mine) flag_all = 0;
         __syncthreads();
         if (flag_all) break;
-        if (tid == 0) flag_timeout = (long long)wall_clock64() - t0 >= a.wait_ticks;
+        if (tid == 0) flag_timeout = (long long)wall_clock64() - t0 >= bound;
         __syncthreads();
         if (flag_timeout) break;
+        bound = a.wait_ticks;
         __builtin_amdgcn_s_sleep(2);       // (16 x 3072 -> 9216 forward 21.4 us; 21.9 with eight times the pause)
     }
     if (tid == 0) flag_ok = flag_all;

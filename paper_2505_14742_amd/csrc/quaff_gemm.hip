@@ -137,6 +137,11 @@ size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, boo
     return tiles * ((size_t)split_flags(parts) * 128 + (size_t)split_slot_sets(parts) * 256 * 96 * 4);
 }
 
+bool gemm_takes_rows(int64_t M, int64_t N, int64_t K, int32_t rank) {
+    double us;
+    return small_split(M, N, K, rank, false) == 1 && choose_shape(M, N, K, rank, false, &us) >= kRows16x16;
+}
+
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
     ProfScope prof(K_GEMM, stream);
     // A second product too wide for the epilogue's LDS staging (more than two 64-wide outlier slices) runs as a launch

@@ -39,7 +39,7 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 // ---- optional per-launch timing (see quaff_profile_* in the C ABI) ------------------------------------
-enum KernelKind { K_PREPARE = 0, K_COLMAX, K_MOMENTUM, K_QUANT, K_LORA, K_GEMM, K_LORA_GRAD, K_OUTLIER_GRAD, K_CALIB, K_QUANT_LORA, K_COLMAX_LORA, K_WHAT_QUANT, K_FWD_PREP, KERNEL_KINDS };
+enum KernelKind { K_PREPARE = 0, K_COLMAX, K_MOMENTUM, K_QUANT, K_LORA, K_GEMM, K_LORA_GRAD, K_OUTLIER_GRAD, K_CALIB, K_QUANT_LORA, K_COLMAX_LORA, K_WHAT_QUANT, K_FWD_PREP, K_FWD_FEW, KERNEL_KINDS };
 class ProfScope {
 public:
     ProfScope(int kind, hipStream_t stream);
@@ -161,6 +161,17 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
                            uint16_t* T_hi, uint16_t* T_lo, uint16_t* Bt, void* scratch, long long wait_ticks,
                            hipStream_t stream);
 
+// The whole forward step in one launch (quaff_fwd_few.hip).  fwd_few_blocks: 16-channel blocks of a workgroup's tile, 0 for shapes
+// that are better off with the preparation's launches and the product's.  `scratch` as for launch_fwd_prep, with a word for
+// each of fwd_few_groups workgroups, which are zeros again at the end; nobody waits.  Without outliers it is not used.
+int fwd_few_blocks(int64_t t, int64_t c_in, int64_t c_out, int32_t n, int32_t r);
+int fwd_few_groups(int64_t t, int64_t c_out, int blocks);
+hipError_t launch_fwd_few(int blocks, const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const int32_t* O, int32_t n,
+                          const float* wmax_O, float gamma, float* s_O, float* colscale, float* cmax_out, const float* W_O,
+                          int64_t c_out, int8_t* what_int, float* delta_what, int8_t* Xq, float* delta, int8_t* xq_O,
+                          const int8_t* Wq, const float* delta_w, const uint16_t* A, const uint16_t* B, int32_t r, float scale,
+                          float* Y, int64_t ldy, void* scratch, hipStream_t stream);
+
 // Packed weight codes: one int8 copy that serves both products.  Element (j, k) of the [c_out x c_in] code matrix
 // sits in a 128-byte line that holds 64 consecutive k of the two rows j & ~1 and j | 1: every 16-byte chunk is
 // contraction-contiguous for the forward product, and both products fetch whole lines (the input-gradient tiles are
@@ -208,6 +219,8 @@ struct GemmArgs {
 size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K);   // 0 for products that are not split
 size_t gemm_small_split_bytes(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient);   // the same
 bool gemm_small_split_pays_beside(int64_t M, int64_t N, int64_t K, int32_t rank);    // input gradient beside the weight gradients
+// does a forward product of these sizes add its low-rank term in the order of quaff_gemm_rows.hip
+bool gemm_takes_rows(int64_t M, int64_t N, int64_t K, int32_t rank);
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream);
 
 }  // namespace quaff
