@@ -11,7 +11,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libquaff.so")
 
 SOURCES = ["quaff_api.cpp", "quaff_prepare.hip", "quaff_scale.hip", "quaff_quant.hip", "quaff_lora.hip", "quaff_lora_stream.hip", "quaff_quant_lora.hip", "quaff_fwd_step.hip", "quaff_fwd_prep.hip", "quaff_fwd_few.hip", "quaff_what_quant.hip", "quaff_lora_grad.hip", "quaff_outlier_grad.hip", "quaff_calib.hip",
-           "quaff_gemm.hip", "quaff_gemm_fwd.hip", "quaff_gemm_bwd.hip", "quaff_gemm_mid.hip", "quaff_gemm_rows.hip", "quaff_profile.cpp", "quaff_microbench.hip"]
+           "quaff_gemm.hip", "quaff_gemm_fwd.hip", "quaff_gemm_bwd.hip", "quaff_gemm_mid.hip", "quaff_gemm_wide.hip", "quaff_gemm_rows.hip", "quaff_profile.cpp", "quaff_microbench.hip"]
 
 # -ffp-contract=off: the quantizer's fp32 operation sequence is part of the arithmetic contract (no fused
 # multiply-add unless written explicitly); correctly rounded fp32 divide and sqrt for the same reason.

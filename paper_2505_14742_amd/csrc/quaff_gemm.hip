@@ -61,26 +61,50 @@ constexpr Shape kGradient[9] = {
 constexpr Shape kDeep[2] = {{kTile128x192Deep, 128, 192, 1, 6.69, 4.59, 1.80, 12.68, 4.17, 1.26},
                             {kTile128x192Deep, 128, 192, 1, 5.83, 4.04, 1.49, 13.27, 3.81, 1.42}};
 
+double shape_us(const Shape& s, int64_t M, int64_t N, int64_t K, int32_t rank) {
+    const int64_t tm = (M + s.bm - 1) / s.bm, tn = (N + s.bn - 1) / s.bn, tiles = tm * tn;
+    int64_t n = (tiles + 255) / 256;
+    if (n <= 16) {                    // (with many tiles per unit the regions' edges don't matter)
+        const TileGrid r = tile_grid((int)tm, (int)tn, s.bm, s.bn);
+        n = ((int64_t)r.rm * r.rn + 31) / 32;
+    }
+    const double busy = tiles < 256 ? (double)tiles / 256.0 : 1.0;
+    const int columns = s.id >= kRows16x16 ? (rank / 16) * (rank / 16) : (rank + 31) / 32;
+    return s.fixed + s.round * (double)((n - 1) / s.fit) + s.next * (double)(n - 1) +
+           (double)n * ((s.bm + s.bn) * (double)K * 1e-6 * (s.kb + s.busy * busy) + s.lora * columns);
+}
+
 int choose_shape(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double* us_estimate) {
-    const int count = gradient ? 9 : 10, staged = (rank + 31) / 32, fetched = (rank / 16) * (rank / 16);
     int best = -1;
     double best_us = 0.0;
-    for (int c = 0; c < count; ++c) {
-        Shape s = gradient ? kGradient[c] : kForward[c];
-        const int64_t tm = (M + s.bm - 1) / s.bm, tn = (N + s.bn - 1) / s.bn, tiles = tm * tn;
-        if (s.id == kTile128x192 && tiles <= 256) s = kDeep[gradient];
-        int64_t n = (tiles + 255) / 256;
-        if (n <= 16) {                    // (with many tiles per unit the regions' edges don't matter)
-            const TileGrid r = tile_grid((int)tm, (int)tn, s.bm, s.bn);
-            n = ((int64_t)r.rm * r.rn + 31) / 32;
-        }
-        const double busy = tiles < 256 ? (double)tiles / 256.0 : 1.0;
-        const double us = s.fixed + s.round * (double)((n - 1) / s.fit) + s.next * (double)(n - 1) +
-                          (double)n * ((s.bm + s.bn) * (double)K * 1e-6 * (s.kb + s.busy * busy) +
-                                       s.lora * (s.id >= kRows16x16 ? fetched : staged));
-        if (best < 0 || us < best_us) { best_us = us; best = s.id; }
+    for (int c = 0; c < (gradient ? 9 : 10); ++c) {
+        const Shape* s = gradient ? &kGradient[c] : &kForward[c];
+        if (s->id == kTile128x192 && ((M + 127) / 128) * ((N + 191) / 192) <= 256) s = &kDeep[gradient];
+        const double us = shape_us(*s, M, N, K, rank);
+        if (best < 0 || us < best_us) { best_us = us; best = s->id; }
     }
     *us_estimate = best_us;
+    return best;
+}
+
+// A second product too wide for the epilogue's LDS staging (more than two 64-wide outlier slices), in a launch with the main product
+// or in one of its own that the main product accumulates onto.
+// One launch on the tiles that have registers for two sets of accumulators costs the second contraction on top of the first; two
+// cost a launch and an output that is written, read (1.5e-7 us a byte) and written again: 2048 x 8192 -> 3072 with 819 outliers
+// 74.9 us / 62 in one launch.  Wide outputs keep the two launches, whose products take the 256-row tiles (estimated: 16384 x 5120 ->
+// 5120 with 512 outliers 497 us, 540 in one launch), and so do the smallest, by a margin of 5 % (5 x 7424 -> 9408 with 301 outliers
+// forward 39.7 / 41.9).
+int choose_wide(int64_t M, int64_t N, int64_t K, int64_t K2, int32_t rank) {
+    double two, second;
+    choose_shape(M, N, K, rank, false, &two);
+    choose_shape(M, N, K2, 0, false, &second);
+    two += second + 1.5e-7 * 4.0 * (double)M * (double)N;
+    int best = -1;
+    for (int c = 0; c < 4; ++c) {
+        const Shape& s = c == 0 ? kDeep[0] : kForward[3 + c];          // the deep 128 x 192 tile, then 128 x 128, 64 x 128, 64 x 64
+        const double us = shape_us(s, M, N, K + (K2 + 127) / 128 * 128, rank);
+        if (us * (best < 0 ? 1.05 : 1.0) < two) { two = us; best = s.id; }
+    }
     return best;
 }
 }  // namespace
@@ -144,12 +168,12 @@ bool gemm_takes_rows(int64_t M, int64_t N, int64_t K, int32_t rank) {
 
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream) {
     ProfScope prof(K_GEMM, stream);
-    // A second product too wide for the epilogue's LDS staging (more than two 64-wide outlier slices) runs as a launch
-    // of its own that writes row_scale * acc2 * col_scale2, and the main product then accumulates onto it: one extra
-    // write and read of the output instead of a slow epilogue.
+    // (two launches: the first writes row_scale * acc2 * col_scale2, the main product accumulates onto it)
     // bf16 output exists in the single-launch form only
     if (g.C16 && (g.K2 > 128 || dump_acc)) return hipErrorNotSupported;
     if (!dump_acc && g.K2 > 128) {
+        const int wide = choose_wide(g.M, g.N, g.K, g.K2, g.r);
+        if (wide >= 0) return launch_gemm_wide(g, wide, stream);
         GemmArgs c2{};
         c2.A = g.A2; c2.lda = g.K2; c2.B = g.B2; c2.ldb = g.K2;
         c2.M = g.M; c2.N = g.N; c2.K = g.K2;

@@ -435,8 +435,10 @@ __device__ __forceinline__ void gemm_epilogue_dump(const GemmArgs& g, i32x16 (&a
 //   phase B  the low-rank products accumulate onto the fp32 blocks, 32 columns of r per staging round
 //   phase C  stores (all loads precede all stores: they share one in-order counter)
 // ACCUM adds what C already holds.  The caller guarantees (K2 / 64) * K2_PLANES_BYTES <= EPI_LIMIT.
-template <class C, bool ACCUM, bool OUT16 = false>
+// WIDE: the second product has been summed by a main loop of its own into `wide`, nothing of it is staged.
+template <class C, bool ACCUM, bool OUT16 = false, bool WIDE = false>
 __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (&acc)[C::TM][C::TN],
+                                                     const i32x16 (&wide)[WIDE ? C::TM : 1][WIDE ? C::TN : 1],
                                                      lds_i8* __restrict__ dma, const lds_i8* __restrict__ rd,
                                                      int64_t m0, int64_t n0, int wm, int wn, int wave, int lane,
                                                      bool active = true) {
@@ -445,7 +447,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
     constexpr int TM = C::TM, TN = C::TN, BM = C::BM_, BN = C::BN_;
     constexpr int PLANE_A = BM * 64;
     const int l32 = lane & 31, lhi = lane >> 5;
-    const int nk = g.K2 / 64, nl = (g.r + 31) / 32;
+    const int nk = WIDE ? 0 : g.K2 / 64, nl = (g.r + 31) / 32;
     const int k2_bytes = nk * C::K2_PLANES_BYTES;
     const bool overlap = k2_bytes + C::LORA_PLANES_BYTES <= C::EPI_LIMIT;   // both operand sets fit side by side
     const int lora_off = overlap ? k2_bytes : 0;
@@ -526,7 +528,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
     const lds_i8* rs_plane = rd + C::EPI_LIMIT;
     const lds_i8* cs_plane = rs_plane + BM * 4;
     const lds_i8* cs2_plane = cs_plane + C::BN_PAD * 4;
-    const bool has_cs = g.col_scale != nullptr, has_cs2 = nk > 0;
+    const bool has_cs = g.col_scale != nullptr, has_cs2 = WIDE || nk > 0;
     landed();
 
     // fp32 store of one 32x32 block (this lane: 16 rows of one column).  The block's first element is the same for
@@ -689,7 +691,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const float a = (float)acc[i][j][v];
-                const float inner = MODE == 2 ? __builtin_fmaf(a, cs, (float)acc2[v] * cs2) : MODE == 1 ? a * cs : a;
+                const float inner = MODE == 2 ? __builtin_fmaf(a, cs, (float)(WIDE ? wide[WIDE ? i : 0][WIDE ? j : 0][v] : acc2[v]) * cs2) : MODE == 1 ? a * cs : a;
                 const float r = rs[v >> 2][v & 3];
                 c[v] = ADD ? __builtin_fmaf(r, inner, c[v]) : r * inner;
             }
@@ -705,7 +707,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
         f32x16 low[PIPE ? 2 : 1];
         f32x4 rs[4];   // this lane's 16 output rows of a block are 4 runs of 4 consecutive rows
         auto block_ahead = [&](int b, int buf, auto mode, auto simple) {   // the MFMA work of block b
-            if constexpr (decltype(mode)::value == 2) block_k2(b / TN, b % TN, acc2[buf], simple);   // (nk >= 1)
+            if constexpr (decltype(mode)::value == 2 && !WIDE) block_k2(b / TN, b % TN, acc2[buf], simple);   // (nk >= 1)
             if (decltype(simple)::value || nl > 0) {
                 block_lora(b / TN, b % TN, low[buf], std::true_type{}, simple);
             } else {
@@ -745,7 +747,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
                     block_out(i, j, c);
                 } else {
                     f32x16& c = low[0];
-                    if constexpr (MODE == 2) block_k2(i, j, acc2[0], std::false_type{});   // (nk >= 1)
+                    if constexpr (MODE == 2 && !WIDE) block_k2(i, j, acc2[0], std::false_type{});   // (nk >= 1)
                     if constexpr (ACCUM) block_prev(i, j, c);
                     block_dequant(i, j, rs, acc2[0], c, std::integral_constant<bool, ACCUM>{}, mode);
                     block_lora(i, j, c, std::false_type{}, std::false_type{});
@@ -756,10 +758,10 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
                     // block's vector instructions over their latency, then one MFMA of the next block (each depends
                     // on the one before) after every further run, the stores last.
                     if (b + 1 < NB) {
-                        constexpr int NM = (MODE == 2 ? 2 : 0) + 2 * kLoraParts;      // MFMAs of a block
+                        constexpr int NM = (MODE == 2 && !WIDE ? 2 : 0) + 2 * kLoraParts;      // MFMAs of a block
                         constexpr int NV = 16 * (MODE == 2 ? 5 : MODE == 1 ? 3 : 2) + 16; // vector instructions, about
                         constexpr int RUN = NV / (NM + 1);
-                        __builtin_amdgcn_sched_group_barrier(0x100, (MODE == 2 ? 4 : 0) + 1 + 2 * kLoraParts, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, (MODE == 2 && !WIDE ? 4 : 0) + 1 + 2 * kLoraParts, 0);
                         __builtin_amdgcn_sched_group_barrier(0x002, RUN, 0);
 #pragma unroll
                         for (int u = 0; u < NM; ++u) {
@@ -802,7 +804,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& g, i32x16 (
                 const float cs2 = has_cs2 ? *(const lds_f32*)(cs2_plane + lcol * 4) : 0.0f;
                 i32x16 acc2;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc2[v] = 0;
+                for (int v = 0; v < 16; ++v) acc2[v] = WIDE ? wide[WIDE ? i : 0][WIDE ? j : 0][v] : 0;
                 for (int kk = 0; kk < nk; ++kk) {
                     const int off = kk * C::K2_PLANES_BYTES;
 #pragma unroll
@@ -913,7 +915,7 @@ __device__ __forceinline__ void clear_words(const GemmArgs& g, int part, int par
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool DUMP, bool ACCUM = false, bool OUT16 = false,
-          bool BT = false, bool RAGGED = false, int KSPLIT = 1, int BK = 128>
+          bool BT = false, bool RAGGED = false, int KSPLIT = 1, int BK = 128, bool WIDE = false>
 __global__ void __launch_bounds__(64 * WGM * WGN, MINB)
 gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     using C = DmaCfg<BM, BN, WGM, WGN, NS, BK>;
@@ -945,7 +947,7 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     auto swizzle = [](int row) { return BK == 128 ? (row >> 1) & 7 : (row >> 2) & 3; };
     const int8_t* const tileA = g.A + m0 * g.lda;
     const int8_t* const tileB = BT ? g.B : g.B + n0 * g.ldb;      // (n0 is even: the packed rows come in pairs)
-    uint32_t voff[C::NLOAD];
+    uint32_t voff[C::NLOAD], voff2[WIDE ? C::NLOAD : 1];        // voff2: of the second product's operands, rows of K2 bytes
 #pragma unroll
     for (int j = 0; j < C::NLOAD; ++j) {
         int q = j * C::NW + wave;
@@ -956,6 +958,7 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         const int64_t lim = (isA ? g.M - m0 : g.N - n0) - 1;
         row = row < lim ? row : (int)lim;                        // clamp: rows past the edge are never stored
         voff[j] = (uint32_t)row * (uint32_t)(isA ? g.lda : g.ldb) + chunk * 16;
+        if constexpr (WIDE) voff2[j] = (uint32_t)row * (uint32_t)g.K2 + chunk * 16;
         if (!BT && !isA && g.b_layout == kPackedNK) voff[j] = (uint32_t)weight_code_offset(row, chunk * 16, g.ldb);
         if (BT && !isA) {
             // B stored [K x N]: the stage's B part is 128 contraction rows of BN bytes; this lane fills the
@@ -985,6 +988,20 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+    i32x16 wide[WIDE ? C::TM : 1][WIDE ? C::TN : 1];
+    if constexpr (WIDE) {
+        static_assert(!BT && KSPLIT == 1 && BK == 128 && !DUMP && !ACCUM && !OUT16, "forward, fp32 output");
+#pragma unroll
+        for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) wide[i][j][v] = 0;
+        const int kt2 = (g.K2 + 127) / 128;
+        gemm_mainloop<C, false, true>(g.A2 + m0 * g.K2, g.B2 + n0 * g.K2, voff2, kt2, g.K2 - (kt2 - 1) * 128, lds, lds, wave, lane,
+                                      wm * C::WM * BK + frag, b_off, 128, wide);
+        __syncthreads();                                 // nobody reads the ring any more
+    }
     const int KT = RAGGED ? (int)((g.K + 127) / 128) : (int)(g.K / BK) / KSPLIT;
     const int k_last = (int)(g.K - (int64_t)(KT - 1) * 128);
     const int a_frag = wm * C::WM * BK + frag;
@@ -1092,7 +1109,7 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
     if constexpr (DUMP)
         gemm_epilogue_dump<C::TM, C::TN>(g, acc, m0 + wm * C::WM, n0 + wn * C::WN, l32, lhi);
     else
-        gemm_epilogue_staged<C, ACCUM, OUT16>(g, acc, lds, lds, m0, n0, wm, wn, wave, lane, active);
+        gemm_epilogue_staged<C, ACCUM, OUT16, WIDE>(g, acc, wide, lds, lds, m0, n0, wm, wn, wave, lane, active);
 }
 
 // Shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
@@ -1103,6 +1120,7 @@ enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTil
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_mid(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);     // 64 and 128 rows, both readings
+hipError_t launch_gemm_wide(const GemmArgs& g, int tile, hipStream_t stream);    // the deep 128 x 192 tile and these, forward
 hipError_t launch_gemm_rows(const GemmArgs& g, int shape, hipStream_t stream);   // (a dump is recognised by g.acc1)
 
 // host side: choose the XCD region grid for a grid of bm x bn tiles.  Padded work first (a surplus workgroup idles a

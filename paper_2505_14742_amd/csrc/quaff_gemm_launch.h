@@ -5,7 +5,7 @@
 
 namespace quaff {
 
-template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT, int BK = 128>
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT, int BK = 128, bool WIDE = false>
 static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stream) {
     using C = DmaCfg<BM, BN, WGM, WGN, NS, BK>;
     int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
@@ -17,10 +17,12 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
     dim3 grid(8 * (unsigned)tm.gm, (unsigned)tm.rn * KSPLIT, (unsigned)groups), block(C::NT);
     if (tm.rn * KSPLIT > 65535) return hipErrorInvalidValue;
     // the epilogue operands are staged through the idle LDS ring (launch_gemm splits wider second products off)
-    if (!dump && (int64_t)(g.K2 / 64) * C::K2_PLANES_BYTES > C::EPI_LIMIT) return hipErrorInvalidValue;
+    if (!dump && !WIDE && (int64_t)(g.K2 / 64) * C::K2_PLANES_BYTES > C::EPI_LIMIT) return hipErrorInvalidValue;
     const size_t lds = dump ? C::LDS_BYTES : C::LDS_ALLOC;
-    auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT, BK>;
-    if constexpr (KSPLIT > 1) {
+    auto k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, false, BT, RAGGED, KSPLIT, BK, WIDE>;
+    if constexpr (WIDE) {
+        if (dump || g.accumulate || g.C16) return hipErrorInvalidValue;
+    } else if constexpr (KSPLIT > 1) {
         if (dump || g.accumulate) return hipErrorInvalidValue;
         if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, KSPLIT, BK>;
     } else {

@@ -35,6 +35,17 @@ def test_mid_tiles(t, c_in, c_out, n, r):
     check_step(L, R, X, dY, 0.2, tag="mid tiles %d x %d x %d" % (t, c_in, c_out))
 
 
+# more than two slices of outliers: summed in the product's launch on the tiles of 128 x 192, 128 x 128, 64 x 128 and 64 x 64, an odd
+# and an even number of slices; in a launch of its own that the product accumulates onto (few rows)
+_WIDE = [(1990, 336, 3056, 190, 48), (900, 528, 3216, 150, 16), (300, 528, 4128, 210, 48), (240, 1040, 1040, 140, 32), (1500, 272, 2064, 271, 0),
+         (48, 4112, 48, 300, 64)]
+
+
+@pytest.mark.parametrize("t,c_in,c_out,n,r", _WIDE, ids=["%dx%dx%d_n%d_r%d" % c for c in _WIDE])
+def test_wide_outlier_products(t, c_in, c_out, n, r):
+    test_mid_tiles(t, c_in, c_out, n, r)
+
+
 @pytest.mark.parametrize("t,c_in,c_out,r", [(2048, 3072, 1024, 16), (1999, 3056, 784, 48)])
 def test_deep_tile_beside_a_second_stream(t, c_in, c_out, r):
     from paper_2505_14742_amd import binding as q
