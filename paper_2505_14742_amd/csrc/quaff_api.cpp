@@ -38,14 +38,13 @@ void set_weight_operand(quaff::GemmArgs& g, const void* packed, int64_t c_in, bo
 
 // workspace layouts -------------------------------------------------------------------------------
 size_t ws_scale(int64_t t, int32_t n) { return align_up(((size_t)quaff::scale_update_blocks(t) * n + n) * sizeof(float)); }
-struct FwdWs { size_t t_hi, t_lo, lt, at, total; };
+struct FwdWs { size_t t_hi, t_lo, lt, total; };
 FwdWs ws_fwd(int64_t t, int64_t c_in, int64_t c_out, int32_t r) {
     FwdWs w{};
     size_t off = 0;
     w.t_hi = off; off += align_up((size_t)quaff::kLoraParts * t * r * 2);
     w.t_lo = off; off += align_up((size_t)quaff::kLoraParts * t * r * 2);
     w.lt = off;   off += align_up((size_t)c_out * r * 2);
-    w.at = off;   off += quaff::lora_prefers_transposed(r, t) ? align_up((size_t)c_in * r * 2) : 0;   // A^T [r x c_in]
     w.total = off;
     return w;
 }
@@ -72,7 +71,7 @@ void set_small_split(quaff::GemmArgs& g, void* workspace, size_t used, size_t ne
     g.split_wait_ticks = g_grid_wait_ticks.load();
 }
 
-struct GradWs { size_t t1_hi, t1_lo, t2_hi, t2_lo, part_a, part_b, at, total; };
+struct GradWs { size_t t1_hi, t1_lo, t2_hi, t2_lo, part_a, part_b, total; };
 GradWs ws_grad(int64_t t, int64_t c_in, int64_t c_out, int32_t r) {
     GradWs w{};
     const size_t tbytes = align_up((size_t)quaff::kLoraParts * t * r * 2);
@@ -86,7 +85,6 @@ GradWs ws_grad(int64_t t, int64_t c_in, int64_t c_out, int32_t r) {
     w.t2_lo = off; off += tbytes;
     w.part_a = off; off += align_up((size_t)nslab_a * r * c_in * 4);
     w.part_b = off; off += align_up((size_t)nslab_b * r * c_out * 4);
-    w.at = off; off += quaff::lora_prefers_transposed(r, t) ? align_up((size_t)c_in * r * 2) : 0;   // A^T [r x c_in]
     w.total = off;
     return w;
 }
@@ -248,8 +246,7 @@ static int linear_fwd_impl(const int8_t* Xq, const float* delta_x, const int8_t*
         uint16_t* lt = reinterpret_cast<uint16_t*>(base + w.lt);
         // T = scale * X A (A is [c_in x r]); B [r x c_out] -> B^T [c_out x r] for the epilogue
         st = hip_status(quaff::launch_lora_down(X, t, c_in, ldx, lora_A, false, lora_rank, lora_scale, t_hi, t_lo,
-                                                lora_B, lt, lora_rank, c_out, s,
-                                                reinterpret_cast<uint16_t*>(base + w.at)));
+                                                lora_B, lt, lora_rank, c_out, s));
         if (st != QUAFF_OK) return st;
         g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank;
     }
@@ -405,8 +402,7 @@ int quaff_lora_bwd_weights(const uint16_t* X, int64_t ldx, const uint16_t* dY, i
     // T1 = scale dY B^T (B is [r x c_out]) and T2 = scale X A (A is [c_in x r]), as the hi/lo parts of the
     // down-projection
     int st = hip_status(quaff::launch_lora_down_pair(dY, lddy, c_out, lora_B, u16(w.t1_hi), u16(w.t1_lo), X, ldx, c_in,
-                                                     lora_A, u16(w.t2_hi), u16(w.t2_lo), t, lora_rank, lora_scale,
-                                                     u16(w.at), s));
+                                                     lora_A, u16(w.t2_hi), u16(w.t2_lo), t, lora_rank, lora_scale, s));
     if (st != QUAFF_OK) return st;
     // dA^T [r x c_in] = T1^T X, stored transposed;  dB [r x c_out] = T2^T dY
     return hip_status(quaff::launch_lora_grad_pair(X, ldx, c_in, u16(w.t1_hi), u16(w.t1_lo),
@@ -441,7 +437,7 @@ int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uin
     // is what the dX call leaves in its part of the workspace
     auto weight_grads = [&](hipStream_t gs) -> int {
         int st = hip_status(quaff::launch_lora_down(X, t, c_in, ldx, lora_A, false, lora_rank, lora_scale, u16(w.t2_hi),
-                                                    u16(w.t2_lo), nullptr, nullptr, 0, 0, gs, u16(w.at)));
+                                                    u16(w.t2_lo), nullptr, nullptr, 0, 0, gs));
         if (st != QUAFF_OK) return st;
         return hip_status(quaff::launch_lora_grad_pair(X, ldx, c_in, t1_hi, t1_lo,
                                                        reinterpret_cast<float*>(base + w.part_a), dA, dY, lddy, c_out,
@@ -630,8 +626,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     uint32_t* part = reinterpret_cast<uint32_t*>(wsf);
     float* s_prev = wsf + (int64_t)nslab * n_outlier;
     int st = hip_status(quaff::launch_colmax_lora(X, t, c_in, ldx, O, n_outlier, part, s_O, s_prev, nslab, lora_A,
-                                                  lora_rank, lora_scale, t_hi, t_lo, lora_B, lt, c_out, s,
-                                                  reinterpret_cast<uint16_t*>(lin + wf.at)));
+                                                  lora_rank, lora_scale, t_hi, t_lo, lora_B, lt, c_out, s));
     if (st != QUAFF_OK) return st;
     // The second combined launch pays off while all its workgroups are resident at once (it runs the quantizer at
     // the requantization role's register budget); long inputs take the two stand-alone kernels.

@@ -73,21 +73,14 @@ hipError_t launch_quant_act(const uint16_t* X, int64_t t, int64_t c, int64_t ldx
 // optional transposed copy of a second factor (src [rows x cols] -> dst [cols x rows]).
 hipError_t launch_lora_down(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const uint16_t* L, bool L_is_r_by_c,
                             int32_t r, float scale, uint16_t* T_hi, uint16_t* T_lo, const uint16_t* tr_src,
-                            uint16_t* tr_dst, int64_t tr_rows, int64_t tr_cols, hipStream_t stream,
-                            uint16_t* Lt_scratch = nullptr);
+                            uint16_t* tr_dst, int64_t tr_rows, int64_t tr_cols, hipStream_t stream);
 // The two down-projections of the LoRA weight gradients, T1 = scale dY B^T (B [r x c_out]) and T2 = scale X A
 // (A [c_in x r]), in one launch where that is possible (rank 16, inputs short enough for the per-block kernel), else
 // one after the other; same bits as two launch_lora_down calls.
 hipError_t launch_lora_down_pair(const uint16_t* dY, int64_t lddy, int64_t c_out, const uint16_t* B, uint16_t* T1_hi,
                                  uint16_t* T1_lo, const uint16_t* X, int64_t ldx, int64_t c_in, const uint16_t* A,
                                  uint16_t* T2_hi, uint16_t* T2_lo, int64_t t, int32_t r, float scale,
-                                 uint16_t* At_scratch, hipStream_t stream);
-// A [c x r] factor of rank 32 or more is better transposed once to [r x c] (scratch of c * r elements) than slice by
-// slice through LDS by every workgroup (the result is the same bit for bit).  At rank 16 it is not, not even with
-// 1024 row blocks: 16384 x 5120 takes 118 us with the transposed copy against 89 us without (measured).
-inline bool lora_prefers_transposed(int32_t r, int64_t /*t*/) { return r >= 32; }
-hipError_t launch_transpose_bf16(const uint16_t* src, int64_t rows, int64_t cols, uint16_t* dst, hipStream_t stream);
-
+                                 hipStream_t stream);
 // LoRA weight gradients (quaff_lora_grad.hip).  lora_grad_plan: how the token range is cut into slabs (workspace
 // sizing); launch_lora_grad_pair: both gradient products (out = sum_i P[i, :]^T Q[i, :]) in one launch, P given as
 // the hi / lo parts [kLoraParts x t x r] of a down-projection, followed by the launch that sums the slabs; partial
@@ -134,7 +127,7 @@ int scale_update_gather_slabs(int64_t t, int32_t n);   // slab count the gather 
 hipError_t launch_colmax_lora(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const int32_t* O, int32_t n,
                               uint32_t* part, const float* s_O, float* s_prev, int nslab, const uint16_t* A, int32_t r,
                               float scale, uint16_t* T_hi, uint16_t* T_lo, const uint16_t* B, uint16_t* Bt,
-                              int64_t c_out, hipStream_t stream, uint16_t* At_scratch = nullptr);
+                              int64_t c_out, hipStream_t stream);
 hipError_t launch_momentum(const uint32_t* part, int nslab, int n, int n_pad, const float* wmax_O, const float* s_prev,
                            float gamma, const int32_t* O, float* s_O, float* colscale, float* cmax_out,
                            const float* W_O, int64_t c_out, int8_t* what_int, float* delta_what, hipStream_t stream);

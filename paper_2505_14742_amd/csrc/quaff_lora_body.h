@@ -10,10 +10,19 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLoraWaves = 16;
-// contraction steps whose loads are issued together (latency hiding); even.  With the contraction-contiguous factor
-// and r = 16 a wavefront's whole slice of a 9216-wide row (ten steps) is in flight at once.
-template <int R16, bool L_RC, int RG = 1> struct LoraUnroll {
-    static constexpr int value = RG == 2 ? 2 : (L_RC && R16 == 1) ? 10 : 6;
+// Contraction-contiguous factor: steps whose loads are issued together (latency hiding); even.  At r = 16 a wavefront's whole slice of a
+// 9216-wide row (ten steps) is in flight at once.
+template <int R16, int RG = 1> struct LoraUnroll {
+    static constexpr int value = RG == 2 ? 2 : R16 == 1 ? 10 : 6;
+};
+// Factor [c x r]: 64 columns of it (two steps) go through a wavefront's piece of LDS as they are, rows of `row` bytes with `pad` more
+// after every 16, and come back through the transposing read ds_read_b64_tr_b16; the four rows that sixteen lanes read lie in
+// different banks (rank 64: the 16-byte chunks of rows 2 and 3 of every four trade places two by two).  `depth` pairs of steps are in
+// flight.  The sums over the wavefronts use the same memory afterwards: at rank 16 the 40 KB then fit beside a workgroup of the
+// input-gradient product.
+template <int R16> struct LoraRows {
+    static constexpr int row = R16 * 32, pad = R16 == 1 ? 128 : R16 == 4 ? 0 : 32, block = 16 * row + pad, bytes = 4 * block;
+    static constexpr int depth = R16 == 1 ? 2 : 1;
 };
 // Row groups of 16 rows per workgroup.  From rank 48 on a workgroup takes 32 rows: every workgroup fetches its share of
 // L (c x r against 16 x c of rows: four times the rows' bytes at rank 64), and its 128 registers per lane leave room
@@ -37,24 +46,21 @@ __device__ __forceinline__ void lora_down_body(int bx, int by, int nbx, const ui
                                                uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int row_blocks,
                                                const uint16_t* __restrict__ tr_src, uint16_t* __restrict__ tr_dst,
                                                int64_t tr_rows, int64_t tr_cols) {
-    static_assert(RG == 1 || L_RC, "several row groups only with a contraction-contiguous factor");
     constexpr int r = R16 * 16;
     constexpr int NT = 64 * kLoraWaves;
-    constexpr int kLoraUnroll = LoraUnroll<R16, L_RC, RG>::value;
-    constexpr int TROW = 40;                       // padded row (in bf16) of the transposed slice: 32 + 8
+    constexpr int kLoraUnroll = LoraUnroll<R16, RG>::value;
+    using Rows = LoraRows<R16>;
     if (bx >= row_blocks) {
         if (by != 0) return;
         // transposed copy: dst [cols x rows] <- src [rows x cols]
-        int64_t total = tr_rows * tr_cols;
-        int64_t nb = nbx - row_blocks;
-        for (int64_t e = ((int64_t)bx - row_blocks) * NT + threadIdx.x; e < total; e += nb * NT) {
-            int64_t col = e / tr_rows, row = e % tr_rows;
-            tr_dst[e] = tr_src[row * tr_cols + col];
-        }
+        const uint32_t total = (uint32_t)(tr_rows * tr_cols), rows = (uint32_t)tr_rows;     // (at most 64 x 2^20)
+        for (uint32_t e = (uint32_t)(bx - row_blocks) * NT + threadIdx.x; e < total; e += (uint32_t)(nbx - row_blocks) * NT)
+            tr_dst[e] = tr_src[(int64_t)(e % rows) * tr_cols + e / rows];
         return;
     }
-    __shared__ float red[kLoraWaves][R16][64][4];
-    __shared__ __attribute__((aligned(16))) uint16_t lt[L_RC ? 1 : kLoraWaves][L_RC ? 1 : r][L_RC ? 8 : TROW];
+    constexpr int RED = kLoraWaves * R16 * 64 * 4 * (int)sizeof(float), LT = L_RC ? 0 : kLoraWaves * Rows::bytes;
+    __shared__ __attribute__((aligned(16))) char lora_lds[RED > LT ? RED : LT];
+    float (*red)[R16][64][4] = reinterpret_cast<float (*)[R16][64][4]>(lora_lds);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, g = lane >> 4;
     bool live[RG];
@@ -81,69 +87,103 @@ __device__ __forceinline__ void lora_down_body(int bx, int by, int nbx, const ui
     const int kbeg = cbeg + wave * kw, kend = kbeg + kw < cend ? kbeg + kw : cend;
     T_hi += (int64_t)by * t * r;
     T_lo += (int64_t)by * t * r;
-    for (int kk0 = kbeg; kk0 < kend; kk0 += 32 * kLoraUnroll) {
-        u32x4 xa[kLoraUnroll][RG], lb[kLoraUnroll][R16];
-        // all global loads of the batch first
+    // Two consecutive steps share 64 columns: lane group g takes columns 16 g .. 16 g + 7 in the even step and 16 g + 8 .. 16 g + 15
+    // in the odd one (any assignment of contraction indices to MFMA slots is valid as long as both operands use it), so the four
+    // groups of a row read one whole 128-byte line per step pair instead of two half lines.
+    auto mfmas = [&](const u32x4 (&x)[RG], const u32x4 (&l)[R16]) {
 #pragma unroll
-        for (int u = 0; u < kLoraUnroll; ++u) {
-            // Two consecutive steps share 64 columns: lane group g takes columns 16 g .. 16 g + 7 in the even step
-            // and 16 g + 8 .. 16 g + 15 in the odd one (any assignment of contraction indices to MFMA slots is
-            // valid as long as both operands use it), so the four groups of a row read one whole 128-byte line
-            // per step pair instead of two half lines.
-            const int k0 = kk0 + (u >> 1) * 64 + (u & 1) * 8;
-            const int k = k0 + g * 16;         // this lane's eight contraction indices
-            // loads are unconditional (address clamped into the row) so that the whole batch is in flight together;
-            // a step past the end contributes zero because its x fragment is cleared
-            const int kc = k < kend ? k : c - 8;
+        for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
-            for (int rg = 0; rg < RG; ++rg) {
-                xa[u][rg] = *reinterpret_cast<const u32x4*>(xrow[rg] + kc);
-                if (!(live[rg] && k < kend)) xa[u][rg] = (u32x4){0, 0, 0, 0};
-            }
-            if (L_RC) {
+            for (int b = 0; b < R16; ++b)
+                acc[rg][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[rg]), __builtin_bit_cast(bf16x8, l[b]),
+                                                                     acc[rg][b], 0, 0, 0);
+    };
+    if constexpr (L_RC) {
+        for (int kk0 = kbeg; kk0 < kend; kk0 += 32 * kLoraUnroll) {
+            u32x4 xa[kLoraUnroll][RG], lb[kLoraUnroll][R16];
+            // all global loads of the batch first
+#pragma unroll
+            for (int u = 0; u < kLoraUnroll; ++u) {
+                const int k = kk0 + (u >> 1) * 64 + (u & 1) * 8 + g * 16;         // this lane's eight contraction indices
+                // loads are unconditional (address clamped into the row) so that the whole batch is in flight together;
+                // a step past the end contributes zero because its x fragment is cleared
+                const int kc = k < kend ? k : c - 8;
+#pragma unroll
+                for (int rg = 0; rg < RG; ++rg) {
+                    xa[u][rg] = *reinterpret_cast<const u32x4*>(xrow[rg] + kc);
+                    if (!(live[rg] && k < kend)) xa[u][rg] = (u32x4){0, 0, 0, 0};
+                }
 #pragma unroll
                 for (int b = 0; b < R16; ++b)
                     lb[u][b] = *reinterpret_cast<const u32x4*>(L + (int64_t)(b * 16 + m) * c + kc);
-            } else {
-                // L[k0 .. k0+32) x r arrives as 16-byte vectors along r; kept in lb[u][*] until it is transposed
-                constexpr int VEC = 32 * r / 8;
-#pragma unroll
-                for (int b = 0; b < R16; ++b) {   // VEC = 64 * R16: one vector per lane per b
-                    int v = b * 64 + lane;
-                    int kk = v / (r / 8), p0 = (v % (r / 8)) * 8;
-                    const int km = k0 + (kk >> 3) * 16 + (kk & 7);   // slot kk of the step holds this column
-                    const int kr = km < c ? km : c - 1;
-                    lb[u][b] = *reinterpret_cast<const u32x4*>(L + (int64_t)kr * r + p0);
-                }
-                (void)VEC;
             }
+#pragma unroll
+            for (int u = 0; u < kLoraUnroll; ++u) mfmas(xa[u], lb[u]);
         }
+    } else {
+        typedef short v4s __attribute__((ext_vector_type(4)));
+        typedef short v8s __attribute__((ext_vector_type(8)));
+        typedef __attribute__((address_space(3))) v4s lds_v4s;
+        constexpr int D = Rows::depth, CPR = r / 8;                 // 16-byte chunks per row of L
+        char* const mine = lora_lds + wave * Rows::bytes;
+        auto at = [&](int kk, int chunk) {                           // row kk of the pair's 64
+            return (kk >> 4) * Rows::block + (kk & 15) * Rows::row + (R16 == 4 ? chunk ^ (((kk >> 1) & 1) * 2) : chunk) * 16;
+        };
+        const int pairs = kend > kbeg ? (kend - kbeg + 63) / 64 : 0;
+        u32x4 xa[D][2][RG], lb[D][2 * R16];
+        auto load = [&](int p, int slot) {
+            const int k0 = kbeg + p * 64, k = k0 + g * 16;
 #pragma unroll
-        for (int u = 0; u < kLoraUnroll; ++u) {
-            if (!L_RC) {
-                // transpose this step's slice through the wavefront's LDS piece: lt[p][kk]
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int b = 0; b < R16; ++b) {
-                    int v = b * 64 + lane;
-                    int kk = v / (r / 8), p0 = (v % (r / 8)) * 8;
+                for (int rg = 0; rg < RG; ++rg)
+                    xa[slot][h][rg] = *reinterpret_cast<const u32x4*>(xrow[rg] + (k < kend ? k + h * 8 : c - 8));
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        lt[wave][p0 + 2 * w][kk] = (uint16_t)(lb[u][b][w] & 0xFFFFu);
-                        lt[wave][p0 + 2 * w + 1][kk] = (uint16_t)(lb[u][b][w] >> 16);
+            for (int i = 0; i < 2 * R16; ++i) {
+                const int id = i * 64 + lane, kr = k0 + id / CPR;
+                lb[slot][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(L) +
+                                                              (uint32_t)((kr < c ? kr : c - 1) * (2 * r) + (id % CPR) * 16));
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < pairs) load(d, d);
+        for (int p0 = 0; p0 < pairs; p0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int p = p0 + d;
+                if (p >= pairs) break;                               // (uniform over the wavefront, whose LDS operations run in order)
+#pragma unroll
+                for (int i = 0; i < 2 * R16; ++i) {
+                    const int id = i * 64 + lane;
+                    *reinterpret_cast<u32x4*>(mine + at(id / CPR, id % CPR)) = lb[d][i];
+                }
+                u32x4 x[2][RG];                                      // (a step past the end meets zeros)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int rg = 0; rg < RG; ++rg)
+                        x[h][rg] = live[rg] && kbeg + p * 64 + g * 16 < kend ? xa[d][h][rg] : (u32x4){0, 0, 0, 0};
+                if (p + D < pairs) load(p + D, d);
+                // lane (m, g): rank 16 b + m, columns 16 g .. (even step), 16 g + 8 .. (odd); lane m of a group of sixteen addresses
+                // column m / 4 of the four it wants, ranks 4 (m % 4) .. + 3, and receives rank m of all four
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    u32x4 l[R16];
+#pragma unroll
+                    for (int b = 0; b < R16; ++b) {
+                        auto four = [&](int col0) {
+                            return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                (lds_v4s*)(mine + at(g * 16 + col0 + (m >> 2), b * 2 + ((m & 3) >> 1)) + (m & 1) * 8));
+                        };
+                        const v4s f0 = four(h * 8), f1 = four(h * 8 + 4);
+                        l[b] = __builtin_bit_cast(u32x4, (v8s){f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3]});
                     }
+                    mfmas(x[h], l);
                 }
-#pragma unroll
-                for (int b = 0; b < R16; ++b)
-                    lb[u][b] = *reinterpret_cast<const u32x4*>(&lt[wave][b * 16 + m][g * 8]);
             }
-#pragma unroll
-            for (int rg = 0; rg < RG; ++rg)
-#pragma unroll
-                for (int b = 0; b < R16; ++b)
-                    acc[rg][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[u][rg]),
-                                                                         __builtin_bit_cast(bf16x8, lb[u][b]), acc[rg][b],
-                                                                         0, 0, 0);
         }
+        __syncthreads();                                             // (the sums below take the place of the slices)
     }
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
