@@ -21,7 +21,7 @@ quant_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx,
     constexpr int RG = lora_row_groups(R16);                 // 16-row groups per down-projection workgroup
     const int lora_blocks = lora_row_blocks * kLoraParts;
     if ((int)blockIdx.x < lora_blocks)
-        lora_down_body<R16, true, RG>(blockIdx.x % lora_row_blocks, blockIdx.x / lora_row_blocks, lora_row_blocks, X, t, c,
+        lora_down_body<R16, true, RG, R16 == 1 ? 4 : R16 == 2 ? 2 : 1>(blockIdx.x % lora_row_blocks, blockIdx.x / lora_row_blocks, lora_row_blocks, X, t, c,
                                       ldx, L, scale, T_hi, T_lo, lora_row_blocks, nullptr, nullptr, 0, 0);
     else {
         // The hardware deals consecutive workgroups to the eight XCDs in turn and every XCD has its own L2: the
