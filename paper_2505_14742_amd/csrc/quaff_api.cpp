@@ -291,7 +291,8 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
                               int64_t c_in, int64_t c_out, const uint16_t* lora_A, const uint16_t* lora_B,
                               int32_t lora_rank, float lora_scale, float* dX, uint16_t* dX16, int64_t lddx,
                               void* workspace, size_t workspace_bytes, void* stream,
-                              const std::function<int()>* before_product = nullptr, size_t split_at = 0, bool beside = false) {
+                              const std::function<int()>* before_product = nullptr, size_t split_at = 0, bool beside = false,
+                              quaff::LoraJob* job = nullptr) {
     if (!dY || !Wq_packed || !delta_w || (!dX && !dX16)) return QUAFF_ERR_NULL;
     if (dX16 && c_out % 64 != 0) return QUAFF_ERR_SHAPE;
     if (dX16 && (!aligned16(dX16) || lddx % 8 != 0)) return QUAFF_ERR_ALIGN;
@@ -320,7 +321,7 @@ static int linear_bwd_dx_impl(const uint16_t* dY, int64_t t, int64_t lddy, const
         // The quantizer and this down-projection both only read dY: one launch runs them side by side when it can.
         hipError_t e = hipSuccess;
         quantized = quaff::launch_quant_lora(dY, t, c_out, lddy, delta_w, gq, dg, lora_B, lora_rank, lora_scale, t_hi,
-                                             t_lo, s, &e);
+                                             t_lo, s, &e, job);
         if (quantized) {
             if ((st = hip_status(e)) != QUAFF_OK) return st;
         } else {
@@ -435,8 +436,10 @@ int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uin
     uint16_t* t1_lo = reinterpret_cast<uint16_t*>(bwd + wb.t_lo);
     // T2 = scale X A, then the two products of quaff_lora_bwd_weights, on stream `gs`; T1 = scale dY B^T (hi / lo parts)
     // is what the dX call leaves in its part of the workspace
+    // (T2 is taken along by the launch that prepares dY where everything runs on one stream)
+    quaff::LoraJob job{X, ldx, c_in, lora_A, u16(w.t2_hi), u16(w.t2_lo), false};
     auto weight_grads = [&](hipStream_t gs) -> int {
-        int st = hip_status(quaff::launch_lora_down(X, t, c_in, ldx, lora_A, false, lora_rank, lora_scale, u16(w.t2_hi),
+        int st = job.done ? QUAFF_OK : hip_status(quaff::launch_lora_down(X, t, c_in, ldx, lora_A, false, lora_rank, lora_scale, u16(w.t2_hi),
                                                     u16(w.t2_lo), nullptr, nullptr, 0, 0, gs));
         if (st != QUAFF_OK) return st;
         return hip_status(quaff::launch_lora_grad_pair(X, ldx, c_in, t1_hi, t1_lo,
@@ -464,7 +467,7 @@ int quaff_linear_bwd_step(const uint16_t* dY, int64_t t, int64_t lddy, const uin
     };
     int st = linear_bwd_dx_impl(dY, t, lddy, Wq_packed, delta_w, c_in, c_out, lora_A, lora_B, lora_rank, lora_scale, dX,
                                 nullptr, lddx, workspace, workspace_bytes, stream, &fork,
-                                wb.total + w.total, use_side);
+                                wb.total + w.total, use_side, use_side ? nullptr : &job);
     if (forked) {
         // Whatever happened after the fork, the caller's stream joins everything that was put on the side stream,
         // so that the buffers that work reads and writes stay ordered before the caller's next use of them.
@@ -622,7 +625,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     float* wsf = static_cast<float*>(workspace);
     // (the persistent down-projection of long inputs yields the abs-max slabs itself, one per row group)
     const int nslab = quaff::lora_stream_applies(lora_rank, t, c_in, n_outlier) ? quaff::lora_stream_row_groups(t)
-                                                                                : quaff::scale_update_gather_slabs(t, n_outlier);
+                                                                                : quaff::fwd_step_slabs(t, n_outlier);
     uint32_t* part = reinterpret_cast<uint32_t*>(wsf);
     float* s_prev = wsf + (int64_t)nslab * n_outlier;
     int st = hip_status(quaff::launch_colmax_lora(X, t, c_in, ldx, O, n_outlier, part, s_O, s_prev, nslab, lora_A,

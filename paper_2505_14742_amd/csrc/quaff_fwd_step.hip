@@ -14,9 +14,10 @@ colmax_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx
                    uint16_t* __restrict__ T_lo, int row_blocks, int lora_nbx, const uint16_t* __restrict__ tr_src,
                    uint16_t* __restrict__ tr_dst, int64_t tr_rows, int64_t tr_cols) {
     __shared__ uint32_t wred[16 * kLoraWaves];
+    __shared__ __attribute__((aligned(16))) char lora_lds[lora_lds_bytes<R16, false>()];
     const int lora_blocks = lora_nbx * kLoraParts;
     if ((int)blockIdx.x < lora_blocks)
-        lora_down_body<R16, false, lora_row_groups(R16)>(blockIdx.x % lora_nbx, blockIdx.x / lora_nbx, lora_nbx, X,
+        lora_down_body<R16, false, lora_row_groups(R16)>(lora_lds, blockIdx.x % lora_nbx, blockIdx.x / lora_nbx, lora_nbx, X,
                                                                     t, c, ldx, L, scale, T_hi, T_lo, row_blocks, tr_src,
                                                                     tr_dst, tr_rows, tr_cols);
     else

@@ -104,12 +104,15 @@ hipError_t launch_calibrate(const uint16_t* X, int64_t ldx, int64_t c_in, int64_
                             int32_t n_samples, double ratio, int32_t budget, int32_t* xi, int32_t* O, int32_t* n_out,
                             uint16_t* colmax, double* part_sum, int32_t* rank, hipStream_t stream);
 
+// A down-projection T = scale X L (L [c x r], bf16 hi / lo parts as above) that another launch may take along; `done` tells.
+struct LoraJob { const uint16_t* X; int64_t ldx, c; const uint16_t* L; uint16_t* T_hi; uint16_t* T_lo; bool done; };
+
 // Quantizer (colscale = cs, no outlier copy) and LoRA down-projection with a contraction-contiguous factor
 // L [r x c] of the same bf16 matrix X in ONE launch (quaff_quant_lora.hip).  Returns false, with nothing enqueued,
 // for shapes it does not cover; otherwise *err holds the launch status.
 bool launch_quant_lora(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const float* cs, int8_t* Xq, float* delta,
                        const uint16_t* L_r_by_c, int32_t r, float scale, uint16_t* T_hi, uint16_t* T_lo,
-                       hipStream_t stream, hipError_t* err);
+                       hipStream_t stream, hipError_t* err, LoraJob* job = nullptr);
 
 // Persistent LoRA down-projection for long inputs at rank 16 (quaff_lora_stream.hip): same bits as launch_lora_down.
 // With O / part / s_O / s_prev (n > 0) the same pass writes the abs-max slabs part [lora_stream_row_groups(t) x n] of the
@@ -124,6 +127,8 @@ hipError_t launch_lora_stream(const uint16_t* X, int64_t t, int64_t c, int64_t l
 // Pieces of the fused forward step (quaff_linear_fwd_step): the abs-max slabs and the LoRA down-projection of X in
 // one launch (quaff_fwd_step.hip), then the momentum / what kernel on those slabs (quaff_scale.hip).
 int scale_update_gather_slabs(int64_t t, int32_t n);   // slab count the gather variant of the abs-max uses
+// the same beside the down-projection: few, because every quantizing workgroup of the next launch folds them (32 are a round trip)
+inline int fwd_step_slabs(int64_t t, int32_t n) { const int b = scale_update_gather_slabs(t, n); return b < 64 ? b : 64; }
 hipError_t launch_colmax_lora(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const int32_t* O, int32_t n,
                               uint32_t* part, const float* s_O, float* s_prev, int nslab, const uint16_t* A, int32_t r,
                               float scale, uint16_t* T_hi, uint16_t* T_lo, const uint16_t* B, uint16_t* Bt,

@@ -21,7 +21,8 @@ __global__ void __launch_bounds__(64 * kLoraWaves, R16 <= 2 ? 8 : 4)
 lora_down_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const uint16_t* __restrict__ L,
                  float scale, uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int row_blocks,
                  const uint16_t* __restrict__ tr_src, uint16_t* __restrict__ tr_dst, int64_t tr_rows, int64_t tr_cols) {
-    lora_down_body<R16, L_RC, lora_row_groups(R16)>(blockIdx.x, blockIdx.y, gridDim.x, X, t, c, ldx, L, scale,
+    __shared__ __attribute__((aligned(16))) char lora_lds[lora_lds_bytes<R16, L_RC>()];
+    lora_down_body<R16, L_RC, lora_row_groups(R16)>(lora_lds, blockIdx.x, blockIdx.y, gridDim.x, X, t, c, ldx, L, scale,
                                                                 T_hi, T_lo, row_blocks, tr_src, tr_dst, tr_rows, tr_cols);
 }
 
@@ -33,11 +34,13 @@ struct LoraPairArgs {
 };
 __global__ void __launch_bounds__(64 * kLoraWaves, 8)
 lora_down_pair_kernel(LoraPairArgs a) {
+    __shared__ __attribute__((aligned(16))) char lora_lds[lora_lds_bytes<1, false>()];
+    static_assert(lora_lds_bytes<1, true>() <= lora_lds_bytes<1, false>(), "either role");
     if (blockIdx.z == 0)
-        lora_down_body<1, true>(blockIdx.x, blockIdx.y, gridDim.x, a.X[0], a.t, a.c[0], a.ldx[0], a.L[0], a.scale, a.T_hi[0],
+        lora_down_body<1, true>(lora_lds, blockIdx.x, blockIdx.y, gridDim.x, a.X[0], a.t, a.c[0], a.ldx[0], a.L[0], a.scale, a.T_hi[0],
                                 a.T_lo[0], a.row_blocks, nullptr, nullptr, 0, 0);
     else
-        lora_down_body<1, false>(blockIdx.x, blockIdx.y, gridDim.x, a.X[1], a.t, a.c[1], a.ldx[1], a.L[1], a.scale, a.T_hi[1],
+        lora_down_body<1, false>(lora_lds, blockIdx.x, blockIdx.y, gridDim.x, a.X[1], a.t, a.c[1], a.ldx[1], a.L[1], a.scale, a.T_hi[1],
                                  a.T_lo[1], a.row_blocks, nullptr, nullptr, 0, 0);
 }
 

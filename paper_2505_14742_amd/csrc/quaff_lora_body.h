@@ -24,6 +24,10 @@ template <int R16, bool L_RC> struct LoraRows {
     static constexpr int bytes = L_RC ? R16 * 16 * 128 : 4 * block;
     static constexpr int depth = R16 == 1 ? 2 : 1;
 };
+// LDS of lora_down_body
+template <int R16, bool L_RC> constexpr int lora_lds_bytes() {
+    return kLoraWaves * (LoraRows<R16, L_RC>::bytes > R16 * 1024 ? LoraRows<R16, L_RC>::bytes : R16 * 1024);
+}
 // Row groups of 16 rows per workgroup.  From rank 48 on a workgroup takes 32 rows: every workgroup fetches its share of
 // L (c x r against 16 x c of rows: four times the rows' bytes at rank 64), and its 128 registers per lane leave room
 // for one 16-wavefront workgroup per compute unit only, so 16-row workgroups would also need two rounds at 4096 rows.
@@ -41,7 +45,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
 // Work of one workgroup (64 * kLoraWaves threads): `bx` < row_blocks is its block of 16 RG rows and `by` its part of the
 // contraction range; workgroups bx >= row_blocks (nbx in all, by = 0 only) write the transposed copy.
 template <int R16, bool L_RC, int RG = 1, int DEPTH = LoraRows<R16, L_RC>::depth>
-__device__ __forceinline__ void lora_down_body(int bx, int by, int nbx, const uint16_t* __restrict__ X, int64_t t, int c,
+__device__ __forceinline__ void lora_down_body(char* lora_lds, int bx, int by, int nbx, const uint16_t* __restrict__ X, int64_t t, int c,
                                                int64_t ldx, const uint16_t* __restrict__ L, float scale,
                                                uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int row_blocks,
                                                const uint16_t* __restrict__ tr_src, uint16_t* __restrict__ tr_dst,
@@ -57,8 +61,6 @@ __device__ __forceinline__ void lora_down_body(int bx, int by, int nbx, const ui
             tr_dst[e] = tr_src[(int64_t)(e % rows) * tr_cols + e / rows];
         return;
     }
-    constexpr int RED = kLoraWaves * R16 * 64 * 4 * (int)sizeof(float), LT = kLoraWaves * Rows::bytes;
-    __shared__ __attribute__((aligned(16))) char lora_lds[RED > LT ? RED : LT];
     float (*red)[R16][64][4] = reinterpret_cast<float (*)[R16][64][4]>(lora_lds);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, g = lane >> 4;

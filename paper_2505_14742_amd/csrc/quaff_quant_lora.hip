@@ -10,6 +10,12 @@
 
 namespace quaff {
 
+// What a launch takes along: the down-projection of the layer's input for the weight gradients, in the `blocks` workgroups that
+// follow those of dY (row_blocks of 16 or 32 rows, two parts each; 0 = nothing).  With a
+// launch of its own / so, us: whole training steps 512 x 3072 -> 3072 at
+// rank 16 55.7 / 51.3, 1003 x 1040 -> 2064 at rank 32 53.5 / 51.3.
+struct Along { const uint16_t* X; int64_t ldx; int c; const uint16_t* L; uint16_t* T_hi; uint16_t* T_lo; int row_blocks, blocks; };
+
 // rows per quantizing workgroup: TPR threads take one, or all of them share eight (TPR = 1024)
 constexpr int quant_rows_per_block(int TPR) { return TPR <= 256 ? 64 * kLoraWaves / TPR : 8; }
 
@@ -17,18 +23,24 @@ template <int R16, int TPR, int NV>
 __global__ void __launch_bounds__(64 * kLoraWaves)
 quant_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const float* __restrict__ cs,
                   int8_t* __restrict__ Xq, float* __restrict__ delta, const uint16_t* __restrict__ L, float scale,
-                  uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int lora_row_blocks) {
+                  uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int lora_row_blocks, const Along along) {
     constexpr int RG = lora_row_groups(R16);                 // 16-row groups per down-projection workgroup
+    __shared__ __attribute__((aligned(16))) char lora_lds[lora_lds_bytes<R16, false>()];
+    static_assert(lora_lds_bytes<R16, true>() <= lora_lds_bytes<R16, false>(), "either role");
     const int lora_blocks = lora_row_blocks * kLoraParts;
     if ((int)blockIdx.x < lora_blocks)
-        lora_down_body<R16, true, RG, R16 == 1 ? 4 : R16 == 2 ? 2 : 1>(blockIdx.x % lora_row_blocks, blockIdx.x / lora_row_blocks, lora_row_blocks, X, t, c,
+        lora_down_body<R16, true, RG, R16 == 1 ? 4 : R16 == 2 ? 2 : 1>(lora_lds, blockIdx.x % lora_row_blocks, blockIdx.x / lora_row_blocks, lora_row_blocks, X, t, c,
                                       ldx, L, scale, T_hi, T_lo, lora_row_blocks, nullptr, nullptr, 0, 0);
-    else {
+    else if ((int)blockIdx.x < lora_blocks + along.blocks) {
+        const int b = blockIdx.x - lora_blocks;
+        lora_down_body<R16, false, RG>(lora_lds, b % along.row_blocks, b / along.row_blocks, along.row_blocks, along.X, t, along.c, along.ldx,
+                                       along.L, scale, along.T_hi, along.T_lo, along.row_blocks, nullptr, nullptr, 0, 0);
+    } else {
         // The hardware deals consecutive workgroups to the eight XCDs in turn and every XCD has its own L2: the
         // quantizing workgroups of a row block are renumbered so that they land on the XCD whose down-projection
         // workgroups (index = row block of 16 RG rows, same residue modulo 8) read the same rows at about the same time.
         constexpr int ROWS = quant_rows_per_block(TPR), QPG = 16 / ROWS;   // quantizing workgroups per 16-row block
-        const int local = blockIdx.x - lora_blocks;
+        const int local = blockIdx.x - lora_blocks - along.blocks;
         const int xcd = local & 7, m = local >> 3;
         const int mq = m / QPG;
         const int rb = ((mq / RG) * 8 + xcd) * RG + mq % RG;   // 16-row block
@@ -60,11 +72,23 @@ __device__ __forceinline__ void lds_barrier() {
 
 // RESIDENT = false: rows too long to keep a slice of L and a second group of rows in registers; L is fetched (from L2,
 // where it stays) a few steps at a time for every group and the next group's rows are not requested ahead.
-template <int R16, int NSTEP, bool RESIDENT = true>
+// ALONG: workgroups from gridDim.x - along.blocks on take the other down-projection.
+template <int R16, int NSTEP, bool RESIDENT = true, bool ALONG = false>
 __global__ void __launch_bounds__(64 * kLoraWaves)
 quant_lora_rows8_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const float* __restrict__ cs,
                         int8_t* __restrict__ Xq, float* __restrict__ delta, const uint16_t* __restrict__ L, float scale,
-                        uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int ngroups) {
+                        uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int ngroups, const Along along) {
+    const int workers = ALONG ? (int)gridDim.x - along.blocks : (int)gridDim.x;
+    if constexpr (ALONG) {
+        if ((int)blockIdx.x >= workers) {
+            __shared__ __attribute__((aligned(16))) char lora_lds[lora_lds_bytes<R16, false>()];
+            const int b = blockIdx.x - workers;
+            lora_down_body<R16, false, lora_row_groups(R16)>(lora_lds, b % along.row_blocks, b / along.row_blocks, along.row_blocks, along.X, t, along.c,
+                                                             along.ldx, along.L, scale, along.T_hi, along.T_lo, along.row_blocks, nullptr,
+                                                             nullptr, 0, 0);
+            return;
+        }
+    }
     static_assert(kLoraParts == 2 && kLoraWaves == 16, "two parts of eight wavefronts each");
     constexpr int r = R16 * 16;
     __shared__ float red[kLoraWaves][R16][32][4];
@@ -128,10 +152,10 @@ quant_lora_rows8_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_
     __syncthreads();
     const lds_float* csl = (const lds_float*)cs_copy;
 
-    for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+    for (int grp = blockIdx.x; grp < ngroups; grp += workers) {
         const int64_t row = (int64_t)grp * 8 + (m & 7);
         const bool live = row < t;
-        if (PF) load_rows(grp + gridDim.x, xn);      // the next group's rows travel while this one is worked on
+        if (PF) load_rows(grp + workers, xn);      // the next group's rows travel while this one is worked on
         f32x4 acc0[R16], acc1[R16];                  // first-half products (rows 0..7 valid), second-half (rows 8..15)
 #pragma unroll
         for (int b = 0; b < R16; ++b) acc0[b] = acc1[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -233,29 +257,32 @@ quant_lora_rows8_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_
         if (PF) {
 #pragma unroll
             for (int u = 0; u < NSTEP; ++u) xa[u] = xn[u];
-        } else if (grp + (int)gridDim.x < ngroups) {
-            load_rows(grp + gridDim.x, xa);
+        } else if (grp + workers < ngroups) {
+            load_rows(grp + workers, xa);
         }
     }
 }
 
 template <int R16>
 static bool launch_rows8(const uint16_t* X, int64_t t, int c, int64_t ldx, const float* cs, int8_t* Xq, float* delta,
-                         const uint16_t* L, float scale, uint16_t* T_hi, uint16_t* T_lo, hipStream_t stream) {
+                         const uint16_t* L, float scale, uint16_t* T_hi, uint16_t* T_lo, hipStream_t stream, Along& along) {
     const int cp = ((c + kLoraParts * 64 - 1) / (kLoraParts * 64)) * 64;
     const int nstep = (cp + 8 * 64 - 1) / (8 * 64);          // 64-column steps per wavefront
     // one persistent workgroup per compute unit (fewer when there are fewer 8-row groups)
     const int ngroups = (int)((t + 7) / 8);
-    const dim3 grid((unsigned)(ngroups < 256 ? ngroups : 256)), block(64 * kLoraWaves);
+    const int workers = ngroups < 256 ? ngroups : 256;
+    const dim3 block(64 * kLoraWaves);
 #define QUAFF_R8(NS, RES)                                                                                             \
     {                                                                                                                 \
         const size_t lds = (((size_t)c * 4 + 255) & ~(size_t)255) +                                                   \
                            (size_t)kLoraWaves * 8 * (NS > 9 ? (NS + 1) / 2 : NS) * 64;                                \
-        auto kern = quant_lora_rows8_kernel<R16, NS, RES>;                                                            \
+        if (!RES) along.blocks = 0;                /* (no LDS left beside long rows) */                               \
+        auto kern = RES && along.blocks > 0 ? quant_lora_rows8_kernel<R16, NS, RES, RES> : quant_lora_rows8_kernel<R16, NS, RES>; \
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,      \
                                 (int)lds) != hipSuccess)                                                              \
             return false;                                                                                             \
-        hipLaunchKernelGGL(kern, grid, block, lds, stream, X, t, c, ldx, cs, Xq, delta, L, scale, T_hi, T_lo, ngroups); \
+        hipLaunchKernelGGL(kern, dim3((unsigned)(workers + along.blocks)), block, lds, stream, X, t, c, ldx, cs, Xq, delta, L, scale, \
+                           T_hi, T_lo, ngroups, along);                                                               \
     }
     // Longer rows: nine and more steps of resident L fragments and prefetched rows do not fit the 128 registers a
     // 16-wavefront workgroup has per lane.  The form that fetches L again for every group then moves twice the bytes of
@@ -273,7 +300,7 @@ static bool launch_rows8(const uint16_t* X, int64_t t, int c, int64_t ldx, const
 
 template <int R16>
 static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const float* cs, int8_t* Xq, float* delta,
-                     const uint16_t* L, float scale, uint16_t* T_hi, uint16_t* T_lo, hipStream_t stream) {
+                     const uint16_t* L, float scale, uint16_t* T_hi, uint16_t* T_lo, hipStream_t stream, const Along& along) {
     constexpr int NT = 64 * kLoraWaves;
     constexpr int RG = lora_row_groups(R16);
     const int row_blocks = (int)((t + 15) / 16);
@@ -281,10 +308,10 @@ static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const flo
     const int vec = (c + 7) / 8;
 #define QUAFF_QL(TPR, NV)                                                                                             \
     hipLaunchKernelGGL((quant_lora_kernel<R16, TPR, NV>),                                                             \
-                       dim3((unsigned)(lora_row_blocks * kLoraParts +                                                 \
+                       dim3((unsigned)(lora_row_blocks * kLoraParts + along.blocks +                                  \
                                        8 * RG * ((row_blocks + 8 * RG - 1) / (8 * RG)) * (16 / quant_rows_per_block(TPR)))),         \
                        dim3(NT), 0,                                                                                   \
-                       stream, X, t, c, ldx, cs, Xq, delta, L, scale, T_hi, T_lo, lora_row_blocks)
+                       stream, X, t, c, ldx, cs, Xq, delta, L, scale, T_hi, T_lo, lora_row_blocks, along)
     if (vec <= 64 * 2) QUAFF_QL(64, 2);
     else if (vec <= 64 * 4) QUAFF_QL(64, 4);
     else if (vec <= 64 * 6) QUAFF_QL(64, 6);
@@ -309,24 +336,34 @@ static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const flo
 // Returns false (nothing enqueued) for shapes this launch does not cover: the caller then issues the two launches.
 bool launch_quant_lora(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const float* cs, int8_t* Xq, float* delta,
                        const uint16_t* L_r_by_c, int32_t r, float scale, uint16_t* T_hi, uint16_t* T_lo,
-                       hipStream_t stream, hipError_t* err) {
+                       hipStream_t stream, hipError_t* err, LoraJob* job) {
     if (r < 16 || r > 64 || r % 16 != 0 || c > 256 * 8 * 8) return false;
     ProfScope prof(K_QUANT_LORA, stream);
     bool ok = false;
+    Along along{};
+    if (job && !lora_stream_applies(r, t, job->c, 0)) {
+        const int rows = lora_rows_per_block(r), row_blocks = (int)((t + rows - 1) / rows);
+        along = Along{job->X, job->ldx, (int)job->c, job->L, job->T_hi, job->T_lo, row_blocks, row_blocks * kLoraParts};
+    }
     // One pass over dY with eight rows per persistent workgroup where it pays: the smallest rank (a wavefront keeps
     // its slice of L in registers) and rows short enough for the registers.  Measured at 16384 x 5120: 85 us against
     // 130 us for the two-role launch (which reads dY twice); at 2048 and 4096 rows the two forms are level.
     if (r == 16 && cs != nullptr) {
-        ok = launch_rows8<1>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream);
-        if (ok) { *err = hipGetLastError(); return true; }
+        ok = launch_rows8<1>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream, along);
+        if (ok) {
+            *err = hipGetLastError();
+            if (job) job->done = along.blocks > 0;
+            return true;
+        }
     }
     switch (r / 16) {
-        case 1: ok = launch_r<1>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream); break;
-        case 2: ok = launch_r<2>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream); break;
-        case 3: ok = launch_r<3>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream); break;
-        case 4: ok = launch_r<4>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream); break;
+        case 1: ok = launch_r<1>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream, along); break;
+        case 2: ok = launch_r<2>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream, along); break;
+        case 3: ok = launch_r<3>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream, along); break;
+        case 4: ok = launch_r<4>(X, t, (int)c, ldx, cs, Xq, delta, L_r_by_c, scale, T_hi, T_lo, stream, along); break;
     }
     *err = hipGetLastError();
+    if (job) job->done = ok && along.blocks > 0;
     return ok;
 }
 

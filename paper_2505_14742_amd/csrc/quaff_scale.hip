@@ -8,7 +8,7 @@
 //                           of the previous scales so that the in-place update below has no read/write race;
 //   momentum_what_kernel    every block reduces the partial maxima and evaluates Eq. 8 / Eq. 7 for all outlier
 //                           channels (a few hundred flops, cheaper than another launch); block 0 publishes s,
-//                           1/s and cmax; then each thread requantizes one output channel of what.
+//                           1/s and cmax; then the block requantizes sixteen output channels of what.
 // Maxima of non-negative floats are taken on their bit patterns (same order as unsigned integers), which is exact
 // and independent of the order in which they are combined.
 #include "quaff_scale_body.h"
@@ -44,8 +44,7 @@ hipError_t scale_update_static_scratch(float** ptr) {
     return hipSuccess;
 }
 
-constexpr int kWhatThreads = 128;   // output channels per workgroup of momentum_what_kernel
-constexpr int kPartBatch = 32;     // partial maxima loaded per thread before the first is used
+constexpr int kPartWords = 4096;    // partial maxima that a workgroup of momentum_what_kernel folds
 
 int scale_update_blocks(int64_t t) {
     int64_t b = (t + kRowsPerSlab - 1) / kRowsPerSlab;
@@ -57,17 +56,6 @@ colmax_outlier_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t ldx, co
                       uint32_t* __restrict__ part, const float* __restrict__ s_O, float* __restrict__ s_prev) {
     __shared__ uint32_t wred[16 * 256 / 64];
     colmax_outlier_body<256>(blockIdx.x, gridDim.x, wred, X, t, ldx, O, n, part, s_O, s_prev);
-}
-
-__global__ void __launch_bounds__(kWhatThreads)
-momentum_what_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad, const float* __restrict__ wmax_O,
-                     const float* __restrict__ s_prev, float gamma, const int32_t* __restrict__ O,
-                     float* __restrict__ s_O, float* __restrict__ colscale, float* __restrict__ cmax_out,
-                     const float* __restrict__ W_O, int64_t c_out, int8_t* __restrict__ what_int,
-                     float* __restrict__ delta_what) {
-    extern __shared__ float sm1[];                                  // [n] : s_k - 1, then [n] maxima
-    momentum_what_body<kWhatThreads, kPartBatch>(blockIdx.x, sm1, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O,
-                                                 colscale, cmax_out, W_O, c_out, what_int, delta_what);
 }
 
 // Dense variant of the column abs-max for outlier sets that touch most 64-byte segments of a row anyway (the
@@ -134,125 +122,16 @@ colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int
     }
 }
 
-// momentum_what_kernel for more than 64 outlier channels.  A workgroup owns 16 output channels; its NT / 16 thread
-// groups take four consecutive outliers of every NT / 4, NB times.  What bounds it is the chain of memory round trips, so both long
-// reads are in flight at once: this workgroup's part of W_O (kept in registers, one sweep instead of one for the maxima
-// and one for the codes) and the partial maxima, folded with one column of them per thread (coalesced, an LDS atomic per
-// thread instead of one per partial maximum).  The codes leave through LDS: sixteen output channels are contiguous in what_int.
-// HELD = false: more outliers than NB NT / 4, which a second sweep of W_O fetches again.
-// Measured at 2048 x 8192 -> 3072 with 819 outliers: 11.2 us; with 32 channels a workgroup, 128 slabs of partial maxima
-// folded with one LDS atomic each and W_O swept twice in chains of eight loads 34.7 us.
-constexpr int kWideCh = 16;
 template <int NT, int NB, bool HELD>
 __global__ void __launch_bounds__(NT)
-momentum_what_wide_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad,
-                          const float* __restrict__ wmax_O, const float* __restrict__ s_prev, float gamma,
-                          const int32_t* __restrict__ O, float* __restrict__ s_O, float* __restrict__ colscale,
-                          float* __restrict__ cmax_out, const float* __restrict__ W_O, int64_t c_out,
-                          int8_t* __restrict__ what_int, float* __restrict__ delta_what) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int GROUPS = NT / kWideCh, SPAN = 4 * GROUPS * NB;        // outliers per sweep
-    constexpr int ROW = SPAN + 16;                                  // LDS row of codes: 16 channels in 16 different banks
-    __shared__ __attribute__((aligned(16))) uint32_t codes[kWideCh * ROW / 4];
-    __shared__ float red[NT / 64][kWideCh];
-    extern __shared__ uint32_t smax[];                              // [n] : maxima, then s_k - 1
-    float* const sm1 = reinterpret_cast<float*>(smax);
-    const int jj = threadIdx.x % kWideCh, grp = threadIdx.x / kWideCh;
-    const int64_t j0 = (int64_t)blockIdx.x * kWideCh, j = j0 + jj;
-    const int64_t jc = j < c_out ? j : c_out - 1;
-    float w[NB][4];
-    auto first_k = [&](int base, int b) { return base + (b * GROUPS + grp) * 4; };
-    auto load = [&](int base) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = first_k(base, b) + u;
-                w[b][u] = W_O[(int64_t)(k < n ? k : n - 1) * c_out + jc];
-            }
-    };
-    if (HELD) load(0);
-    for (int k = threadIdx.x; k < n; k += NT) smax[k] = 0u;
-    __syncthreads();
-    // thread (share, k): column k of the slabs share, share + shares, ...
-    const int width = n < NT ? (n + 63) / 64 * 64 : NT, shares = NT / width;
-    const int share = threadIdx.x / width;
-    for (int k = threadIdx.x % width; k < n && share < shares; k += width) {
-        uint32_t m = 0u;
-        for (int s0 = share; s0 < nslab; s0 += 16 * shares) {
-            uint32_t v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int sl = s0 + u * shares;                     // (a repeated slab changes no maximum)
-                v[u] = part[(int64_t)(sl < nslab ? sl : s0) * n + k];
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) m = max(m, v[u]);
-        }
-        atomicMax(&smax[k], m);
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += NT) {
-        const float cmax = __uint_as_float(smax[k]);
-        const float s = momentum_scale(cmax, wmax_O[k], s_prev[k], gamma);
-        sm1[k] = __fsub_rn(s, 1.0f);
-        if (blockIdx.x == 0) {
-            s_O[k] = s;
-            colscale[O[k]] = __fdiv_rn(1.0f, s);
-            if (cmax_out) cmax_out[k] = cmax;
-        }
-    }
-    __syncthreads();
-    // max_k |what[k, j]|: this thread's share, the wavefront's four groups, the wavefronts
-    float m = 0.0f;
-    for (int base = 0; base < n; base += SPAN) {
-        if (!HELD) load(base);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = first_k(base, b) + u;
-                const float v = k < n ? __fmul_rn(sm1[k < n ? k : 0], w[b][u]) : 0.0f;
-                if (HELD) w[b][u] = v;
-                m = fmaxf(m, fabsf(v));
-            }
-        if (HELD) break;
-    }
-    m = fmaxf(m, __shfl_xor(m, 16, 64));
-    m = fmaxf(m, __shfl_xor(m, 32, 64));
-    if ((threadIdx.x & 63) < kWideCh) red[threadIdx.x >> 6][jj] = m;
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < NT / 64; ++v) m = fmaxf(m, red[v][jj]);
-    float d, c;
-    rtn_steps(m, d, c);
-    if (grp == 0 && j < c_out) delta_what[j] = d;
-    const int channels = c_out - j0 < kWideCh ? (int)(c_out - j0) : kWideCh;
-    for (int base = 0; base < n_pad; base += SPAN) {
-        if (!HELD) load(base);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int k0 = first_k(base, b);
-            uint32_t q = 0u;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = k0 + u;
-                float v = w[b][u];
-                if (!HELD) v = k < n ? __fmul_rn(sm1[k < n ? k : 0], v) : 0.0f;
-                q |= (uint32_t)(rtn_code(v, c) & 0xFF) << (8 * u);  // (zero beyond n: code 0)
-            }
-            codes[(jj * ROW + k0 - base) >> 2] = q;
-        }
-        __syncthreads();
-        const int span = n_pad - base < SPAN ? n_pad - base : SPAN, per_row = span / 16;   // 16-byte chunks
-        for (int e = threadIdx.x; e < channels * per_row; e += NT) {
-            const int row = e / per_row, at = (e - row * per_row) * 16;
-            *reinterpret_cast<u32x4*>(what_int + (j0 + row) * n_pad + base + at) =
-                *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(codes) + row * ROW + at);
-        }
-        if (HELD) break;
-        __syncthreads();
-    }
+momentum_what_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad,
+                     const float* __restrict__ wmax_O, const float* __restrict__ s_prev, float gamma,
+                     const int32_t* __restrict__ O, float* __restrict__ s_O, float* __restrict__ colscale,
+                     float* __restrict__ cmax_out, const float* __restrict__ W_O, int64_t c_out,
+                     int8_t* __restrict__ what_int, float* __restrict__ delta_what) {
+    extern __shared__ uint32_t smax[];                              // [n]
+    momentum_what_body<NT, NB, HELD>(blockIdx.x, smax, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O, colscale, cmax_out, W_O,
+                                     c_out, what_int, delta_what);
 }
 
 // Validity of an outlier index list (Sec. 3.3 fixes O before fine-tuning: one check per layer).  One workgroup scans
@@ -278,11 +157,10 @@ hipError_t launch_check_outliers(const int32_t* O, int32_t n, int64_t c_in, int3
     return hipGetLastError();
 }
 
-// as many slabs as the rows allow, but no more partial maxima than momentum_what_kernel reduces in one batch
+// as many slabs as the rows allow, but no more partial maxima than that
 int scale_update_gather_slabs(int64_t t, int32_t n) {
     int nslab = scale_update_blocks(t);
-    const int one_batch = kPartBatch * kWhatThreads / n;
-    const int cap = one_batch > 16 ? one_batch : 16;
+    const int cap = kPartWords / n > 16 ? kPartWords / n : 16;
     return nslab < cap ? nslab : cap;
 }
 
@@ -326,16 +204,12 @@ hipError_t launch_momentum(const uint32_t* part, int nslab, int n, int n_pad, co
                                   float* cmax_out, const float* W_O, int64_t c_out, int8_t* what_int,
                                   float* delta_what, hipStream_t stream) {
     ProfScope prof(K_MOMENTUM, stream);
-    if (n <= 64) {
-        hipLaunchKernelGGL(momentum_what_kernel, dim3((unsigned)((c_out + kWhatThreads - 1) / kWhatThreads)),
-                           dim3(kWhatThreads), 2 * n * sizeof(float), stream, part, nslab, n, n_pad, wmax_O, s_prev,
-                           gamma, O, s_O, colscale, cmax_out, W_O, c_out, what_int, delta_what);
-    } else {
+    {
         const size_t lds = (size_t)n * sizeof(uint32_t);
         const dim3 grid((unsigned)((c_out + kWideCh - 1) / kWideCh));
 #define QUAFF_WIDE(NT, NB, HELD)                                                                                      \
     {                                                                                                                 \
-        auto k = momentum_what_wide_kernel<NT, NB, HELD>;                                                             \
+        auto k = momentum_what_kernel<NT, NB, HELD>;                                                             \
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),                                          \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                     \
         if (e != hipSuccess) return e;                                                                                \
@@ -348,7 +222,8 @@ hipError_t launch_momentum(const uint32_t* part, int nslab, int n, int n_pad, co
         // outliers 7.8 / 7.6 and 13.0 / 10.2.  With more maxima to fold and every workgroup resident 1024 are faster: 2048 tokens,
         // 256 outliers, 4096 channels 9.5 / 9.8, 11008 channels 15.0 / 13.7.
         const bool resident = c_out <= 256 * kWideCh;
-        if (n <= 128) QUAFF_WIDE(512, 1, true)
+        if (n <= 64) QUAFF_WIDE(256, 1, true)
+        else if (n <= 128) QUAFF_WIDE(512, 1, true)
         else if (n <= 256 && !resident) QUAFF_WIDE(512, 2, true)
         else if (n <= 256) QUAFF_WIDE(1024, 1, true)
         else if (n <= 512) QUAFF_WIDE(1024, 2, true)

@@ -67,98 +67,127 @@ __device__ __forceinline__ float momentum_scale(float cmax, float wmax, float s_
     return __fadd_rn(__fmul_rn(gamma, s_prev), __fmul_rn(__fsub_rn(1.0f, gamma), beta));       // Eq. 7
 }
 
-// Work of workgroup `block` (NT threads, one output channel of what each): reduce the partial maxima, evaluate
-// Eq. 8 / Eq. 7 for all outlier channels (workgroup 0 publishes s, 1/s and cmax), requantize what.  sm1 is 2 n words
-// of LDS; PB partial maxima are loaded per thread before the first is used.
-template <int NT, int PB>
-__device__ __forceinline__ void momentum_what_body(int block, float* sm1, const uint32_t* __restrict__ part, int nslab,
-                                                   int n, int n_pad, const float* __restrict__ wmax_O,
-                                                   const float* __restrict__ s_prev, float gamma,
+// Work of workgroup `block` (NT threads): reduce the partial maxima, evaluate Eq. 8 / Eq. 7 for all outlier channels (workgroup 0
+// publishes s, 1/s and cmax), requantize what.  A workgroup owns 16 output channels; its NT / 16 thread
+// groups take four consecutive outliers of every NT / 4, NB times.  What bounds it is the chain of memory round trips, so both long
+// reads are in flight at once: this workgroup's part of W_O (kept in registers, one sweep instead of one for the maxima
+// and one for the codes) and the partial maxima, folded with one column of them per thread (coalesced, an LDS atomic per
+// thread instead of one per partial maximum).  The codes leave through LDS: sixteen output channels are contiguous in what_int.
+// HELD = false: more outliers than NB NT / 4, which a second sweep of W_O fetches again.
+// Measured at 2048 x 8192 -> 3072 with 819 outliers: 11.2 us, at 2048 x 3072 -> 3072 with 31 (256 threads) 4.0 and at 13824 channels
+// with 64 outliers 6.5; with a thread per channel, which walks the outliers in a chain, 8.2 and 13.4.  At 819 outliers with 32 channels a workgroup, 128 slabs of partial maxima
+// folded with one LDS atomic each and W_O swept twice in chains of eight loads 34.7 us.
+constexpr int kWideCh = 16;
+template <int NT, int NB, bool HELD>
+__device__ __forceinline__ void momentum_what_body(int block, uint32_t* smax /* LDS [n]: maxima, then s_k - 1 */,
+                                                   const uint32_t* __restrict__ part, int nslab, int n, int n_pad,
+                                                   const float* __restrict__ wmax_O, const float* __restrict__ s_prev, float gamma,
                                                    const int32_t* __restrict__ O, float* __restrict__ s_O,
                                                    float* __restrict__ colscale, float* __restrict__ cmax_out,
-                                                   const float* __restrict__ W_O, int64_t c_out,
-                                                   int8_t* __restrict__ what_int, float* __restrict__ delta_what) {
-    uint32_t* smax = reinterpret_cast<uint32_t*>(sm1 + n);         // [n]
+                                                   const float* __restrict__ W_O, int64_t c_out, int8_t* __restrict__ what_int,
+                                                   float* __restrict__ delta_what) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const int64_t j = (int64_t)block * NT + threadIdx.x;
+    constexpr int GROUPS = NT / kWideCh, SPAN = 4 * GROUPS * NB;        // outliers per sweep
+    constexpr int ROW = SPAN + 16;                                  // LDS row of codes: 16 channels in 16 different banks
+    __shared__ __attribute__((aligned(16))) uint32_t codes[kWideCh * ROW / 4];
+    __shared__ float red[NT / 64][kWideCh];
+    float* const sm1 = reinterpret_cast<float*>(smax);
+    const int jj = threadIdx.x % kWideCh, grp = threadIdx.x / kWideCh;
+    const int64_t j0 = (int64_t)block * kWideCh, j = j0 + jj;
     const int64_t jc = j < c_out ? j : c_out - 1;
-    const bool small = n <= 64;
-    // Every global load that does not depend on the reduction is issued first, so that the kernel pays about one
-    // memory round trip instead of three: this thread's column of W_O (n <= 64: kept in registers), its share of the
-    // partial maxima, and the per-outlier constants.
-    float w[64];
-    if (small) {
+    float w[NB][4];
+    auto first_k = [&](int base, int b) { return base + (b * GROUPS + grp) * 4; };
+    auto load = [&](int base) {
 #pragma unroll
-        for (int k = 0; k < 64; ++k) w[k] = W_O[(int64_t)(k < n ? k : n - 1) * c_out + jc];
-    }
-    const int kk = threadIdx.x < n ? threadIdx.x : n - 1;          // outlier handled by this thread (first pass)
-    const float wmax0 = wmax_O[kk], sprev0 = s_prev[kk];
-    const int o0 = O[kk];
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = first_k(base, b) + u;
+                w[b][u] = W_O[(int64_t)(k < n ? k : n - 1) * c_out + jc];
+            }
+    };
+    if (HELD) load(0);
     for (int k = threadIdx.x; k < n; k += NT) smax[k] = 0u;
     __syncthreads();
-    const int total = nslab * n;
-    for (int e0 = threadIdx.x; e0 < total; e0 += PB * NT) {   // one round trip for up to 4096 partials
-        uint32_t v[PB];
+    // thread (share, k): column k of the slabs share, share + shares, ...
+    const int width = n < NT ? (n + 63) / 64 * 64 : NT, shares = NT / width;
+    const int share = threadIdx.x / width;
+    for (int k = threadIdx.x % width; k < n && share < shares; k += width) {
+        uint32_t m = 0u;
+        for (int s0 = share; s0 < nslab; s0 += 16 * shares) {
+            uint32_t v[16];
 #pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            int e = e0 + u * NT;
-            v[u] = part[e < total ? e : total - 1];
-        }
+            for (int u = 0; u < 16; ++u) {
+                const int sl = s0 + u * shares;                     // (a repeated slab changes no maximum)
+                v[u] = part[(int64_t)(sl < nslab ? sl : s0) * n + k];
+            }
 #pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            int e = e0 + u * NT;
-            if (e < total) atomicMax(&smax[e % n], v[u]);
+            for (int u = 0; u < 16; ++u) m = max(m, v[u]);
         }
+        atomicMax(&smax[k], m);
     }
     __syncthreads();
     for (int k = threadIdx.x; k < n; k += NT) {
-        const bool first = k == (int)threadIdx.x;
-        float cmax = __uint_as_float(smax[k]);
-        float s = momentum_scale(cmax, first ? wmax0 : wmax_O[k], first ? sprev0 : s_prev[k], gamma);
+        const float cmax = __uint_as_float(smax[k]);
+        const float s = momentum_scale(cmax, wmax_O[k], s_prev[k], gamma);
         sm1[k] = __fsub_rn(s, 1.0f);
         if (block == 0) {
             s_O[k] = s;
-            colscale[first ? o0 : O[k]] = __fdiv_rn(1.0f, s);
+            colscale[O[k]] = __fdiv_rn(1.0f, s);
             if (cmax_out) cmax_out[k] = cmax;
         }
     }
     __syncthreads();
-    if (j >= c_out) return;
-    // what[k, j] for this output channel (Eq. 5), quantized per output channel (Eq. 1)
-    u32x4* dst = reinterpret_cast<u32x4*>(what_int + j * n_pad);
-    float d, c;
-    if (small) {
-        float m = 0.0f;
+    // max_k |what[k, j]|: this thread's share, the wavefront's four groups, the wavefronts
+    float m = 0.0f;
+    for (int base = 0; base < n; base += SPAN) {
+        if (!HELD) load(base);
 #pragma unroll
-        for (int k = 0; k < 64; ++k) {
-            w[k] = k < n ? __fmul_rn(sm1[k < n ? k : n - 1], w[k]) : 0.0f;
-            m = fmaxf(m, fabsf(w[k]));
-        }
-        rtn_steps(m, d, c);
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int k16 = 0; k16 < 64; k16 += 16) {
-            u32x4 q4 = (u32x4){0, 0, 0, 0};
-#pragma unroll
-            for (int u = 0; u < 16; ++u) q4[u >> 2] |= (uint32_t)(rtn_code(w[k16 + u], c) & 0xFF) << (8 * (u & 3));
-            dst[k16 >> 4] = q4;
-        }
-    } else {
-        float m = 0.0f;
-        for (int k = 0; k < n; ++k) m = fmaxf(m, fabsf(__fmul_rn(sm1[k], W_O[(int64_t)k * c_out + j])));
-        rtn_steps(m, d, c);
-        for (int k16 = 0; k16 < n_pad; k16 += 16) {
-            u32x4 q4 = (u32x4){0, 0, 0, 0};
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                int k = k16 + u;
-                int q = 0;
-                if (k < n) q = rtn_code(__fmul_rn(sm1[k], W_O[(int64_t)k * c_out + j]), c);
-                q4[u >> 2] |= (uint32_t)(q & 0xFF) << (8 * (u & 3));
+            for (int u = 0; u < 4; ++u) {
+                const int k = first_k(base, b) + u;
+                const float v = k < n ? __fmul_rn(sm1[k < n ? k : 0], w[b][u]) : 0.0f;
+                if (HELD) w[b][u] = v;
+                m = fmaxf(m, fabsf(v));
             }
-            dst[k16 >> 4] = q4;
-        }
+        if (HELD) break;
     }
-    delta_what[j] = d;
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if ((threadIdx.x & 63) < kWideCh) red[threadIdx.x >> 6][jj] = m;
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NT / 64; ++v) m = fmaxf(m, red[v][jj]);
+    float d, c;
+    rtn_steps(m, d, c);
+    if (grp == 0 && j < c_out) delta_what[j] = d;
+    const int channels = c_out - j0 < kWideCh ? (int)(c_out - j0) : kWideCh;
+    for (int base = 0; base < n_pad; base += SPAN) {
+        if (!HELD) load(base);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int k0 = first_k(base, b);
+            uint32_t q = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + u;
+                float v = w[b][u];
+                if (!HELD) v = k < n ? __fmul_rn(sm1[k < n ? k : 0], v) : 0.0f;
+                q |= (uint32_t)(rtn_code(v, c) & 0xFF) << (8 * u);  // (zero beyond n: code 0)
+            }
+            codes[(jj * ROW + k0 - base) >> 2] = q;
+        }
+        __syncthreads();
+        const int span = n_pad - base < SPAN ? n_pad - base : SPAN, per_row = span / 16;   // 16-byte chunks
+        for (int e = threadIdx.x; e < channels * per_row; e += NT) {
+            const int row = e / per_row, at = (e - row * per_row) * 16;
+            *reinterpret_cast<u32x4*>(what_int + (j0 + row) * n_pad + base + at) =
+                *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(codes) + row * ROW + at);
+        }
+        if (HELD) break;
+        __syncthreads();
+    }
 }
 
 }  // namespace quaff

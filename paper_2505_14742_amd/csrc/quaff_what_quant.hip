@@ -9,8 +9,6 @@
 
 namespace quaff {
 
-constexpr int kWqBatch = 16;   // partial maxima per thread and round trip: 256 x 16 = 4096 cover the usual slab counts
-
 template <int TPR, int NV>
 __global__ void __launch_bounds__(256)
 what_quant_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad, const float* __restrict__ wmax_O,
@@ -21,7 +19,7 @@ what_quant_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad
                   float* __restrict__ delta, int8_t* __restrict__ xq_O) {
     extern __shared__ float dyn[];
     if ((int)blockIdx.x < what_blocks) {
-        momentum_what_body<256, kWqBatch>(blockIdx.x, dyn, part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O, colscale,
+        momentum_what_body<256, 1, true>(blockIdx.x, reinterpret_cast<uint32_t*>(dyn), part, nslab, n, n_pad, wmax_O, s_prev, gamma, O, s_O, colscale,
                                           cmax_out, W_O, c_out, what_int, delta_what);
         return;
     }
@@ -34,22 +32,20 @@ what_quant_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad
         for (int i = threadIdx.x * 4; i < c; i += 1024)
             *reinterpret_cast<f32x4_*>(dyn + i) = *reinterpret_cast<const f32x4_*>(colscale + i);
         __syncthreads();
-        const int total = nslab * n;
-        for (int e0 = threadIdx.x; e0 < total; e0 += kWqBatch * 256) {
-            uint32_t v[kWqBatch];
+        // wavefront w: columns of the slabs w, w + 4, ... (n <= 64)
+        const int k = threadIdx.x & 63;
+        uint32_t m = 0u;
+        if (k < n)
+            for (int s0 = threadIdx.x >> 6; s0 < nslab; s0 += 32) {
+                uint32_t v[8];
 #pragma unroll
-            for (int u = 0; u < kWqBatch; ++u) {
-                int e = e0 + u * 256;
-                v[u] = part[e < total ? e : total - 1];
-            }
+                for (int u = 0; u < 8; ++u) v[u] = part[(s0 + 4 * u < nslab ? s0 + 4 * u : s0) * n + k];
 #pragma unroll
-            for (int u = 0; u < kWqBatch; ++u) {
-                int e = e0 + u * 256;
-                if (e < total) atomicMax(&smax[e % n], v[u]);
+                for (int u = 0; u < 8; ++u) m = max(m, v[u]);
             }
-        }
+        if (k < n) atomicMax(&smax[k], m);
         __syncthreads();
-        for (int k = threadIdx.x; k < n; k += 256) {
+        if (threadIdx.x < n) {
             float s = momentum_scale(__uint_as_float(smax[k]), wmax_O[k], s_prev[k], gamma);
             dyn[O[k]] = __fdiv_rn(1.0f, s);
         }
@@ -81,7 +77,7 @@ bool launch_what_quant(const uint32_t* part, int nslab, int32_t n, const float* 
     if (n < 1 || n > 64 || vec > 256 * 8 || lds > 64 * 1024) return false;
     ProfScope prof(K_WHAT_QUANT, stream);
     const int n_pad = (n + kPadK - 1) / kPadK * kPadK;
-    const int what_blocks = (int)((c_out + 255) / 256);
+    const int what_blocks = (int)((c_out + kWideCh - 1) / kWideCh);
 #define QUAFF_WQ(TPR, NV)                                                                                              \
     launch_wq<TPR, NV>(dim3((unsigned)(what_blocks + (t + 256 / TPR - 1) / (256 / TPR))), lds, stream, part, nslab, n,  \
                        n_pad, wmax_O, s_prev, gamma, O, s_O, colscale, cmax_out, W_O, c_out, what_int, delta_what,      \
