@@ -18,6 +18,15 @@ quant_rows_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx,
     quant_rows_body<256, TPR, NV>(blockIdx.x, X, t, c, ldx, cs, O, n, n_pad, Xq, delta, xq_O);
 }
 
+// The workgroup's NT threads share ROWS rows.
+template <int NT, int ROWS, int NV, int KO>
+__global__ void __launch_bounds__(NT)
+quant_rows_shared_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const float* __restrict__ cs,
+                         const int32_t* __restrict__ O, int n, int n_pad, int8_t* __restrict__ Xq, float* __restrict__ delta,
+                         int8_t* __restrict__ xq_O) {
+    quant_rows_shared_body<NT, ROWS, NV, KO>(blockIdx.x, X, t, c, ldx, cs, Xq, delta, O, n, n_pad, xq_O);
+}
+
 // Fallback for very long rows: one workgroup per row, two passes over the row.
 __global__ void __launch_bounds__(256)
 quant_rows_twopass_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const float* __restrict__ cs,
@@ -57,6 +66,13 @@ static void launch_rows(const uint16_t* X, int64_t t, int c, int64_t ldx, const 
                        c, ldx, cs, O, n, n_pad, Xq, delta, xq_O);
 }
 
+template <int NT, int ROWS, int NV>
+static void launch_shared(const uint16_t* X, int64_t t, int c, int64_t ldx, const float* cs, const int32_t* O, int n,
+                          int n_pad, int8_t* Xq, float* delta, int8_t* xq_O, hipStream_t stream) {
+    auto k = !xq_O ? quant_rows_shared_kernel<NT, ROWS, NV, 0> : quant_rows_shared_kernel<NT, ROWS, NV, 1>;
+    hipLaunchKernelGGL(k, dim3((unsigned)((t + ROWS - 1) / ROWS)), dim3(NT), 0, stream, X, t, c, ldx, cs, O, n, n_pad, Xq, delta, xq_O);
+}
+
 hipError_t launch_quant_act(const uint16_t* X, int64_t t, int64_t c64, int64_t ldx, const float* cs, const int32_t* O,
                             int32_t n, int8_t* Xq, float* delta, int8_t* xq_O, hipStream_t stream) {
     ProfScope prof(K_QUANT, stream);
@@ -64,6 +80,21 @@ hipError_t launch_quant_act(const uint16_t* X, int64_t t, int64_t c64, int64_t l
     const int n_pad = (n + kPadK - 1) / kPadK * kPadK;
     const int vec = (c + 7) / 8;   // 16-byte vectors per row
 #define QUAFF_ROWS(TPR, NV) launch_rows<TPR, NV>(X, t, c, ldx, cs, O, n, n_pad, Xq, delta, xq_O, stream)
+#define QUAFF_SHARED(NT, ROWS, NV) launch_shared<NT, ROWS, NV>(X, t, c, ldx, cs, O, n, n_pad, Xq, delta, xq_O, stream)
+    // Four rows share the column scales in registers where there are enough rows to fill the chip so, and few outliers, whose
+    // values every thread then gathers for all of them.  Us, own rows / shared: no outliers 2048 x 16384 27.9 / 17.5, 4096 x 11008 35.0 /
+    // 28.5, 2048 x 6144 9.5 / 9.1, 1024 x 6144 5.6 / 6.5, 2048 x 3072 6.4 / 6.5; 40 outliers 2048 x 16384 29.8 / 22.1, 4096 x 8192 28.2 / 23.1,
+    // 2048 x 8192 13.5 / 16.1, 8192 x 4096 29.9 / 29.9; 819 outliers 2048 x 8192 16.9 / 20.7.  From 3080 to 4096 columns, eight vectors to a lane
+    // of a wavefront that has a row to itself, at any number of rows: 512 x 4096 6.3 / 5.0, 256 x 4096 with 40 outliers 6.7 / 5.9.
+    const bool shared = xq_O ? n <= 128 && (vec > 1024 ? t >= 2048 : vec > 512 ? t >= 4096 : t < 8192) : vec <= 512 || t >= 2048;
+    if (vec > 64 * 6 && vec <= 256 * 8 && shared) {
+        if (vec <= 512) QUAFF_SHARED(256, 4, 2);
+        else if (vec <= 768) QUAFF_SHARED(256, 4, 3);
+        else if (vec <= 1024) QUAFF_SHARED(256, 4, 4);
+        else if (vec <= 1536) QUAFF_SHARED(512, 4, 3);
+        else QUAFF_SHARED(512, 4, 4);
+        return hipGetLastError();
+    }
     if (vec <= 64 * 1) QUAFF_ROWS(64, 1);
     else if (vec <= 64 * 2) QUAFF_ROWS(64, 2);
     else if (vec <= 64 * 4) QUAFF_ROWS(64, 4);
@@ -77,6 +108,7 @@ hipError_t launch_quant_act(const uint16_t* X, int64_t t, int64_t c64, int64_t l
         hipLaunchKernelGGL(quant_rows_twopass_kernel, dim3((unsigned)t), dim3(256), 0, stream, X, t, c, ldx, cs, O, n,
                            n_pad, Xq, delta, xq_O);
 #undef QUAFF_ROWS
+#undef QUAFF_SHARED
     return hipGetLastError();
 }
 

@@ -160,14 +160,15 @@ __device__ __forceinline__ void quant_rows_body(int block, const uint16_t* __res
     }
 }
 
-// The same for long rows without outlier codes: the workgroup's NT threads share ROWS rows, every thread holding the same
+// The same with the column scales in registers: the workgroup's NT threads share ROWS rows, every thread holding the same
 // NV x 8 columns of all of them, so that a column scale is fetched once per workgroup and stays in registers.  (With a
 // row to itself a quarter of the workgroup fetches each scale twice per element, maximum pass and code pass: four times the
-// traffic of dY through the L1.  cs may be null.)
-template <int NT, int ROWS, int NV>
+// traffic of dY through the L1.  cs may be null.)  KO NT outlier columns are gathered while the rows travel, more behind them.
+template <int NT, int ROWS, int NV, int KO = 0>
 __device__ __forceinline__ void quant_rows_shared_body(int block, const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx,
                                                        const float* __restrict__ cs, int8_t* __restrict__ Xq,
-                                                       float* __restrict__ delta) {
+                                                       float* __restrict__ delta, const int32_t* __restrict__ O = nullptr, int n = 0,
+                                                       int n_pad = 0, int8_t* __restrict__ xq_O = nullptr) {
     __shared__ float red[NT / 64][ROWS];
     __shared__ float steps[ROWS];
     const int64_t row0 = (int64_t)block * ROWS;
@@ -187,6 +188,23 @@ __device__ __forceinline__ void quant_rows_shared_body(int block, const uint16_t
         if (cs && col < c) {
             s[i][0] = *reinterpret_cast<const f32x4*>(cs + col);
             s[i][1] = *reinterpret_cast<const f32x4*>(cs + col + 4);
+        }
+    }
+    float xo[KO > 0 ? KO : 1][ROWS];                // scaled values of outlier tid + j NT
+    auto outlier = [&](int k, int r) {
+        const int col = O[k];
+        const float x = bf16_bits_to_f32(X[(row0 + r) * ldx + col]);
+        return cs ? __fmul_rn(x, cs[col]) : x;
+    };
+    if constexpr (KO > 0) {
+#pragma unroll
+        for (int j = 0; j < KO; ++j) {
+            const int k = j * NT + threadIdx.x;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                xo[j][r] = 0.0f;
+                if (k < n && r < live) xo[j][r] = outlier(k, r);
+            }
         }
     }
     auto scaled = [&](int r, int i, float (&v)[8]) {
@@ -237,6 +255,17 @@ __device__ __forceinline__ void quant_rows_shared_body(int block, const uint16_t
                 float v[8];
                 scaled(r, i, v);
                 *reinterpret_cast<u32x2*>(Xq + (row0 + r) * (int64_t)c + col) = pack_codes(v, cc);
+            }
+        }
+        if constexpr (KO > 0) {
+            if (r < live) {
+                int8_t* const dst = xq_O + (row0 + r) * n_pad;
+#pragma unroll
+                for (int j = 0; j < KO; ++j) {
+                    const int k = j * NT + threadIdx.x;
+                    if (k < n_pad) dst[k] = (int8_t)rtn_code(xo[j][r], cc);     // (0 beyond n: code 0)
+                }
+                for (int k = KO * NT + threadIdx.x; k < n_pad; k += NT) dst[k] = (int8_t)(k < n ? rtn_code(outlier(k, r), cc) : 0);
             }
         }
     }

@@ -16,8 +16,8 @@ namespace quaff {
 // rank 16 55.7 / 51.3, 1003 x 1040 -> 2064 at rank 32 53.5 / 51.3.
 struct Along { const uint16_t* X; int64_t ldx; int c; const uint16_t* L; uint16_t* T_hi; uint16_t* T_lo; int row_blocks, blocks; };
 
-// rows per quantizing workgroup: TPR threads take one, or all of them share eight (TPR = 1024)
-constexpr int quant_rows_per_block(int TPR) { return TPR <= 256 ? 64 * kLoraWaves / TPR : 8; }
+// rows per quantizing workgroup: TPR threads take one, or all of them share eight (TPR = 1024) or four (2048)
+constexpr int quant_rows_per_block(int TPR) { return TPR <= 256 ? 64 * kLoraWaves / TPR : TPR == 1024 ? 8 : 4; }
 
 template <int R16, int TPR, int NV>
 __global__ void __launch_bounds__(64 * kLoraWaves)
@@ -324,10 +324,11 @@ static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const flo
     // are level or faster (rank 32, 4096 x 11008 56.7 / 60.3).
     else if (R16 >= 3 && t > 2048 && vec <= 1024) { if constexpr (R16 >= 3) QUAFF_QL(1024, 1); }
     else if (R16 >= 3 && t > 2048 && vec <= 1024 * 2) { if constexpr (R16 >= 3) QUAFF_QL(1024, 2); }
-    else if (vec <= 256 * 3) QUAFF_QL(256, 3);
-    else if (vec <= 256 * 4) QUAFF_QL(256, 4);
-    else if (vec <= 256 * 6) QUAFF_QL(256, 6);
-    else if (vec <= 256 * 8) QUAFF_QL(256, 8);
+    // Otherwise four rows share the scales, two such workgroups to a unit at ranks 16 and 32.  Input gradient into 256 channels, us, a
+    // quarter of the workgroup for each row / so: rank 16, 2048 x 16384 71.6 / 67.2, 2048 x 9216 42.2 / 40.0, 4096 x 11008 80.6 / 75.3; rank 32,
+    // 4096 x 11008 83.6 / 79.3, 2048 x 6144 33.1 / 33.2.
+    else if (vec <= 1024) QUAFF_QL(2048, 1);
+    else if (vec <= 1024 * 2) QUAFF_QL(2048, 2);
     else return false;
 #undef QUAFF_QL
     return true;
