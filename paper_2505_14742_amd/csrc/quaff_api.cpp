@@ -581,7 +581,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     // One launch prepares everything the product needs where it can (a few thousand tokens, at most 64 outlier
     // channels, rank 0 or 16); two combined launches cover the other usual cases; everything else is the three calls
     // one after the other.
-    const size_t words_bytes = quaff::fwd_prep_covers(t, c_in, n_outlier, lora_rank) ? quaff::fwd_prep_words_bytes(t, c_in, c_out, n_outlier) : 0;
+    const size_t words_bytes = quaff::fwd_prep_covers(t, c_in, n_outlier, lora_rank) ? quaff::fwd_prep_words_bytes(t, c_in, c_out, n_outlier, lora_rank) : 0;
     const bool fused = words_bytes > 0 && workspace_bytes >= prep_at + quaff::kFwdPrepWordsAt + words_bytes;
     const bool combined = !fused && n_outlier > 0 && n_outlier <= 1024 && (int64_t)n_outlier * 64 < c_in && lora_rank > 0;
     if (!fused && !combined) {
@@ -618,7 +618,7 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
         if (st != QUAFF_OK) return st;
         if (lora_rank > 0) { g.T_hi = t_hi; g.T_lo = t_lo; g.L = lt; g.r = lora_rank; }
         g.C = Y; g.ldc = ldy;
-        g.clear = base + prep_at + quaff::kFwdPrepWordsAt; g.clear_bytes = (int32_t)words_bytes;
+        g.clear = base + prep_at + quaff::kFwdPrepWordsAt; g.clear_bytes = quaff::fwd_prep_direct(t, c_out, n_outlier, lora_rank) ? 0 : (int32_t)words_bytes;
         set_small_split(g, workspace, split_at, split_fwd(t, c_in, c_out, lora_rank), workspace_bytes);
         return hip_status(quaff::launch_gemm(g, false, s));
     }

@@ -58,7 +58,9 @@ struct FwdPrepArgs {
 
 
 // NSTEP: 64-column steps a wavefront holds (two slices of the down-projection's summation order)
-template <int NSTEP, bool HAS_LORA>
+// DIRECT: few values in the outlier columns; every workgroup gathers them all instead of waiting for the others' maxima, and the last to
+// have read the old scales publishes the new ones at its end (see quaff_fwd_few.hip).
+template <int NSTEP, bool HAS_LORA, bool DIRECT>
 __global__ void __launch_bounds__(kPrepThreads)
 fwd_prep_kernel(const FwdPrepArgs a) {
     static_assert(kLoraParts == 2 && kLoraWaves == 16, "two parts of eight wavefronts each");
@@ -73,7 +75,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
     float (*red)[32][4] = reinterpret_cast<float (*)[32][4]>(stage + kLoraWaves * 4 * kPrepLtBlock);
     __shared__ float rmax[kLoraWaves][kPrepRows];
     __shared__ uint32_t smax[64];                  // column maxima over all rows
-    __shared__ float sm1[64], rinv[64], sprev[64], wmx[64];
+    __shared__ float sm1[64], rinv[64], sprev[64], wmx[64], snew[DIRECT ? 64 : 1];
     __shared__ int ocol[64];
     __shared__ float rowc[kPrepRows];
     __shared__ uint32_t wmaxbits[kWhatChunk];
@@ -83,7 +85,10 @@ fwd_prep_kernel(const FwdPrepArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
     const int blk = blockIdx.x, G = a.groups, n = a.n, c = a.c;
-    const int64_t row0 = (int64_t)blk * kPrepRows;
+    // (DIRECT: the down-projection has row owners of its own, so that neither result waits for the other's work)
+    const int owners = (int)((a.t + kPrepRows - 1) / kPrepRows);
+    const bool quantizes = !(DIRECT && HAS_LORA) || blk < owners, projects = HAS_LORA && (!DIRECT || blk >= owners);
+    const int64_t row0 = (int64_t)(quantizes ? blk : blk - owners) * kPrepRows;
     const int64_t row = row0 + (m & 7);
     const bool live = row < a.t;
     const bool has_rows = row0 < a.t;              // uniform over the workgroup
@@ -110,6 +115,18 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         xa[u] = (u32x4){0, 0, 0, 0};
         if (live && k < slice_end(u) && (u % SPS) * 64 < kw) xa[u] = *reinterpret_cast<const u32x4*>(xrow + k);
     }
+    // DIRECT: thread (k, slot) takes rows slot, slot + slots, ... of outlier k; slots = 1024 over the power of two that n fits
+    uint32_t all_max = 0;
+    int slots_log2 = 0, dk = 0;
+    if constexpr (DIRECT) {
+        slots_log2 = n > 32 ? 4 : n > 16 ? 5 : n > 8 ? 6 : n > 4 ? 7 : n > 2 ? 8 : n > 1 ? 9 : 10;
+        dk = tid >> slots_log2;
+        if (dk < n) {
+            const uint16_t* const col = a.X + a.O[dk];
+            for (int r = tid & ((1 << slots_log2) - 1); r < (int)a.t; r += 1 << slots_log2)
+                all_max = max(all_max, (uint32_t)col[(int64_t)r * a.ldx] & 0x7FFFu);
+        }
+    }
     // Every global load that depends on nothing computed here is issued now, so that the kernel pays for few memory
     // round trips one after the other: the slices of A of the first AB steps, this thread's element of the transposed
     // copy of B, and its share of the first chunk of W_O.
@@ -130,7 +147,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
             }
         }
     };
-    if (HAS_LORA && has_rows) load_a(0);
+    if (projects && has_rows) load_a(0);
     const int64_t bt_total = HAS_LORA ? 16 * a.c_out : 0;     // Bt [c_out x 16] <- B [16 x c_out]
     const int64_t bt_e0 = (int64_t)blk * kPrepThreads + tid;
     uint16_t bt_first = 0;
@@ -163,7 +180,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
     // Device-scope atomic loads and stores go past the per-XCD L2s: no cache write-back or invalidation is needed to
     // hand the words from one workgroup to another.
     const uint64_t epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t mark = prep_mark(epoch + 1);
+    const uint64_t mark = DIRECT ? (epoch + 1) * 0x9E3779B97F4A7C15ull | 1ull : prep_mark(epoch + 1);
     // ---- maxima of this workgroup's rows on the outlier columns: lanes 8 k .. 8 k + 7 hold the eight rows of column k
     uint16_t xo_raw = 0;     // X[row0 + tid % 8, O[tid / 8]]: also what the compact outlier codes are made from
     {
@@ -173,17 +190,27 @@ fwd_prep_kernel(const FwdPrepArgs a) {
             xo_raw = a.X[(row0 + rr) * a.ldx + a.O[k]];
             v = ((uint32_t)xo_raw & 0x7FFFu) << 16;
         }
-        v = max(v, (uint32_t)__shfl_xor((int)v, 1, 64));
-        v = max(v, (uint32_t)__shfl_xor((int)v, 2, 64));
-        v = max(v, (uint32_t)__shfl_xor((int)v, 4, 64));
+        if constexpr (!DIRECT) {
+            v = max(v, (uint32_t)__shfl_xor((int)v, 1, 64));
+            v = max(v, (uint32_t)__shfl_xor((int)v, 2, 64));
+            v = max(v, (uint32_t)__shfl_xor((int)v, 4, 64));
+        }
         // The previous scales must have been READ (not just requested) by this workgroup before its maxima become
         // visible, because whoever sees all maxima may overwrite them: the barrier follows the LDS writes of the
         // loaded values.  (The epoch feeds the stored word itself.)
-        const uint32_t odd = (uint32_t)__shfl_down((int)v, 8, 64);    // column k + 1 (zero beyond n)
-        const uint64_t word = mark | (uint64_t)(odd >> 16) << kMagBits | (v >> 16);
-        __syncthreads();
-        if (k < n && (tid & 15) == 0)
-            __hip_atomic_store(&a.part[(int64_t)(k >> 1) * G + blk], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (DIRECT) {
+            if (tid < 64) smax[tid] = 0u;
+            __syncthreads();
+            if (tid == 0) __hip_atomic_store(&a.part[blk], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int off = 1; off < 64 && off < 1 << slots_log2; off *= 2) all_max = max(all_max, (uint32_t)__shfl_xor((int)all_max, off, 64));
+            if (dk < n && (lane & ((1 << slots_log2) - 1)) == 0) atomicMax(&smax[dk], all_max << 16);
+        } else {
+            const uint32_t odd = (uint32_t)__shfl_down((int)v, 8, 64);    // column k + 1 (zero beyond n)
+            const uint64_t word = mark | (uint64_t)(odd >> 16) << kMagBits | (v >> 16);
+            __syncthreads();
+            if (k < n && (tid & 15) == 0)
+                __hip_atomic_store(&a.part[(int64_t)(k >> 1) * G + blk], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 
     // ---- work that needs no other workgroup: transposed copy of B, copy of the column scales, down-projection
@@ -197,7 +224,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         const int i = (tid + v * kPrepThreads) * 4;
         if (i < c) *reinterpret_cast<f32x4*>(cs_copy + i) = cs_first[v];
     }
-    if (HAS_LORA && has_rows) {
+    if (projects && has_rows) {
         f32x4 acc[2];
         acc[0] = acc[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -248,7 +275,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         }
     }
     __syncthreads();
-    if (HAS_LORA && has_rows) {
+    if (projects && has_rows) {
         // fixed-order sums over the sixteen slices of each part
         for (int e = tid; e < kLoraParts * 32 * 4; e += kPrepThreads) {
             const int v = e & 3, ln = (e >> 2) & 31, p = e >> 7;
@@ -267,6 +294,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         }
     }
 
+    if constexpr (!DIRECT) {
     // ---- bounded wait for the other workgroups' maxima: wavefront w reads pairs w and w + 16 of columns (G contiguous words
     // each) and reduces them with wavefront shuffles; the pass is repeated until every word carries this launch's mark
     // (never given up before the second pass: only loads issued after this workgroup's own words have reached memory, which the
@@ -345,6 +373,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         }
     }
     __syncthreads();
+    }
     if (tid < n) {
         const float cmax = __uint_as_float(smax[tid]);
         const float s = momentum_scale(cmax, wmx[tid], sprev[tid], a.gamma);
@@ -352,16 +381,18 @@ fwd_prep_kernel(const FwdPrepArgs a) {
         sm1[tid] = __fsub_rn(s, 1.0f);
         rinv[tid] = ri;
         cs_copy[ocol[tid]] = ri;
-        if (flag_ok) {             // every workgroup has written its maxima, so it has read the previous scales
+        if constexpr (DIRECT) snew[tid] = s;
+        if (!DIRECT && flag_ok) {             // every workgroup has written its maxima, so it has read the previous scales
             a.s_O[tid] = s;
             a.colscale[ocol[tid]] = ri;
             if (a.cmax_out) a.cmax_out[tid] = cmax;
         }
     }
-    if (tid == 0 && flag_ok) __hip_atomic_store(a.epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!DIRECT && tid == 0 && flag_ok) __hip_atomic_store(a.epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
 
     // ---- per-token quantization of this workgroup's rows, from the registers
+    if (quantizes) {               // uniform over the workgroup
     const lds_float* csl = (const lds_float*)cs_copy;
     constexpr bool KEEP = NSTEP <= 4;              // the scaled fp32 values stay in registers for the code pass
     float xs[KEEP ? NSTEP : 1][8];
@@ -444,6 +475,7 @@ fwd_prep_kernel(const FwdPrepArgs a) {
             a.xq_O[(row0 + rr) * a.n_pad + k] = (int8_t)q;
         }
     }
+    }
 
     // ---- this workgroup's share of what = (s_O - 1) W_O, requantized per output channel (Eq. 5, Eq. 1)
     for (int64_t jc = j0; jc < j1; jc += kWhatChunk) {
@@ -482,6 +514,32 @@ fwd_prep_kernel(const FwdPrepArgs a) {
                 *reinterpret_cast<const u32x4*>(&wcodes[tid >> 2][(tid & 3) * 16]);
         __syncthreads();
     }
+    if constexpr (DIRECT) {
+        if (wave == 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this workgroup's mark has reached memory; are all there?
+            bool all = true;
+            for (int i = lane; i < G; i += 64)
+                all = all && __hip_atomic_load(&a.part[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+            if (__all(all)) {
+                if (lane < n) {
+                    a.s_O[lane] = snew[lane];
+                    a.colscale[ocol[lane]] = rinv[lane];
+                    if (a.cmax_out) a.cmax_out[lane] = __uint_as_float(smax[lane]);
+                }
+                if (lane == 0) __hip_atomic_store(a.epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int i = lane; i < G; i += 64) __hip_atomic_store(&a.part[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+}
+
+// Few values in the outlier columns: gathering them costs every workgroup a line of X for each, waiting a chain of four trips to memory
+// (words out, everybody's words in) behind the last to arrive; and the down-projection gets row owners of its own.  Of 20886 random
+// forward steps of up to 512 rows and 4096 values, those of rank 16 take 0.87 of the time up to 2048 values (0.79 beyond 4096 columns: 8 x 8192
+// -> 3072 26.1 -> 20.1 us, 16 x 3072 -> 3072 16.9 -> 13.9, 16 x 3072 -> 9216 21.5 -> 20.4) and 0.92 beyond; without an adapter 0.92 up to
+// 2048 channels and 0.87 from 12288 on, level between (16 x 1536 -> 8320 15.5 / 18.5, 32 x 1024 -> 4096 0.97), where it is left out.
+bool fwd_prep_direct(int64_t t, int64_t c_out, int32_t n, int32_t r) {
+    return t <= 512 && t * n <= 2048 && (r > 0 || c_out < 2048 || c_out >= 12288);
 }
 
 int fwd_prep_groups(int64_t t) { return (int)((t + kPrepRows - 1) / kPrepRows); }
@@ -503,7 +561,7 @@ int fwd_prep_groups(int64_t t) { return (int)((t + kPrepRows - 1) / kPrepRows); 
 //   from 1024 to 1535 columns also with two rounds for each of 64 owners or more: 512 x 1024 -> 5120 27.3 / 28.7, 640 x 1152 -> 8192
 //   28.5 / 29.6; at 896 and at 1536 columns filled up takes 0.97 to 1.03 of the time.
 // By this rule 4 of the 1018 are more than 1.5 % slower than owners alone, at most 2.5 % (384 x 1152 -> 5120).
-static void fwd_prep_split(int64_t t, int64_t c_in, int64_t c_out, int* groups, int* what_first) {
+static void fwd_prep_split(int64_t t, int64_t c_in, int64_t c_out, bool direct_lora, int* groups, int* what_first) {
     const int rows = fwd_prep_groups(t);
     const int64_t rounds = (c_out + kWhatChunk - 1) / kWhatChunk;
     const int cap = c_in > 4096 ? kPrepMaxGroups : rows <= 8 && rows + rounds <= 192 ? 192 : 128;
@@ -511,8 +569,9 @@ static void fwd_prep_split(int64_t t, int64_t c_in, int64_t c_out, int* groups, 
                       (c_in >= 1024 && c_in < 1536 && rows >= 64 && rounds <= 2 * (int64_t)rows);
     const int room = none || rows > cap ? 0 : cap - rows;
     const int extra = (int)(rounds < room ? rounds : room);
-    *groups = rows + extra;
-    *what_first = 2 * (int64_t)extra >= rounds ? rows : 0;
+    const int projecting = direct_lora ? rows : 0;
+    *groups = rows + projecting + extra;
+    *what_first = 2 * (int64_t)extra >= rounds ? rows + projecting : 0;
 }
 
 // shapes the one-launch preparation covers
@@ -522,16 +581,17 @@ bool fwd_prep_covers(int64_t t, int64_t c_in, int32_t n, int32_t r) {
 
 // the words of one launch, and the most that any number of rows and channels takes with n outliers; each after 256 bytes
 // that hold the epoch
-size_t fwd_prep_words_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n) {
+size_t fwd_prep_words_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n, int32_t r) {
     int groups, what_first;
-    fwd_prep_split(t, c_in, c_out, &groups, &what_first);
+    fwd_prep_split(t, c_in, c_out, r > 0 && fwd_prep_direct(t, c_out, n, r), &groups, &what_first);
     return (size_t)((n + 1) / 2) * groups * 8;
 }
 size_t fwd_prep_scratch_bytes(int32_t n) { return kFwdPrepWordsAt + (size_t)((n + 1) / 2) * kPrepMaxGroups * 8; }
 
 template <int NSTEP>
-static hipError_t launch_prep(bool has_lora, dim3 grid, size_t lds, hipStream_t stream, const FwdPrepArgs& a) {
-    auto k = has_lora ? fwd_prep_kernel<NSTEP, true> : fwd_prep_kernel<NSTEP, false>;
+static hipError_t launch_prep(bool has_lora, bool direct, dim3 grid, size_t lds, hipStream_t stream, const FwdPrepArgs& a) {
+    auto k = direct ? (has_lora ? fwd_prep_kernel<NSTEP, true, true> : fwd_prep_kernel<NSTEP, false, true>)
+                    : (has_lora ? fwd_prep_kernel<NSTEP, true, false> : fwd_prep_kernel<NSTEP, false, false>);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, grid, dim3(kPrepThreads), lds, stream, a);
@@ -552,7 +612,7 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
     a.W_O = W_O; a.c_out = c_out; a.what_int = what_int; a.delta_what = delta_what;
     a.Xq = Xq; a.delta = delta; a.xq_O = xq_O;
     a.A = A; a.scale = scale; a.T_hi = T_hi; a.T_lo = T_lo; a.B = B; a.Bt = Bt;
-    fwd_prep_split(t, c, c_out, &a.groups, &a.what_first);
+    fwd_prep_split(t, c, c_out, r > 0 && fwd_prep_direct(t, c_out, n, r), &a.groups, &a.what_first);
     a.part = reinterpret_cast<uint64_t*>(static_cast<char*>(scratch) + kFwdPrepWordsAt);
     a.epoch = reinterpret_cast<uint64_t*>(scratch);
     a.wait_ticks = wait_ticks;
@@ -566,9 +626,9 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
     const size_t stage_codes = (size_t)kLoraWaves * 2 * kPrepRows * (nstep <= 2 ? 1 : nstep <= 4 ? 2 : 4) * 64;
     const size_t lds = (((size_t)c * 4 + 255) & ~(size_t)255) + (stage_lora > stage_codes ? stage_lora : stage_codes);
     const bool has_lora = r == 16;
-    if (nstep <= 2) return launch_prep<2>(has_lora, grid, lds, stream, a);
-    if (nstep <= 4) return launch_prep<4>(has_lora, grid, lds, stream, a);
-    if (nstep <= 8) return launch_prep<8>(has_lora, grid, lds, stream, a);
+    if (nstep <= 2) return launch_prep<2>(has_lora, fwd_prep_direct(t, c_out, n, r), grid, lds, stream, a);
+    if (nstep <= 4) return launch_prep<4>(has_lora, fwd_prep_direct(t, c_out, n, r), grid, lds, stream, a);
+    if (nstep <= 8) return launch_prep<8>(has_lora, fwd_prep_direct(t, c_out, n, r), grid, lds, stream, a);
     return hipErrorInvalidValue;
 }
 

@@ -149,8 +149,9 @@ bool launch_what_quant(const uint32_t* part, int nslab, int32_t n, const float* 
 // and, from byte kFwdPrepWordsAt on, fwd_prep_words_bytes bytes of per-workgroup column maxima, which whoever launches it
 // has to clear afterwards (GemmArgs::clear); wait_ticks bounds that wait (100 MHz ticks).
 bool fwd_prep_covers(int64_t t, int64_t c_in, int32_t n, int32_t r);
+bool fwd_prep_direct(int64_t t, int64_t c_out, int32_t n, int32_t r);      // nobody waits, and the launch clears its words itself
 constexpr size_t kFwdPrepWordsAt = 256;
-size_t fwd_prep_words_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n);
+size_t fwd_prep_words_bytes(int64_t t, int64_t c_in, int64_t c_out, int32_t n, int32_t r);
 size_t fwd_prep_scratch_bytes(int32_t n);        // the most that these and the counter take, for any t, c_in and c_out
 hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const int32_t* O, int32_t n,
                            const float* wmax_O, float gamma, float* s_O, float* colscale, float* cmax_out,

@@ -51,3 +51,15 @@ def test_words_and_counter():
         if fill == 0:
             want = [x.clone() for x in (L.s_O, L.colscale, L.Y, L.what_int)]
         assert all(torch.equal(a, b) for a, b in zip(want, (L.s_O, L.colscale, L.Y, L.what_int)))
+
+
+# the preparation's launch where every workgroup gathers the outlier columns itself: both sides of 2048 values, 512 rows and, without
+# an adapter, 2048 and 12288 channels; one and 64 outliers, owners of rows alone and filled up, more channels than extra workgroups
+_GATHERED = [(16, 3072, 4112, 31, 16), (512, 1040, 2064, 4, 16), (513, 1040, 2064, 3, 16), (32, 4112, 9232, 64, 16), (33, 4112, 1040, 64, 16),
+             (1, 8192, 16384, 1, 16), (9, 2064, 2032, 5, 0), (9, 2064, 2048, 5, 0), (40, 2064, 12288, 33, 0), (40, 2064, 12272, 33, 0),
+             (257, 2064, 528, 7, 16), (3, 7680, 528, 17, 0)]
+
+
+@pytest.mark.parametrize("t,c_in,c_out,n,r", _GATHERED, ids=["%dx%dx%d_n%d_r%d" % c for c in _GATHERED])
+def test_gathered_maxima(t, c_in, c_out, n, r):
+    test_fwd_few(t, c_in, c_out, n, r)
