@@ -584,7 +584,9 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     const size_t words_bytes = quaff::fwd_prep_covers(t, c_in, n_outlier, lora_rank) ? quaff::fwd_prep_words_bytes(t, c_in, c_out, n_outlier, lora_rank) : 0;
     const bool fused = words_bytes > 0 && workspace_bytes >= prep_at + quaff::kFwdPrepWordsAt + words_bytes;
     const bool combined = !fused && n_outlier > 0 && n_outlier <= 1024 && (int64_t)n_outlier * 64 < c_in && lora_rank > 0;
-    if (!fused && !combined) {
+    const bool dense = !fused && !combined && n_outlier > 0 && n_outlier <= 8192 && (int64_t)n_outlier * 64 >= c_in && lora_rank > 0 &&
+                       !quaff::lora_stream_applies(lora_rank, t, c_in, 0);
+    if (!fused && !combined && !dense) {
         int st = quaff_scale_update(X, t, c_in, ldx, O, n_outlier, W_O, wmax_O, c_out, gamma, s_O, colscale, what_int,
                                     delta_what, cmax_out, workspace, scale_bytes, stream);
         if (st != QUAFF_OK) return st;
@@ -624,17 +626,21 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
     }
     float* wsf = static_cast<float*>(workspace);
     // (the persistent down-projection of long inputs yields the abs-max slabs itself, one per row group)
-    const int nslab = quaff::lora_stream_applies(lora_rank, t, c_in, n_outlier) ? quaff::lora_stream_row_groups(t)
+    int chunks, slab_rows;
+    const int nslab = dense ? quaff::scale_update_dense_slabs(t, c_in, &chunks, &slab_rows)
+                    : quaff::lora_stream_applies(lora_rank, t, c_in, n_outlier) ? quaff::lora_stream_row_groups(t)
                                                                                 : quaff::fwd_step_slabs(t, n_outlier);
     uint32_t* part = reinterpret_cast<uint32_t*>(wsf);
     float* s_prev = wsf + (int64_t)nslab * n_outlier;
-    int st = hip_status(quaff::launch_colmax_lora(X, t, c_in, ldx, O, n_outlier, part, s_O, s_prev, nslab, lora_A,
-                                                  lora_rank, lora_scale, t_hi, t_lo, lora_B, lt, c_out, s));
+    int st = hip_status(dense ? quaff::launch_colmax_dense_lora(X, t, c_in, ldx, O, n_outlier, part, s_O, s_prev, lora_A, lora_rank,
+                                                                lora_scale, t_hi, t_lo, lora_B, lt, c_out, s)
+                              : quaff::launch_colmax_lora(X, t, c_in, ldx, O, n_outlier, part, s_O, s_prev, nslab, lora_A,
+                                                          lora_rank, lora_scale, t_hi, t_lo, lora_B, lt, c_out, s));
     if (st != QUAFF_OK) return st;
     // The second combined launch pays off while all its workgroups are resident at once (it runs the quantizer at
     // the requantization role's register budget); long inputs take the two stand-alone kernels.
     hipError_t e = hipSuccess;
-    if (t <= 4096 &&
+    if (t <= 4096 && !dense &&
         quaff::launch_what_quant(part, nslab, n_outlier, wmax_O, s_prev, gamma, O, s_O, colscale, cmax_out, W_O, c_out,
                                  what_int, delta_what, X, t, c_in, ldx, Xq, delta_x, xq_O, s, &e)) {
         if ((st = hip_status(e)) != QUAFF_OK) return st;

@@ -450,7 +450,8 @@ fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
     }
 }
 
-// The narrowest tiles that make a single round: up to 256 workgroups without outliers and 2048 columns; with outliers, whose columns
+// The narrowest tiles that make a single round: up to 256 workgroups without outliers and 2048 columns (1024 without an adapter: 5 x 1456
+// -> 336 6.6 / 7.3); with outliers, whose columns
 // every workgroup gathers and whose words every workgroup reads, up to 64 workgroups, 1024 columns and 1024 gathered values.
 // Of 292 forward steps of 1 to 512 rows and up to 2048 columns, every tile timed, the rule takes 151: 0.75 of the time of the two
 // launches in the geometric mean, none more than 2 % slower.  Beyond it, two launches / this one, us: 256 x 512 -> 512 with 8 outliers
@@ -458,7 +459,7 @@ fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
 // (every workgroup quantizes 16 rows of 3072 columns, 3.5 us of vector instructions, and fetches them and A at 45 KB/us), 77 x 2944
 // -> 576 without outliers 15.0 / 14.6.  With an adapter the product's order of summation must be this kernel's.
 int fwd_few_blocks(int64_t t, int64_t c_in, int64_t c_out, int32_t n, int32_t r) {
-    if ((r != 0 && r != 16) || n > 64 || c_in > (n > 0 ? 1024 : 2048) || (int64_t)n * t > 1024) return 0;
+    if ((r != 0 && r != 16) || n > 64 || c_in > (n > 0 || r == 0 ? 1024 : 2048) || (int64_t)n * t > 1024) return 0;
     for (int blocks = 1; blocks <= 4; blocks *= 2)
         if ((t + kFewRows - 1) / kFewRows * ((c_out + blocks * 16 - 1) / (blocks * 16)) <= (n > 0 ? 64 : 256))
             return r == 0 || gemm_takes_rows(t, c_out, c_in, r) ? blocks : 0;

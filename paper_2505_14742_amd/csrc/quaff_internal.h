@@ -133,6 +133,11 @@ hipError_t launch_colmax_lora(const uint16_t* X, int64_t t, int64_t c, int64_t l
                               uint32_t* part, const float* s_O, float* s_prev, int nslab, const uint16_t* A, int32_t r,
                               float scale, uint16_t* T_hi, uint16_t* T_lo, const uint16_t* B, uint16_t* Bt,
                               int64_t c_out, hipStream_t stream);
+// the same for dense outlier sets, slabs as scale_update_dense_slabs cuts them (chunks of 2048 columns, rows per slab)
+int scale_update_dense_slabs(int64_t t, int64_t c_in, int* chunks, int* rows);
+hipError_t launch_colmax_dense_lora(const uint16_t* X, int64_t t, int64_t c, int64_t ldx, const int32_t* O, int32_t n, uint32_t* part,
+                                    const float* s_O, float* s_prev, const uint16_t* A, int32_t r, float scale, uint16_t* T_hi,
+                                    uint16_t* T_lo, const uint16_t* B, uint16_t* Bt, int64_t c_out, hipStream_t stream);
 hipError_t launch_momentum(const uint32_t* part, int nslab, int n, int n_pad, const float* wmax_O, const float* s_prev,
                            float gamma, const int32_t* O, float* s_O, float* colscale, float* cmax_out,
                            const float* W_O, int64_t c_out, int8_t* what_int, float* delta_what, hipStream_t stream);

@@ -58,68 +58,12 @@ colmax_outlier_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t ldx, co
     colmax_outlier_body<256>(blockIdx.x, gridDim.x, wred, X, t, ldx, O, n, part, s_O, s_prev);
 }
 
-// Dense variant of the column abs-max for outlier sets that touch most 64-byte segments of a row anyway (the
-// paper's 4 % - 10 % budgets): every column of a 2048-column chunk is reduced over the slab's rows with coalesced
-// 16-byte loads (bf16 magnitudes compare as integers), then the chunk's outlier columns are picked out of LDS.
-// Four groups of 256 threads share a slab's rows: as many loads in flight as with four times the slabs, whose partial
-// maxima every workgroup of the next launch would have to fold.
-constexpr int kDenseGroups = 4, kDenseThreads = 256 * kDenseGroups;
 __global__ void __launch_bounds__(kDenseThreads)
 colmax_dense_kernel(const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int64_t ldx, const int32_t* __restrict__ O,
                     int n, uint32_t* __restrict__ part, const float* __restrict__ s_O, float* __restrict__ s_prev,
                     int rows_per_slab) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     __shared__ __attribute__((aligned(16))) uint16_t cm[kDenseGroups][2048];
-    __shared__ int krange[2];
-    const int chunk0 = blockIdx.x * 2048, slab = blockIdx.y;
-    const int lane = threadIdx.x & 255, grp = threadIdx.x >> 8;
-    if (blockIdx.x == 0 && slab == 0)
-        for (int k = threadIdx.x; k < n; k += kDenseThreads) s_prev[k] = s_O[k];
-    if (threadIdx.x < 2) {
-        // first outlier index >= chunk0 (thread 0) and >= chunk0 + 2048 (thread 1): O is sorted
-        const int target = chunk0 + 2048 * (int)threadIdx.x;
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            int mid = (lo + hi) >> 1;
-            if (O[mid] < target) lo = mid + 1; else hi = mid;
-        }
-        krange[threadIdx.x] = lo;
-    }
-    const int64_t col = chunk0 + (int64_t)lane * 8;
-    const int64_t r0 = (int64_t)slab * rows_per_slab;
-    const int64_t r1 = r0 + rows_per_slab < t ? r0 + rows_per_slab : t;
-    uint32_t mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (col < c_in) {
-        const uint16_t* src = X + col;
-        for (int64_t row = r0 + grp; row < r1; row += 4 * kDenseGroups) {   // four independent loads in flight
-            u32x4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t rr = row + u * kDenseGroups < r1 ? row + u * kDenseGroups : r1 - 1;
-                v[u] = *reinterpret_cast<const u32x4*>(src + rr * ldx);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {     // a repeated row changes no maximum
-                    uint32_t lo = v[u][w] & 0x7FFFu, hi = (v[u][w] >> 16) & 0x7FFFu;
-                    mx[2 * w] = lo > mx[2 * w] ? lo : mx[2 * w];
-                    mx[2 * w + 1] = hi > mx[2 * w + 1] ? hi : mx[2 * w + 1];
-                }
-        }
-    }
-    u32x4 packed;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) packed[w] = mx[2 * w] | (mx[2 * w + 1] << 16);
-    *reinterpret_cast<u32x4*>(&cm[grp][lane * 8]) = packed;
-    __syncthreads();
-    for (int k = krange[0] + threadIdx.x; k < krange[1]; k += kDenseThreads) {
-        const int at = O[k] - chunk0;
-        uint32_t m = 0;
-#pragma unroll
-        for (int u = 0; u < kDenseGroups; ++u) m = max(m, (uint32_t)cm[u][at]);
-        part[(int64_t)slab * n + k] = m << 16;                              // |x| as fp32 bits
-    }
+    colmax_dense_body(blockIdx.x, blockIdx.y, cm, X, t, c_in, ldx, O, n, part, s_O, s_prev, rows_per_slab);
 }
 
 template <int NT, int NB, bool HELD>
@@ -164,6 +108,14 @@ int scale_update_gather_slabs(int64_t t, int32_t n) {
     return nslab < cap ? nslab : cap;
 }
 
+// one (chunk, slab) workgroup per compute unit, within the slab count the workspace was sized for
+int scale_update_dense_slabs(int64_t t, int64_t c_in, int* chunks, int* rows) {
+    *chunks = (int)((c_in + 2047) / 2048);
+    const int want = (256 + *chunks - 1) / *chunks, most = scale_update_blocks(t), nslab = want < most ? want : most;
+    *rows = (int)((t + nslab - 1) / nslab);
+    return (int)((t + *rows - 1) / *rows);
+}
+
 hipError_t launch_scale_update(const uint16_t* X, int64_t t, int64_t c_in, int64_t ldx, const int32_t* O, int32_t n,
                                const float* W_O, const float* wmax_O, int64_t c_out, float gamma, float* s_O,
                                float* colscale, int8_t* what_int, float* delta_what, float* cmax_out, float* ws,
@@ -173,12 +125,8 @@ hipError_t launch_scale_update(const uint16_t* X, int64_t t, int64_t c_in, int64
     int nslab = scale_update_blocks(t);
     const bool dense = (int64_t)n * 64 >= c_in;          // most 64-byte segments of a row hold an outlier anyway
     if (dense) {
-        // one (chunk, slab) workgroup per compute unit, within the slab count the workspace was sized for
-        const int chunks = (int)((c_in + 2047) / 2048);
-        const int want = (256 + chunks - 1) / chunks;
-        if (want < nslab) nslab = want;
-        const int rows = (int)((t + nslab - 1) / nslab);
-        nslab = (int)((t + rows - 1) / rows);
+        int chunks, rows;
+        nslab = scale_update_dense_slabs(t, c_in, &chunks, &rows);
         float* s_prev = ws + (int64_t)nslab * n;
         {
             ProfScope prof(K_COLMAX, stream);

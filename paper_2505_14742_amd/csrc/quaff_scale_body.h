@@ -60,6 +60,69 @@ __device__ __forceinline__ void colmax_outlier_body(int block, int nslab, uint32
     }
 }
 
+// Dense variant of the column abs-max for outlier sets that touch most 64-byte segments of a row anyway (the
+// paper's 4 % - 10 % budgets): every column of a 2048-column chunk is reduced over the slab's rows with coalesced
+// 16-byte loads (bf16 magnitudes compare as integers), then the chunk's outlier columns are picked out of LDS.
+// Four groups of 256 threads share a slab's rows: as many loads in flight as with four times the slabs, whose partial
+// maxima every workgroup of the next launch would have to fold.
+constexpr int kDenseGroups = 4, kDenseThreads = 256 * kDenseGroups;
+__device__ __forceinline__ void colmax_dense_body(int chunk, int slab, uint16_t (*cm)[2048] /* LDS [kDenseGroups] */,
+                                                  const uint16_t* __restrict__ X, int64_t t, int64_t c_in, int64_t ldx,
+                                                  const int32_t* __restrict__ O, int n, uint32_t* __restrict__ part,
+                                                  const float* __restrict__ s_O, float* __restrict__ s_prev, int rows_per_slab) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __shared__ int krange[2];
+    const int chunk0 = chunk * 2048;
+    const int lane = threadIdx.x & 255, grp = threadIdx.x >> 8;
+    if (chunk == 0 && slab == 0)
+        for (int k = threadIdx.x; k < n; k += kDenseThreads) s_prev[k] = s_O[k];
+    if (threadIdx.x < 2) {
+        // first outlier index >= chunk0 (thread 0) and >= chunk0 + 2048 (thread 1): O is sorted
+        const int target = chunk0 + 2048 * (int)threadIdx.x;
+        int lo = 0, hi = n;
+        while (lo < hi) {
+            int mid = (lo + hi) >> 1;
+            if (O[mid] < target) lo = mid + 1; else hi = mid;
+        }
+        krange[threadIdx.x] = lo;
+    }
+    const int64_t col = chunk0 + (int64_t)lane * 8;
+    const int64_t r0 = (int64_t)slab * rows_per_slab;
+    const int64_t r1 = r0 + rows_per_slab < t ? r0 + rows_per_slab : t;
+    uint32_t mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (col < c_in) {
+        const uint16_t* src = X + col;
+        for (int64_t row = r0 + grp; row < r1; row += 4 * kDenseGroups) {   // four independent loads in flight
+            u32x4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t rr = row + u * kDenseGroups < r1 ? row + u * kDenseGroups : r1 - 1;
+                v[u] = *reinterpret_cast<const u32x4*>(src + rr * ldx);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {     // a repeated row changes no maximum
+                    uint32_t lo = v[u][w] & 0x7FFFu, hi = (v[u][w] >> 16) & 0x7FFFu;
+                    mx[2 * w] = lo > mx[2 * w] ? lo : mx[2 * w];
+                    mx[2 * w + 1] = hi > mx[2 * w + 1] ? hi : mx[2 * w + 1];
+                }
+        }
+    }
+    u32x4 packed;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) packed[w] = mx[2 * w] | (mx[2 * w + 1] << 16);
+    *reinterpret_cast<u32x4*>(&cm[grp][lane * 8]) = packed;
+    __syncthreads();
+    for (int k = krange[0] + threadIdx.x; k < krange[1]; k += kDenseThreads) {
+        const int at = O[k] - chunk0;
+        uint32_t m = 0;
+#pragma unroll
+        for (int u = 0; u < kDenseGroups; ++u) m = max(m, (uint32_t)cm[u][at]);
+        part[(int64_t)slab * n + k] = m << 16;                              // |x| as fp32 bits
+    }
+}
+
 // Eq. 7 with Eq. 8 for one outlier channel, in fp32 with one rounding per operation
 __device__ __forceinline__ float momentum_scale(float cmax, float wmax, float s_prev, float gamma) {
     float beta = 1.0f;
