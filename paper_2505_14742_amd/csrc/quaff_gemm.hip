@@ -222,6 +222,11 @@ hipError_t launch_gemm_one(const GemmArgs& g, bool dump_acc, hipStream_t stream)
         if (tile >= kRows16x16) return launch_gemm_rows(g, tile, stream);
     }
     if (!gradient && narrow_stages(g, tile)) tile += kTileNarrow;
+    // Sixteen wavefronts of 64 x 64 instead of eight of 128 x 64, the same bits, where every unit has several tiles and the epilogue's low-rank
+    // operands fit one staging round: 16384 x 5120 outputs at K = 5120 and rank 16, us, eight / sixteen wavefronts: forward 427 / 414, gradient 418 /
+    // 397, at 13824 1003 / 980.  One tile for a unit is level or slower (4096 x 4096 at 4096 78.5 / 80.1), rank 64 too (8192 x 11008 455 / 454).
+    if (tile == kTile256x256 && g.r <= 16 && !g.accumulate && g.K >= 4096 && ((g.M + 255) / 256) * ((g.N + 255) / 256) > 512)
+        tile = kTile256x256Many;
     // (the same bits; its wavefronts leave half of a compute unit's registers to the weight gradients on the second stream: training step
     // of 2048 x 3072 -> 9216 191.6 us, 214.1 with eight wavefronts of 165 registers)
     if (g.beside && tile == kTile128x192Deep) tile = kTile128x192Beside;

@@ -1114,9 +1114,9 @@ gemm_i8_dma_kernel(const GemmArgs g, const TileMap tmap) {
 
 // Shapes (quaff_gemm.hip chooses one) and the launchers of the two readings of B.
 enum GemmTile { kTile256x256 = 0, kTile256x288, kTile256x128, kTile128x192, kTile128x192Deep, kTile128x192Beside, kTile128x128, kTile64x128, kTile64x64,
-                kTileSplit, kTileSplitSmall2, kTileSplitSmall4,
+                kTile256x256Many, kTileSplit, kTileSplitSmall2, kTileSplitSmall4,
                 kTileNarrow,           // kTileNarrow + one of the first three: stages of 64 bytes (forward only)
-                kRows16x16 = 16, kRows32x32, kRows32x64, kRows16x64 };   // quaff_gemm_rows.hip
+                kRows16x16 = 20, kRows32x32, kRows32x64, kRows16x64 };   // quaff_gemm_rows.hip
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);
 hipError_t launch_gemm_mid(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream);     // 64 and 128 rows, both readings

@@ -64,3 +64,36 @@ def test_deep_tile_beside_a_second_stream(t, c_in, c_out, r):
             x.fill_(-3.0)
         q.linear_bwd_step(dYd, Xd, L.Wq_packed, L.delta_w, c_in, c_out, L.A, L.B, r, 1.0, *out, ws, side=how)
         assert torch.equal(out[0], L.dX)
+
+
+@pytest.mark.parametrize("r", [0, 16])
+def test_many_large_tiles(r):
+    """More than 512 tiles of 256 x 256, sixteen wavefronts each (ragged rows, columns and contraction): without an adapter the bits of
+    the same rows in a product of few tiles; with one, whose products may be added in another order there, 1e-6 of the result."""
+    from paper_2505_14742_amd import binding as q
+    from tests.gpu_harness import DEV
+    t, c_in, c_out = 8447, 4112, 5104
+    print("many large tiles", r, flush=True)
+    sys.stdout.flush()
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    W = torch.randn(c_in, c_out, generator=gen, device=DEV) * 0.02
+    Wq, dw = torch.empty(q.packed_weight_bytes(c_in, c_out), dtype=torch.int8, device=DEV), torch.empty(c_out, device=DEV)
+    q.prepare_weight(W, None, Wq, dw, None, None, None, torch.empty(q.prepare_workspace_bytes(c_in, c_out), dtype=torch.int8, device=DEV))
+    X = torch.randn(t, c_in, generator=gen, device=DEV).to(torch.bfloat16)
+    A = (torch.randn(c_in, r, generator=gen, device=DEV) / 64).to(torch.bfloat16) if r else None
+    B = (torch.randn(r, c_out, generator=gen, device=DEV) * 0.02).to(torch.bfloat16) if r else None
+    ws = torch.empty(q.workspace_bytes(t, c_in, c_out, 0, r), dtype=torch.int8, device=DEV)
+
+    def forward(x):
+        n = x.shape[0]
+        Xq, d = torch.empty(n, c_in, dtype=torch.int8, device=DEV), torch.empty(n, device=DEV)
+        q.quant_act(x, None, None, Xq, d, None)
+        Y = torch.full((n, c_out), -3.0, device=DEV)
+        q.linear_fwd(Xq, d, None, Wq, dw, c_in, c_out, None, None, 0, x if r else None, A, B, r, 1.0, Y, ws)
+        return Y
+
+    whole, parts = forward(X), torch.cat([forward(X[i:i + 300]) for i in range(0, t, 300)])
+    if r == 0:
+        assert torch.equal(whole, parts)
+    else:
+        assert float((whole.double() - parts.double()).norm() / parts.double().norm()) <= 1e-6
