@@ -474,8 +474,10 @@ static hipError_t launch_few(bool lora, dim3 grid, hipStream_t stream, const Fwd
     auto k = lora ? fwd_few_kernel<SPS, SL, NB, true> : fwd_few_kernel<SPS, SL, NB, false>;
     const size_t red = lora ? 2 * kFewSlices * 1024 : 0, exchange = (size_t)kFewWaves * NB * 1024;
     const size_t lds = (((size_t)a.c * 4 + 255) & ~(size_t)255) + (lora ? (size_t)kFewWaves * 4 * kFewLt : 0) + (red > exchange ? red : exchange);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    if (lds > kPlainLds) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k, grid, dim3(kFewThreads), lds, stream, a, O);
     return hipGetLastError();
 }

@@ -592,8 +592,10 @@ template <int NSTEP>
 static hipError_t launch_prep(bool has_lora, bool direct, dim3 grid, size_t lds, hipStream_t stream, const FwdPrepArgs& a) {
     auto k = direct ? (has_lora ? fwd_prep_kernel<NSTEP, true, true> : fwd_prep_kernel<NSTEP, false, true>)
                     : (has_lora ? fwd_prep_kernel<NSTEP, true, false> : fwd_prep_kernel<NSTEP, false, false>);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    if (lds > kPlainLds) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k, grid, dim3(kPrepThreads), lds, stream, a);
     return hipGetLastError();
 }
@@ -624,8 +626,8 @@ hipError_t launch_fwd_prep(const uint16_t* X, int64_t t, int64_t c, int64_t ldx,
     // column scales, then the larger of the down-projection's staging (A slices + partial sums) and the code rows
     const size_t stage_lora = (size_t)kLoraWaves * 4 * kPrepLtBlock + 2 * kLoraWaves * 32 * 4 * sizeof(float);
     const size_t stage_codes = (size_t)kLoraWaves * 2 * kPrepRows * (nstep <= 2 ? 1 : nstep <= 4 ? 2 : 4) * 64;
-    const size_t lds = (((size_t)c * 4 + 255) & ~(size_t)255) + (stage_lora > stage_codes ? stage_lora : stage_codes);
     const bool has_lora = r == 16;
+    const size_t lds = (((size_t)c * 4 + 255) & ~(size_t)255) + (has_lora && stage_lora > stage_codes ? stage_lora : stage_codes);
     if (nstep <= 2) return launch_prep<2>(has_lora, fwd_prep_direct(t, c_out, n, r), grid, lds, stream, a);
     if (nstep <= 4) return launch_prep<4>(has_lora, fwd_prep_direct(t, c_out, n, r), grid, lds, stream, a);
     if (nstep <= 8) return launch_prep<8>(has_lora, fwd_prep_direct(t, c_out, n, r), grid, lds, stream, a);

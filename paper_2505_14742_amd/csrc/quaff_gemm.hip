@@ -62,7 +62,9 @@ constexpr Shape kDeep[2] = {{kTile128x192Deep, 128, 192, 1, 6.69, 4.59, 1.80, 12
                             {kTile128x192Deep, 128, 192, 1, 5.83, 4.04, 1.49, 13.27, 3.81, 1.42}};
 
 double shape_us(const Shape& s, int64_t M, int64_t N, int64_t K, int32_t rank) {
-    const int64_t tm = (M + s.bm - 1) / s.bm, tn = (N + s.bn - 1) / s.bn, tiles = tm * tn;
+    // (32-bit divisions: M is below 2^30, N below 2^20)
+    const uint32_t tm = ((uint32_t)M + s.bm - 1) / (uint32_t)s.bm, tn = ((uint32_t)N + s.bn - 1) / (uint32_t)s.bn;
+    const int64_t tiles = (int64_t)tm * tn;
     int64_t n = (tiles + 255) / 256;
     if (n <= 16) {                    // (with many tiles per unit the regions' edges don't matter)
         const TileGrid r = tile_grid((int)tm, (int)tn, s.bm, s.bn);
@@ -137,7 +139,7 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 // workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 / 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
 static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double gain = 1.04) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
-    if (tiles > 128 || K % 256 != 0) return 1;
+    if (tiles > 128 || K % 256 != 0 || K < 6144) return 1;      // (nothing is gained below: no need to estimate)
     double alone;
     choose_shape(M, N, K, rank, gradient, &alone);
     const double k = (double)K / 1024.0, busy = tiles / 256.0;

@@ -11,6 +11,10 @@ constexpr int kPadK = 64;   // outlier count is padded to the INT8 MFMA contract
 constexpr int kLoraParts = 2;   // the LoRA down-projection splits its contraction range over this many workgroups;
                                 // the partial results T[p] ([t x r] each, hi/lo bf16 pairs) are summed by the GEMM epilogue
 
+// dynamic LDS that a launch may ask for without hipFuncAttributeMaxDynamicSharedMemorySize (64 KB with the kernel's own; the call is a
+// good part of what a launch costs the host)
+constexpr size_t kPlainLds = 40 * 1024;
+
 // ---- device helpers -------------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
 
