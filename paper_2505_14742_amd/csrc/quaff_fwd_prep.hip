@@ -567,9 +567,10 @@ static void fwd_prep_split(int64_t t, int64_t c_in, int64_t c_out, bool direct_l
     const int cap = c_in > 4096 ? kPrepMaxGroups : rows <= 8 && rows + rounds <= 192 ? 192 : 128;
     const bool none = (c_in <= 2048 && rounds <= rows && (c_in >= 768 || rows >= 48)) ||
                       (c_in >= 1024 && c_in < 1536 && rows >= 64 && rounds <= 2 * (int64_t)rows);
-    const int room = none || rows > cap ? 0 : cap - rows;
+    const int projecting = direct_lora ? rows : 0, most = kPrepMaxGroups - rows - projecting;
+    int room = none || rows > cap ? 0 : cap - rows;
+    room = room < most ? room : most;
     const int extra = (int)(rounds < room ? rounds : room);
-    const int projecting = direct_lora ? rows : 0;
     *groups = rows + projecting + extra;
     *what_first = 2 * (int64_t)extra >= rounds ? rows + projecting : 0;
 }
