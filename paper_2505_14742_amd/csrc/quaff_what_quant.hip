@@ -56,14 +56,21 @@ what_quant_kernel(const uint32_t* __restrict__ part, int nslab, int n, int n_pad
 }
 
 template <int TPR, int NV>
-static void launch_wq(dim3 grid, size_t lds, hipStream_t stream, const uint32_t* part, int nslab, int n, int n_pad,
-                      const float* wmax_O, const float* s_prev, float gamma, const int32_t* O, float* s_O,
-                      float* colscale, float* cmax_out, const float* W_O, int64_t c_out, int8_t* what_int,
-                      float* delta_what, int what_blocks, const uint16_t* X, int64_t t, int c, int64_t ldx, int8_t* Xq,
-                      float* delta, int8_t* xq_O) {
+static hipError_t launch_wq(dim3 grid, size_t lds, hipStream_t stream, const uint32_t* part, int nslab, int n, int n_pad,
+                            const float* wmax_O, const float* s_prev, float gamma, const int32_t* O, float* s_O,
+                            float* colscale, float* cmax_out, const float* W_O, int64_t c_out, int8_t* what_int,
+                            float* delta_what, int what_blocks, const uint16_t* X, int64_t t, int c, int64_t ldx, int8_t* Xq,
+                            float* delta, int8_t* xq_O) {
+    // (the requantizing role's own arrays come on top: 64 KB without the attribute are exceeded from about 15900 columns on)
+    if (lds > kPlainLds) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(what_quant_kernel<TPR, NV>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((what_quant_kernel<TPR, NV>), grid, dim3(256), lds, stream, part, nslab, n, n_pad, wmax_O, s_prev,
                        gamma, O, s_O, colscale, cmax_out, W_O, c_out, what_int, delta_what, what_blocks, X, t, c, ldx,
                        Xq, delta, xq_O);
+    return hipGetLastError();
 }
 
 // Returns false (nothing enqueued) for shapes this launch does not cover.
@@ -79,7 +86,7 @@ bool launch_what_quant(const uint32_t* part, int nslab, int32_t n, const float* 
     const int n_pad = (n + kPadK - 1) / kPadK * kPadK;
     const int what_blocks = (int)((c_out + kWideCh - 1) / kWideCh);
 #define QUAFF_WQ(TPR, NV)                                                                                              \
-    launch_wq<TPR, NV>(dim3((unsigned)(what_blocks + (t + 256 / TPR - 1) / (256 / TPR))), lds, stream, part, nslab, n,  \
+    *err = launch_wq<TPR, NV>(dim3((unsigned)(what_blocks + (t + 256 / TPR - 1) / (256 / TPR))), lds, stream, part, nslab, n,  \
                        n_pad, wmax_O, s_prev, gamma, O, s_O, colscale, cmax_out, W_O, c_out, what_int, delta_what,      \
                        what_blocks, X, t, c, ldx, Xq, delta, xq_O)
     if (vec <= 64 * 1) QUAFF_WQ(64, 1);
@@ -92,7 +99,6 @@ bool launch_what_quant(const uint32_t* part, int nslab, int32_t n, const float* 
     else if (vec <= 256 * 6) QUAFF_WQ(256, 6);
     else QUAFF_WQ(256, 8);
 #undef QUAFF_WQ
-    *err = hipGetLastError();
     return true;
 }
 

@@ -82,3 +82,15 @@ def test_fwd_step_when_the_grid_wide_wait_gives_up(case):
     finally:
         q.debug_grid_wait_ticks(prev)
     assert q.debug_grid_wait_ticks(-1) == prev
+
+
+# both sides of the row length from which the combined launch of quantizer and requantization takes more than 64 KB of LDS with its
+# own arrays (15872 / 16128 columns), of the one from which it gives way to two launches (16384 less two for each outlier)
+_WIDEST = [(100, 15872, 31, 16), (100, 16128, 31, 16), (33, 16256, 64, 32), (100, 16368, 3, 64), (20, 16384, 8, 16)]
+
+
+@pytest.mark.parametrize("t,c_in,n,r", _WIDEST, ids=["%dx%d_n%d_r%d" % c for c in _WIDEST])
+def test_fwd_step_widest_rows(t, c_in, n, r):
+    O = [k * (c_in - 1) // (n - 1) for k in range(n)]
+    X, dY, W, O, A, B = synth.edge_case_inputs(synth.EdgeCase("widest_rows", t, c_in, 272, O, r), 149)
+    _compare(W, O, A, B, 0.5, [X, X[::-1].copy()], 0.2, "widest rows %d x %d n=%d r=%d" % (t, c_in, n, r))
