@@ -81,12 +81,17 @@ hipError_t launch_quant_act(const uint16_t* X, int64_t t, int64_t c64, int64_t l
     const int vec = (c + 7) / 8;   // 16-byte vectors per row
 #define QUAFF_ROWS(TPR, NV) launch_rows<TPR, NV>(X, t, c, ldx, cs, O, n, n_pad, Xq, delta, xq_O, stream)
 #define QUAFF_SHARED(NT, ROWS, NV) launch_shared<NT, ROWS, NV>(X, t, c, ldx, cs, O, n, n_pad, Xq, delta, xq_O, stream)
-    // Four rows share the column scales in registers where there are enough rows to fill the chip so, and few outliers, whose
-    // values every thread then gathers for all of them.  Us, own rows / shared: no outliers 2048 x 16384 27.9 / 17.5, 4096 x 11008 35.0 /
-    // 28.5, 2048 x 6144 9.5 / 9.1, 1024 x 6144 5.6 / 6.5, 2048 x 3072 6.4 / 6.5; 40 outliers 2048 x 16384 29.8 / 22.1, 4096 x 8192 28.2 / 23.1,
-    // 2048 x 8192 13.5 / 16.1, 8192 x 4096 29.9 / 29.9; 819 outliers 2048 x 8192 16.9 / 20.7.  From 3080 to 4096 columns, eight vectors to a lane
-    // of a wavefront that has a row to itself, at any number of rows: 512 x 4096 6.3 / 5.0, 256 x 4096 with 40 outliers 6.7 / 5.9.
-    const bool shared = xq_O ? n <= 128 && (vec > 1024 ? t >= 2048 : vec > 512 ? t >= 4096 : t < 8192) : vec <= 512 || t >= 2048;
+    // Four rows share the column scales in registers where there are enough rows to fill the chip so, and few outliers, whose values every
+    // thread then gathers for all of them.  18650 calls of 1 to 16384 rows and 3088 to 16384 columns timed both ways, in the geometric
+    // mean and at worst shared / own rows, one X in the cache; rotating X from HBM where that differs:
+    //   no outliers, up to 4096 columns 0.80 (0.88); 0.85 (0.96) from 2048 rows at more, 1.1 to 1.5 below
+    //   up to 128 outliers, up to 4096 columns and below 6144 rows 0.88 (1.03); rotating X 1.06 (1.18) from 1536 to 4096 rows; 1.0 (1.23) beyond
+    //   6145 to 8192 columns from 6144 rows on 0.97 (1.06); with 4097 to 6144, or fewer rows, 1.0 to 1.7
+    //   11265 columns and more 0.80 (0.89) up to 2048 rows, which are two workgroups for every unit, 1.02 (1.10) from there to 2400,
+    //   0.94 (1.05) beyond; with 8193 to 9900 columns 1.06 (1.19)
+    //   more outliers 0.9 to 2.2.
+    const bool shared = !xq_O ? vec <= 512 || t >= 2048
+                      : n <= 128 && (vec <= 512 ? t < 6144 : vec <= 1024 ? vec > 768 && t >= 6144 : vec > 1408 && t >= 1920 && (t <= 2048 || t >= 2400));
     if (vec > 64 * 6 && vec <= 256 * 8 && shared) {
         if (vec <= 512) QUAFF_SHARED(256, 4, 2);
         else if (vec <= 768) QUAFF_SHARED(256, 4, 3);
