@@ -204,6 +204,12 @@ int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ld
  * up at once, which exercises the recomputing path with kernels that still finish normally. */
 long long quaff_debug_grid_wait_ticks(long long ticks);
 
+/* Test aid (not part of the method): name of the kernel form that the product of a layer takes at these sizes.  how: 0 forward
+ * product with the workspace the query functions ask for, 1 with the smallest accepted one, 2 and 3 the same for the input gradient,
+ * 4 input gradient of quaff_linear_bwd_step with a second stream.  Host code only; the string is static or valid until the
+ * thread's next call, and empty for sizes out of range. */
+const char* quaff_debug_product_form(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank, int how);
+
 /* quaff_linear_fwd with the result rounded (to nearest even) to bf16 instead of stored as fp32: the output write,
  * which a launch cannot overlap with anything at a few thousand tokens, is halved.  Everything up to the final
  * rounding is the same arithmetic.  Restrictions: c_in a multiple of 64, n_outlier <= 128 (QUAFF_ERR_SHAPE

@@ -58,6 +58,7 @@ SIGNATURES = {
     "quaff_linear_fwd_step": (C.c_int, [_vp, _i64, _i64, _i64, _vp, _i32, _vp, _vp, _i64, _f32, _vp, _vp, _vp, _vp, _vp,
                                         _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _f32, _vp, _i64, _vp, _sz, _vp]),
     "quaff_debug_grid_wait_ticks": (C.c_longlong, [C.c_longlong]),
+    "quaff_debug_product_form": (C.c_char_p, [_i64, _i64, _i64, _i32, _i32, C.c_int]),
     "quaff_profile_enable": (C.c_int, [C.c_int]),
     "quaff_profile_collect": (_i64, []),
     "quaff_profile_launch": (C.c_int, [_i64, C.POINTER(C.c_int), C.POINTER(C.c_float)]),
@@ -293,6 +294,12 @@ def linear_fwd_step(X, O, W_O, wmax_O, c_out, gamma, s_O, colscale, what_int, de
 def debug_grid_wait_ticks(ticks: int) -> int:
     """Set (ticks >= 0) or read (ticks < 0) the bound of the one-launch forward preparation's grid-wide wait."""
     return int(lib().quaff_debug_grid_wait_ticks(ticks))
+
+
+def debug_product_form(t: int, c_in: int, c_out: int, n_outlier: int, lora_rank: int, how: int) -> str:
+    """Kernel form of a layer's product at these sizes (how: 0 forward, 1 with the smallest workspace; 2, 3 the input
+    gradient; 4 the input gradient beside a second stream)."""
+    return lib().quaff_debug_product_form(t, c_in, c_out, n_outlier, lora_rank, how).decode()
 
 
 def linear_bwd_dx_acc(dY, Wq_packed, delta_w, c_in, c_out, Gq, delta_g, acc):

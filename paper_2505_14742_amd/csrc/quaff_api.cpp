@@ -543,6 +543,23 @@ long long quaff_debug_grid_wait_ticks(long long ticks) {
     return ticks < 0 ? g_grid_wait_ticks.load() : g_grid_wait_ticks.exchange(ticks);
 }
 
+const char* quaff_debug_product_form(int64_t t, int64_t c_in, int64_t c_out, int32_t n_outlier, int32_t lora_rank, int how) {
+    if (!dims_ok(t, c_in, c_out) || n_outlier < 0 || n_outlier > c_in || !rank_ok(lora_rank) || how < 0 || how > 4) return "";
+    const bool gradient = how >= 2;
+    quaff::GemmArgs g{};
+    set_weight_operand(g, nullptr, c_in, gradient);
+    g.M = t; g.N = gradient ? c_in : c_out; g.K = gradient ? c_out : c_in;
+    g.K2 = !gradient && n_outlier > 0 ? pad_outliers(n_outlier) : 0;
+    g.r = lora_rank;
+    g.beside = how == 4;
+    static char room[16];                // (an address: nothing is read or written)
+    if (gradient && quaff::gemm_split_bytes(t, c_in, c_out) > 0) g.split_scratch = room;
+    const size_t shared = gradient ? split_bwd(t, c_in, c_out, lora_rank) : split_fwd(t, c_in, c_out, lora_rank);
+    if ((how == 0 || how == 2 || (how == 4 && (lora_rank < 32 || quaff::gemm_small_split_pays_beside(t, c_in, c_out, lora_rank)))) && shared > 0)
+        g.small_split_scratch = room;
+    return quaff::gemm_form_name(g);
+}
+
 int quaff_linear_fwd_step(const uint16_t* X, int64_t t, int64_t c_in, int64_t ldx, const int32_t* O, int32_t n_outlier,
                           const float* W_O, const float* wmax_O, int64_t c_out, float gamma, float* s_O,
                           float* colscale, int8_t* what_int, float* delta_what, float* cmax_out, int8_t* Xq,

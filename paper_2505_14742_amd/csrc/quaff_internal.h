@@ -230,5 +230,6 @@ bool gemm_small_split_pays_beside(int64_t M, int64_t N, int64_t K, int32_t rank)
 // does a forward product of these sizes add its low-rank term in the order of quaff_gemm_rows.hip
 bool gemm_takes_rows(int64_t M, int64_t N, int64_t K, int32_t rank);
 hipError_t launch_gemm(const GemmArgs& g, bool dump_acc, hipStream_t stream);
+const char* gemm_form_name(const GemmArgs& g);     // what launch_gemm launches for these sizes and scratch (nothing is read or written)
 
 }  // namespace quaff
