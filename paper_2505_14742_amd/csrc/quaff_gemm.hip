@@ -136,9 +136,9 @@ size_t gemm_split_bytes(int64_t M, int64_t N, int64_t K) {
 }
 
 // Outputs of at most 128 tiles of 128 x 192 with a long contraction: two or four workgroups per tile share it where that pays for the
-// exchange of their sums through the L2.  Estimated as shape_us does, from the same products; 2 % must be gained.  One workgroup per
-// tile in its best shape / two or four, us: forward 1098 x 2048 outputs at 8192 35.4 / 34.3, 763 x 1408 at 14336 and rank 64 37.8 / 33.8
-// (four), 479 x 2176 at 16384 44.4 / 35.4, 2021 x 1152 at 16384 61.5 / 52.6; input gradient with its quantizer 970 x 2944 <- 16384 83.8 / 78.4.
+// exchange of their sums through the L2.  Estimated as shape_us does, from the same products; 6 % must be gained (of 39 products
+// that 2 % would share 16 are faster alone, of these 20 eight).  One workgroup per
+// tile in its best shape / two or four, us: forward 763 x 1408 outputs at 14336 37.8 / 33.8 (four), 479 x 2176 at 16384 44.4 / 35.4, 2021 x 1152 at 16384 61.5 / 52.6; input gradient with its quantizer 970 x 2944 <- 16384 83.8 / 78.4.
 // Below K = 6144 the tiles of 64 rows are faster (512 x 3072 at 3072 11.7 us, two workgroups per 128 x 192 tile 17.0).
 static double shared_us(int parts, int64_t tiles, int64_t K, int32_t rank, bool gradient) {
     struct Parts { double fixed, unit, chip, chain, low, low2; };
@@ -152,7 +152,7 @@ static double shared_us(int parts, int64_t tiles, int64_t K, int32_t rank, bool 
 // The workgroups of a tile run on one XCD and one of them fills a compute unit: no more of them than the 32 units of an XCD,
 // or the last tiles start when the first have ended (1408 x 2112 outputs, 11 x 11 tiles, 18 of them on an XCD, one / two
 // workgroups per tile: 27.8 / 40.1 us at K = 4096, 45.1 / 58.1 at 8192; 640 x 2048 outputs, one / four: 25.6 / 30.5 at 4096).
-static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double gain = 1.02) {
+static int small_split(int64_t M, int64_t N, int64_t K, int32_t rank, bool gradient, double gain = 1.06) {
     const int64_t tiles = ((M + 127) / 128) * ((N + 191) / 192);
     if (tiles > 128 || K % 256 != 0 || K < 6144) return 1;
     double alone;
