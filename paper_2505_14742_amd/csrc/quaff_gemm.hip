@@ -233,7 +233,7 @@ static int product_tile(const GemmArgs& g, bool dump_acc) {
     if (g.split_scratch && one_launch && split_applies(g.M, g.N, g.K)) return kTileSplit;
     if (parts > 1 && g.small_split_scratch) return parts == 2 ? kTileSplitSmall2 : kTileSplitSmall4;
     if (parts > 1 && g.r > 0) {
-        tile = kTile128x192;             // (no room for the exchange: the shared form's tile and epilogue, one workgroup each)
+        tile = kTile128x192Deep;         // (no room for the exchange, or not worth it beside a second stream: the shared form's tile and epilogue)
     } else {
         double us;
         tile = choose_shape(g.M, g.N, g.K, g.r, gradient, &us);

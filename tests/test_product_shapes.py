@@ -49,3 +49,12 @@ def test_products_the_limits_of_the_model_once_got_wrong():
     assert form(86, 15360, 1152, 15, 16, 0) == "32x32 rows"
     assert form(5723, 6400, 1280, 0, 64, 2) == "128x192"
     assert form(2156, 4480, 1216, 0, 64, 2) == "128x192"
+
+
+def test_a_product_without_room_for_the_exchange_keeps_the_deep_ring():
+    """At most 128 tiles of 128 x 192, one for a compute unit: the ring of three stages (two: 8192 -> 3072 forward 74.1 us for 61.7)."""
+    form = q.debug_product_form
+    for shape, parts in (((195, 10752, 2208, 1, 16), 4), ((2021, 16384, 1152, 3, 16), 2), ((662, 14336, 2736, 65, 64), 2)):
+        assert form(*shape, 0) == "128x192 shared by %d" % parts and form(*shape, 1) == "128x192 deep"
+    gradient = (685, 2768, 11264, 0, 48)
+    assert form(*gradient, 2) == "128x192 shared by 2" and form(*gradient, 3) == "128x192 deep" and form(*gradient, 4) == "128x192 beside"
