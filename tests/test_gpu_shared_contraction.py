@@ -11,11 +11,19 @@ from paper_2505_14742_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# (t, c_in, c_out, number of outliers, rank): four parts forward; two; two in the gradient; ragged edges with both; four
-# parts in the gradient, whole and ragged
-_CASES = [(257, 8192, 3056, 1, 16), (512, 3072, 3072, 31, 16), (500, 3088, 4096, 70, 48), (129, 8192, 6160, 0, 0),
-          (1000, 4096, 3008, 65, 64), (384, 4096, 8192, 13, 32),
-          (256, 4096, 4096, 5, 16), (257, 3056, 8192, 31, 32)]
+# (t, c_in, c_out, number of outliers, rank) and the parts of the forward product and the input gradient: ragged rows and columns, no,
+# one and two outlier slices, every rank form
+_CASES = [((195, 10752, 2208, 1, 16), 4, 1), ((203, 8704, 2096, 0, 0), 4, 1), ((2090, 11264, 912, 70, 16), 2, 1),
+          ((646, 14336, 2736, 65, 48), 2, 1), ((323, 13312, 1296, 13, 64), 4, 1), ((212, 10752, 2112, 31, 32), 4, 1),
+          ((198, 2112, 13824, 5, 16), 1, 4), ((917, 2064, 6144, 31, 32), 1, 2), ((527, 1680, 11264, 0, 0), 1, 2),
+          ((685, 2768, 11264, 3, 48), 1, 2), ((208, 2064, 15872, 2, 64), 1, 4), ((65, 8704, 10752, 2, 16), 4, 4)]
+# long and medium contractions that are faster unshared: the size of the workspace makes no difference
+_CASES += [(case, 1, 1) for case in [(257, 8192, 3056, 1, 16), (512, 3072, 3072, 31, 16), (500, 3088, 4096, 70, 48), (129, 8192, 6160, 0, 0),
+                                     (1000, 4096, 3008, 65, 64), (384, 4096, 8192, 13, 32), (256, 4096, 4096, 5, 16), (257, 3056, 8192, 31, 32)]]
+
+
+def _parts(form):
+    return int(form.rsplit(" ", 1)[1]) if "shared by" in form else 1
 
 
 def _forward(q, L, X, dY, ws):
@@ -35,10 +43,12 @@ def _outputs(q, L, X, dY, ws):
     return _forward(q, L, X, dY, ws), _gradient(q, L, X, dY, ws)
 
 
-@pytest.mark.parametrize("t,c_in,c_out,n,r", _CASES, ids=["%dx%dx%d_n%d_r%d" % c for c in _CASES])
-def test_shared_contraction(t, c_in, c_out, n, r):
+@pytest.mark.parametrize("case,forward,gradient", _CASES, ids=["%dx%dx%d_n%d_r%d" % c[0] for c in _CASES])
+def test_shared_contraction(case, forward, gradient):
+    t, c_in, c_out, n, r = case
     from paper_2505_14742_amd import binding as q
     from tests.gpu_harness import Layer, bf16_dev, smallest_workspace
+    assert [_parts(q.debug_product_form(*case, how)) for how in range(4)] == [forward, 1, gradient, 1]
     O = [k * (c_in - 1) // max(n - 1, 1) for k in range(n)]
     print("shared contraction", t, c_in, c_out, n, r, flush=True)
     sys.stdout.flush()
@@ -51,7 +61,6 @@ def test_shared_contraction(t, c_in, c_out, n, r):
     alone = []
     for call in (_forward, _gradient):
         small = smallest_workspace(lambda size: call(q, L, Xd, dYd, ws[:size]), ws.numel())
-        assert small < ws.numel()
         alone.append(call(q, L, Xd, dYd, ws[:small]))
     prev = q.debug_grid_wait_ticks(0)
     try:
@@ -83,21 +92,25 @@ def _steps(t, c_in, c_out, r):
     return q, L, Xd, dYd, ws, backward
 
 
-# four parts (and weight gradients whose workgroups leave no room beside the sharing ones: rank 64), two parts, ragged; two parts
-# that are not worth it beside such weight gradients
-_STEPS = [(256, 4096, 4096, 64), (512, 3072, 3072, 16), (257, 3056, 8192, 32), (1900, 1536, 4096, 32)]
+# (t, c_in, c_out, rank), parts alone and beside a second stream: four and two parts that are worth it beside the weight gradients of
+# every rank (at rank 32 and more these leave the sharing workgroups no room on a unit) and that are not, ragged
+_STEPS = [((647, 2864, 6144, 16), 2, 2), ((202, 2064, 14336, 16), 4, 4), ((662, 2720, 10240, 32), 2, 2), ((917, 2064, 6144, 32), 2, 1),
+          ((200, 2112, 13824, 32), 4, 1), ((792, 1040, 15360, 32), 4, 4), ((700, 2832, 16384, 64), 2, 2), ((650, 3040, 10752, 64), 2, 1),
+          ((788, 1072, 15360, 64), 4, 4), ((208, 2064, 15872, 64), 4, 1)]
+_STEPS += [(case, 1, 1) for case in [(256, 4096, 4096, 64), (512, 3072, 3072, 16), (257, 3056, 8192, 32), (1900, 1536, 4096, 32)]]
 
 
-@pytest.mark.parametrize("t,c_in,c_out,r", _STEPS, ids=["%dx%dx%d_r%d" % c for c in _STEPS])
-def test_shared_contraction_in_the_backward_step(t, c_in, c_out, r):
+@pytest.mark.parametrize("case,alone,beside", _STEPS, ids=["%dx%dx%d_r%d" % c[0] for c in _STEPS])
+def test_shared_contraction_in_the_backward_step(case, alone, beside):
     """Behind the weight gradients' area of the workspace, alone and beside a second stream that fills the chip, with the wait
     as it is and forced to give up, and without room for the exchange: the bits of quaff_linear_bwd_dx."""
     from tests.gpu_harness import smallest_workspace
+    t, c_in, c_out, r = case
     q, L, Xd, dYd, ws, backward = _steps(t, c_in, c_out, r)
+    assert [_parts(q.debug_product_form(t, c_in, c_out, 2, r, how)) for how in (2, 3, 4)] == [alone, 1, beside]
     L.linear_bwd_dx(dYd)
     first = backward(None)
     small = smallest_workspace(lambda size: backward(None, ws[:size]), ws.numel())
-    assert small < ws.numel()
     side = q.SideStream()
     prev = q.debug_grid_wait_ticks(-1)
     for ticks in (prev, 0):
@@ -116,7 +129,9 @@ def test_shared_contraction_in_the_backward_step(t, c_in, c_out, r):
 def test_shared_contraction_in_a_captured_step():
     """A forward and a backward step whose products share their contraction, captured once and replayed between eager steps on
     the same workspaces: every replay gives the bits of the eager step from the same state."""
-    q, L, Xd, dYd, ws, backward = _steps(512, 3072, 3072, 16)
+    t, c_in, c_out, r = 66, 8704, 10752, 16
+    q, L, Xd, dYd, ws, backward = _steps(t, c_in, c_out, r)
+    assert [_parts(q.debug_product_form(t, c_in, c_out, 2, r, how)) for how in (0, 4)] == [4, 4]
     side = q.SideStream()
 
     def step():
