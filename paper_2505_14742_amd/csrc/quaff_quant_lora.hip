@@ -19,8 +19,9 @@ struct Along { const uint16_t* X; int64_t ldx; int c; const uint16_t* L; uint16_
 // rows per quantizing workgroup: TPR threads take one, or all of them share eight (TPR = 1024) or four (2048)
 constexpr int quant_rows_per_block(int TPR) { return TPR <= 256 ? 64 * kLoraWaves / TPR : TPR == 1024 ? 8 : 4; }
 
-template <int R16, int TPR, int NV>
-__global__ void __launch_bounds__(64 * kLoraWaves)
+// PAIR: held to 64 registers, so that two workgroups share a compute unit (rank 32 spills four of them).
+template <int R16, int TPR, int NV, bool PAIR = false>
+__global__ void __launch_bounds__(64 * kLoraWaves, PAIR ? 8 : 4)
 quant_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const float* __restrict__ cs,
                   int8_t* __restrict__ Xq, float* __restrict__ delta, const uint16_t* __restrict__ L, float scale,
                   uint16_t* __restrict__ T_hi, uint16_t* __restrict__ T_lo, int lora_row_blocks, const Along along) {
@@ -29,8 +30,8 @@ quant_lora_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx,
     static_assert(lora_lds_bytes<R16, true>() <= lora_lds_bytes<R16, false>(), "either role");
     const int lora_blocks = lora_row_blocks * kLoraParts;
     if ((int)blockIdx.x < lora_blocks)
-        lora_down_body<R16, true, RG, R16 == 1 ? 4 : R16 == 2 ? 2 : 1>(lora_lds, blockIdx.x % lora_row_blocks, blockIdx.x / lora_row_blocks, lora_row_blocks, X, t, c,
-                                      ldx, L, scale, T_hi, T_lo, lora_row_blocks, nullptr, nullptr, 0, 0);
+        lora_down_body<R16, true, RG>(lora_lds, blockIdx.x % lora_row_blocks, blockIdx.x / lora_row_blocks, lora_row_blocks, X, t, c, ldx,
+                                      L, scale, T_hi, T_lo, lora_row_blocks, nullptr, nullptr, 0, 0);
     else if ((int)blockIdx.x < lora_blocks + along.blocks) {
         const int b = blockIdx.x - lora_blocks;
         lora_down_body<R16, false, RG>(lora_lds, b % along.row_blocks, b / along.row_blocks, along.row_blocks, along.X, t, along.c, along.ldx,
@@ -306,31 +307,50 @@ static bool launch_r(const uint16_t* X, int64_t t, int c, int64_t ldx, const flo
     const int row_blocks = (int)((t + 15) / 16);
     const int lora_row_blocks = (int)((t + 16 * RG - 1) / (16 * RG));
     const int vec = (c + 7) / 8;
-#define QUAFF_QL(TPR, NV)                                                                                             \
-    hipLaunchKernelGGL((quant_lora_kernel<R16, TPR, NV>),                                                             \
+#define QUAFF_QL(TPR, NV) QUAFF_QL_AS(TPR, NV, false)
+#define QUAFF_QL_AS(TPR, NV, PAIR)                                                                                    \
+    hipLaunchKernelGGL((quant_lora_kernel<R16, TPR, NV, PAIR>),                                                           \
                        dim3((unsigned)(lora_row_blocks * kLoraParts + along.blocks +                                  \
                                        8 * RG * ((row_blocks + 8 * RG - 1) / (8 * RG)) * (16 / quant_rows_per_block(TPR)))),         \
                        dim3(NT), 0,                                                                                   \
                        stream, X, t, c, ldx, cs, Xq, delta, L, scale, T_hi, T_lo, lora_row_blocks, along)
-    if (vec <= 64 * 2) QUAFF_QL(64, 2);
-    else if (vec <= 64 * 4) QUAFF_QL(64, 4);
-    else if (vec <= 64 * 6) QUAFF_QL(64, 6);
-    else if (vec <= 64 * 8) QUAFF_QL(64, 8);
+    // Two workgroups to a unit (64 registers) where there are rows enough to use them: at rank 16 from 1024 rows on, at rank 32, which
+    // spills, beyond 4096.  Us, 102 (rank 16) and 92 registers with more steps in flight / two workgroups: rank 16, 2911 x 5312 -> 4288 backward
+    // step 124.8 / 117.7, gradient 3509 x 5312 -> 4160 121.5 / 115.5; rank 32, 9749 x 4736 -> 640 159.7 / 148.5, 5518 x 6016 -> 256
+    // 102.8 / 94.3.  At fewer rows 70 registers without a spill are ahead of both: rank 16, 730 x 6144 -> 288 20.2 / 21.2, rank 32, 41 x 14752
+    // -> 8592 73.4 / 74.9; and at more than 8192 columns, where two workgroups spill (1014 x 16144 -> 4224 144.5 / 152.6).
+    // (Rank 16 takes the one-pass kernel up to 5120 columns.)
+    if (vec <= 1024 && ((R16 == 1 && t >= 1024) || (R16 == 2 && t > 4096))) {
+        if constexpr (R16 == 2) {
+            if (vec <= 64 * 2) { QUAFF_QL_AS(64, 2, true); return true; }
+            if (vec <= 64 * 4) { QUAFF_QL_AS(64, 4, true); return true; }
+            if (vec <= 64 * 6) { QUAFF_QL_AS(64, 6, true); return true; }
+            if (vec <= 64 * 8) { QUAFF_QL_AS(64, 8, true); return true; }
+        }
+        if constexpr (R16 <= 2) { QUAFF_QL_AS(2048, 1, true); return true; }
+    }
+    if constexpr (R16 > 1) {
+        if (vec <= 64 * 2) { QUAFF_QL(64, 2); return true; }
+        if (vec <= 64 * 4) { QUAFF_QL(64, 4); return true; }
+        if (vec <= 64 * 6) { QUAFF_QL(64, 6); return true; }
+        if (vec <= 64 * 8) { QUAFF_QL(64, 8); return true; }
+    }
     // From rank 48 on a compute unit holds one workgroup of this launch, and with more than 2048 rows the quantizing ones come
     // in several rounds: eight rows each, sharing the column scales, instead of four.  This launch, us, four / eight rows: rank
     // 64, 4096 x 11008 65.6 / 58.0, 4096 x 4864 32.9 / 29.2; rank 48 55.4 / 52.8 and 27.2 / 24.6.  At 2048 rows rank 64 is level (24.8 /
     // 25.8 at 6144 columns, 35.7 / 36.5 at 9216, 60.0 / 59.8 at 16384) and rank 48 is not beyond 8192 columns (25.2 / 25.8, 36.4 / 31.8,
-    // 60.4 / 53.0): one line for both ranks leaves that out.  At lower ranks, where two workgroups of four rows share a unit, four
-    // are level or faster (rank 32, 4096 x 11008 56.7 / 60.3).
-    else if (R16 >= 3 && t > 2048 && vec <= 1024) { if constexpr (R16 >= 3) QUAFF_QL(1024, 1); }
-    else if (R16 >= 3 && t > 2048 && vec <= 1024 * 2) { if constexpr (R16 >= 3) QUAFF_QL(1024, 2); }
-    // Otherwise four rows share the scales, two such workgroups to a unit at ranks 16 and 32.  Input gradient into 256 channels, us, a
-    // quarter of the workgroup for each row / so: rank 16, 2048 x 16384 71.6 / 67.2, 2048 x 9216 42.2 / 40.0, 4096 x 11008 80.6 / 75.3; rank 32,
-    // 4096 x 11008 83.6 / 79.3, 2048 x 6144 33.1 / 33.2.
-    else if (vec <= 1024) QUAFF_QL(2048, 1);
+    // 60.4 / 53.0): one line for both ranks leaves that out.  At lower ranks four are level or faster (rank 32, 4096 x 11008 56.7 / 60.3).
+    if constexpr (R16 >= 3) {
+        if (t > 2048 && vec <= 1024) { QUAFF_QL(1024, 1); return true; }
+        if (t > 2048 && vec <= 1024 * 2) { QUAFF_QL(1024, 2); return true; }
+    }
+    // Otherwise four rows share the scales.  Input gradient into 256 channels, us, a quarter of the workgroup for each row / so: rank 16,
+    // 2048 x 16384 71.6 / 67.2, 2048 x 9216 42.2 / 40.0, 4096 x 11008 80.6 / 75.3; rank 32, 4096 x 11008 83.6 / 79.3, 2048 x 6144 33.1 / 33.2.
+    if (vec <= 1024) QUAFF_QL(2048, 1);
     else if (vec <= 1024 * 2) QUAFF_QL(2048, 2);
     else return false;
 #undef QUAFF_QL
+#undef QUAFF_QL_AS
     return true;
 }
 
