@@ -1136,6 +1136,23 @@ inline TileGrid tile_grid(int tiles_m, int tiles_n, int bm, int bn) {
         const int64_t cost = (int64_t)rm * rn * 1000000 + (int64_t)rm * bm + (int64_t)rn * bn;
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = TileGrid{l, rm, rn}; }
     }
+    // Eight row stripes, every XCD crossing the whole width, only where they save a turn of the 32 units: otherwise the regions with
+    // the fewest operand rows among those of as few turns, and beyond two turns also those of 7 % more tiles.  Eight stripes / so, us:
+    // gradient 10176 x 12288 at 1024, rank 32 (256 x 288 tiles, 5 x 43 and 20 x 11 of them to an XCD) 317 / 234, 5917 x 10048 at 1024 124 /
+    // 102, forward 9339 x 6304 at 656 133 / 96; of 60 products none takes more than 1.01 of the time.  With two turns a third costs more
+    // (gradient 6370 x 1600 at 6016 130 / 148), and other regions are not worth a turn (4766 x 16320 at 384 102 / 128).
+    if (best.xm_log2 == 3 && best.rm * best.rn > 32) {
+        const int stripes = best.rm * best.rn;
+        for (int more = 0; more < (stripes > 64 ? 2 : 1) && best.xm_log2 == 3; ++more) {
+            best_cost = (int64_t)best.rm * bm + (int64_t)best.rn * bn;
+            for (int l = 0; l < 3; ++l) {
+                const int rm = (tiles_m + (1 << l) - 1) >> l, rn = (tiles_n + (8 >> l) - 1) >> (3 - l);
+                const int64_t cost = (int64_t)rm * bm + (int64_t)rn * bn;
+                const bool fits = (rm * rn + 31) / 32 <= (stripes + 31) / 32 || (more && rm * rn <= stripes + stripes / 14);
+                if (fits && cost < best_cost) { best_cost = cost; best = TileGrid{l, rm, rn}; }
+            }
+        }
+    }
     return best;
 }
 inline TileMap make_tile_map(int tiles_m, int tiles_n, int bm, int bn, int wgs_per_cu) {
