@@ -30,6 +30,11 @@ namespace {
 // three tiles of 64 and 128 rows in 1.7 % (forward) and 0.5 % (input gradient) of the products.  With no term for what all
 // units fetch together it is 4.1 % and 2.8 % (86 x 1152 at 15360: 16 x 16 for 32 x 32 blocks, 23.9 / 17.9 us; gradient 5723 x
 // 6400 at 1280, rank 64: 256 x 256 for 128 x 192 tiles, 128 / 96).
+// The three smallest forward shapes are fitted for the choice itself: by how much the time of the chosen one exceeds the best one's, over
+// these and 540 more products of up to 1200 rows.  Fitted for their times alone they mixed up neighbours (16 x 9216 at K = 3072: 16 x 16
+// for 32 x 64 blocks, forward step at rank 16 22.4 / 20.9; 26 x 3280 at 14896 32 x 32 for 16 x 16, 38.4 / 34.6): more than 1.03 of
+// the choice without a term for what all units fetch in 3.9 % of the 540, now 1.7 (342 x 1088 at 896 11.2 / 10.0, 116 x 2880 at 4672, rank 64,
+// forward step 34.3 / 31.4).
 // What the three tiles give, us, without / with them: 1003 x 2064 at 1040 15.1 / 10.0, 2048 x 1024 at 3072 19.3 / 12.2, 768 x 1536 at
 // 1536 13.7 / 7.8, gradient 1003 x 1040 at 2064 with its quantizer 26.0 / 15.3; 0.89 in the geometric mean.
 struct Shape { int id, bm, bn, fit; double fixed, round, next, unit, chip, chain, low, low2; };
@@ -41,9 +46,9 @@ constexpr Shape kForward[10] = {
     {kTile128x128, 128, 128, 1, 5.70, 3.62, 0.99, 7.05, 6.18, 1.08, 0.60, 2.07},
     {kTile64x128, 64, 128, 2, 4.41, 1.84, 1.23, 5.27, 4.82, 1.59, 0.35, 0.65},
     {kTile64x64, 64, 64, 3, 4.29, 1.41, 0.82, 2.27, 6.27, 1.64, 0.24, 0.46},
-    {kRows32x64, 32, 64, 4, 4.72, 21.29, 1.64, 5.76, 10.19, 0.47, 0.08, 0.00},
-    {kRows32x32, 32, 32, 8, 3.63, 32.71, 0.68, 7.56, 8.79, 0.40, 0.04, 0.00},
-    {kRows16x16, 16, 16, 8, 3.38, 2.25, 0.41, 7.41, 10.95, 0.14, 0.02, 0.00}};
+    {kRows32x64, 32, 64, 4, 4.69, 21.29, 1.20, 3.76, 10.52, 0.60, 0.09, 0.00},
+    {kRows32x32, 32, 32, 8, 3.64, 22.94, 0.45, 9.42, 8.02, 0.40, 0.05, 0.00},
+    {kRows16x16, 16, 16, 8, 3.35, 3.55, 0.50, 7.34, 11.79, 0.11, 0.02, 0.00}};
 constexpr Shape kGradient[9] = {
     {kTile256x256, 256, 256, 1, 10.07, 8.04, 2.10, 8.13, 11.79, 3.11, 1.80, 6.87},
     {kTile256x288, 256, 288, 1, 10.58, 9.94, 2.96, 8.39, 12.99, 3.33, 1.20, 7.43},

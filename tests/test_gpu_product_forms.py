@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 # (t, c_in, c_out, number of outliers, rank), form of the forward product
 _FORWARD = [
     ((1, 192, 208, 5, 16), "16x16 rows"), ((1, 192, 4720, 5, 32), "32x32 rows"), ((33, 960, 4720, 0, 16), "32x64 rows"),
-    ((17, 192, 8464, 0, 32), "64x64"), ((1, 192, 8688, 70, 64), "64x64"), ((523, 192, 1584, 70, 0), "64x128"), ((132, 192, 5232, 70, 48), "64x128"),
+    ((199, 192, 2544, 0, 32), "64x64"), ((1, 192, 8688, 70, 64), "64x64"), ((523, 192, 1584, 70, 0), "64x128"), ((132, 192, 5232, 70, 48), "64x128"),
     ((202, 192, 8816, 0, 0), "128x128"), ((4174, 848, 464, 70, 48), "128x128"), ((4194, 192, 1776, 70, 0), "128x192"),
     ((12450, 192, 544, 5, 32), "128x192"), ((9768, 192, 800, 0, 48), "128x192"), ((6312, 192, 528, 5, 32), "128x192 deep"),
     ((8227, 192, 400, 70, 64), "128x192 deep"), ((1077, 208, 4720, 0, 0), "256x128"), ((10747, 256, 416, 70, 32), "256x128"),
@@ -23,13 +23,13 @@ _FORWARD = [
     ((1, 192, 240, 175, 48), "64x64 wide"), ((94, 192, 8784, 156, 48), "64x128 wide"), ((585, 192, 3232, 192, 16), "128x128 wide"),
     ((8611, 448, 272, 275, 64), "128x128 wide"), ((11014, 240, 272, 240, 16), "128x192 deep wide"), ((3248, 192, 1168, 170, 48), "128x192 deep wide"),
     # ... or the main product accumulating onto the outliers' (the tiles of 64 and 128 rows do from 16384 columns on only)
-    ((1, 928, 208, 293, 16), "16x16 rows onto 16x16 rows"), ((20, 2112, 2080, 233, 16), "32x32 rows onto 32x32 rows"),
+    ((1, 928, 208, 293, 16), "16x16 rows onto 16x16 rows"), ((173, 2592, 608, 257, 16), "32x32 rows onto 32x32 rows"),
     ((17, 5744, 8224, 250, 48), "32x64 rows onto 32x32 rows"), ((1357, 8512, 6304, 141, 32), "128x192 onto 128x192"),
     ((12930, 8656, 528, 259, 64), "128x192 onto 128x192"), ((11668, 10048, 416, 568, 64), "256x128 narrow onto 256x128 narrow"),
     ((10250, 11264, 432, 140, 64), "256x128 onto 256x128 narrow"), ((10352, 1952, 1232, 204, 32), "256x256 onto 256x256"),
     ((1913, 1808, 6288, 290, 0), "256x256 onto 256x256 narrow"), ((8468, 3648, 1568, 221, 0), "256x288 onto 256x288"),
     ((3281, 2752, 4320, 221, 48), "256x288 onto 256x288"), ((2050, 2528, 6624, 265, 48), "256x288 onto 256x288 narrow"),
-    ((35, 37472, 9344, 1589, 16), "64x64 onto 64x64"), ((74, 27392, 8784, 776, 32), "64x128 onto 64x128"),
+    ((35, 37472, 9344, 1589, 16), "64x64 onto 64x64"), ((198, 28336, 4400, 2414, 32), "64x128 onto 64x128"),
     ((134, 32944, 10976, 170, 64), "128x128 onto 128x128"), ((4132, 33424, 784, 1117, 64), "128x192 deep onto 64x128")]
 
 # (t, c_in, c_out, rank), form of the input gradient

@@ -58,3 +58,11 @@ def test_a_product_without_room_for_the_exchange_keeps_the_deep_ring():
         assert form(*shape, 0) == "128x192 shared by %d" % parts and form(*shape, 1) == "128x192 deep"
     gradient = (685, 2768, 11264, 0, 48)
     assert form(*gradient, 2) == "128x192 shared by 2" and form(*gradient, 3) == "128x192 deep" and form(*gradient, 4) == "128x192 beside"
+
+
+def test_neighbouring_small_shapes_the_model_once_mixed_up():
+    """1.1 to 1.2 of the time of the form that is named, on one operand set and on rotating ones."""
+    form = q.debug_product_form
+    assert form(16, 3072, 9216, 0, 0, 0) == "32x64 rows" and form(16, 3072, 9216, 5, 16, 0) == "32x64 rows"
+    assert form(26, 14896, 3280, 0, 0, 0) == "16x16 rows" and form(23, 10368, 2688, 0, 0, 0) == "16x16 rows"
+    assert form(31, 6848, 2816, 0, 0, 0) == "16x16 rows" and form(407, 3328, 256, 0, 64, 0) != "32x64 rows"
