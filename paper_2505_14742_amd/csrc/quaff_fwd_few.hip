@@ -44,7 +44,9 @@ struct FwdFewArgs {
     uint64_t* words; uint64_t* epoch;
 };
 
-// SPS: 64-column steps of a slice, SL: slices of a wavefront at most, NB: 16-channel blocks of a tile
+// SPS: 64-column steps of a slice, SL: slices of a wavefront at most, NB: 16-channel blocks of a tile.  (At most 2048 columns: SPS is 1, and all
+// steps of A and of the weights are in flight.  Written for that alone the compiler orders the loads differently: 17 x 704 -> 1120 with 38 outliers
+// 13.5 -> 15.8 us, 30 x 1536 -> 2432 11.0 -> 11.7.)
 template <int SPS, int SL, int NB, bool HAS_LORA>
 __global__ void __launch_bounds__(kFewThreads)
 fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
@@ -57,7 +59,6 @@ fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
     float* const cs_copy = reinterpret_cast<float*>(few_lds);                       // column scales [c]
     char* const lt = few_lds + (((size_t)a.c * 4 + 255) & ~(size_t)255);            // per wavefront: a step of A
     // the down-projection's partial sums [32 slices][64 lanes][4], then the product's [wavefront][block][64 lanes][4]
-    constexpr int RED = HAS_LORA ? 2 * kFewSlices * 1024 : 0, EXCHANGE = kFewWaves * NB * 1024;
     char* const area = lt + (HAS_LORA ? kFewWaves * 4 * kFewLt : 0);
     __shared__ float rmax[kFewWaves][kFewRows];
     __shared__ uint32_t smax[64];
@@ -136,13 +137,9 @@ fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
             if (k < n && live) xo[i] = a.X[row * a.ldx + col];
         }
     }
-    f32x4 cs_first[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = (tid + v * kFewThreads) * 4;
-        cs_first[v] = (f32x4){1.f, 1.f, 1.f, 1.f};
-        if (v * kFewThreads * 4 < c && i < c) cs_first[v] = *reinterpret_cast<const f32x4*>(a.colscale + i);
-    }
+    static_assert(2 * kFewSlices * 64 <= 4 * kFewThreads, "columns: a vector of their scales to a thread");
+    f32x4 cs_first = {1.f, 1.f, 1.f, 1.f};
+    if (tid * 4 < c) cs_first = *reinterpret_cast<const f32x4*>(a.colscale + tid * 4);
     constexpr int WV = 64 * BN / kFewThreads;                   // values of W_O of a thread: element e = (k, channel)
     float w_o[WV];
 #pragma unroll
@@ -208,11 +205,7 @@ fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
             }
         }
     }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = (tid + v * kFewThreads) * 4;
-        if (i < c) *reinterpret_cast<f32x4*>(cs_copy + i) = cs_first[v];
-    }
+    if (tid * 4 < c) *reinterpret_cast<f32x4*>(cs_copy + tid * 4) = cs_first;
     if (tid < BN) {
         dw[tid] = dw_first;
         wmaxbits[tid] = 0u;
@@ -454,7 +447,7 @@ fwd_few_kernel(const FwdFewArgs a, const int32_t* __restrict__ O) {
 // -> 336 6.6 / 7.3); with outliers, whose columns
 // every workgroup gathers and whose words every workgroup reads, up to 64 workgroups, 1024 columns and 1024 gathered values.
 // Of 292 forward steps of 1 to 512 rows and up to 2048 columns, every tile timed, the rule takes 151: 0.75 of the time of the two
-// launches in the geometric mean, none more than 2 % slower.  Beyond it, two launches / this one, us: 256 x 512 -> 512 with 8 outliers
+// launches in the geometric mean, none more than 2 % slower; on 300 operand sets in turn 55 of them 0.69 (rank 16) and 0.72.  Beyond it, two launches / this one, us: 256 x 512 -> 512 with 8 outliers
 // (128 workgroups) 12.1 / 12.4, 11 x 1792 -> 1024 with 5 11.6 / 11.4, 16 x 3072 -> 9216 with 31 outliers and rank 16 21.6 / 23.8
 // (every workgroup quantizes 16 rows of 3072 columns, 3.5 us of vector instructions, and fetches them and A at 45 KB/us), 77 x 2944
 // -> 576 without outliers 15.0 / 14.6.  With an adapter the product's order of summation must be this kernel's.

@@ -11,7 +11,7 @@ hipError_t launch_gemm_kn(const GemmArgs& g, int tile, bool dump_acc, hipStream_
         case kTile256x128: return launch_dma<256, 128, 4, 2, 2, 1, true>(g, dump_acc, stream);
         case kTile128x192: return launch_dma<128, 192, 2, 2, 2, 2, true>(g, dump_acc, stream);
         case kTile128x192Deep: return launch_dma<128, 192, 4, 2, 3, 2, true>(g, dump_acc, stream);
-        case kTile128x192Beside: return launch_dma<128, 192, 2, 2, 3, 2, true>(g, dump_acc, stream);
+        case kTile128x192Beside: return launch_dma<128, 192, 2, 2, 3, 2, true, 0>(g, dump_acc, stream);      // (of the backward step only)
         case kTile128x128: case kTile64x128: case kTile64x64: return launch_gemm_mid(g, tile, dump_acc, stream);
         case kTileSplit: return launch_dma_form<256, 192, 4, 2, 2, 1, true, false, 2>(g, dump_acc, stream);
         case kTileSplitSmall2: return launch_dma_form<128, 192, 2, 2, 3, 2, true, false, 2>(g, dump_acc, stream);

@@ -6,7 +6,7 @@ namespace quaff {
 hipError_t launch_gemm_nk(const GemmArgs& g, int tile, bool dump_acc, hipStream_t stream) {
     switch (tile) {
         case kTile256x256: return launch_dma<256, 256, 2, 4, 2, 1, false>(g, dump_acc, stream);
-        case kTile256x256Many: return launch_dma<256, 256, 4, 4, 2, 1, false>(g, dump_acc, stream);
+        case kTile256x256Many: return launch_dma<256, 256, 4, 4, 2, 1, false, kFormDump | kFormBf16>(g, dump_acc, stream);
         case kTile256x288: return launch_dma<256, 288, 4, 3, 2, 1, false>(g, dump_acc, stream);
         case kTile256x128: return launch_dma<256, 128, 4, 2, 2, 1, false>(g, dump_acc, stream);
         case kTile128x192: return launch_dma<128, 192, 2, 2, 2, 2, false>(g, dump_acc, stream);

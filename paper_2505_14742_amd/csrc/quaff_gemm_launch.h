@@ -5,7 +5,10 @@
 
 namespace quaff {
 
-template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT, int BK = 128, bool WIDE = false>
+// What a tile shape is compiled for beside the fp32 output
+constexpr int kFormDump = 1, kFormBf16 = 2, kFormAccumulate = 4, kAllForms = 7;
+
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, bool RAGGED, int KSPLIT, int BK = 128, bool WIDE = false, int FORMS = kAllForms>
 static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stream) {
     using C = DmaCfg<BM, BN, WGM, WGN, NS, BK>;
     int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
@@ -26,11 +29,15 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
         if (dump || g.accumulate) return hipErrorInvalidValue;
         if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, KSPLIT, BK>;
     } else {
-        if (dump) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED, 1, BK>;
-        else if (g.C16) k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, 1, BK>;
-        else if (g.accumulate) {
+        if (dump) {
+            if constexpr (!(FORMS & kFormDump)) return hipErrorInvalidValue;
+            else k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, true, false, false, BT, RAGGED, 1, BK>;
+        } else if (g.C16) {
+            if constexpr (!(FORMS & kFormBf16)) return hipErrorInvalidValue;
+            else k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, false, true, BT, RAGGED, 1, BK>;
+        } else if (g.accumulate) {
             // (only a forward product has a wide second product to accumulate onto)
-            if constexpr (BT) return hipErrorInvalidValue;
+            if constexpr (BT || !(FORMS & kFormAccumulate)) return hipErrorInvalidValue;
             else k = gemm_i8_dma_kernel<BM, BN, WGM, WGN, NS, MINB, false, true, false, BT, RAGGED, 1, BK>;
         }
     }
@@ -41,10 +48,10 @@ static hipError_t launch_dma_form(const GemmArgs& g, bool dump, hipStream_t stre
 }
 
 // BM x BN tile, WGM x WGN wavefronts, NS stages in the ring, MINB workgroups per compute unit to compile for
-template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT>
+template <int BM, int BN, int WGM, int WGN, int NS, int MINB, bool BT, int FORMS = kAllForms>
 static hipError_t launch_dma(const GemmArgs& g, bool dump, hipStream_t stream) {
-    if (g.K % 128 != 0) return launch_dma_form<BM, BN, WGM, WGN, NS, MINB, BT, true, 1>(g, dump, stream);
-    return launch_dma_form<BM, BN, WGM, WGN, NS, MINB, BT, false, 1>(g, dump, stream);
+    if (g.K % 128 != 0) return launch_dma_form<BM, BN, WGM, WGN, NS, MINB, BT, true, 1, 128, false, FORMS>(g, dump, stream);
+    return launch_dma_form<BM, BN, WGM, WGN, NS, MINB, BT, false, 1, 128, false, FORMS>(g, dump, stream);
 }
 
 }  // namespace quaff

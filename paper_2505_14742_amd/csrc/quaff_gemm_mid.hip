@@ -2,7 +2,8 @@
 // both readings of B.  Many wavefronts for their size (32 x 32 of the output each, 32 x 64 in the largest tile): they share the
 // issue of the direct loads and the epilogue, which are what such a launch consists of beside the delivery of its operands.
 // Us, 64 x 128 tile with four / eight wavefronts: 512 x 3072 outputs at K = 3072 14.9 / 11.7, 2048 x 1024 at 3072 14.6 / 12.2; 128 x 128
-// tile: 1003 x 2064 at 1040 11.8 / 10.0, 1536 x 2048 at 2048 13.8 / 13.0.
+// tile: 1003 x 2064 at 1040 11.8 / 10.0, 1536 x 2048 at 2048 13.8 / 13.0.  (Their accumulating forms are reached by contractions beyond 16384
+// columns only: 134 x 32944 -> 10976 with 170 outliers.)
 #include "quaff_gemm_launch.h"
 
 namespace quaff {

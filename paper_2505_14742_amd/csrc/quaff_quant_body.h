@@ -265,7 +265,6 @@ __device__ __forceinline__ void quant_rows_shared_body(int block, const uint16_t
                     const int k = j * NT + threadIdx.x;
                     if (k < n_pad) dst[k] = (int8_t)rtn_code(xo[j][r], cc);     // (0 beyond n: code 0)
                 }
-                for (int k = KO * NT + threadIdx.x; k < n_pad; k += NT) dst[k] = (int8_t)(k < n ? rtn_code(outlier(k, r), cc) : 0);
             }
         }
     }
