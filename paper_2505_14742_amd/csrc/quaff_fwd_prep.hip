@@ -537,7 +537,8 @@ fwd_prep_kernel(const FwdPrepArgs a) {
 // (words out, everybody's words in) behind the last to arrive; and the down-projection gets row owners of its own.  Of 20886 random
 // forward steps of up to 512 rows and 4096 values, those of rank 16 take 0.87 of the time up to 2048 values (0.79 beyond 4096 columns: 8 x 8192
 // -> 3072 26.1 -> 20.1 us, 16 x 3072 -> 3072 16.9 -> 13.9, 16 x 3072 -> 9216 21.5 -> 20.4) and 0.92 beyond; without an adapter 0.92 up to
-// 2048 channels and 0.87 from 12288 on, level between (16 x 1536 -> 8320 15.5 / 18.5, 32 x 1024 -> 4096 0.97), where it is left out.
+// 2048 channels and 0.87 from 12288 on, level between (16 x 1536 -> 8320 15.5 / 18.5, 32 x 1024 -> 4096 0.97; the cause is not known), where it is left out.  On 300 operand
+// sets in turn, more than the L2s hold, 54 steps take 0.82 (rank 16) and 0.96 (without) of the time of the exchange.
 bool fwd_prep_direct(int64_t t, int64_t c_out, int32_t n, int32_t r) {
     return t <= 512 && t * n <= 2048 && (r > 0 || c_out < 2048 || c_out >= 12288);
 }

@@ -113,7 +113,8 @@ struct DmaCfg {
     // 53 bytes per clock and compute unit at the full MFMA rate against about 40 that the direct-load path sustains,
     // not by LDS reads).
     static constexpr bool MFMA_FIRST = NW >= 8 && TM * TN >= 6;
-    static constexpr bool DMA_ASM = NW >= 8 && !MFMA_FIRST;      // see dma_load_16: only the 256x128 tile gains (3-6 %)
+    static constexpr bool DMA_ASM = NW >= 8 && !MFMA_FIRST;      // see dma_load_16: 3-6 % on the 256x128 tile, taken
+                                                                 // by the other tiles of few MFMAs per sub-step too
     // a stage: BK contraction bytes per row of A, then of B; one direct load (1 KiB) fills 8 rows (16 with BK = 64)
     static_assert(BK == 128 || BK == 64, "stage width");
     static constexpr int STAGE_BYTES = (BM + BN) * BK, A_BYTES = BM * BK;

@@ -2,10 +2,10 @@
 // App. "Model and experimental settings"):  T = scale * X L  with X [t x c] bf16 and L the rank-r factor.
 // Forward: X is the layer input and L = A [c_in x r].  Backward: X is dY and L = B^T, given as B [r x c_out].
 //
-// HBM-bound skinny product (reads X once).  bf16 MFMA 16x16x32 with fp32 accumulation; a workgroup owns 16 rows,
-// its eight wavefronts take interleaved 32-wide contraction steps and are summed in a fixed order, so the result
-// is deterministic.  When L is stored [c x r] the MFMA needs it transposed: each wavefront takes its own
-// 64 x r slices through a private piece of LDS (coalesced 16-byte loads in, transposing reads out).
+// HBM-bound skinny product (reads X once).  bf16 MFMA 16x16x32 with fp32 accumulation; a workgroup owns 16 rows (32 from
+// rank 48 on), its sixteen wavefronts take one contiguous slice of the contraction each, 64 columns at a time, and are summed
+// in a fixed order, so the result is deterministic.  Both layouts of L go through a private piece of LDS for each wavefront
+// (whole lines in; [c x r] back through transposing reads).
 // T is handed to the GEMM epilogue as a bf16 pair (hi + lo, 16 significant bits) so that the up-projection can
 // also run on the bf16 MFMA without losing the fp32 accumulation's accuracy.  Extra workgroups of the same launch
 // write the transposed copy of the other factor that the epilogue reads contraction-contiguous.
@@ -14,8 +14,10 @@
 namespace quaff {
 
 // R16 = r / 16 column blocks of T.  L_RC: L is [r x c] (contraction-contiguous) else [c x r].
-// Up to r = 32 the kernel is held to 64 registers (8 wavefronts per SIMD): its 16-wavefront workgroups then fit on
-// a compute unit beside a workgroup of the input-gradient product, which the one-call backward step runs them next to.
+// Up to r = 32 the kernel is held to 64 registers (8 wavefronts per SIMD), two 16-wavefront workgroups to a compute unit (rank 32
+// with a [r x c] factor spills 4 registers, rank 64 at 128 registers 12).  At rank 16 its 40 KB of LDS fit on a unit beside a workgroup of the
+// input-gradient product, which the one-call backward step runs it next to; the 66 KB of rank 32 do not fit beside the 120 KB of the
+// deep 128 x 192 tile.
 template <int R16, bool L_RC>
 __global__ void __launch_bounds__(64 * kLoraWaves, R16 <= 2 ? 8 : 4)
 lora_down_kernel(const uint16_t* __restrict__ X, int64_t t, int c, int64_t ldx, const uint16_t* __restrict__ L,

@@ -17,7 +17,7 @@ CASES = [(300, 512, 384, 0),        # edge tiles in both directions, no correcti
          (300, 512, 384, 64),       # one full outlier slice
          (257, 1024, 832, 128),     # two slices (the widest set staged in one launch)
          (2051, 3072, 3072, 31),    # the 128x192 tile's one-pass epilogue plus a ragged row tile
-         (515, 1024, 576, 200),     # more than two slices: correction launch + accumulating main launch
+         (515, 1024, 576, 200),     # more than two slices: both contractions in one launch (64x64 tiles)
          (2048, 256, 9216, 65),     # the 256x288 tile
          (64, 208, 144, 5),         # contraction not a multiple of 64: the register-staged kernel
          (1280, 3072, 12288, 0)]    # dX contracts over 12288 channels into a 1280 x 3072 output: the contraction is

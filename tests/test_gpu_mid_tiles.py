@@ -17,7 +17,7 @@ _CASES = [(500, 3056, 3088, 1, 16),     # 64 x 128, 64 x 128
           (1003, 1040, 2064, 13, 32),   # 128 x 128, 64 x 128
           (1290, 2032, 1936, 5, 48),    # 128 x 128, 128 x 128
           (192, 1216, 3600, 0, 0),      # 64 x 64, none of them
-          (900, 2704, 3216, 130, 16),   # 128 x 128 (accumulating onto the outliers' product), 128 x 128
+          (900, 2704, 3216, 130, 16),   # 128 x 128 (both contractions in one launch), 128 x 128
           (449, 1296, 1680, 2, 32),     # 64 x 64, 64 x 64
           (64, 208, 16016, 3, 16)]      # one tile row, 126 columns of tiles
 
